@@ -19,15 +19,13 @@
 // (sample, feature) of the pooled block.
 #define DMT_TM_TAG 1          // this file's instances of the shared GEMM kernels
 #include "dmt_tm_gemm.h"
+#include "dmt_tm_f32.h"
 
 namespace {
 
-constexpr int kTile = 32;        // scalar transposes (float32 path, gradient preparation)
+constexpr int kTile = 32;        // one-element gradient preparation
 constexpr int kVTile = 64;       // 16-bit transpose: 64 x 64 tiles, 8-byte accesses
 constexpr int kMaxItems = 32;
-
-template <int DT> struct EltOf { using type = uint16_t; };
-template <> struct EltOf<DMT_F32> { using type = float; };
 
 // One tower's share of a grouped launch of the small kernels below: block id ->
 // (item, block within the item), like the grouped GEMM.  The meaning of the fields is
@@ -152,35 +150,8 @@ __global__ __launch_bounds__(kBlock) void tmb_prep_dy16(const TmbLaunch L) {
 // elements apart, dst rows ldd; fill = i1, or ldd when that is 0 (a narrower fill writes
 // one column block of a wider matrix).
 // a = src, o0 = dst, n0 = R, n1 = lds, n2 = ldd, i0 = C, i1 = fill.
-// Any element type and alignment: one element per access.
-template <typename E>
-__global__ __launch_bounds__(kBlock) void tmb_transpose(const TmbLaunch L) {
-  __shared__ E tile[kTile][kTile + 1];
-  const int gi = tmb_find(L);
-  const TmbItem& G = L.it[gi];
-  const int lb = blockIdx.x - L.block_start[gi];
-  const E* __restrict__ src = (const E*)G.a;
-  E* __restrict__ dst = (E*)G.o0;
-  const int64_t R = G.n0, lds = G.n1, ldd = G.n2, fill = G.i1 > 0 ? G.i1 : G.n2;
-  const int C = G.i0;
-  const int64_t r0 = (int64_t)(lb % G.nbx) * kTile;
-  const int c0 = (lb / G.nbx) * kTile;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int i = ty; i < kTile; i += kBlock / kTile) {
-    const int64_t r = r0 + i;
-    const int c = c0 + tx;
-    tile[i][tx] = (r < R && c < C) ? src[r * lds + c] : (E)0;
-  }
-  __syncthreads();
-  for (int i = ty; i < kTile; i += kBlock / kTile) {
-    const int c = c0 + i;
-    const int64_t r = r0 + tx;
-    if (c < C && r < fill) dst[(int64_t)c * ldd + r] = tile[tx][i];
-  }
-}
-
-// The same for 16-bit elements with C, lds and ldd multiples of 4 and 8-byte aligned
-// bases: 64 x 64 tiles, four (or, alignment permitting, eight) elements per global access.
+// C, lds and ldd are multiples of 4 and the bases 8-byte aligned: 64 x 64 tiles, four (or,
+// alignment permitting, eight) elements per global access.
 __global__ __launch_bounds__(kBlock) void tmb_transpose16(const TmbLaunch L) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[kVTile][kVTile + 8];
   const int gi = tmb_find(L);
@@ -249,28 +220,23 @@ __global__ __launch_bounds__(kBlock) void tmb_transpose16(const TmbLaunch L) {
   }
 }
 
-// out[r] = sum over c < ncols of src[r][c], float32, in a fixed order: thread t of
-// the row's block adds columns t, t + 256, ... (16-bit types: the 8-column chunks t,
-// t + 256, ..., over the whole padded row, whose padding is zero) and the 256 partial
-// sums are folded by halves.  One block per row.  a = src, o0 = out, n0 = ld (a multiple
-// of 8 for the 16-bit types), n1 = ncols.
+// out[r] = sum over c of src[r][c], float32, in a fixed order: thread t of the row's block adds
+// the 8-column chunks t, t + 256, ... of the whole padded row (the padding is zero) and the 256
+// partial sums are folded by halves.  One block per row.  a = src, o0 = out, n0 = ld (a multiple
+// of 8).
 template <int DT>
 __global__ __launch_bounds__(kBlock) void tmb_rowsum(const TmbLaunch L) {
   __shared__ float part[kBlock];
   const int gi = tmb_find(L);
   const TmbItem& G = L.it[gi];
   const int64_t row = blockIdx.x - L.block_start[gi];
-  const int64_t ld = G.n0, ncols = G.n1;
+  const int64_t ld = G.n0;
   float s = 0.f;
-  if constexpr (DT == DMT_F32) {
-    for (int64_t c = threadIdx.x; c < ncols; c += kBlock) s += load_elt<DT>(G.a, row * ld + c);
-  } else {
-    for (int64_t c = (int64_t)threadIdx.x * 8; c < ld; c += kBlock * 8) {
-      float x[8];
-      dmt::decode_chunk<DT>(x, *(const uint4*)((const uint16_t*)G.a + row * ld + c));
+  for (int64_t c = (int64_t)threadIdx.x * 8; c < ld; c += kBlock * 8) {
+    float x[8];
+    dmt::decode_chunk<DT>(x, *(const uint4*)((const uint16_t*)G.a + row * ld + c));
 #pragma unroll
-      for (int q = 0; q < 8; ++q) s += x[q];
-    }
+    for (int q = 0; q < 8; ++q) s += x[q];
   }
   part[threadIdx.x] = s;
   __syncthreads();
@@ -281,35 +247,13 @@ __global__ __launch_bounds__(kBlock) void tmb_rowsum(const TmbLaunch L) {
   if (threadIdx.x == 0) ((float*)G.o0)[row] = part[0];
 }
 
-// Elementwise kernels over `count` = n0 elements: 8 per thread step for the 16-bit types
-// (count is then a multiple of 8), 1 for float32.  nbx = blocks of the item.
-template <int DT> struct Ew { static constexpr int V = DT == DMT_F32 ? 1 : 8; };
-
-template <int DT>
-__device__ __forceinline__ void ew_load(const void* p, int64_t e, float (&x)[Ew<DT>::V]) {
-  if constexpr (DT == DMT_F32) x[0] = ((const float*)p)[e];
-  else dmt::decode_chunk<DT>(x, *(const uint4*)((const uint16_t*)p + e));
+__device__ __forceinline__ void load_f32x8(const float* p, int64_t e, float (&x)[8]) {
+  const float4 a = *(const float4*)(p + e), b = *(const float4*)(p + e + 4);
+  x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
-template <int DT>
-__device__ __forceinline__ void ew_store(void* p, int64_t e, const float (&x)[Ew<DT>::V]) {
-  if constexpr (DT == DMT_F32) ((float*)p)[e] = x[0];
-  else dmt::store_chunk<DT, 8>(p, e, x);
-}
-template <int V>
-__device__ __forceinline__ void ew_load_f32(const float* p, int64_t e, float (&x)[V]) {
-  if constexpr (V == 1) x[0] = p[e];
-  else {
-    const float4 a = *(const float4*)(p + e), b = *(const float4*)(p + e + 4);
-    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-  }
-}
-template <int V>
-__device__ __forceinline__ void ew_store_f32(float* p, int64_t e, const float (&x)[V]) {
-  if constexpr (V == 1) p[e] = x[0];
-  else {
-    *(float4*)(p + e) = make_float4(x[0], x[1], x[2], x[3]);
-    *(float4*)(p + e + 4) = make_float4(x[4], x[5], x[6], x[7]);
-  }
+__device__ __forceinline__ void store_f32x8(float* p, int64_t e, const float (&x)[8]) {
+  *(float4*)(p + e) = make_float4(x[0], x[1], x[2], x[3]);
+  *(float4*)(p + e + 4) = make_float4(x[4], x[5], x[6], x[7]);
 }
 
 // Dot-product tower: dx[b][i][c] = dZ[b][np_pad + i n + c]
@@ -351,7 +295,7 @@ __global__ __launch_bounds__(kBlock) void tmb_dot_bwd8(const TmbLaunch L) {
   const float* __restrict__ z = (const float*)G.b + b * ldz;
   const uint16_t* __restrict__ x = (const uint16_t*)G.a + b * wt + c;
   float acc[8];
-  ew_load_f32<8>(z, np_pad + r, acc);
+  load_f32x8(z, np_pad + r, acc);
   for (int j = 0; j < nf; ++j) {
     if (j == i) continue;
     const int lo = j < i ? j : i, hi = j < i ? i : j;
@@ -361,7 +305,7 @@ __global__ __launch_bounds__(kBlock) void tmb_dot_bwd8(const TmbLaunch L) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[q] += g * xv[q];
   }
-  ew_store_f32<8>((float*)G.o0, b * wt + r, acc);
+  store_f32x8((float*)G.o0, b * wt + r, acc);
 }
 
 // dw[o][k] = sum over slices s (ascending) of part[s][o][k'], where k' = k for k < np and
@@ -383,41 +327,30 @@ __global__ __launch_bounds__(kBlock) void tmb_sum_slices(const TmbLaunch L) {
   ((float*)G.o0)[e] = s;
 }
 
-// Cross layer backward, elementwise part: du = dxn * x0 (rounded to DT);
+// Cross layer backward of a float32 tower, elementwise part: du = dxn * x0;
 // dx0 = (first ? 0 : dx0) + dxn * u (+ dxn when `last`: the layer's data-gradient contraction
 // then accumulates du W_l on top, which completes dx_0 + dx0 in place).
-// a = dxn, b = x0, c = u, o0 = du, o1 = dx0, i0 = first, i1 = last.
-template <int DT>
+// a = dxn, b = x0, c = u, o0 = du, o1 = dx0, n0 = elements, i0 = first, i1 = last, nbx = blocks.
 __global__ __launch_bounds__(kBlock) void tmb_cross_prep(const TmbLaunch L) {
-  constexpr int V = Ew<DT>::V;
   const int gi = tmb_find(L);
   const TmbItem& G = L.it[gi];
-  const int first = G.i0;
+  const float* __restrict__ dxn = (const float*)G.a;
+  const float* __restrict__ x0 = (const float*)G.b;
+  const float* __restrict__ u = (const float*)G.c;
+  float* __restrict__ du = (float*)G.o0;
+  float* __restrict__ dx0 = (float*)G.o1;
   const float keep = G.i1 ? 1.f : 0.f;
-  const int64_t stride = (int64_t)G.nbx * kBlock * V;
-  for (int64_t e = ((int64_t)(blockIdx.x - L.block_start[gi]) * kBlock + threadIdx.x) * V; e < G.n0;
-       e += stride) {
-    float g[V], x0[V], u[V], acc[V];
-    ew_load_f32<V>((const float*)G.a, e, g);
-    ew_load<DT>(G.b, e, x0);
-    ew_load<DT>(G.c, e, u);
-    if (first) {
-#pragma unroll
-      for (int q = 0; q < V; ++q) acc[q] = 0.f;
-    } else {
-      ew_load_f32<V>((const float*)G.o1, e, acc);
-    }
-#pragma unroll
-    for (int q = 0; q < V; ++q) {
-      acc[q] += g[q] * u[q] + keep * g[q];
-      x0[q] *= g[q];
-    }
-    ew_store<DT>(G.o0, e, x0);
-    ew_store_f32<V>((float*)G.o1, e, acc);
+  const int64_t stride = (int64_t)G.nbx * kBlock;
+  for (int64_t e = (int64_t)(blockIdx.x - L.block_start[gi]) * kBlock + threadIdx.x; e < G.n0; e += stride) {
+    const float g = dxn[e];
+    float acc = G.i0 ? 0.f : dx0[e];
+    acc += g * u[e] + keep * g;
+    du[e] = x0[e] * g;
+    dx0[e] = acc;
   }
 }
 
-// The same for the 16-bit types, writing du^T as well (the weight gradient's operand), so that du
+// The same for a 16-bit tower (du rounded to its type), writing du^T as well (the weight gradient's operand), so that du
 // is not read back by a transpose: 64 x 64 tiles of the [B][W] tensors, 16-byte reads of dxn and
 // dx0, 8-byte accesses of the 16-bit tensors.  W is a multiple of 8.
 // a = dxn, b = x0, c = u, o0 = du, o1 = dx0, o2 = du^T [W][Bp], n0 = B, n1 = Bp, i0 = first,
@@ -701,14 +634,11 @@ bool launch_items(const dmt_plan* p, TmbBatch& batch, Kernel kernel, hipStream_t
   return ok;
 }
 
-inline int64_t ew_blocks(int64_t count, int vec) {
-  return std::min<int64_t>((count / vec + kBlock - 1) / kBlock, 256 * 8);
-}
+inline int64_t ew_blocks(int64_t count) { return std::min<int64_t>((count + kBlock - 1) / kBlock, 256 * 8); }
 
-template <int DT>
 void add_transpose(TmbBatch& b, const void* src, int64_t R, int C, int64_t lds, void* dst, int64_t ldd,
                    int fill = 0) {
-  constexpr int tile = DT == DMT_F32 ? kTile : kVTile;
+  constexpr int tile = kVTile;
   TmbItem it{};
   it.a = src; it.o0 = dst; it.n0 = R; it.n1 = lds; it.n2 = ldd; it.i0 = C; it.i1 = fill;
   it.nbx = (int32_t)(((fill > 0 ? fill : ldd) + tile - 1) / tile);
@@ -717,9 +647,8 @@ void add_transpose(TmbBatch& b, const void* src, int64_t R, int C, int64_t lds, 
 
 // Queues a gradient-preparation item (all fields but nbx set) on the 16-byte kernel when its
 // shape and alignment allow, else on the one-element kernel.
-template <int DT>
 void add_prep(TmbBatch& scalar, TmbBatch& vec, TmbItem it) {
-  const bool v = DT != DMT_F32 && it.i0 % 4 == 0 && it.n2 % 4 == 0 && (it.i3 == 0 || it.i4 % 4 == 0) &&
+  const bool v = it.i0 % 4 == 0 && it.n2 % 4 == 0 && (it.i3 == 0 || it.i4 % 4 == 0) &&
                  ((uintptr_t)it.a & 15) == 0;
   const int tile = v ? kVTile : kTile;
   it.nbx = (int32_t)((it.n1 + tile - 1) / tile);
@@ -727,18 +656,12 @@ void add_prep(TmbBatch& scalar, TmbBatch& vec, TmbItem it) {
 }
 
 template <int DT>
-bool launch_transposes(const dmt_plan* p, TmbBatch& b, hipStream_t s) {
-  if constexpr (DT == DMT_F32) return launch_items(p, b, tmb_transpose<float>, s);
-  else return launch_items(p, b, tmb_transpose16, s);
-}
-
-template <int DT>
 dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<TowerBwdWs>& ws,
                       const void* pooled, const void* tm_out, int64_t B, const float* dy_all,
                       float* dx_all, const dmt_tm_grads* gr, const char* keptp, char* wsp,
                       hipStream_t s) {
-  constexpr int eb = DT == DMT_F32 ? 4 : 2;
-  constexpr int V = Ew<DT>::V;
+  static_assert(DT != DMT_F32, "float32 towers: run_tm_bwd_f32");
+  constexpr int eb = 2;
   const char* x_all = (const char*)pooled;
   const int64_t Bp = ld_batch(B, eb);
   std::vector<int64_t> out_prefix(p->T + 1, 0);
@@ -780,9 +703,9 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
     it.src = x_of(t);
     it.dst = wsp + w.p;
     if (w.np_pad > 0 && !(keptp && kept[t].has_z)) {
-      if (DT != DMT_F32 && 32 % it.nf == 0 && it.n % 16 == 0) {
+      if (dots_mfma_ok(it.nf, it.n)) {
         dots_mfma.push_back(it);
-        nb_mfma.push_back(((B * it.nf + 31) / 32 + 3) / 4);
+        nb_mfma.push_back(dots_mfma_blocks(B, it.nf));
       } else {
         dots_simple.push_back(it);
         nb_simple.push_back((B * w.np_pad + kBlock - 1) / kBlock);
@@ -851,24 +774,24 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
       it.b = it.i2 ? (const void*)((const char*)tm_out + (size_t)B * out_prefix[t] * eb) : nullptr;
       it.o0 = wsp + w.dz; it.o1 = wsp + w.dzT;
       it.n0 = B; it.n1 = Bp; it.n2 = q.out_dim; it.i0 = O; it.i1 = (int32_t)w.Op;
-      add_prep<DT>(batch, prep16, it);
+      add_prep(batch, prep16, it);
     }
     {
       TmbItem it{};
-      it.a = wsp + w.dzT; it.o0 = gr[t].db_proj; it.n0 = Bp; it.n1 = B;
+      it.a = wsp + w.dzT; it.o0 = gr[t].db_proj; it.n0 = Bp;
       batch2.add(it, O);
     }
     // W^T [kin][Op] (a DLRM tower's goes into its combined weights below)
     if (!dlrm)
-      add_transpose<DT>(batch3, dot ? (const void*)wp_of(t) : q.w_proj, O, w.kin, w.kin,
+      add_transpose(batch3, dot ? (const void*)wp_of(t) : q.w_proj, O, w.kin, w.kin,
                         wsp + w.wT, w.Op);
     // z^T [kin][Bp]: the projection's input, transposed
     if (dot) {
-      if (w.np_pad > 0) add_transpose<DT>(batch3, z_of(t), B, w.np_pad, w.np_pad, wsp + w.zT, Bp);
-      add_transpose<DT>(batch3, x_of(t), B, wt, wt, wsp + w.zT + (size_t)w.np_pad * Bp * eb, Bp);
+      if (w.np_pad > 0) add_transpose(batch3, z_of(t), B, w.np_pad, w.np_pad, wsp + w.zT, Bp);
+      add_transpose(batch3, x_of(t), B, wt, wt, wsp + w.zT + (size_t)w.np_pad * Bp * eb, Bp);
     } else {
       const void* z = is_cross(q) ? xl_of(t, q.num_cross_layers) : x_of(t);
-      add_transpose<DT>(batch3, z, B, wt, wt, wsp + w.zT, Bp);
+      add_transpose(batch3, z, B, wt, wt, wsp + w.zT, Bp);
     }
     TmGroup g{};
     g.A1 = wsp + w.dz; g.lda1 = (int32_t)w.Op; g.K1 = (int32_t)w.Op;
@@ -896,21 +819,21 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
         it.o0 = wsp + w.dz2; it.o1 = wsp + w.dz2T;
         it.n0 = BF; it.n1 = BFp; it.n2 = q.out_dim; it.i0 = F; it.i1 = (int32_t)w.Fp;
         it.i3 = nf; it.i4 = F;
-        add_prep<DT>(batch, prep16, it);
+        add_prep(batch, prep16, it);
       }
       {
         TmbItem it{};
-        it.a = wsp + w.dz2T; it.o0 = gr[t].db_cross[0]; it.n0 = BFp; it.n1 = BF;
+        it.a = wsp + w.dz2T; it.o0 = gr[t].db_cross[0]; it.n0 = BFp;
         batch2.add(it, F);
       }
-      add_transpose<DT>(batch3, x_of(t), BF, n, n, wsp + w.x2T, BFp);
+      add_transpose(batch3, x_of(t), BF, n, n, wsp + w.x2T, BFp);
       // data gradient, both layers in one contraction per feature f: the pooled block's columns
       // f n .. f n + n - 1 receive [dz1 | dz2 of feature f] . [W1^T rows f n .. | W_f^T], so
       // grad_pooled is written once; the combined weights are rows of Op + Fp columns
       const int kc = (int)(w.Op + w.Fp);
-      add_transpose<DT>(batch3, q.w_proj, O, wt, wt, wsp + w.wcomb, kc, (int)w.Op);
+      add_transpose(batch3, q.w_proj, O, wt, wt, wsp + w.wcomb, kc, (int)w.Op);
       for (int f = 0; f < nf; ++f) {
-        add_transpose<DT>(batch3, q.w_cross[0], F, n, n,
+        add_transpose(batch3, q.w_cross[0], F, n, n,
                           wsp + w.wcomb + ((size_t)f * n * kc + w.Op) * eb, kc, (int)w.Fp);
         TmGroup g2{};
         g2.A0 = wsp + w.dz; g2.lda0 = (int32_t)w.Op; g2.K0 = (int32_t)w.Op;
@@ -931,9 +854,9 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
     }
   }
   ok &= launch_items(p, batch, tmb_prep_dy<DT>, s);
-  if constexpr (DT != DMT_F32) ok &= launch_items(p, prep16, tmb_prep_dy16<DT>, s);
+  ok &= launch_items(p, prep16, tmb_prep_dy16<DT>, s);
   ok &= launch_items(p, batch2, tmb_rowsum<DT>, s);
-  ok &= launch_transposes<DT>(p, batch3, s);
+  ok &= launch_items(p, batch3, tmb_transpose16, s);
   launch_groups<DT>(p, dgrad, s, false, DMT_K_TM_BWD_GEMM);
   launch_groups<DT>(p, dgrad2, s, false, DMT_K_TM_BWD_GEMM);
   launch_groups<DT>(p, wgrad, s, false, DMT_K_TM_BWD_GEMM);
@@ -964,13 +887,13 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
       TmbItem it{};
       it.a = x_of(t); it.b = wsp + w.dZ; it.o0 = dx_of(t); it.n0 = B;
       it.i0 = p->tower_ntab[t]; it.i1 = p->tower_uniform_dim[t]; it.i2 = w.np_pad; it.i3 = w.kin;
-      if (DT != DMT_F32 && it.i1 % 8 == 0) batch3.add(it, (B * (wt / 8) + kBlock - 1) / kBlock);
+      if (it.i1 % 8 == 0) batch3.add(it, (B * (wt / 8) + kBlock - 1) / kBlock);
       else batch2.add(it, (B * wt + kBlock - 1) / kBlock);
     }
   }
   ok &= launch_items(p, batch, tmb_sum_slices, s);
   ok &= launch_items(p, batch2, tmb_dot_bwd<DT>, s);
-  if constexpr (DT != DMT_F32) ok &= launch_items(p, batch3, tmb_dot_bwd8<DT>, s);
+  ok &= launch_items(p, batch3, tmb_dot_bwd8<DT>, s);
 
   // ---- cross towers: layers from the last to the first; dx0 accumulates in the output block,
   // where the first layer's data gradient then lands on top of it
@@ -985,30 +908,23 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
         TmbItem it{};
         it.a = wsp + w.dxn; it.b = x_of(t); it.c = u_of(t, l); it.o0 = wsp + w.du; it.o1 = dx_of(t);
         it.i0 = l == q.num_cross_layers - 1; it.i1 = l == 0;
-        if constexpr (DT == DMT_F32) {
-          it.n0 = B * wt;
-          it.nbx = (int32_t)ew_blocks(it.n0, V);
-          batch.add(it, it.nbx);
-          add_transpose<DT>(batch2, wsp + w.du, B, wt, wt, wsp + w.duT, Bp);
-        } else {                                     // du and du^T from one pass
-          it.o2 = wsp + w.duT; it.n0 = B; it.n1 = Bp; it.i2 = wt;
-          it.nbx = (int32_t)((Bp + kVTile - 1) / kVTile);
-          prep_t.add(it, (int64_t)it.nbx * ((wt + kVTile - 1) / kVTile));
-        }
+        it.o2 = wsp + w.duT; it.n0 = B; it.n1 = Bp; it.i2 = wt;
+        it.nbx = (int32_t)((Bp + kVTile - 1) / kVTile);
+        prep_t.add(it, (int64_t)it.nbx * ((wt + kVTile - 1) / kVTile));
       }
-      add_transpose<DT>(batch2, xl_of(t, l), B, wt, wt, wsp + w.zT, Bp);
+      add_transpose(batch2, xl_of(t, l), B, wt, wt, wsp + w.zT, Bp);
       {
         TmbItem it{};
-        it.a = wsp + w.duT; it.o0 = gr[t].db_cross[l]; it.n0 = Bp; it.n1 = B;
+        it.a = wsp + w.duT; it.o0 = gr[t].db_cross[l]; it.n0 = Bp;
         batch3.add(it, wt);
       }
       if (q.kind == DMT_TM_CROSS_LOWRANK_LINEAR) {
         // stage 1: dt = du U_l (float32) and dU_l = du^T t_l; stage 2, once dt is rounded and
         // transposed: dx_l = dt V_l + dx_{l+1} and dV_l = dt^T x_l
         const int r = q.feat_out;
-        add_transpose<DT>(batch2, wsp + w.tl[l], B, r, r, wsp + w.tT, Bp);
-        add_transpose<DT>(batch2, q.w_cross[2 * l + 1], wt, r, r, wsp + w.uT, wt);     // U_l^T [r][wt]
-        add_transpose<DT>(batch2, q.w_cross[2 * l], r, wt, wt, wsp + w.vT, w.rp);      // V_l^T [wt][rp]
+        add_transpose(batch2, wsp + w.tl[l], B, r, r, wsp + w.tT, Bp);
+        add_transpose(batch2, q.w_cross[2 * l + 1], wt, r, r, wsp + w.uT, wt);     // U_l^T [r][wt]
+        add_transpose(batch2, q.w_cross[2 * l], r, wt, wt, wsp + w.vT, w.rp);      // V_l^T [wt][rp]
         TmGroup g1{};
         g1.A1 = wsp + w.du; g1.lda1 = wt; g1.K1 = wt;
         g1.W = wsp + w.uT; g1.ldw = wt;
@@ -1033,7 +949,7 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
           TmbItem it{};
           it.a = wsp + w.dtf; it.o0 = wsp + w.dtq; it.o1 = wsp + w.dtT;
           it.n0 = B; it.n1 = Bp; it.n2 = r; it.i0 = r; it.i1 = w.rp;
-          add_prep<DT>(prep_dt, prep_dt16, it);
+          add_prep(prep_dt, prep_dt16, it);
         }
         TmGroup g2{};
         g2.A1 = wsp + w.dtq; g2.lda1 = w.rp; g2.K1 = w.rp;
@@ -1057,7 +973,7 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
         }
         continue;
       }
-      add_transpose<DT>(batch2, q.w_cross[l], wt, wt, wt, wsp + w.wlT, wt);
+      add_transpose(batch2, q.w_cross[l], wt, wt, wt, wsp + w.wlT, wt);
       TmGroup g{};
       g.A1 = wsp + w.du; g.lda1 = wt; g.K1 = wt;
       g.W = wsp + w.wlT; g.ldw = wt;
@@ -1079,19 +995,194 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
         sums.add(it, ((int64_t)wt * wt + kBlock - 1) / kBlock);
       }
     }
-    ok &= launch_items(p, batch, tmb_cross_prep<DT>, s);
-    if constexpr (DT != DMT_F32) ok &= launch_items(p, prep_t, tmb_cross_prep_t<DT>, s);
-    ok &= launch_transposes<DT>(p, batch2, s);
+    ok &= launch_items(p, prep_t, tmb_cross_prep_t<DT>, s);
+    ok &= launch_items(p, batch2, tmb_transpose16, s);
     ok &= launch_items(p, batch3, tmb_rowsum<DT>, s);
     launch_groups<DT>(p, dgrad, s, false, DMT_K_TM_BWD_GEMM);
     launch_groups<DT>(p, wgrad, s, false, DMT_K_TM_BWD_GEMM);
     ok &= launch_items(p, sums, tmb_sum_slices, s);
     // low-rank towers, stage 2 (the slices' buffer is free again after the sums above)
     ok &= launch_items(p, prep_dt, tmb_prep_dy<DT>, s);
-    if constexpr (DT != DMT_F32) ok &= launch_items(p, prep_dt16, tmb_prep_dy16<DT>, s);
+    ok &= launch_items(p, prep_dt16, tmb_prep_dy16<DT>, s);
     launch_groups<DT>(p, dgrad2, s, false, DMT_K_TM_BWD_GEMM);
     launch_groups<DT>(p, wgrad2, s, false, DMT_K_TM_BWD_GEMM);
     ok &= launch_items(p, sums2, tmb_sum_slices, s);
+  }
+  if (!ok) return DMT_ENOTSUP;
+  return hipGetLastError() == hipSuccess ? DMT_OK : DMT_EHIP;
+}
+
+// Float32 towers: every operand is read where it lies (dmt_tm_f32.h), so a stage is one launch: the
+// projections' data, weight and bias gradients of all towers, then, layer by layer, a cross
+// tower's elementwise step and its contractions.
+dmt_status run_tm_bwd_f32(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<TowerBwdWs>& ws,
+                          const float* x_all, const float* y_all, int64_t B, const float* dy_all,
+                          float* dx_all, const dmt_tm_grads* gr, const char* keptp, char* wsp,
+                          hipStream_t s) {
+  std::vector<TmKept> kept;
+  if (keptp) plan_tm_kept(p, tp, B, 4, &kept);
+  auto x_of = [&](int t) { return x_all + B * p->width_prefix[t]; };
+  auto dx_of = [&](int t) { return dx_all + B * p->width_prefix[t]; };
+  auto at = [&](size_t off) { return (float*)(wsp + off); };
+  auto xl_of = [&](int t, int l) -> const float* {
+    if (l == 0) return x_of(t);
+    return keptp ? (const float*)(keptp + kept[t].x[l - 1]) : at(ws[t].xl[l - 1]);
+  };
+  auto u_of = [&](int t, int l) -> const float* {
+    return keptp ? (const float*)(keptp + kept[t].u[l]) : at(ws[t].u[l]);
+  };
+  auto z_of = [&](int t) -> const float* {
+    return keptp && kept[t].has_z ? (const float*)(keptp + kept[t].z) : at(ws[t].p);
+  };
+  bool ok = true;
+  int max_layers = 0;
+
+  // ---- what the forward did not keep: dot terms, cross layers (low-rank: t_l in any case)
+  std::vector<TmAuxItem> dots_mfma, dots_simple;
+  std::vector<int64_t> nb_mfma, nb_simple;
+  for (int32_t t = 0; t < p->T; ++t) {
+    if (is_cross(tp[t])) max_layers = std::max(max_layers, tp[t].num_cross_layers);
+    if (tp[t].kind != DMT_TM_DOT_LINEAR || ws[t].np_pad == 0 || (keptp && kept[t].has_z)) continue;
+    TmAuxItem it{};
+    it.nf = p->tower_ntab[t]; it.n = p->tower_uniform_dim[t]; it.np = ws[t].np; it.np_pad = ws[t].np_pad;
+    it.src = x_of(t);
+    it.dst = at(ws[t].p);
+    if (dots_mfma_ok(it.nf, it.n)) {
+      dots_mfma.push_back(it);
+      nb_mfma.push_back(dots_mfma_blocks(B, it.nf));
+    } else {
+      dots_simple.push_back(it);
+      nb_simple.push_back((B * it.np_pad + kBlock - 1) / kBlock);
+    }
+  }
+  launch_aux<DMT_F32>(p, B, dots_mfma, nb_mfma, 0, s);
+  launch_aux<DMT_F32>(p, B, dots_simple, nb_simple, 1, s);
+  std::vector<TmF32Group> groups, groups2;
+  auto group = [&](const float* A, int lda, int K, const float* W, int ldw, int M, int N, float* C, int ldc,
+                   int epi) {
+    TmF32Group g{};
+    g.A1 = A; g.lda1 = lda; g.K1 = K; g.W1 = W; g.ldw1 = ldw;
+    g.M = M; g.N = N; g.C = C; g.ldc = ldc; g.epi = epi;
+    return g;
+  };
+  for (int l = 0; l < max_layers; ++l) {
+    for (int32_t t = 0; t < p->T; ++t) {
+      const dmt_tm_params& q = tp[t];
+      if (!is_cross(q) || l >= q.num_cross_layers) continue;
+      const int wt = p->tower_width[t], r = q.feat_out;
+      const bool low = q.kind == DMT_TM_CROSS_LOWRANK_LINEAR;
+      const float* xl = xl_of(t, l);
+      if (low)
+        groups.push_back(group(xl, wt, wt, (const float*)q.w_cross[2 * l], wt, (int)B, r, at(ws[t].tl[l]), r, EPI_BIAS));
+      if (keptp) continue;
+      TmF32Group g = low ? group(at(ws[t].tl[l]), r, r, (const float*)q.w_cross[2 * l + 1], r, (int)B, wt,
+                                 at(ws[t].xl[l]), wt, EPI_CROSS)
+                         : group(xl, wt, wt, (const float*)q.w_cross[l], wt, (int)B, wt, at(ws[t].xl[l]), wt,
+                                 EPI_CROSS);
+      g.bias = (const float*)q.b_cross[l];
+      g.X0 = x_of(t); g.ldx = wt; g.XL = xl; g.ldxl = wt;
+      g.U = at(ws[t].u[l]);
+      groups2.push_back(g);
+    }
+    launch_f32(p, groups, s, DMT_K_TM_BWD_GEMM);
+    launch_f32(p, groups2, s, DMT_K_TM_BWD_GEMM);
+  }
+
+  // ---- projections
+  TmbBatch dots, prep;
+  int64_t out_prefix = 0;
+  for (int32_t t = 0; t < p->T; ++t) {
+    const dmt_tm_params& q = tp[t];
+    const TowerBwdWs& w = ws[t];
+    const int wt = p->tower_width[t], nf = p->tower_ntab[t], ldy = q.out_dim;
+    const float* dy = dy_all + B * out_prefix;
+    const float* mask = q.kind == DMT_TM_LINEAR_RELU ? y_all + B * out_prefix : nullptr;
+    out_prefix += q.out_dim;
+    const float* W = (const float*)q.w_proj;
+    const float* z = is_cross(q) ? xl_of(t, q.num_cross_layers) : x_of(t);
+    const bool dot = q.kind == DMT_TM_DOT_LINEAR, dlrm = q.kind == DMT_TM_DLRM;
+    const int F = dlrm ? q.feat_out : 0, O = ldy - nf * F, np = w.np, kin = np + wt;
+    auto dgrad = [&](const float* Wk, int N, float* C, int ldc) {
+      TmF32Group g = group(dy, ldy, O, Wk, kin, (int)B, N, C, ldc, EPI_F32);
+      g.wcol = 1; g.mask = mask;
+      groups.push_back(g);
+    };
+    auto wgrad = [&](const float* zk, int ldz, int N, float* C, float* db) {
+      TmF32Group g = group(dy, ldy, (int)B, zk, ldz, O, N, C, kin, EPI_F32);
+      g.acol = 1; g.wcol = 1; g.mask = mask; g.db = db;
+      groups.push_back(g);
+    };
+    wgrad(z, wt, wt, gr[t].dw_proj + np, gr[t].db_proj);
+    if (dot) {
+      if (np > 0) {
+        wgrad(z_of(t), w.np_pad, np, gr[t].dw_proj, nullptr);
+        dgrad(W, np, at(w.dZ), w.kin);
+      }
+      dgrad(W + np, wt, at(w.dZ) + w.np_pad, w.kin);
+      TmbItem it{};
+      it.a = x_of(t); it.b = at(w.dZ); it.o0 = dx_of(t); it.n0 = B;
+      it.i0 = nf; it.i1 = p->tower_uniform_dim[t]; it.i2 = w.np_pad; it.i3 = w.kin;
+      dots.add(it, (B * wt + kBlock - 1) / kBlock);
+    } else if (dlrm) {
+      // feature f's slice of the pooled block: [dy flat | dy of feature f] . [W rows | shared W]
+      const int n = p->tower_uniform_dim[t];
+      const float* Wf = (const float*)q.w_cross[0];
+      for (int f = 0; f < nf; ++f) {
+        TmF32Group g = group(dy + O + f * F, ldy, F, Wf, n, (int)B, n, dx_of(t) + f * n, wt, EPI_F32);
+        g.A0 = dy; g.lda0 = ldy; g.K0 = O; g.W0 = W + f * n; g.ldw0 = wt; g.wcol = 1;
+        groups.push_back(g);
+      }
+      // the shared layer's weights: a sum over rows (sample, feature)
+      TmF32Group g = group(dy + O, ldy, (int)(B * nf), x_of(t), n, F, n, gr[t].dw_cross[0], n, EPI_F32);
+      g.acol = 1; g.wcol = 1; g.adiv = nf; g.lda2 = F; g.db = gr[t].db_cross[0];
+      groups.push_back(g);
+    } else {
+      dgrad(W, wt, is_cross(q) ? at(w.dxn) : dx_of(t), wt);
+    }
+  }
+  launch_f32(p, groups, s, DMT_K_TM_BWD_GEMM);
+  ok &= launch_items(p, dots, tmb_dot_bwd<DMT_F32>, s);
+
+  // ---- cross layers, last to first
+  for (int l = max_layers - 1; l >= 0; --l) {
+    for (int32_t t = 0; t < p->T; ++t) {
+      const dmt_tm_params& q = tp[t];
+      if (!is_cross(q) || l >= q.num_cross_layers) continue;
+      const TowerBwdWs& w = ws[t];
+      const int wt = p->tower_width[t];
+      TmbItem it{};
+      it.a = at(w.dxn); it.b = x_of(t); it.c = u_of(t, l); it.o0 = at(w.du); it.o1 = dx_of(t);
+      it.n0 = B * wt; it.i0 = l == q.num_cross_layers - 1; it.i1 = l == 0;
+      it.nbx = (int32_t)ew_blocks(it.n0);
+      prep.add(it, it.nbx);
+      float* dx_l = l == 0 ? dx_of(t) : at(w.dxn);
+      const float* du = at(w.du);
+      // dx_l += dv . V with V stored [K][wt]; dV = dv^T x_l
+      auto pair = [&](std::vector<TmF32Group>& gs, const float* dv, int K, const void* V, float* dV, float* db) {
+        TmF32Group g = group(dv, K, K, (const float*)V, wt, (int)B, wt, dx_l, wt, EPI_F32_ADD);
+        g.wcol = 1;
+        gs.push_back(g);
+        g = group(dv, K, (int)B, xl_of(t, l), wt, K, wt, dV, wt, EPI_F32);
+        g.acol = 1; g.wcol = 1; g.db = db;
+        gs.push_back(g);
+      };
+      if (q.kind == DMT_TM_CROSS_LINEAR) {
+        pair(groups, du, wt, q.w_cross[l], gr[t].dw_cross[l], gr[t].db_cross[l]);
+        continue;
+      }
+      // low-rank: dt = du U_l and dU_l = du^T t_l, then the same with dt and V_l
+      const int r = q.feat_out;
+      TmF32Group g = group(du, wt, wt, (const float*)q.w_cross[2 * l + 1], r, (int)B, r, at(w.dtf), r, EPI_F32);
+      g.wcol = 1;
+      groups.push_back(g);
+      g = group(du, wt, (int)B, at(w.tl[l]), r, wt, r, gr[t].dw_cross[2 * l + 1], r, EPI_F32);
+      g.acol = 1; g.wcol = 1; g.db = gr[t].db_cross[l];
+      groups.push_back(g);
+      pair(groups2, at(w.dtf), r, q.w_cross[2 * l], gr[t].dw_cross[2 * l], nullptr);
+    }
+    ok &= launch_items(p, prep, tmb_cross_prep, s);
+    launch_f32(p, groups, s, DMT_K_TM_BWD_GEMM);
+    launch_f32(p, groups2, s, DMT_K_TM_BWD_GEMM);
   }
   if (!ok) return DMT_ENOTSUP;
   return hipGetLastError() == hipSuccess ? DMT_OK : DMT_EHIP;
@@ -1159,8 +1250,8 @@ extern "C" dmt_status dmt_tower_module_bwd(const dmt_plan* plan, const dmt_tm_pa
   char* wsp = (char*)workspace;
   switch (dtype) {
     case DMT_F32:
-      return run_tm_bwd<DMT_F32>(plan, per_tower, ws, pooled, tm_out, B, grad_tm_out, grad_pooled,
-                                 grads, keptp, wsp, s);
+      return run_tm_bwd_f32(plan, per_tower, ws, (const float*)pooled, (const float*)tm_out, B, grad_tm_out,
+                            grad_pooled, grads, keptp, wsp, s);
     case DMT_F16:
       return run_tm_bwd<DMT_F16>(plan, per_tower, ws, pooled, tm_out, B, grad_tm_out, grad_pooled,
                                  grads, keptp, wsp, s);

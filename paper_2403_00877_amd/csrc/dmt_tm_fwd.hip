@@ -18,8 +18,9 @@
 // are a Gram matrix per sample: 32 consecutive (sample, feature) rows form one
 // 32 x 32 MFMA tile whose diagonal blocks hold every sample's dots, so the
 // operand is read once, straight from global memory, as both A and B.
-// float32 towers (a latency-bound toy size) use plain FMA kernels.
+// float32 towers run on the float32 matrix instructions (dmt_tm_f32.h).
 #include "dmt_tm_gemm.h"
+#include "dmt_tm_f32.h"
 
 namespace {
 
@@ -148,13 +149,14 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
     it.src = x_all + (size_t)B * p->width_prefix[t] * eb;
     it.dst = z_of(t);
     if (fused[t]) {
-    } else if (DT != DMT_F32 && 32 % it.nf == 0 && it.n % 16 == 0) {
+    } else if (dots_mfma_ok(it.nf, it.n)) {
       dots_mfma.push_back(it);
-      nb_mfma.push_back(((B * it.nf + 31) / 32 + 3) / 4);
+      nb_mfma.push_back(dots_mfma_blocks(B, it.nf));
     } else {
       dots_simple.push_back(it);
       nb_simple.push_back((B * w.np_pad + kBlock - 1) / kBlock);
     }
+    if (DT == DMT_F32) continue;                    // reads the projection's weights as they are
     it.src = q.w_proj;
     it.dst = wp_of(t);
     packs.push_back(it);
@@ -163,6 +165,17 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
   launch_aux<DT>(p, B, dots_mfma, nb_mfma, 0, s);
   launch_aux<DT>(p, B, dots_simple, nb_simple, 1, s);
   launch_aux<DT>(p, B, packs, nb_pack, 2, s);
+
+  auto launch = [&](std::vector<TmGroup>& gs, bool dots = false) {
+    if constexpr (DT == DMT_F32) {
+      std::vector<TmF32Group> f32;
+      for (const TmGroup& g : gs) f32.push_back(f32_group(g));
+      gs.clear();
+      launch_f32(p, f32, s, DMT_K_TM_GEMM);
+    } else {
+      launch_groups<DT>(p, gs, s, dots);
+    }
+  };
 
   // cross layers, one grouped launch per layer index (low-rank layers: t = V_l x_l first)
   std::vector<TmGroup> groups, groups_t;
@@ -196,8 +209,8 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
       g.M = (int32_t)B; g.N = wt; g.epi = EPI_CROSS;
       groups.push_back(g);
     }
-    launch_groups<DT>(p, groups_t, s);
-    launch_groups<DT>(p, groups, s);
+    launch(groups_t);
+    launch(groups);
   }
 
   // projections of every tower
@@ -213,6 +226,7 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
     if (q.kind == DMT_TM_DOT_LINEAR) {
       g.A0 = z_of(t); g.lda0 = ws[t].np_pad; g.K0 = ws[t].np_pad;
       g.W = wp_of(t); g.ldw = ws[t].np_pad + wt;
+      if (DT == DMT_F32) { g.K0 = ws[t].np; g.W = q.w_proj; g.ldw = ws[t].np + wt; }
     } else if (q.kind == DMT_TM_CROSS_LINEAR || q.kind == DMT_TM_CROSS_LOWRANK_LINEAR) {
       g.A1 = x_layer(t, q.num_cross_layers - 1);
     }
@@ -243,9 +257,13 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
       groups.push_back(g);
     }
   }
-  launch_groups<DT>(p, groups, s);
-  launch_groups<DT>(p, groups_feat, s);
-  if constexpr (DT != DMT_F32) launch_groups<DT>(p, groups_fused, s, true);
+  if constexpr (DT == DMT_F32) {
+    groups.insert(groups.end(), groups_feat.begin(), groups_feat.end());
+    groups_feat.clear();
+  }
+  launch(groups);
+  launch(groups_feat);
+  launch(groups_fused, true);
   return hipGetLastError() == hipSuccess ? DMT_OK : DMT_EHIP;
 }
 

@@ -159,3 +159,33 @@ def test_lowrank_cross_module(dt, rank):
     w.tm_dtype = dt
     w.pooled_dtype = dt
     check_tm(w, chained=dt == "bf16" and rank == 64)
+
+
+@pytest.mark.parametrize("batch,out,dim", [(1, 1, 4), (31, 33, 12), (33, 32, 16), (65, 31, 20), (1100, 64, 64)])
+@pytest.mark.parametrize("kind", ["linear_relu", "dot_linear"])
+def test_float32_tiles_segments_and_k_splits(kind, batch, out, dim):
+    """The float32 contraction at the edges of its 32 x 32 tiles and of its steps of 8 k, with one and
+    with several waves per tile; 7 features: 21 dot terms, so a weight row is not 16-byte aligned, and
+    dims that are (12, 20) and are not (4) served by the Gram-tile kernel."""
+    w = wl.scaled(wl.mid(), max_rows=300, batch=batch, num_tables=9)
+    w.table_dtype = "f32"
+    w.dims = [dim] * 9
+    w.table_to_tower = [0] * 7 + [1] * 2
+    w.tm_kind = kind
+    w.tm_out = [out, out]
+    w.tm_dtype = w.pooled_dtype = "f32"
+    check_tm(w)
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("nf", [2, 3, 7, 13, 31, 32, 33])
+def test_dot_terms_of_any_feature_count(nf, dt):
+    """Feature counts that do and do not divide a 32-row Gram tile, one sample per tile (17 .. 32) and
+    more features than a tile has rows (33: one thread per term); dim 24 leaves half of a 16-column
+    step empty."""
+    w = wl.scaled(wl.mid(), max_rows=100, batch=45, num_tables=nf)
+    w.dims = [24] * nf
+    w.table_to_tower = [0] * nf
+    w.tm_out = [40]
+    w.tm_dtype = w.pooled_dtype = dt
+    check_tm(w)

@@ -492,3 +492,23 @@ def test_whole_tower_step_chains_into_the_sparse_update(which):
                      "%s chained rows of table %d" % (w.name, f))
         assert_close(to_f64(dw.states[f][sel]), ref["new_state"][m].astype(np.float32), rtol,
                      "%s chained state of table %d" % (w.name, f))
+
+
+@pytest.mark.parametrize("batch,out,dim", [(31, 33, 12), (33, 32, 16), (65, 31, 20), (1100, 64, 64)])
+@pytest.mark.parametrize("kind", ["linear_relu", "dot_linear", "dlrm", "cross_linear"])
+def test_float32_operands_read_where_they_lie(kind, batch, out, dim):
+    """The float32 backward at the edges of its tiles and steps, k shared by one and by up to sixteen
+    waves, operands in both orientations, the ReLU mask and the two-level rows of a per-feature
+    layer."""
+    w = wl.scaled(wl.mid(), max_rows=300, batch=batch, num_tables=9)
+    w.table_dtype = "f32"
+    w.dims = [dim] * 9
+    w.table_to_tower = [0] * 7 + [1] * 2
+    w.tm_kind = kind
+    w.tm_out = [out, out]
+    w.tm_cross_layers = 2 if kind == "cross_linear" else 0
+    if kind == "dlrm":
+        w.tm_feat_out = 5
+        w.tm_out = [out + 7 * 5, out + 2 * 5]
+    w.tm_dtype = w.pooled_dtype = "f32"
+    check_tm_bwd(w, rtol=1e-4)
