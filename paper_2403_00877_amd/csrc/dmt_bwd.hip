@@ -41,7 +41,18 @@ constexpr int kDigitsPerThread = (kMaxRadix + kBlock - 1) / kBlock;
 constexpr int kSortTile = kBlock * kSortItems;   // records per sort block
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kBlock * kScanItems;   // records per head-scan block
-constexpr int kReduceTile = 128;                 // sorted records per reduce tile
+// Sorted records per reduce tile (one wave walks one): 128, or down to 16 where a call is too small
+// to fill the chip with tiles of 128.  A wave takes about 0.25 us per record, so 2300 records in
+// tiles of 128 are 18 waves of 30 us (tiles of 16: 7.7); but every run that crosses a tile
+// boundary costs a partial sum and a share of the fix-up, so tiles shrink only until there are
+// kFillTiles of them (four waves per SIMD at 4096, eight at 8192).
+constexpr int kReduceTile = 128, kMinReduceTile = 16;
+inline int64_t fill_tiles(int max_dim) { return max_dim <= 128 ? 8192 : 4096; }
+inline int reduce_tile(int64_t nnz, int max_dim) {
+  int tile = kReduceTile;
+  while (tile > kMinReduceTile && (nnz + tile / 2 - 1) / (tile / 2) <= fill_tiles(max_dim)) tile /= 2;
+  return tile;
+}
 #ifndef DMT_RU
 #define DMT_RU 4
 #endif
@@ -59,11 +70,11 @@ struct BwdWs {
   uint32_t* blk_table;    // [nblk_sort] table of each sort block
   uint32_t* blk_heads;    // [nblk_scan]
   uint32_t* seg_off;      // [nnz + 1]
-  uint32_t* tile_first;   // [ntiles + 1] run heads before each reduce tile
   uint32_t* num_unique;   // [1]
-  float* partials;        // [2 * ntiles][Dmax]
+  float* partials;        // [2 * tiles][Dmax]
   size_t bytes;
   int64_t nblk_sort, nblk_scan, ntiles;
+  int tile;               // records per reduce tile
 };
 
 BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
@@ -71,7 +82,12 @@ BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
   const int64_t n = nnz > 0 ? nnz : 1;
   w.nblk_sort = (n + kSortTile - 1) / kSortTile + p->F;   // every table may end in a partial block
   w.nblk_scan = (n + kScanTile - 1) / kScanTile;
-  w.ntiles = (n + kReduceTile - 1) / kReduceTile;
+  w.tile = reduce_tile(n, p->max_dim);
+  w.ntiles = (n + w.tile - 1) / w.tile;
+  // partial slots for the tiles of this and of every smaller call (a workspace sized for the largest
+  // serves all of them)
+  const int64_t slots = std::max((n + kReduceTile - 1) / kReduceTile,
+                                 std::min((n + kMinReduceTile - 1) / kMinReduceTile, fill_tiles(p->max_dim)));
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
@@ -86,9 +102,8 @@ BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
   w.blk_table = (uint32_t*)take(sizeof(uint32_t) * w.nblk_sort);
   w.blk_heads = (uint32_t*)take(sizeof(uint32_t) * (w.nblk_scan + 1));
   w.seg_off = (uint32_t*)take(sizeof(uint32_t) * (n + 1));
-  w.tile_first = (uint32_t*)take(sizeof(uint32_t) * (w.ntiles + 1));
   w.num_unique = (uint32_t*)take(sizeof(uint32_t) * 64);
-  w.partials = (float*)take(sizeof(float) * 2 * w.ntiles * p->max_dim);
+  w.partials = (float*)take(sizeof(float) * 2 * slots * p->max_dim);
   w.bytes = off;
   return w;
 }
@@ -452,7 +467,7 @@ __global__ __launch_bounds__(1024) void heads_scan(uint32_t* __restrict__ blk_he
 
 __global__ __launch_bounds__(kBlock) void heads_write(
     const uint64_t* __restrict__ pk, int64_t nnz, const uint32_t* __restrict__ blk_heads,
-    uint32_t* __restrict__ seg_off, uint32_t* __restrict__ tile_first) {
+    uint32_t* __restrict__ seg_off) {
   __shared__ uint32_t sm[kBlock / 64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t wave_base = (int64_t)blockIdx.x * kScanTile + (int64_t)wave * (kScanItems * 64);
@@ -469,7 +484,6 @@ __global__ __launch_bounds__(kBlock) void heads_write(
     const uint32_t mine = before + (uint32_t)__popcll(ballots[i] & lt);   // heads before p
     const bool head = (ballots[i] >> lane) & 1;
     if (p < nnz) {
-      if ((p & (kReduceTile - 1)) == 0) tile_first[p / kReduceTile] = mine;
       if (head) seg_off[mine] = (uint32_t)p;
       if (p == nnz - 1) seg_off[mine + (head ? 1 : 0)] = (uint32_t)nnz;
     }
@@ -559,7 +573,7 @@ constexpr int kWaveUnroll = 6;                   // gradient rows the wave-per-t
 static_assert(kReduceUnroll <= kQueueSlots && kWaveUnroll <= kQueueSlotsWave,
               "a step of the walk parks at most as many runs as the queue holds");
 
-// Each group of GL = 2^LG lanes walks one tile of kReduceTile sorted records,
+// Each group of GL = 2^LG lanes walks one tile of `tile` sorted records,
 // summing the bags' gradient slices run by run (float32, record order).  Runs
 // that lie wholly inside the tile are parked in an LDS queue (their gradient
 // sum, row and state address); the queue is drained four rows at a time, so the
@@ -572,7 +586,7 @@ template <int TD, int LG, bool UD>
 __global__ __launch_bounds__(kBlock) void bwd_reduce_update(
     const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ pk, int64_t nnz, uint32_t B,
     uint32_t nbags, uint32_t total_rows, const float* __restrict__ grad,
-    float* __restrict__ partials, int Dmax, int64_t ntiles, int64_t blocks_per_xcd, float lr,
+    float* __restrict__ partials, int Dmax, int tile, int64_t ntiles, int64_t blocks_per_xcd, float lr,
     float eps, const unsigned long long* __restrict__ err_offsets) {
   if (*err_offsets != ~0ULL) return;              // malformed offsets: the records mean nothing
   constexpr int GL = 1 << LG, NG = kBlock >> LG;
@@ -598,8 +612,8 @@ __global__ __launch_bounds__(kBlock) void bwd_reduce_update(
   bool cont_prev = false, cont_next = false;
   uint32_t carry = 0;
   if (live) {
-    p0 = t * kReduceTile;
-    n = (int)min((int64_t)kReduceTile, nnz - p0);
+    p0 = t * tile;
+    n = (int)min((int64_t)tile, nnz - p0);
     const uint32_t first_key = (uint32_t)(pk[p0] >> 32);
     if (p0 > 0) {
       carry = (uint32_t)(pk[p0 - 1] >> 32);
@@ -670,7 +684,7 @@ __global__ __launch_bounds__(kBlock) void bwd_reduce_update(
     qn = 0;
   };
 
-  for (int sub = 0; sub < kReduceTile; sub += GL) {
+  for (int sub = 0; sub < tile; sub += GL) {
     const int cnt = min(GL, n - sub);            // <= 0 once this group's tile is done
     if (!__any(cnt > 0)) break;
     // every lane prepares its own record: gradient offset, row and state address
@@ -833,7 +847,7 @@ template <int TD, int EPL, bool UD>
 __global__ __launch_bounds__(kBlock) void bwd_reduce_update_wave(
     const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ pk, int64_t nnz, uint32_t B,
     uint32_t nbags, uint32_t total_rows, const float* __restrict__ grad,
-    float* __restrict__ partials, int Dmax, int64_t ntiles, int64_t blocks_per_xcd, float lr,
+    float* __restrict__ partials, int Dmax, int tile, int64_t ntiles, int64_t blocks_per_xcd, float lr,
     float eps, const unsigned long long* __restrict__ err_offsets) {
   if (*err_offsets != ~0ULL) return;              // malformed offsets: the records mean nothing
   constexpr int NW = kBlock / 64;
@@ -853,8 +867,8 @@ __global__ __launch_bounds__(kBlock) void bwd_reduce_update_wave(
   const bool lane_on = lane * EPL < Dmax;
   const Vec* __restrict__ gradv = (const Vec*)grad;
 
-  const int64_t p0 = t * kReduceTile;
-  const int n = (int)min((int64_t)kReduceTile, nnz - p0);
+  const int64_t p0 = t * tile;
+  const int n = (int)min((int64_t)tile, nnz - p0);
   const uint32_t first_key = __builtin_amdgcn_readfirstlane((uint32_t)(pk[p0] >> 32));
   uint32_t carry = 0;
   bool cont_prev = false;
@@ -1056,7 +1070,7 @@ __global__ __launch_bounds__(kBlock) void bwd_reduce_update_wave(
 
 // The tile walk for rows of at most 128 columns, built to spend as few instructions per sorted
 // record as the hardware allows and to keep a wave's row updates off its critical path.
-//  * One wave per tile of kReduceTile records.  A tile is cut into chunks of up to 64
+//  * One wave per tile of `tile` records.  A tile is cut into chunks of up to 64
 //    consecutive records of ONE table, one record per lane (two chunks, more only where the
 //    tile straddles a table boundary), so everything a table decides (row width, gradient
 //    base, row and state base) sits in scalar registers.
@@ -1091,7 +1105,7 @@ template <int TD>
 __global__ __launch_bounds__(kLeanBlock) void bwd_reduce_update_lean(
     const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ pk, int64_t nnz, uint32_t B,
     uint32_t bag_mul, uint32_t bag_shift, uint32_t F, const float* __restrict__ grad,
-    float* __restrict__ partials, int Dmax, int64_t ntiles, int64_t blocks_per_xcd, float lr,
+    float* __restrict__ partials, int Dmax, int tile, int64_t ntiles, int64_t blocks_per_xcd, float lr,
     float eps, const unsigned long long* __restrict__ err_offsets) {
   if (*err_offsets != ~0ULL) return;              // malformed offsets: the records mean nothing
   constexpr int NW = kLeanBlock / 64;
@@ -1105,8 +1119,8 @@ __global__ __launch_bounds__(kLeanBlock) void bwd_reduce_update_lean(
   const int64_t tb = (int64_t)(blockIdx.x & 7) * blocks_per_xcd + (blockIdx.x >> 3);
   const int64_t t = tb * NW + wave;
   if (t >= ntiles) return;
-  const int64_t p0 = t * kReduceTile;
-  const int n = (int)min((int64_t)kReduceTile, nnz - p0);
+  const int64_t p0 = t * tile;
+  const int n = (int)min((int64_t)tile, nnz - p0);
   const int qd = lane >> 4, ql = lane & 15;        // row updates: quarter-wave qd, 8 columns from 8 ql
   float* const qbase = &q_g[wave][0][0];
 
@@ -1326,14 +1340,14 @@ template <int TD>
 __global__ __launch_bounds__(kFixBlock) void bwd_fixup_update(
     const DmtTableMeta* __restrict__ meta, uint32_t B, uint32_t nbags,
     const uint64_t* __restrict__ pk, int64_t nnz, uint32_t total_rows,
-    const float* __restrict__ partials, int Dmax, int log2_gl, int64_t ntiles, float lr, float eps,
+    const float* __restrict__ partials, int Dmax, int log2_gl, int tile, int64_t ntiles, float lr, float eps,
     const unsigned long long* __restrict__ err_offsets) {
   if (*err_offsets != ~0ULL) return;
   const int GL = 1 << log2_gl;
   const int64_t t0 = (int64_t)blockIdx.x * (kFixBlock >> log2_gl) + (threadIdx.x >> log2_gl);
   if (t0 >= ntiles - 1) return;
   const int gl = threadIdx.x & (GL - 1);
-  const int64_t p0 = t0 * kReduceTile, p1 = p0 + kReduceTile;    // p1 < nnz here
+  const int64_t p0 = t0 * tile, p1 = p0 + tile;    // p1 < nnz here
   // (the four records the decisions below look at are requested together: their latencies
   // would otherwise follow one another in every group)
   const uint64_t r_last = pk[p1 - 1], r_next = pk[p1], r_first = pk[p0], r_before = pk[p0 > 0 ? p0 - 1 : 0];
@@ -1351,12 +1365,12 @@ __global__ __launch_bounds__(kFixBlock) void bwd_fixup_update(
   // (gallop first: most runs end within a tile or two)
   int64_t t1 = t0 + 1, hi = ntiles;               // holds at t1, fails at hi
   for (int64_t step = 1; t1 + step < hi; step <<= 1) {
-    if ((uint32_t)(pk[(t1 + step) * kReduceTile] >> 32) == k_last) t1 += step;
+    if ((uint32_t)(pk[(t1 + step) * tile] >> 32) == k_last) t1 += step;
     else { hi = t1 + step; break; }
   }
   while (hi - t1 > 1) {
     const int64_t mid = (t1 + hi) >> 1;
-    if ((uint32_t)(pk[mid * kReduceTile] >> 32) == k_last) t1 = mid; else hi = mid;
+    if ((uint32_t)(pk[mid * tile] >> 32) == k_last) t1 = mid; else hi = mid;
   }
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   const bool on = gl * 4 < Dmax;
@@ -1441,7 +1455,7 @@ void launch_reduce_wave(const ReduceCall& c) {
                                             : bwd_reduce_update_wave<TD, EPL, false>;
   timed_launch(c.plan, DMT_K_BWD_REDUCE_UPDATE, c.s, kernel, per_xcd * 8, kBlock, c.plan->d_meta,
                c.sorted, c.nnz, (uint32_t)c.B, c.nbags, c.total_rows, c.grad, c.w->partials,
-               c.plan->max_dim, c.w->ntiles, per_xcd, c.lr, c.eps, c.plan->d_error + 1);
+               c.plan->max_dim, c.w->tile, c.w->ntiles, per_xcd, c.lr, c.eps, c.plan->d_error + 1);
 }
 
 // bag / B for bag < 2^31 as (bag * mul) >> (32 + shift); B = 1 is handled by the kernel.
@@ -1463,7 +1477,7 @@ void launch_reduce_lean(const ReduceCall& c) {
   bag_divider((uint32_t)c.B, mul, shift);
   timed_launch(c.plan, DMT_K_BWD_REDUCE_UPDATE, c.s, bwd_reduce_update_lean<TD>, per_xcd * 8, kLeanBlock,
                c.plan->d_meta, c.sorted, c.nnz, (uint32_t)c.B, mul, shift, (uint32_t)c.plan->F, c.grad,
-               c.w->partials, c.plan->max_dim, c.w->ntiles, per_xcd, c.lr, c.eps,
+               c.w->partials, c.plan->max_dim, c.w->tile, c.w->ntiles, per_xcd, c.lr, c.eps,
                c.plan->d_error + 1);
 }
 
@@ -1475,7 +1489,7 @@ void launch_reduce_grouped(const ReduceCall& c) {
                                             : bwd_reduce_update<TD, LG, false>;
   timed_launch(c.plan, DMT_K_BWD_REDUCE_UPDATE, c.s, kernel, per_xcd * 8, kBlock, c.plan->d_meta,
                c.sorted, c.nnz, (uint32_t)c.B, c.nbags, c.total_rows, c.grad, c.w->partials,
-               c.plan->max_dim, c.w->ntiles, per_xcd, c.lr, c.eps, c.plan->d_error + 1);
+               c.plan->max_dim, c.w->tile, c.w->ntiles, per_xcd, c.lr, c.eps, c.plan->d_error + 1);
 }
 
 // Segment reduce + row update, then the rows whose run spans tiles.
@@ -1504,7 +1518,7 @@ void launch_reduce_and_fixup(const ReduceCall& c) {
   const int64_t blocks = (c.w->ntiles + (kFixBlock >> log2_gl) - 1) / (kFixBlock >> log2_gl);
   timed_launch(c.plan, DMT_K_BWD_FIXUP, c.s, bwd_fixup_update<TD>, blocks, kFixBlock, c.plan->d_meta,
                (uint32_t)c.B, c.nbags, c.sorted, c.nnz, c.total_rows, c.w->partials, max_dim,
-               log2_gl, c.w->ntiles, c.lr, c.eps, c.plan->d_error + 1);
+               log2_gl, c.w->tile, c.w->ntiles, c.lr, c.eps, c.plan->d_error + 1);
 }
 
 }  // namespace
@@ -1537,9 +1551,12 @@ static dmt_status bwd_update_run(const dmt_plan* plan, const int32_t* indices,
   const uint64_t* sorted = w.pk_a;
 
   if (nnz > 0) {
-    // keys; bags per block: about 4096 lookups' worth (a power of two, at most kKeysMaxBags)
+    // keys; bags per block: about 4096 lookups' worth (a power of two, at most kKeysMaxBags), or
+    // what it takes to give every CU four blocks, but at least a lookup per thread (260 K lookups:
+    // 51 blocks of 4096 took 25.5 us, 813 of 320 take 5.7)
     const double mean_len = (double)nnz / (double)nbags;
-    int log2_bpb = ilog2_ceil((int64_t)(4096.0 / (mean_len > 1.0 ? mean_len : 1.0) + 0.5));
+    const double want = std::min(4096.0, std::max(256.0, (double)nnz / 1024.0));
+    int log2_bpb = ilog2_ceil((int64_t)(want / (mean_len > 1.0 ? mean_len : 1.0) + 0.5));
     if (plan->sw.keys_lg >= 0) log2_bpb = plan->sw.keys_lg;
     log2_bpb = log2_bpb < 4 ? 4 : (log2_bpb > 10 ? 10 : log2_bpb);
     const int64_t key_blocks = ((int64_t)nbags + (1 << log2_bpb) - 1) >> log2_bpb;
@@ -1585,7 +1602,7 @@ static dmt_status bwd_update_run(const dmt_plan* plan, const int32_t* indices,
       timed_launch(plan, DMT_K_BWD_HEADS, s, heads_scan, 1, 1024, w.blk_heads, w.nblk_scan,
                    w.num_unique);
       timed_launch(plan, DMT_K_BWD_HEADS, s, heads_write, w.nblk_scan, kBlock, sorted, nnz,
-                   w.blk_heads, w.seg_off, w.tile_first);
+                   w.blk_heads, w.seg_off);
     }
     const int64_t n = nnz + 1;
     hipLaunchKernelGGL(bwd_export, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,

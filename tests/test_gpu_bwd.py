@@ -120,6 +120,17 @@ def test_imbalanced_scaled_mixed_dims():
     check_bwd(wl.scaled(wl.imbalanced(), max_rows=5000, batch=1111, num_tables=24))
 
 
+@pytest.mark.parametrize("batch", [16384, 16385, 32769, 75000])
+def test_every_reduce_tile_size(batch):
+    """One lookup per bag, 8 tables: 131072 (tiles of 16 records), 131080 (32), 262152 (64) and 600000
+    (128) lookups, with runs that end inside a tile and runs that span many."""
+    w = wl.scaled(wl.mid(True), max_rows=3000, batch=batch, num_tables=8)
+    w.table_dtype = "f32"
+    w.dims = [4] * 8
+    w.len_dist, w.len_param, w.len_cap = "uniform", 1, 1
+    check_bwd(w)
+
+
 @pytest.mark.parametrize("dims", [[32, 64], [64], [32], [256]])
 def test_narrow_and_wide_rows(dims):
     """Dims up to 128 run the lean walk, 256 the wave-per-tile kernel."""
