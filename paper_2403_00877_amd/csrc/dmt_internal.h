@@ -68,9 +68,8 @@ struct DmtProfile {
 // Kernel-choice switches, read from the environment ONCE, when the plan is created (tests reach
 // both variants of a choice, sweeps need no rebuild); 0 / -1 = the library's own choice.
 struct DmtSwitches {
-  int tm_big = 1;        // DMT_TM_BIG=0: every contraction on the 128 x 128 kernel
+  int tm_big = 1;        // DMT_TM_BIG=0 / 2: 128 x 128 / 256 x 256 contraction tiles whatever the size
   int tm_fuse = 1;       // DMT_TM_FUSE=0: dot terms by their own kernel, not inside the projection
-  int tm_direct = 1;     // DMT_TM_DIRECT=0: interior launches of the 256 x 256 kernel stage through registers too
   int tmb_ksplit = 0;    // DMT_TMB_KSPLIT=n: slices of every weight gradient
   int bwd_kernel = 0;    // DMT_BWD_KERNEL=1 / 2: the wave-per-tile / lane-group segment reduce
   int keys_lg = -1;      // DMT_KEYS_LG=l: 2^l bags per key-build block

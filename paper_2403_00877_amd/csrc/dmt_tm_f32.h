@@ -229,16 +229,16 @@ __global__ __launch_bounds__(kF32Waves * 64) void tm_gemm_f32(const TmF32Launch 
   }
 }
 
-// A forward-shaped group (both operands k contiguous, the weight rows one piece of K0 + K1).
+// A forward-shaped group (both operands k contiguous).
 inline TmF32Group f32_group(const TmGroup& g) {
   TmF32Group f{};
   f.A0 = (const float*)g.A0; f.lda0 = g.lda0; f.K0 = g.K0;
   f.A1 = (const float*)g.A1; f.lda1 = g.lda1; f.K1 = g.K1;
-  f.W0 = (const float*)g.W; f.ldw0 = g.ldw;
-  f.W1 = (const float*)g.W + g.K0; f.ldw1 = g.ldw;
+  f.W0 = (const float*)g.W0; f.ldw0 = g.ldw0;
+  f.W1 = (const float*)g.W1; f.ldw1 = g.ldw1;
   f.bias = (const float*)g.bias;
   f.X0 = (const float*)g.X0; f.ldx = g.ldx;
-  f.XL = (const float*)(g.XL ? g.XL : g.A1); f.ldxl = g.XL ? g.ldxl : g.lda1;
+  f.XL = (const float*)g.XL; f.ldxl = g.ldxl;
   f.C = (float*)g.C; f.ldc = g.ldc; f.rdiv = g.rdiv; f.ldc2 = g.ldc2;
   f.U = (float*)g.U;
   f.M = g.M; f.N = g.N; f.epi = g.epi;

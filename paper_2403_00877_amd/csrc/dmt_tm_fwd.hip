@@ -10,9 +10,7 @@
 //   DLRM           the flat projection next to one projection shared by every
 //                  feature's embedding: a second contraction over the pooled block
 //                  viewed as [B * features][dim]                  (Listing 1, c > 0)
-// 16-bit types run on MFMA (v_mfma_f32_32x32x16, float32 accumulate): block tile
-// 128 x 128 x 64, four waves of 64 x 64, operands staged through padded LDS, the
-// next K tile prefetched into registers while the current one is multiplied.
+// 16-bit types run on MFMA (tm_gemm in dmt_tm_gemm.h, float32 accumulate).
 // All towers of one stage go into ONE launch (a grouped GEMM: block id -> tower,
 // tile), because a single tower's grid cannot fill 256 CUs.  The pairwise dots
 // are a Gram matrix per sample: 32 consecutive (sample, feature) rows form one
@@ -124,15 +122,10 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
 
   // A dot-product tower whose shape fits computes its dot terms inside the projection GEMM.
   std::vector<char> fused(p->T, 0);
-  if (DT != DMT_F32 && p->sw.tm_fuse != 0 && p->sw.tm_big != 0)
-    for (int32_t t = 0; t < p->T; ++t) {
-      const dmt_tm_params& q = tp[t];
-      if (q.kind != DMT_TM_DOT_LINEAR) continue;
-      const int nf = p->tower_ntab[t], n = p->tower_uniform_dim[t], wt = p->tower_width[t];
-      TmGroup g{};
-      g.M = (int32_t)B; g.N = q.out_dim; g.K1 = wt; g.lda1 = wt; g.ldw = ws[t].np_pad + wt;
-      fused[t] = nf >= 2 && 32 % nf == 0 && n % 16 == 0 && ws[t].np_pad <= BK && big_ok(g, true);
-    }
+  if (DT != DMT_F32 && p->sw.tm_fuse != 0)
+    for (int32_t t = 0; t < p->T; ++t)
+      fused[t] = tp[t].kind == DMT_TM_DOT_LINEAR && p->tower_ntab[t] >= 2 && p->tower_uniform_dim[t] % 8 == 0 &&
+                 ws[t].np_pad <= BK;
 
   // stage 0: dot terms and repacked projection weights, one grouped launch per kind
   std::vector<TmAuxItem> dots_mfma, dots_simple, packs;
@@ -156,7 +149,7 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
       dots_simple.push_back(it);
       nb_simple.push_back((B * w.np_pad + kBlock - 1) / kBlock);
     }
-    if (DT == DMT_F32) continue;                    // reads the projection's weights as they are
+    if (DT == DMT_F32 || dot_weights_as_is(q.w_proj, w.np)) continue;
     it.src = q.w_proj;
     it.dst = wp_of(t);
     packs.push_back(it);
@@ -188,22 +181,20 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
       const void* x0 = x_all + (size_t)B * p->width_prefix[t] * eb;
       const void* xl = l == 0 ? x0 : (const void*)x_layer(t, l - 1);
       TmGroup g{};
-      g.A0 = nullptr; g.lda0 = 0; g.K0 = 0;
       g.A1 = xl; g.lda1 = wt; g.K1 = wt;
-      g.W = q.w_cross[l]; g.ldw = wt; g.bias = q.b_cross[l];
+      g.W1 = q.w_cross[l]; g.ldw1 = wt; g.bias = q.b_cross[l];
       if (low) {
         const int r = q.feat_out;
         TmGroup h{};
         h.A1 = xl; h.lda1 = wt; h.K1 = wt;
-        h.W = q.w_cross[2 * l]; h.ldw = wt; h.bias = nullptr;
+        h.W1 = q.w_cross[2 * l]; h.ldw1 = wt; h.bias = nullptr;
         h.C = wsp + ws[t].t_off; h.ldc = r;
         h.M = (int32_t)B; h.N = r; h.epi = EPI_BIAS;
         groups_t.push_back(h);
         g.A1 = wsp + ws[t].t_off; g.lda1 = r; g.K1 = r;
-        g.W = q.w_cross[2 * l + 1]; g.ldw = r;
-        g.XL = xl; g.ldxl = wt;
+        g.W1 = q.w_cross[2 * l + 1]; g.ldw1 = r;
       }
-      g.X0 = x0; g.ldx = wt;
+      g.X0 = x0; g.ldx = wt; g.XL = xl; g.ldxl = wt;
       g.C = x_layer(t, l); g.ldc = wt;
       if (keptp) g.U = keptp + kept[t].u[l];
       g.M = (int32_t)B; g.N = wt; g.epi = EPI_CROSS;
@@ -220,13 +211,14 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
     const int wt = p->tower_width[t];
     const void* x = x_all + (size_t)B * p->width_prefix[t] * eb;
     TmGroup g{};
-    g.A0 = nullptr; g.lda0 = 0; g.K0 = 0;
     g.A1 = x; g.lda1 = wt; g.K1 = wt;
-    g.W = q.w_proj; g.ldw = wt;
+    g.W1 = q.w_proj; g.ldw1 = wt;
     if (q.kind == DMT_TM_DOT_LINEAR) {
-      g.A0 = z_of(t); g.lda0 = ws[t].np_pad; g.K0 = ws[t].np_pad;
-      g.W = wp_of(t); g.ldw = ws[t].np_pad + wt;
-      if (DT == DMT_F32) { g.K0 = ws[t].np; g.W = q.w_proj; g.ldw = ws[t].np + wt; }
+      const bool as_is = DT == DMT_F32 || dot_weights_as_is(q.w_proj, ws[t].np);
+      const int skip = as_is ? ws[t].np : ws[t].np_pad;    // columns of the dot terms in a weight row
+      g.A0 = z_of(t); g.lda0 = ws[t].np_pad; g.K0 = DT == DMT_F32 ? ws[t].np : ws[t].np_pad;
+      g.W0 = as_is ? (const char*)q.w_proj : wp_of(t); g.ldw0 = skip + wt;
+      g.W1 = (const char*)g.W0 + (size_t)skip * eb; g.ldw1 = skip + wt;
     } else if (q.kind == DMT_TM_CROSS_LINEAR || q.kind == DMT_TM_CROSS_LOWRANK_LINEAR) {
       g.A1 = x_layer(t, q.num_cross_layers - 1);
     }
@@ -242,7 +234,7 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
       g.N = q.out_dim - nf * q.feat_out;
       TmGroup h{};
       h.A1 = x; h.lda1 = n; h.K1 = n;
-      h.W = q.w_cross[0]; h.ldw = n; h.bias = q.b_cross[0];
+      h.W1 = q.w_cross[0]; h.ldw1 = n; h.bias = q.b_cross[0];
       h.C = y_all + ((size_t)B * out_prefix[t] + g.N) * eb;
       h.ldc = q.out_dim; h.rdiv = nf; h.ldc2 = q.feat_out;
       h.M = (int32_t)(B * nf); h.N = q.feat_out; h.epi = EPI_BIAS;

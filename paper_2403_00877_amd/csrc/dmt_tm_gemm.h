@@ -1,8 +1,7 @@
 // Grouped contractions of the Tower Module, shared by its forward and backward:
-//   C = epilogue(A . W^T [+ b])  with both operands contiguous along the reduction
-// dimension, one launch for all towers of a stage (block id -> tower, tile).
-// 16-bit types run on MFMA (v_mfma_f32_32x32x16, float32 accumulate) in two tilings
-// (128 x 128 x 64 with four waves, 256 x 256 x 64 with eight); float32 has its own kernel
+//   C = epilogue(A . W^T [+ b]), either operand contiguous along the reduction dimension or along
+// its own, one launch for all towers of a stage (block id -> tower, tile).
+// 16-bit types run on MFMA (v_mfma_f32_32x32x16, float32 accumulate); float32 has its own kernel
 // (dmt_tm_f32.h).  Also the pairwise-dot (Gram tile) kernels and the projection-weight
 // repack of the dot-product form.  Everything lives in an unnamed namespace: each
 // translation unit that includes this header gets its own copy.
@@ -19,59 +18,69 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-constexpr int kBlock = 256;
-constexpr int BM = 128, BN = 128, BK = 64;
-constexpr int kLdsStride = BK + 8;       // elements; 144-byte rows keep ds_read_b128 conflict-free
+constexpr int kBlock = 256;              // threads of the small kernels' blocks
+constexpr int BK = 64;                   // K step of the matrix kernels
 constexpr int kMaxGroups = 16;
 
 // EPI_F32 / EPI_F32_ADD: C is float32 whatever the operand type, no bias: C = acc / C += acc
 // (gradients: the backward's accumulations stay in float32)
-enum { EPI_BIAS = 0, EPI_BIAS_RELU = 1, EPI_CROSS = 2, EPI_F32 = 3, EPI_F32_ADD = 4 };
+// EPI_CROSS_GRAD: a cross tower's gradient on its way down, acc being the data gradient of layer l or
+// of the projection (l = the number of layers):
+//   g_l = acc + g_{l+1}                       (float32; the sum without GN for the projection)
+//   C = g_l                                   (where C is set: layers below need it)
+//   DU = du_{l-1} = g_l * x0                  (rounded), DBP its column sums
+//   ACC (+)= g_{l+1} * u_l [+ g_1 * u_0 + g_1 where U0 is set, l = 1]
+enum { EPI_BIAS = 0, EPI_BIAS_RELU = 1, EPI_CROSS = 2, EPI_F32 = 3, EPI_F32_ADD = 4, EPI_CROSS_GRAD = 5 };
 
-// One contraction of a grouped launch.  A is given as two K segments (the dot
-// terms, then the pooled values); a plain GEMM has K0 = 0.
+// How an operand lies in memory: OP_ROW with its K columns contiguous ([M][ld], k in a row), or
+// OP_COL with its row index contiguous ([K][ld]).  A data gradient contracts dz (OP_ROW) with the
+// weights as they are (OP_COL), a weight gradient dz with x (both OP_COL): nothing is transposed.
+enum { OP_ROW = 0, OP_COL = 1 };
+
+// One contraction of a grouped launch, C[m][n] = sum over k of A(m, k) W(n, k).  K comes in two
+// segments (the dot terms, then the pooled values); a plain contraction has K0 = 0.  Operand rows
+// are multiples of 8 elements apart, the bases 16-byte aligned (W0 / W1: 4-byte aligned).
 struct TmGroup {
-  const void* A0;   // [M][lda0], first K0 columns of the operand
-  const void* A1;   // [M][lda1], next K1 columns
-  const void* W;    // [N][ldw], K0 + K1 columns used
-  const void* bias; // [N]
-  const void* X0;   // EPI_CROSS: [M][ldx] (x0); the x_l term is A1
+  const void* A0;   // first K0 of the contraction
+  const void* A1;   // next K1
+  const void* W0;
+  const void* W1;
+  const void* bias; // [N] or NULL (no bias)
+  const void* X0;   // EPI_CROSS: [M][ldx] (x0)
+  const void* XL;   // EPI_CROSS: the x_l term, [M][ldxl]
   void* C;          // [M][ldc]
-  int32_t lda0, K0, lda1, K1, ldw, ldc, ldx, M, N, epi;
-  int32_t nf, fdim;       // dot terms computed in-kernel: number of features and their dim
-  // Split K (EPI_F32 with K0 = 0 only): ksplit > 1 cuts the K1 columns into slices of klen
-  // (a multiple of 8); slice s is a contraction of its own whose result goes to
-  // C + s * cstride floats, and the caller adds the slices up in a fixed order.
-  int32_t ksplit, klen;
-  int64_t cstride;
-  // Two-level output rows (128 x 128 and plain kernels only): with rdiv > 0 row m of C starts at
-  // (m / rdiv) * ldc + (m % rdiv) * ldc2, i.e. rdiv consecutive rows of the contraction share
-  // one row of the output tensor.
-  int32_t rdiv, ldc2;
   // EPI_CROSS: when set, u = acc + bias (before the cross product) is also stored here, laid
   // out like C (what the backward needs of a cross layer).  A group whose dot terms are computed
   // in-kernel: when set, they are also stored here as [M][K0], zeros in the padding columns.
   void* U;
-  // EPI_CROSS: the x_l term, [M][ldxl]; NULL when it is the operand A1 itself (a full-rank
-  // layer).  A low-rank layer contracts t = V x_l instead, and adds x_l from here.
-  const void* XL;
-  int32_t ldxl;
+  int32_t lda0, K0, lda1, K1, ldw0, ldw1, ldc, ldx, ldxl, M, N, epi;
+  int32_t nf, fdim;       // dot terms computed in-kernel: number of features and their dim
+  // Split K (EPI_F32 with K0 = 0 only): ksplit > 1 cuts the K1 columns into slices of klen
+  // (a multiple of BK); slice s is a contraction of its own whose result goes to
+  // C + s * cstride floats, and the caller adds the slices up in a fixed order.
+  int32_t ksplit, klen;
+  int64_t cstride;
+  // EPI_CROSS_GRAD: [M][ldc] float32 / 16-bit tensors, and the column sums of du, one row per 128 rows
+  // of C
+  const float* GN;        // g_{l+1} or NULL
+  const void* UL;         // u_l (with GN)
+  const void* U0;         // u_0 or NULL
+  float* ACC;
+  void* DU;
+  float* DBP;             // [(M + 127) / 128][N]
+  int32_t acc_first;      // ACC holds nothing yet
+  // Two-level output rows: with rdiv > 0 row m of C starts at (m / rdiv) * ldc + (m % rdiv) * ldc2,
+  // i.e. rdiv consecutive rows of the contraction share one row of the output tensor.
+  int32_t rdiv, ldc2;
 };
-
-// bias may be NULL (no bias)
-__device__ __forceinline__ const void* tm_xl(const TmGroup& g) { return g.XL ? g.XL : g.A1; }
-__device__ __forceinline__ int tm_ldxl(const TmGroup& g) { return g.XL ? g.ldxl : g.lda1; }
-
-__device__ __forceinline__ int64_t tm_crow(const TmGroup& g, int m) {
-  return g.rdiv > 0 ? (int64_t)(m / g.rdiv) * g.ldc + (int64_t)(m % g.rdiv) * g.ldc2
-                    : (int64_t)m * g.ldc;
-}
 
 __host__ __device__ inline int tm_slices(const TmGroup& g) { return g.ksplit > 1 ? g.ksplit : 1; }
 
 struct TmLaunch {
   int32_t ngroups;
-  int32_t tile_start[kMaxGroups + 1];
+  int32_t super;                       // tiles of a super-tile (dealt to one XCD), at most
+  int32_t cap;                         // block slots of a super-tile
+  int32_t tile_start[kMaxGroups + 1];  // first super-tile of each group
   TmGroup g[kMaxGroups];
 };
 
@@ -98,324 +107,281 @@ template <int DT> __device__ __forceinline__ void store_elt(void* p, int64_t i, 
 }
 
 // ------------------------------------------------------------- MFMA grouped GEMM
+//
+// Two tilings of one kernel.  256 x 256 x 64, eight waves (two per SIMD) of 128 x 64, one block per
+// CU: a 128 x 128 tile needs 1 byte from L2 per 64 FLOP, which caps the matrix cores at a fraction
+// of their rate, and 256 x 256 halves that.  128 x 128 x 64, four waves of 64 x 64, two blocks per
+// CU: for launches that would leave CUs without a 256 x 256 tile, and for outputs of at most 128
+// rows or columns.
+//
+// Operand tiles go from global memory straight into LDS (buffer_load_dwordx4 ... lds: a wave's 64
+// lanes fill 1 KB of consecutive LDS, 16 bytes a lane), two stages deep: tile kt + 2 is requested
+// into the stage tile kt is being read from, behind the barrier inside step kt, and every wave waits
+// for its own requests before the next step's barrier.  The buffer's bounds stand in for all edges:
+// rows past the operand's last, and chunks past the last k (their lanes ask for an offset that is
+// never in bounds), arrive as zeros.  (The requests are inline assembly: told about them, the
+// compiler makes every LDS read of the current tile wait for the next tile's requests, since it
+// cannot tell the two stages apart.)
+//
+// OP_ROW tile: 128-byte rows (64 k) without padding; column chunk c (8 elements) of row r sits in
+// slot c ^ (r / 2) % 8.  A fragment read (ds_read_b128, 16 lanes a cycle from 64 banks) touches 16
+// rows: 2 r and 2 r + 1 lie in the two halves of one 256-byte bank row and share a slot, the eight
+// pairs differ in it, so it is conflict-free.
+// OP_COL tile: 64 rows of BM (BN) elements, one per k; chunk c of row k sits in slot
+// c ^ 4 (k % 4).  Fragments come through ds_read_b64_tr_b16, which transposes 4 x 4 blocks among 16
+// lanes: lane p of a group names row k + p / 4, elements 4 (p % 4) ..., and receives column p of the
+// four rows.  The four rows of a group lie on the same banks but for the slot, which spreads them.
+//
+// The MFMAs take the W fragment as their first operand, so the accumulators hold the tile
+// transposed: a lane owns one row and four consecutive columns per register quad, which the
+// epilogue parks in LDS with 16-byte stores.
 
-// TAG (here and below) only marks the including source file in the kernel's name, so that a
-// profile tells the forward's launches from the backward's.
+// TAG only marks the including source file in the kernel's name, so that a profile tells the
+// forward's launches from the backward's.
 #ifndef DMT_TM_TAG
 #define DMT_TM_TAG 0
 #endif
 
-// KEEPU: the cross epilogue also stores u (TmGroup::U), in a pass of its own over the
-// accumulators: a second store inside the fully unrolled epilogue cost the bf16 kernel 40
-// registers and made it spill.
-template <int DT, bool KEEPU = false, int TAG = DMT_TM_TAG>
-__global__ __launch_bounds__(kBlock, 2) void tm_gemm_mfma(const TmLaunch L) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[BM * kLdsStride];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[BN * kLdsStride];
-  int gi = 0;
-  while (gi + 1 < L.ngroups && (int)blockIdx.x >= L.tile_start[gi + 1]) ++gi;
-  const TmGroup& G = L.g[gi];
-  int tile = blockIdx.x - L.tile_start[gi];
-  const int tiles_n = (G.N + BN - 1) / BN;
-  const int tiles_mn = ((G.M + BM - 1) / BM) * tiles_n;
-  const int slice = tile / tiles_mn;                 // 0 unless K is split
-  tile -= slice * tiles_mn;
-  const int kofs = G.ksplit > 1 ? slice * G.klen : 0;
-  const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
-  const int M = G.M, N = G.N, K0 = G.K0;
-  const int K = G.K0 + (G.ksplit > 1 ? min(G.klen, G.K1 - kofs) : G.K1);
-  const uint16_t* A0 = (const uint16_t*)G.A0;
-  const uint16_t* A1 = (const uint16_t*)G.A1 + kofs;
-  const uint16_t* W = (const uint16_t*)G.W + kofs;
-  const int lda0 = G.lda0, lda1 = G.lda1, ldw = G.ldw;
+constexpr uint32_t kOobOffset = 0x80000000u;      // beyond any buffer (sizes are clamped below it)
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  // staging: chunk c = tid + 256*i covers row c/8, 8 elements at column (c%8)*8
-  const int srow = tid >> 3, scol = (tid & 7) * 8;
-
-  floatx16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  uint4 ra[4], rb[4];
-  auto load_tile = [&](int kt) {
-    const int k = kt * BK + scol;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = m0 + srow + i * 32;
-      ra[i] = make_uint4(0, 0, 0, 0);
-      if (m < M && k < K)
-        ra[i] = (k < K0) ? *(const uint4*)(A0 + (int64_t)m * lda0 + k)
-                         : *(const uint4*)(A1 + (int64_t)m * lda1 + (k - K0));
-      const int n = n0 + srow + i * 32;
-      rb[i] = make_uint4(0, 0, 0, 0);
-      if (n < N && k < K) rb[i] = *(const uint4*)(W + (int64_t)n * ldw + k);
-    }
-  };
-  auto store_tile = [&]() {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      *(uint4*)(As + (srow + i * 32) * kLdsStride + scol) = ra[i];
-      *(uint4*)(Bs + (srow + i * 32) * kLdsStride + scol) = rb[i];
-    }
-  };
-
-  const int nk = (K + BK - 1) / BK;
-  load_tile(0);
-  for (int kt = 0; kt < nk; ++kt) {
-    store_tile();
-    __syncthreads();
-    if (kt + 1 < nk) load_tile(kt + 1);
-    const uint16_t* ap = As + (wm * 64 + (lane & 31)) * kLdsStride + (lane >> 5) * 8;
-    const uint16_t* bp = Bs + (wn * 64 + (lane & 31)) * kLdsStride + (lane >> 5) * 8;
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      uint4 a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        a[i] = *(const uint4*)(ap + i * 32 * kLdsStride + kk * 16);
-        b[i] = *(const uint4*)(bp + i * 32 * kLdsStride + kk * 16);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma32<DT>(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-
-  // epilogue: lane holds column n = lane % 32 of rows (v/4)*8 + (lane/32)*4 + v%4
-  const int epi = G.epi;
-  if constexpr (KEEPU) {
-    if (epi == EPI_CROSS && G.U) {
-      for (int j = 0; j < 2; ++j) {
-        const int n = n0 + wn * 64 + j * 32 + (lane & 31);
-        if (n >= N) continue;
-        const float bias = G.bias ? load_elt<DT>(G.bias, n) : 0.f;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int m = m0 + wm * 64 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-            if (m < M) store_elt<DT>(G.U, (int64_t)m * G.ldc + n, acc[i][j][v] + bias);
-          }
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int n = n0 + wn * 64 + j * 32 + (lane & 31);
-    if (n >= N) continue;
-    const float bias = (epi >= EPI_F32 || !G.bias) ? 0.f : load_elt<DT>(G.bias, n);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int m = m0 + wm * 64 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-        if (m >= M) continue;
-        if (epi >= EPI_F32) {
-          float* c = (float*)G.C + slice * G.cstride + tm_crow(G, m) + n;
-          *c = epi == EPI_F32_ADD ? *c + acc[i][j][v] : acc[i][j][v];
-          continue;
-        }
-        float y = acc[i][j][v] + bias;
-        if (epi == EPI_BIAS_RELU) y = y > 0.f ? y : 0.f;
-        if (epi == EPI_CROSS) {
-          y = load_elt<DT>(G.X0, (int64_t)m * G.ldx + n) * y +
-              load_elt<DT>(tm_xl(G), (int64_t)m * tm_ldxl(G) + n);
-        }
-        store_elt<DT>(G.C, tm_crow(G, m) + n, y);
-      }
-    }
-  }
+// Buffer descriptor of `bytes` bytes from p (uniform).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tm_buffer(const void* p, int64_t bytes) {
+  const int64_t n = bytes < 0 ? 0 : bytes > 0x7fffffff ? 0x7fffffff : bytes;
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)n, 0x00020000);
+}
+// 64 lanes' 16-byte pieces of a buffer to 1 KB of LDS at byte address lds.
+__device__ __forceinline__ void tm_request(uint32_t lds, __amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(off), "s"(rsrc) : "memory");
 }
 
-// ------------------------------------------- MFMA grouped GEMM, 256 x 256 tiles
-//
-// For wide outputs (N > 128).  A 128 x 128 block tile needs 1 byte from L2 per 64
-// FLOP, which caps the matrix cores at a fraction of their rate; 256 x 256 halves
-// that.  Eight waves (two per SIMD, so one wave's LDS waits hide behind the other's
-// MFMAs) of 128 x 64 each (4 x 2 MFMA tiles, 128 accumulator registers), one block
-// per CU, two LDS stages (147 KB of the CU's 160 KB): tile k+1 goes from registers
-// to LDS and the global loads of tile k+2 are issued before the MFMAs of tile k, so
-// a whole K step of matrix work covers the memory latency and one barrier per K
-// step suffices.  The MFMAs take the W fragment as their first operand, so the accumulators
-// hold the tile transposed: a lane owns one row and four consecutive columns per register
-// quad, which the epilogue parks in LDS with 16-byte stores.
-constexpr int LBM = 256, LBN = 256;
-constexpr int kBigThreads = 512;
-constexpr int kSuper = 32;                                  // tiles an XCD keeps resident (its CUs)
-constexpr int kBigTileElems = LBM * kLdsStride;            // one operand, one stage
-constexpr int kBigLdsBytes = 4 * kBigTileElems * 2;         // 2 stages x (A + B)
+// One operand's side of a block tile of R rows (A: R = BM, W: R = BN), staged by NW waves.
+template <int LAY, int R, int NW>
+struct TmStage {
+  static constexpr int kInstr = R * BK * 2 / 1024 / NW;    // requests per wave and K step
+  static_assert(NW % 2 == 0 && kInstr * NW * 1024 == R * BK * 2, "");
+  uint32_t off[kInstr];                            // this lane's byte offsets from the tile's first element
+  int chunk;                                       // OP_ROW: this lane's column chunk (the same in every request)
 
-// DOTS: the operand's first K0 columns are the tower's pairwise dot terms, which the block
-// computes itself (Gram tiles, as in tm_dots_mfma) straight into the first LDS stage, so the
-// pooled tensor is read once and the dot terms never exist in global memory.
-//
-// DIRECT (launches whose tiles are all interior: M and N multiples of 256, K of 64, no dot
-// terms): the operand tiles go from global memory straight into LDS (global_load_lds_dwordx4:
-// a wave's 64 lanes fill 1 KB of consecutive LDS, 16 bytes a lane), so the K loop has no
-// register stage and no LDS stores.  LDS rows are then 128 bytes with no padding; each lane
-// fetches the 16-byte column chunk (slot ^ (row / 2) % 8) of its row and the fragment reads
-// apply the same exclusive-or.  A ds_read_b128 serves 16 lanes at a time from 64 banks; the
-// 16 rows they read then fall on 16 different 16-byte bank groups (rows 2 r and 2 r + 1 lie in
-// the two halves of one 256-byte bank row and share a slot, the eight pairs differ in it):
-// conflict-free without padding (with slot ^ row % 8, rows r and r + 8 collide and half the
-// LDS cycles are conflict cycles).  Tile kt + 2 is requested into the stage tile kt is being
-// read from, behind the barrier inside step kt; every wave waits for its own requests before
-// the next step's barrier.  (The requests are written as inline assembly: told about them,
-// the compiler would make every LDS read of the current tile wait for the next tile's
-// requests, since it cannot tell the two stages apart.)
-template <int DT, bool DOTS, int TAG = DMT_TM_TAG, bool KEEPZ = false, bool DIRECT = false>
-__global__ __launch_bounds__(kBigThreads, 1) void tm_gemm_mfma_256(const TmLaunch L) {
-  static_assert(!(DIRECT && DOTS), "in-kernel dot terms are written into a padded first stage");
+  // ld: row pitch; cols: operand rows left in the tile (OP_COL: chunks past them are not asked for)
+  __device__ __forceinline__ void init(int ld, int cols, int wave, int lane) {
+    chunk = LAY == OP_ROW ? (lane & 7) ^ (((wave & 1) << 2) | (lane >> 4)) : 0;
+#pragma clang loop unroll(full)
+    for (int j = 0; j < kInstr; ++j) {
+      if constexpr (LAY == OP_ROW) {
+        off[j] = ((uint32_t)((j * NW + wave) * 8 + (lane >> 3)) * (uint32_t)ld + chunk * 8) * 2u;
+      } else {
+        constexpr int kRowLanes = R / 8;           // 16-byte slots of one k row
+        const int k = (j * NW + wave) * (64 / kRowLanes) + lane / kRowLanes;
+        const int c = (lane % kRowLanes) ^ ((k & 3) << 2);
+        off[j] = c * 8 < cols ? ((uint32_t)k * (uint32_t)ld + c * 8) * 2u : kOobOffset;
+      }
+    }
+  }
+  // Requests the tile's columns k .. k + 63 of a segment that ends at K.  p: the operand; row0: the
+  // tile's first row; rows: the operand's row count.
+  __device__ __forceinline__ void request(uint32_t lds, const uint16_t* p, int64_t ld, int row0, int rows, int k, int K,
+                                          int wave) const {
+    // (the last row counts to the end of its last chunk, which its pitch has room for: the bounds
+    // check is by 4 bytes and would drop an odd last element)
+    const __amdgpu_buffer_rsrc_t rsrc =
+        LAY == OP_ROW ? tm_buffer(p + row0 * ld + k, ((rows - 1 - row0) * ld + ((K - k + 7) & ~7)) * 2)
+                      : tm_buffer(p + k * ld + row0, ((K - 1 - k) * ld + ((rows - row0 + 7) & ~7)) * 2);
+    if (LAY == OP_ROW && K - k < BK) {             // (uniform) the segment's last, partial step
+      const bool in = chunk * 8 < K - k;
+#pragma clang loop unroll(full)
+      for (int j = 0; j < kInstr; ++j) tm_request(lds + (j * NW + wave) * 1024, rsrc, in ? off[j] : kOobOffset);
+    } else {
+#pragma clang loop unroll(full)
+      for (int j = 0; j < kInstr; ++j) tm_request(lds + (j * NW + wave) * 1024, rsrc, off[j]);
+    }
+  }
+};
+
+// One operand's fragment reads: NF fragments of 32 rows from row `first` (a multiple of 32 NF) of a
+// staged tile of R rows.
+template <int LAY, int R, int NF>
+struct TmFrag {
+  static constexpr int kReads = LAY == OP_ROW ? NF : 2 * NF;   // LDS instructions per K slice
+  int at[LAY == OP_ROW ? BK / 16 : NF];
+  __device__ __forceinline__ void init(int first, int lane) {
+    if constexpr (LAY == OP_ROW) {
+#pragma clang loop unroll(full)
+      for (int kk = 0; kk < BK / 16; ++kk)
+        at[kk] = (first + (lane & 31)) * BK + ((kk * 2 + (lane >> 5)) ^ ((lane >> 1) & 7)) * 8;
+    } else {
+      const int p = lane & 15;
+#pragma clang loop unroll(full)
+      for (int i = 0; i < NF; ++i) {
+        const int c = (((first / 32 + i) ^ (p >> 2)) << 2) + ((lane >> 4) & 1) * 2 + ((p & 3) >> 1);
+        at[i] = ((lane >> 5) * 8 + (p >> 2)) * R + c * 8 + (p & 1) * 4;
+      }
+    }
+  }
+  __device__ __forceinline__ void read(uint4 (&f)[NF], const uint16_t* tile, int kk) const {
+    if constexpr (LAY == OP_ROW) {
+#pragma clang loop unroll(full)
+      for (int i = 0; i < NF; ++i) f[i] = *(const uint4*)(tile + at[kk] + i * 32 * BK);
+    } else {
+      typedef short short4v __attribute__((ext_vector_type(4)));
+      typedef __attribute__((address_space(3))) short4v lds_short4;
+#pragma clang loop unroll(full)
+      for (int i = 0; i < NF; ++i) {
+        const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                                       (lds_short4*)(tile + at[i] + kk * 16 * R)));
+        const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                                       (lds_short4*)(tile + at[i] + (kk * 16 + 4) * R)));
+        f[i] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      }
+    }
+  }
+};
+
+// TILE: 256 or 128.  DOTS: the operand's first K0 (<= 64) columns are the tower's pairwise dot
+// terms, which the block computes itself (Gram tiles, as in tm_dots_mfma) straight into the first
+// LDS stage, so the dot terms never exist in global memory (unless KEEPZ: a training forward keeps
+// them).
+template <int TILE> struct TmTile {
+  static constexpr int WM = 2, WN = TILE == 256 ? 4 : 2, kWaves = WM * WN, kThreads = kWaves * 64;
+  static constexpr int MT = TILE / WM / 32, NT = TILE / WN / 32;     // MFMA tiles of a wave
+  static constexpr int kStageBytes = 2 * TILE * BK * 2;              // A then W
+  static constexpr int kHalf = TILE / WM;                            // rows the epilogue parks at a time
+  static constexpr int kParkStride = TILE + 4;   // floats; rows 4 banks apart: 16 lanes' float4 stores spread over all 64
+  static constexpr int kLdsBytes = 2 * kStageBytes > kHalf * kParkStride * 4 ? 2 * kStageBytes : kHalf * kParkStride * 4;
+};
+
+template <int DT, int TILE, int ALAY, int WLAY, bool DOTS = false, bool KEEPZ = false, int TAG = DMT_TM_TAG>
+__global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void tm_gemm(const TmLaunch L) {
+  using T = TmTile<TILE>;
+  static_assert(!DOTS || (ALAY == OP_ROW && WLAY == OP_ROW), "");
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   // XCD-aware rasterisation.  Consecutive block ids go to different XCDs, so block b belongs
   // to XCD b % 8 and is that XCD's (b / 8)-th block.  The launch's tiles are cut into
-  // super-tiles of up to kSuper tiles (a few tile rows x all tile columns of one group) that
-  // are dealt to the XCDs in turn: the 32 blocks resident on an XCD then share their A rows
+  // super-tiles of up to L.super tiles (a few tile rows x all tile columns of one group) that
+  // are dealt to the XCDs in turn: the blocks resident on an XCD then share their A rows
   // and W columns in that XCD's L2 instead of every XCD pulling every A tile over the fabric.
-  // Here L.tile_start[] counts super-tiles.
   const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-  const int gs = (idx / kSuper) * 8 + xcd, within = idx % kSuper;
+  const int gs = (idx / L.cap) * 8 + xcd, within = idx % L.cap;
   if (gs >= L.tile_start[L.ngroups]) return;
   int gi = 0;
   while (gi + 1 < L.ngroups && gs >= L.tile_start[gi + 1]) ++gi;
   const TmGroup& G = L.g[gi];
-  const int tiles_n = (G.N + LBN - 1) / LBN, tiles_m = (G.M + LBM - 1) / LBM;
-  const int sm = tiles_n >= kSuper ? 1 : kSuper / tiles_n;       // tile rows per super-tile
+  const int tiles_n = (G.N + TILE - 1) / TILE, tiles_m = (G.M + TILE - 1) / TILE;
+  const int sm = tiles_n >= L.super ? 1 : L.super / tiles_n;     // tile rows per super-tile
   if (within >= sm * tiles_n) return;
   // a split K multiplies the tile rows: virtual row tmv = slice * tiles_m + tm
   const int tmv = (gs - L.tile_start[gi]) * sm + within / tiles_n, tn = within % tiles_n;
   if (tmv >= tiles_m * tm_slices(G)) return;
   const int slice = tmv / tiles_m, tm = tmv - slice * tiles_m;
-  const int kofs = G.ksplit > 1 ? slice * G.klen : 0;
-  const int m0 = tm * LBM, n0 = tn * LBN;
-  const int kshift = DOTS ? G.K0 : 0;              // operand columns in front of A's own
-  const int M = G.M, N = G.N;
-  const int K1 = G.ksplit > 1 ? min(G.klen, G.K1 - kofs) : G.K1, K = K1 + kshift;
-  const uint16_t* __restrict__ A = (const uint16_t*)G.A1 + kofs;
-  const uint16_t* __restrict__ W = (const uint16_t*)G.W + kofs;
-  const int lda = G.lda1, ldw = G.ldw;
+  const int m0 = tm * TILE, n0 = tn * TILE;
+  const int M = G.M, N = G.N, K0 = G.K0;
+  const int kofs = G.ksplit > 1 ? slice * G.klen : 0, kend = G.ksplit > 1 ? min(G.K1, kofs + G.klen) : G.K1;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3;        // 2 x 4 waves of 128 x 64
-  const int srow = tid >> 3, scol = (tid & 7) * 8;
-
-  floatx16 acc[4][2];
+  const int wm = wave / T::WN, wn = wave % T::WN;
+  floatx16 acc[T::MT][T::NT];
 #pragma clang loop unroll(full)
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < T::MT; ++i)
 #pragma clang loop unroll(full)
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < T::NT; ++j)
 #pragma clang loop unroll(full)
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  // element offsets of this thread's 4 + 4 chunks at k = 0 (rows past the edge are clamped
-  // to the last row and zeroed on the way to LDS)
-  uint32_t offa[4], offb[4];
-  uint32_t oka = 0, okb = 0;
-#pragma clang loop unroll(full)
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + srow + i * 64, n = n0 + srow + i * 64;
-    offa[i] = (uint32_t)min(m, M - 1) * (uint32_t)lda + scol;
-    offb[i] = (uint32_t)min(n, N - 1) * (uint32_t)ldw + scol;
-    oka |= (m < M ? 1u : 0u) << i;
-    okb |= (n < N ? 1u : 0u) << i;
-  }
-
-  uint4 ra[4], rb[4];
-  // Loads are never predicated (edge rows are clamped to a valid row, a K tail to column 0),
-  // so they stay in flight across the multiply; edge tiles zero what they must not use when
-  // the registers are written to LDS.
-  const bool interior = !DOTS && m0 + LBM <= M && n0 + LBN <= N && K % BK == 0;
-  auto load_tile = [&](int kt) __attribute__((always_inline)) {
-    const int kw = (kt * BK + scol < K) ? kt * BK : -scol;          // W column block
-    int ka = kt * BK - kshift;                                       // A column block
-    if (ka + scol < 0 || ka + scol >= K1) ka = -scol;
-#pragma clang loop unroll(full)
-    for (int i = 0; i < 4; ++i) {
-      ra[i] = *(const uint4*)(A + offa[i] + ka);
-      rb[i] = *(const uint4*)(W + offb[i] + kw);
-    }
-  };
-  auto store_tile = [&](int stage, int kt) __attribute__((always_inline)) {
-    uint16_t* As = lds + stage * 2 * kBigTileElems;
-    uint16_t* Bs = As + kBigTileElems;
-    const int ca = kt * BK + scol - kshift;                          // this thread's A column
-    if (!interior) {
-      const bool kin = kt * BK + scol < K, ain = ca >= 0 && ca < K1;
-#pragma clang loop unroll(full)
-      for (int i = 0; i < 4; ++i) {
-        if (!(ain && ((oka >> i) & 1))) ra[i] = make_uint4(0, 0, 0, 0);
-        if (!(kin && ((okb >> i) & 1))) rb[i] = make_uint4(0, 0, 0, 0);
-      }
-    }
-#pragma clang loop unroll(full)
-    for (int i = 0; i < 4; ++i) {
-      *(uint4*)(As + (srow + i * 64) * kLdsStride + scol) = ra[i];
-      *(uint4*)(Bs + (srow + i * 64) * kLdsStride + scol) = rb[i];
-    }
-  };
-
-  const int nk = (K + BK - 1) / BK;
-  if constexpr (DIRECT) {
-    constexpr int kStageEl = 2 * LBM * BK;         // one stage: A then W, 128-byte rows
-    // instruction j of wave w fills LDS rows (j * 8 + w) * 8 .. + 7 of an operand; lane l holds
-    // slot l % 8 of row r = (j * 8 + w) * 8 + l / 8 there and fetches column chunk
-    // (l % 8) ^ ((r / 2) % 8) of that row, (r / 2) % 8 being (w % 2) * 4 + l / 16
+  // ---- K loop
+  {
+    TmStage<ALAY, TILE, T::kWaves> sa;
+    TmStage<WLAY, TILE, T::kWaves> sw;
+    TmStage<ALAY, TILE, T::kWaves> sa0;            // segment 0 has pitches of its own
+    TmStage<WLAY, TILE, T::kWaves> sw0;
+    sa.init(G.lda1, M - m0, wave, lane);
+    sw.init(G.ldw1, N - n0, wave, lane);
+    const int nk0 = (K0 + BK - 1) / BK, nk = nk0 + (kend - kofs + BK - 1) / BK;
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint16_t*)lds;
-    const int chunk = (lane & 7) ^ (((wave & 1) << 2) | (lane >> 4));
-    uint32_t va[4], vb[4];                         // byte offsets of this lane's chunks at k = 0
-#pragma clang loop unroll(full)
-    for (int j = 0; j < 4; ++j) {
-      const int r = (j * 8 + wave) * 8 + (lane >> 3);
-      va[j] = ((uint32_t)(m0 + r) * (uint32_t)lda + chunk * 8) * 2u;
-      vb[j] = ((uint32_t)(n0 + r) * (uint32_t)ldw + chunk * 8) * 2u;
-    }
     auto request_tile = [&](int stage, int kt) __attribute__((always_inline)) {
-      const uint16_t* ak = A + kt * BK;
-      const uint16_t* wk = W + kt * BK;
-#pragma clang loop unroll(full)
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t da = __builtin_amdgcn_readfirstlane(
-            lds0 + (uint32_t)(stage * kStageEl * 2 + (j * 8 + wave) * 1024));
-        const uint32_t db = da + LBM * BK * 2;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     :: "s"(da), "v"(va[j]), "s"(ak) : "memory");
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     :: "s"(db), "v"(vb[j]), "s"(wk) : "memory");
+      const uint32_t la = lds0 + stage * T::kStageBytes, lw = la + TILE * BK * 2;
+      if (kt >= nk0) {
+        const int k = kofs + (kt - nk0) * BK;
+        sa.request(la, (const uint16_t*)G.A1, G.lda1, m0, M, k, kend, wave);
+        sw.request(lw, (const uint16_t*)G.W1, G.ldw1, n0, N, k, kend, wave);
+      } else {                                     // (few steps: their offsets are not kept in registers)
+        const int k = kt * BK;
+        if constexpr (!DOTS) {
+          sa0.init(G.lda0, M - m0, wave, lane);
+          sa0.request(la, (const uint16_t*)G.A0, G.lda0, m0, M, k, K0, wave);
+        }
+        sw0.init(G.ldw0, N - n0, wave, lane);
+        sw0.request(lw, (const uint16_t*)G.W0, G.ldw0, n0, N, k, K0, wave);
       }
     };
-    // fragment reads: row (lane % 32) of a 32-row block, chunk 2 kk + lane / 32, in slot
-    // chunk ^ ((lane % 32) / 2) % 8
-    int sw[BK / 16];
-#pragma clang loop unroll(full)
-    for (int kk = 0; kk < BK / 16; ++kk)
-      sw[kk] = (((kk * 2 + (lane >> 5)) ^ ((lane >> 1) & 7)) * 8);
-    // Fragments are double-buffered in registers: the six reads of K slice kk + 1 are issued
-    // before the eight MFMAs of slice kk, so LDS latency hides behind matrix work of the same
-    // wave.  The barrier of a K step sits in front of its last slice's MFMAs: behind it come
-    // the requests for tile kt + 2 (every wave has read the whole current stage by then) and
-    // the first reads of tile kt + 1, and the last slice's MFMAs cover both.
-    uint4 fa[2][4], fb[2][2];
+    TmFrag<ALAY, TILE, T::MT> ra;
+    TmFrag<WLAY, TILE, T::NT> rw;
+    ra.init(wm * T::MT * 32, lane);
+    rw.init(wn * T::NT * 32, lane);
+    // Fragments are double-buffered in registers: the reads of K slice kk + 1 are issued before the
+    // MFMAs of slice kk, so LDS latency hides behind matrix work of the same wave.  The barrier of
+    // a K step sits in front of its last slice's MFMAs: behind it come the requests for tile
+    // kt + 2 (every wave has read the whole current stage by then) and the first reads of tile
+    // kt + 1, and the last slice's MFMAs cover both.
+    uint4 fa[2][T::MT], fw[2][T::NT];
     auto read_frag = [&](int buf, int stage, int kk) __attribute__((always_inline)) {
-      const uint16_t* ap = lds + stage * kStageEl + (wm * 128 + (lane & 31)) * BK + sw[kk];
-      const uint16_t* bp = lds + stage * kStageEl + LBM * BK + (wn * 64 + (lane & 31)) * BK + sw[kk];
-#pragma clang loop unroll(full)
-      for (int i = 0; i < 4; ++i) fa[buf][i] = *(const uint4*)(ap + i * 32 * BK);
-#pragma clang loop unroll(full)
-      for (int j = 0; j < 2; ++j) fb[buf][j] = *(const uint4*)(bp + j * 32 * BK);
+      const uint16_t* t = lds + stage * (T::kStageBytes / 2);
+      ra.read(fa[buf], t, kk);
+      rw.read(fw[buf], t + TILE * BK, kk);
     };
     request_tile(0, 0);
+    if constexpr (DOTS) {
+      if (nk > 1) request_tile(1, 1);
+      // pairwise dots of this block's samples into the first stage's A tile, zeros behind them: a
+      // wave takes 32 / nf samples at a time, whose (sample, feature) rows are one Gram tile
+#pragma clang loop unroll(full)
+      for (int q = 0; q < TILE * BK * 2 / 16 / T::kThreads; ++q)
+        *(uint4*)(lds + (q * T::kThreads + tid) * 8) = make_uint4(0, 0, 0, 0);
+      __syncthreads();
+      const int nf = G.nf, fd = G.fdim, spg = 32 / nf;
+      const uint16_t* A = (const uint16_t*)G.A1;
+      const int c = lane & 31, sc = c / nf, j = c % nf, h8 = (lane >> 5) * 8;
+      const int np = nf * (nf - 1) / 2, npad = K0 - np;
+      for (int s0 = wave * spg; s0 < TILE; s0 += T::kWaves * spg) {
+        const int s = s0 + sc;
+        const bool on = sc < spg && s < TILE && m0 + s < M;
+        const uint16_t* xp = A + (on ? (int64_t)(m0 + s) * G.lda1 + j * fd + h8 : 0);
+        floatx16 d;
+#pragma clang loop unroll(full)
+        for (int v = 0; v < 16; ++v) d[v] = 0.f;
+        for (int k = 0; k < fd; k += 64) {
+          uint4 a[4];
+#pragma clang loop unroll(full)
+          for (int u = 0; u < 4; ++u)               // (never past the tensor: what is not wanted reads its start)
+            a[u] = *(const uint4*)(on && k + u * 16 + h8 < fd ? xp + k + u * 16 : A);
+#pragma clang loop unroll(full)
+          for (int u = 0; u < 4; ++u) {
+            if (!(on && k + u * 16 + h8 < fd)) a[u] = make_uint4(0, 0, 0, 0);
+            d = mfma32<DT>(a[u], a[u], d);
+          }
+        }
+#pragma clang loop unroll(full)
+        for (int v = 0; v < 16; ++v) {
+          const int rr = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+          const int i = rr % nf;
+          if (rr / nf == sc && i < j && on) {
+            const int term = i * (2 * nf - i - 1) / 2 + (j - i - 1);
+            store_elt<DT>(lds, s * BK + (((term >> 3) ^ ((s >> 1) & 7)) << 3) + (term & 7), d[v]);
+            if constexpr (KEEPZ)
+              if (G.U) store_elt<DT>(G.U, (int64_t)(m0 + s) * K0 + term, d[v]);
+          }
+        }
+        if constexpr (KEEPZ) {
+          if (G.U)
+            for (int e = lane; e < spg * npad; e += 64) {
+              const int row = s0 + e / npad;
+              if (row < TILE && m0 + row < M) store_elt<DT>(G.U, (int64_t)(m0 + row) * K0 + np + e % npad, 0.f);
+            }
+        }
+      }
+    }
     __builtin_amdgcn_s_waitcnt(0x0f70);            // vmcnt(0): this wave's requests have landed
     __syncthreads();
-    if (nk > 1) request_tile(1, 1);
+    if (!DOTS && nk > 1) request_tile(1, 1);
     read_frag(0, 0, 0);
     for (int kt = 0; kt < nk; ++kt) {
       const int cur = kt & 1;
@@ -430,263 +396,255 @@ __global__ __launch_bounds__(kBigThreads, 1) void tm_gemm_mfma_256(const TmLaunc
           if (kt + 1 < nk) read_frag(0, cur ^ 1, 0);
         }
 #pragma clang loop unroll(full)
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < T::MT; ++i)
 #pragma clang loop unroll(full)
-          for (int j = 0; j < 2; ++j) acc[i][j] = mfma32<DT>(fb[kk & 1][j], fa[kk & 1][i], acc[i][j]);
-        // one LDS read, one MFMA, ...: left alone, the scheduler puts each read right in front
+          for (int j = 0; j < T::NT; ++j) acc[i][j] = mfma32<DT>(fw[kk & 1][j], fa[kk & 1][i], acc[i][j]);
+        // LDS reads and MFMAs alternately: left alone, the scheduler puts each read right in front
         // of the MFMA that needs it, to save registers
         if (kk + 1 < BK / 16) {
+          constexpr int kReads = TmFrag<ALAY, TILE, T::MT>::kReads + TmFrag<WLAY, TILE, T::NT>::kReads;
+          constexpr int kMfma = T::MT * T::NT, kPer = (kReads + kMfma - 1) / kMfma, kPairs = kReads / kPer;
 #pragma clang loop unroll(full)
-          for (int q = 0; q < 6; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          for (int q = 0; q < kPairs; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x100, kPer, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
           }
-          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+          if (kMfma > kPairs) __builtin_amdgcn_sched_group_barrier(0x008, kMfma - kPairs, 0);
         }
       }
     }
-  } else {
-  load_tile(0);
-  store_tile(0, 0);
-  if (nk > 1) load_tile(1);
-  if constexpr (DOTS) {
-    // pairwise dots of this block's 256 samples, written over the zeros the first tile store
-    // left in the operand's leading columns: 32 consecutive (sample, feature) rows are one
-    // 32 x 32 Gram tile; eight waves share the 256 * nf / 32 row groups
-    __syncthreads();
-    const int nf = G.nf, fd = G.fdim;
-    const int64_t nrows = (int64_t)M * nf;
-    const int ngroups = LBM * nf / 32;
-    for (int rg = wave; rg < ngroups; rg += kBigThreads / 64) {
-      const int64_t r = (int64_t)m0 * nf + rg * 32 + (lane & 31);
-      const uint16_t* xp = A + r * fd + (lane >> 5) * 8;
-      floatx16 d;
-#pragma clang loop unroll(full)
-      for (int v = 0; v < 16; ++v) d[v] = 0.f;
-      const uint16_t* xq = r < nrows ? xp : A + (lane >> 5) * 8;   // rows past the edge: row 0, zeroed
-      for (int k = 0; k < fd; k += 64) {
-        uint4 a[4];
-#pragma clang loop unroll(full)
-        for (int u = 0; u < 4; ++u) a[u] = *(const uint4*)(xq + (k + u * 16 < fd ? k + u * 16 : 0));
-#pragma clang loop unroll(full)
-        for (int u = 0; u < 4; ++u) {
-          if (!(r < nrows && k + u * 16 < fd)) a[u] = make_uint4(0, 0, 0, 0);
-          d = mfma32<DT>(a[u], a[u], d);
-        }
-      }
-      const int c = lane & 31, sc = c / nf, j = c % nf;
-      const int s_local = rg * 32 / nf + sc;
-#pragma clang loop unroll(full)
-      for (int v = 0; v < 16; ++v) {
-        const int rr = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-        const int i = rr % nf;
-        if (rr / nf == sc && i < j) {
-          const int term = i * (2 * nf - i - 1) / 2 + (j - i - 1);
-          store_elt<DT>(lds, s_local * kLdsStride + term, d[v]);
-          if constexpr (KEEPZ)
-            if (G.U && m0 + s_local < M) store_elt<DT>(G.U, (int64_t)(m0 + s_local) * G.K0 + term, d[v]);
-        }
-      }
-      if constexpr (KEEPZ) {
-        // zeros behind the terms of the row group's samples
-        const int np = nf * (nf - 1) / 2, npad = G.K0 - np, spg = 32 / nf;
-        if (G.U)
-          for (int e = lane; e < spg * npad; e += 64) {
-            const int row = m0 + rg * spg + e / npad;
-            if (row < M) store_elt<DT>(G.U, (int64_t)row * G.K0 + np + e % npad, 0.f);
-          }
-      }
-    }
   }
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) store_tile(cur ^ 1, kt + 1);
-    if (kt + 2 < nk) load_tile(kt + 2);
-    const uint16_t* ap = lds + cur * 2 * kBigTileElems + (wm * 128 + (lane & 31)) * kLdsStride +
-                         (lane >> 5) * 8;
-    const uint16_t* bp = lds + cur * 2 * kBigTileElems + kBigTileElems +
-                         (wn * 64 + (lane & 31)) * kLdsStride + (lane >> 5) * 8;
-#pragma clang loop unroll(full)
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      uint4 a[4], b[2];
-#pragma clang loop unroll(full)
-      for (int i = 0; i < 4; ++i) a[i] = *(const uint4*)(ap + i * 32 * kLdsStride + kk * 16);
-#pragma clang loop unroll(full)
-      for (int j = 0; j < 2; ++j) b[j] = *(const uint4*)(bp + j * 32 * kLdsStride + kk * 16);
-#pragma clang loop unroll(full)
-      for (int i = 0; i < 4; ++i)
-#pragma clang loop unroll(full)
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma32<DT>(b[j], a[i], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  }
-  // Epilogue through LDS, one 128-row half of the tile at a time: the waves that own the half
-  // park their float32 accumulators (a lane holds four consecutive columns of one row per
-  // register quad: too narrow for global memory), then all 512 threads walk the half in
-  // 8-column pieces, so bias, x0, x_l and the output move as 16-byte accesses.
+
+  // ---- epilogue through LDS, the rows of one wave row at a time: the waves that own them park their
+  // float32 accumulators (a lane holds four consecutive columns of one row per register quad: too
+  // narrow for global memory), then all threads walk them in 8-column pieces, so bias, x0, x_l
+  // and the output move as 16-byte accesses.
   const int epi = G.epi;
-  float* stage = (float*)lds;
-  constexpr int kStageStride = LBN + 4;            // rows 4 banks apart: 16 lanes' float4 stores spread over all 64
-  const bool vec_ok =
-      G.ldc % 8 == 0 && n0 + LBN <= N &&
-      (((uintptr_t)G.C | (uintptr_t)G.bias | (uintptr_t)G.U) & 15) == 0 &&
-      (epi != EPI_CROSS ||
-       (G.ldx % 8 == 0 && tm_ldxl(G) % 8 == 0 && (((uintptr_t)G.X0 | (uintptr_t)tm_xl(G)) & 15) == 0));
-  const uint16_t* __restrict__ XLp = (const uint16_t*)tm_xl(G);
-  const int ldxl = tm_ldxl(G);
-  // The two epilogues that read global memory (cross: x0 and x_l; accumulate: C itself) request
-  // all of a half's operands before the accumulators are parked: with one block per CU nothing
-  // else hides that latency, and a thread's eight chunks one after another cost eight of them.
-  constexpr int kChunks = 128 * (LBN / 8) / kBigThreads;
-  // (byte offsets from the operand's base fit 32 bits: one register per address instead of two)
-  const bool fast_cross = epi == EPI_CROSS && vec_ok && (int64_t)M * G.ldx < (1LL << 31) &&
-                          (int64_t)M * ldxl < (1LL << 31) && (int64_t)M * G.ldc < (1LL << 31);
-  const bool fast_add = epi == EPI_F32_ADD && n0 + LBN <= N && G.ldc % 4 == 0 &&
-                        (int64_t)M * G.ldc < (1LL << 30) &&
-                        (((uintptr_t)((float*)G.C + slice * G.cstride)) & 15) == 0;
-  // bias / bias + ReLU / plain float32 tiles walk the same unrolled loop (nothing to prefetch)
-  const bool fast_plain = vec_ok && epi <= EPI_BIAS_RELU && (int64_t)M * G.ldc < (1LL << 31);
-  const bool fast_f32 = epi == EPI_F32 && n0 + LBN <= N && G.ldc % 4 == 0 &&
-                        (int64_t)M * G.ldc < (1LL << 30) &&
-                        (((uintptr_t)((float*)G.C + slice * G.cstride)) & 15) == 0;
-  const bool fast = fast_cross || fast_add || fast_plain || fast_f32;
-  const char* const pre_a = fast_cross ? (const char*)G.X0 : (const char*)((float*)G.C + slice * G.cstride);
-  const char* const pre_b = fast_cross ? (const char*)XLp : pre_a + 16;
-  const uint32_t pre_lda = fast_cross ? (uint32_t)G.ldx * 2u : (uint32_t)G.ldc * 4u;   // row pitch, bytes
-  const uint32_t pre_ldb = fast_cross ? (uint32_t)ldxl * 2u : pre_lda;
-  const uint32_t pre_col = fast_cross ? 2u : 4u;                                        // bytes per column
+  float* park = (float*)lds;
+  auto park_half = [&]() __attribute__((always_inline)) {
 #pragma clang loop unroll(full)
-  for (int h = 0; h < 2; ++h) {
-    uint4 pa[kChunks], pb[kChunks];
-    if (fast_cross || fast_add) {
+    for (int j = 0; j < T::NT; ++j)
 #pragma clang loop unroll(full)
-      for (int u = 0; u < kChunks; ++u) {
-        const int c = tid + u * kBigThreads;
-        const int r = c / (LBN / 8), cc = (c % (LBN / 8)) * 8;
-        const uint32_t m = (uint32_t)min(m0 + h * 128 + r, M - 1), n = (uint32_t)(n0 + cc);
-        pa[u] = *(const uint4*)(pre_a + (m * pre_lda + n * pre_col));
-        pb[u] = *(const uint4*)(pre_b + (m * pre_ldb + n * pre_col));
-      }
-    }
-    if (wm == h) {
+      for (int i = 0; i < T::MT; ++i)
 #pragma clang loop unroll(full)
-      for (int j = 0; j < 2; ++j)
+        for (int g = 0; g < 4; ++g)
+          *(float4*)(park + (i * 32 + (lane & 31)) * T::kParkStride + wn * T::NT * 32 + j * 32 + g * 8 + (lane >> 5) * 4) =
+              make_float4(acc[i][j][g * 4], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
+  };
+  constexpr int kRowThreads = TILE / 8, kRowStep = T::kThreads / kRowThreads, kChunks = T::kHalf / kRowStep;
+  constexpr int kAhead = 2, kBufs = TILE == 256 ? 3 : 4;     // pieces whose operands are requested together, batches of them
+  static_assert(kChunks % kAhead == 0, "");
+  const int r0 = tid / kRowThreads, cc = (tid % kRowThreads) * 8;
+  constexpr bool kForward = ALAY == OP_ROW && WLAY == OP_ROW;        // 16-bit outputs and x0; the others are gradients
+  if constexpr (!kForward) {
+    // Float32 outputs, four columns a lane, so that a wave's store covers whole lines (eight columns a
+    // lane, two stores of every other 16 bytes: 2.5 GB of data gradients took 715 us, now 644).
+    constexpr int kRow4 = T::kThreads / (TILE / 4), kPieces = T::kHalf / kRow4;
+    constexpr int kBatch = TILE == 256 ? 2 : 4, kBatchesHalf = kPieces / kBatch, kBatchesAll = T::WM * kBatchesHalf, kDeep = 2;
+    const int r4 = tid / (TILE / 4), c4 = (tid % (TILE / 4)) * 4;
+    const bool on = n0 + c4 < N;
+    const int64_t corner = (int64_t)m0 * G.ldc + n0;
+    char* const c = (char*)((float*)G.C + slice * G.cstride + corner);
+    const bool grad = ALAY == OP_ROW && epi == EPI_CROSS_GRAD, add = epi == EPI_F32_ADD;
+    if (grad || (epi >= EPI_F32 && N % 4 == 0 && G.ldc % 4 == 0 && G.rdiv == 0 && ((uintptr_t)c & 15) == 0)) {
+      // What a piece reads is requested a batch of pieces ahead, the first before the accumulators are
+      // parked: with one block per CU nothing else hides that latency.  EPI_CROSS_GRAD: whole
+      // pieces only (N and ldc are a tower's width, the tensors the library's own or blocks of
+      // grad_pooled).
+      const char *gn = add ? c : (const char*)(G.GN + corner), *ul = (const char*)G.UL + corner * 2;
+      const char *x0 = (const char*)G.X0 + corner * 2, *u0 = (const char*)G.U0 + corner * 2;
+      char *a0 = (char*)(G.ACC + corner), *du = (char*)G.DU + corner * 2;
+      const bool has_gn = add || (grad && G.GN), has_u0 = grad && G.U0, acc_old = grad && !G.acc_first && (G.GN || G.U0);
+      float4 pg[kDeep][kBatch], po[kDeep][kBatch];
+      uint2 px[kDeep][kBatch], pu[kDeep][kBatch], pv[kDeep][kBatch];
+      auto request = [&](int buf, int b) __attribute__((always_inline)) {
 #pragma clang loop unroll(full)
-        for (int i = 0; i < 4; ++i)
-#pragma clang loop unroll(full)
-          for (int g = 0; g < 4; ++g)
-            *(float4*)(stage + (i * 32 + (lane & 31)) * kStageStride + wn * 64 + j * 32 + g * 8 + (lane >> 5) * 4) =
-                make_float4(acc[i][j][g * 4], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
-    }
-    __syncthreads();
-    if (fast) {
-      // chunk u of half h is row h * 128 + u * 16 + tid / 32 of the tile, the thread's own 8
-      // columns: one 32-bit byte offset from C (and U), advanced by a uniform step
-      const int r0 = tid / (LBN / 8), cc = (tid % (LBN / 8)) * 8;
-      const uint32_t esz = epi >= EPI_F32 ? 4u : 2u;
-      char* const cbase = epi >= EPI_F32 ? (char*)((float*)G.C + slice * G.cstride) : (char*)G.C;
-      const uint32_t ostep = 16u * (uint32_t)G.ldc * esz;
-      uint32_t off = ((uint32_t)(m0 + h * 128 + r0) * (uint32_t)G.ldc + (uint32_t)(n0 + cc)) * esz;
-      // a thread's chunks all lie in one 8-column piece of the tile: one bias load serves them
-      uint4 bias_raw = make_uint4(0, 0, 0, 0);
-      if ((fast_cross || fast_plain) && G.bias) bias_raw = *(const uint4*)((const uint16_t*)G.bias + n0 + cc);
-#pragma clang loop unroll(full)
-      for (int u = 0; u < kChunks; ++u, off += ostep) {
-        const int r = r0 + u * 16;
-        if (m0 + h * 128 + r >= M) continue;
-        float y[8];
-        const float4 s0 = *(const float4*)(stage + r * kStageStride + cc);
-        const float4 s1 = *(const float4*)(stage + r * kStageStride + cc + 4);
-        y[0] = s0.x; y[1] = s0.y; y[2] = s0.z; y[3] = s0.w;
-        y[4] = s1.x; y[5] = s1.y; y[6] = s1.z; y[7] = s1.w;
-        if (fast_add) {
-          const float4 p0 = __builtin_bit_cast(float4, pa[u]), p1 = __builtin_bit_cast(float4, pb[u]);
-          *(float4*)(cbase + off) = make_float4(y[0] + p0.x, y[1] + p0.y, y[2] + p0.z, y[3] + p0.w);
-          *(float4*)(cbase + off + 16) = make_float4(y[4] + p1.x, y[5] + p1.y, y[6] + p1.z, y[7] + p1.w);
-        } else if (fast_f32) {
-          *(float4*)(cbase + off) = s0;
-          *(float4*)(cbase + off + 16) = s1;
-        } else {
-          float bv[8];
-          dmt::decode_chunk<DT>(bv, bias_raw);
-#pragma clang loop unroll(full)
-          for (int q = 0; q < 8; ++q) y[q] += bv[q];
-          if (fast_plain) {
-            if (epi == EPI_BIAS_RELU) {
-#pragma clang loop unroll(full)
-              for (int q = 0; q < 8; ++q) y[q] = y[q] > 0.f ? y[q] : 0.f;
+        for (int u = 0; u < kBatch; ++u) {
+          // (rows and columns past the edge read in bounds and are not stored)
+          const uint32_t m = (uint32_t)min(b / kBatchesHalf * T::kHalf + r4 + (b % kBatchesHalf * kBatch + u) * kRow4, M - 1 - m0);
+          const uint32_t e = m * (uint32_t)G.ldc + (on ? (uint32_t)c4 : 0u);
+          if (has_gn) pg[buf][u] = *(const float4*)(gn + e * 4u);
+          if constexpr (ALAY == OP_ROW) {
+            if (grad) {
+              px[buf][u] = *(const uint2*)(x0 + e * 2u);
+              if (G.GN) pu[buf][u] = *(const uint2*)(ul + e * 2u);
+              if (has_u0) pv[buf][u] = *(const uint2*)(u0 + e * 2u);
+              if (acc_old) po[buf][u] = *(const float4*)(a0 + e * 4u);
             }
-          } else {
-            float xv[8], lv[8];
-            if (G.U) dmt::store_chunk<DT, 8>((char*)G.U + off, 0, y);
-            dmt::decode_chunk<DT>(xv, pa[u]);
-            dmt::decode_chunk<DT>(lv, pb[u]);
-#pragma clang loop unroll(full)
-            for (int q = 0; q < 8; ++q) y[q] = xv[q] * y[q] + lv[q];
           }
-          dmt::store_chunk<DT, 8>(cbase + off, 0, y);
+        }
+      };
+      float4 sums = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (has_gn || grad) request(0, 0);
+#pragma clang loop unroll(full)
+      for (int b = 0; b < kBatchesAll; ++b) {
+        const int h = b / kBatchesHalf, buf = b % kDeep;
+        if (b % kBatchesHalf == 0) {
+          if (wm == h) park_half();
+          __syncthreads();
+        }
+        if ((has_gn || grad) && b + 1 < kBatchesAll) request((b + 1) % kDeep, b + 1);
+#pragma clang loop unroll(full)
+        for (int u = 0; u < kBatch; ++u) {
+          const int r = r4 + (b % kBatchesHalf * kBatch + u) * kRow4;
+          if (m0 + h * T::kHalf + r >= M || !on) continue;
+          const uint32_t e = (uint32_t)(h * T::kHalf + r) * (uint32_t)G.ldc + (uint32_t)c4;
+          float4 g = *(const float4*)(park + r * T::kParkStride + c4);
+          if (has_gn) {
+            const float4 n = pg[buf][u];
+            g.x += n.x; g.y += n.y; g.z += n.z; g.w += n.w;
+          }
+          if constexpr (ALAY == OP_ROW) {
+            if (grad) {
+              float v0, v1, v2, v3;
+              if (G.GN || has_u0) {
+                float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (acc_old) t = po[buf][u];
+                if (G.GN) {
+                  const float4 n = pg[buf][u];
+                  dmt::unpack2<DT>(pu[buf][u].x, v0, v1);
+                  dmt::unpack2<DT>(pu[buf][u].y, v2, v3);
+                  t.x += n.x * v0; t.y += n.y * v1; t.z += n.z * v2; t.w += n.w * v3;
+                }
+                if (has_u0) {
+                  dmt::unpack2<DT>(pv[buf][u].x, v0, v1);
+                  dmt::unpack2<DT>(pv[buf][u].y, v2, v3);
+                  t.x += g.x * v0 + g.x; t.y += g.y * v1 + g.y; t.z += g.z * v2 + g.z; t.w += g.w * v3 + g.w;
+                }
+                *(float4*)(a0 + e * 4u) = t;
+              }
+              dmt::unpack2<DT>(px[buf][u].x, v0, v1);
+              dmt::unpack2<DT>(px[buf][u].y, v2, v3);
+              const uint2 d = make_uint2(dmt::pack2<DT>(g.x * v0, g.y * v1), dmt::pack2<DT>(g.z * v2, g.w * v3));
+              *(uint2*)(du + e * 2u) = d;
+              dmt::unpack2<DT>(d.x, v0, v1);       // the bias gradient sums the rounded values
+              dmt::unpack2<DT>(d.y, v2, v3);
+              sums.x += v0; sums.y += v1; sums.z += v2; sums.w += v3;
+              if (!G.C) continue;
+            }
+          }
+          *(float4*)(c + e * 4u) = g;
+        }
+        if (b % kBatchesHalf == kBatchesHalf - 1) {
+          __syncthreads();                         // the parked rows have been read
+          if (grad && (TILE == 256 || h == T::WM - 1)) {
+            // column sums of 128 rows: the row steps' sums, added in order
+            *(float4*)(park + r4 * TILE + c4) = sums;
+            sums = make_float4(0.f, 0.f, 0.f, 0.f);
+            __syncthreads();
+            const int block = (m0 + (TILE == 256 ? h * T::kHalf : 0)) / 128;
+            if (tid < TILE && n0 + tid < N && block * 128 < M) {
+              float y = 0.f;
+#pragma clang loop unroll(full)
+              for (int q = 0; q < kRow4; ++q) y += park[q * TILE + tid];
+              G.DBP[(int64_t)block * N + n0 + tid] = y;
+            }
+            __syncthreads();
+          }
         }
       }
-      __syncthreads();
-      continue;
+      return;
     }
-    for (int c = tid; c < 128 * (LBN / 8); c += kBigThreads) {
-      const int r = c / (LBN / 8), cc = (c % (LBN / 8)) * 8;
-      const int m = m0 + h * 128 + r, n = n0 + cc;
-      if (m >= M || n >= N) continue;
-      float y[8];
-      const float4 s0 = *(const float4*)(stage + r * kStageStride + cc);
-      const float4 s1 = *(const float4*)(stage + r * kStageStride + cc + 4);
-      y[0] = s0.x; y[1] = s0.y; y[2] = s0.z; y[3] = s0.w;
-      y[4] = s1.x; y[5] = s1.y; y[6] = s1.z; y[7] = s1.w;
-      if (epi >= EPI_F32) {
-        float* c = (float*)G.C + slice * G.cstride + (int64_t)m * G.ldc + n;
-        if (n + 8 <= N && ((uintptr_t)c & 15) == 0) {
-          float4 lo = make_float4(y[0], y[1], y[2], y[3]), hi = make_float4(y[4], y[5], y[6], y[7]);
-          if (epi == EPI_F32_ADD) {
-            const float4 p0 = *(const float4*)c, p1 = *(const float4*)(c + 4);
-            lo.x += p0.x; lo.y += p0.y; lo.z += p0.z; lo.w += p0.w;
-            hi.x += p1.x; hi.y += p1.y; hi.z += p1.z; hi.w += p1.w;
-          }
-          *(float4*)c = lo;
-          *(float4*)(c + 4) = hi;
-          continue;
-        }
-        for (int q = 0; q < 8 && n + q < N; ++q) c[q] = epi == EPI_F32_ADD ? c[q] + y[q] : y[q];
-        continue;
-      }
-      if (vec_ok) {
-        float bv[8], xv[8], lv[8];
-        if (G.bias) {
-          dmt::decode_chunk<DT>(bv, *(const uint4*)((const uint16_t*)G.bias + n));
+  }
+  const bool f32out = epi >= EPI_F32;
+  // byte addresses of the 16-bit tensors: the tile's corner (uniform, 64 bits) + an offset inside the tile
+  char* const cbase = (char*)G.C + ((int64_t)m0 * G.ldc + n0) * 2;
+  char* const ubase = (char*)G.U + ((int64_t)m0 * G.ldc + n0) * 2;
+  const char* const xbase = (const char*)G.X0 + ((int64_t)m0 * G.ldx + n0) * 2;
+  const char* const lbase = (const char*)G.XL + ((int64_t)m0 * G.ldxl + n0) * 2;
+  // whole 16-byte pieces everywhere (all tiles of a group alike): N and the pitches multiples of 8
+  bool fast = !f32out && G.N % 8 == 0 && G.ldc % 8 == 0 && G.ldc2 % 8 == 0 && (((uintptr_t)cbase | (uintptr_t)G.bias) & 15) == 0;
+  if (epi == EPI_CROSS)
+    fast = fast && G.ldx % 8 == 0 && G.ldxl % 8 == 0 && (((uintptr_t)xbase | (uintptr_t)lbase | (uintptr_t)ubase) & 15) == 0;
+  const bool cols_on = n0 + cc < N;
+  if (fast) {
+    const bool pre_cross = kForward && epi == EPI_CROSS;
+    const uint32_t la = (uint32_t)G.ldx * 2u, lb = (uint32_t)G.ldxl * 2u, col = cols_on ? (uint32_t)cc * 2u : 0u;
+    // a thread's chunks all lie in one 8-column piece of the tile: one bias load serves them
+    uint4 bias_raw = make_uint4(0, 0, 0, 0);
+    if (G.bias && cols_on) bias_raw = *(const uint4*)((const uint16_t*)G.bias + n0 + cc);
+    // The cross epilogue requests its operands (x0 and x_l) for two pieces together, kBufs - 1
+    // batches ahead of the one being walked and the first before the accumulators are parked: with
+    // one block per CU nothing else hides that latency, and more is more registers than a wave
+    // has beside its accumulators.
+    uint4 pa[kBufs][kAhead], pb[kBufs][kAhead];
+    auto request = [&](int buf, int batch) __attribute__((always_inline)) {
+      const int h = batch / (kChunks / kAhead), u1 = batch % (kChunks / kAhead) * kAhead;
 #pragma clang loop unroll(full)
-          for (int q = 0; q < 8; ++q) y[q] += bv[q];
+      for (int u = 0; u < kAhead; ++u) {
+        const uint32_t m = (uint32_t)min(h * T::kHalf + r0 + (u1 + u) * kRowStep, M - 1 - m0);
+        pa[buf][u] = *(const uint4*)(xbase + (m * la + col));
+        pb[buf][u] = *(const uint4*)(lbase + (m * lb + col));
+      }
+    };
+    constexpr int kBatches = T::WM * (kChunks / kAhead);
+    if (pre_cross)
+#pragma clang loop unroll(full)
+      for (int q = 0; q < kBufs - 1 && q < kBatches; ++q) request(q, q);
+#pragma clang loop unroll(full)
+    for (int batch = 0; batch < kBatches; ++batch) {
+      const int h = batch / (kChunks / kAhead), u1 = batch % (kChunks / kAhead) * kAhead, buf = batch % kBufs;
+      if (u1 == 0) {
+        if (wm == h) park_half();
+        __syncthreads();
+      }
+      if (pre_cross && batch + kBufs - 1 < kBatches) request((batch + kBufs - 1) % kBufs, batch + kBufs - 1);
+#pragma clang loop unroll(full)
+      for (int u = 0; u < kAhead; ++u) {
+        const int r = r0 + (u1 + u) * kRowStep;
+        if (m0 + h * T::kHalf + r >= M || !cols_on) continue;
+        const float4 s0 = *(const float4*)(park + r * T::kParkStride + cc);
+        const float4 s1 = *(const float4*)(park + r * T::kParkStride + cc + 4);
+        char* c = cbase + ((uint32_t)(h * T::kHalf + r) * (uint32_t)G.ldc + (uint32_t)cc) * 2u;
+        if (G.rdiv > 0) {
+          const int m = m0 + h * T::kHalf + r;
+          c = (char*)G.C + ((int64_t)(m / G.rdiv) * G.ldc + (int64_t)(m % G.rdiv) * G.ldc2 + n0 + cc) * 2;
         }
+        float y[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+        float bv[8];
+        dmt::decode_chunk<DT>(bv, bias_raw);
+#pragma clang loop unroll(full)
+        for (int q = 0; q < 8; ++q) y[q] += bv[q];
         if (epi == EPI_BIAS_RELU) {
 #pragma clang loop unroll(full)
           for (int q = 0; q < 8; ++q) y[q] = y[q] > 0.f ? y[q] : 0.f;
-        }
-        if (epi == EPI_CROSS) {
-          if (G.U) dmt::store_chunk<DT, 8>(G.U, (int64_t)m * G.ldc + n, y);
-          dmt::decode_chunk<DT>(xv, *(const uint4*)((const uint16_t*)G.X0 + (int64_t)m * G.ldx + n));
-          dmt::decode_chunk<DT>(lv, *(const uint4*)(XLp + (int64_t)m * ldxl + n));
+        } else if (kForward && epi == EPI_CROSS) {
+          float xv[8], lv[8];
+          if (G.U) dmt::store_chunk<DT, 8>(ubase + ((uint32_t)(h * T::kHalf + r) * (uint32_t)G.ldc + (uint32_t)cc) * 2u, 0, y);
+          dmt::decode_chunk<DT>(xv, pa[buf][u]);
+          dmt::decode_chunk<DT>(lv, pb[buf][u]);
 #pragma clang loop unroll(full)
           for (int q = 0; q < 8; ++q) y[q] = xv[q] * y[q] + lv[q];
         }
-        dmt::store_chunk<DT, 8>(G.C, (int64_t)m * G.ldc + n, y);
-      } else {
-        for (int q = 0; q < 8 && n + q < N; ++q) {
-          float z = y[q] + (G.bias ? load_elt<DT>(G.bias, n + q) : 0.f);
-          if (epi == EPI_BIAS_RELU) z = z > 0.f ? z : 0.f;
-          if (epi == EPI_CROSS) {
-            if (G.U) store_elt<DT>(G.U, (int64_t)m * G.ldc + n + q, z);
-            z = load_elt<DT>(G.X0, (int64_t)m * G.ldx + n + q) * z +
-                load_elt<DT>(XLp, (int64_t)m * ldxl + n + q);
-          }
-          store_elt<DT>(G.C, (int64_t)m * G.ldc + n + q, z);
+        dmt::store_chunk<DT, 8>(c, 0, y);
+      }
+      if (u1 + kAhead == kChunks && h + 1 < T::WM) __syncthreads();
+    }
+    return;
+  }
+  // odd widths, unaligned rows: the same, element by element
+  for (int h = 0; h < T::WM; ++h) {
+    if (wm == h) park_half();
+    __syncthreads();
+    for (int r = r0; r < T::kHalf; r += kRowStep) {
+      const int m = m0 + h * T::kHalf + r;
+      if (m >= M) break;
+      const int64_t row = G.rdiv > 0 ? (int64_t)(m / G.rdiv) * G.ldc + (int64_t)(m % G.rdiv) * G.ldc2 : (int64_t)m * G.ldc;
+      for (int q = 0; q < 8 && n0 + cc + q < N; ++q) {
+        const int n = n0 + cc + q;
+        float y = park[r * T::kParkStride + cc + q];
+        if (f32out) {
+          float* c = (float*)G.C + slice * G.cstride + row + n;
+          *c = epi == EPI_F32_ADD ? *c + y : y;
+          continue;
         }
+        if (G.bias) y += load_elt<DT>(G.bias, n);
+        if (epi == EPI_BIAS_RELU) y = y > 0.f ? y : 0.f;
+        if (epi == EPI_CROSS) {
+          if (G.U) store_elt<DT>(G.U, row + n, y);
+          y = load_elt<DT>(G.X0, (int64_t)m * G.ldx + n) * y + load_elt<DT>(G.XL, (int64_t)m * G.ldxl + n);
+        }
+        store_elt<DT>(G.C, row + n, y);
       }
     }
     __syncthreads();
@@ -824,11 +782,16 @@ __global__ __launch_bounds__(kBlock) void tm_pack_w(const TmAuxLaunch L) {
   ((uint16_t*)G.dst)[e] = (k >= np && k < np_pad) ? (uint16_t)0 : ((const uint16_t*)G.src)[src];
 }
 
+// Whether a dot tower's projection weights ([O][np + wt], 16-bit) can be read as they are: both
+// pieces of a row then start on a 4-byte boundary, which is what the straight-to-LDS loads need.
+// Otherwise (an odd number of dot terms) they are repacked by tm_pack_w first.
+inline bool dot_weights_as_is(const void* w_proj, int np) { return np % 2 == 0 && ((uintptr_t)w_proj & 3) == 0; }
+
 // What a training forward keeps for the backward: for every cross layer l of a cross tower
 // (full-rank or low-rank), x_{l+1} and u_l = W_l x_l + b_l, each [B][W_t] in the compute type;
 // for a dot-product tower its dot terms, [B][np_pad] (np_pad = the F (F - 1) / 2 terms rounded
-// up to 8, zeros behind them), and its projection weights with zero columns inserted to match,
-// [O][np_pad + W_t].  Offsets in bytes from a 256-byte-aligned base; towers of other
+// up to 8, zeros behind them), and, where they cannot be read as they are, its projection weights
+// with zero columns inserted to match, [O][np_pad + W_t].  Offsets in bytes from a 256-byte-aligned base; towers of other
 // kinds keep nothing (their backward needs only the pooled values).
 struct TmKept {
   size_t x[DMT_MAX_CROSS_LAYERS] = {}, u[DMT_MAX_CROSS_LAYERS] = {};
@@ -862,93 +825,79 @@ inline size_t plan_tm_kept(const dmt_plan* p, const dmt_tm_params* tp, int64_t B
   return off;
 }
 
-// Whether a group can go to the 256 x 256 kernel (dots: with in-kernel dot terms).  At most 128
-// rows or columns (a weight gradient with few outputs) would leave half of every tile empty.
-inline bool big_ok(const TmGroup& g, bool dots) {
-  return g.N > 128 && g.M > 128 && g.N <= kSuper * LBN && g.K1 >= 128 && (dots || g.K0 == 0) &&
-         g.rdiv == 0 &&
-         (int64_t)g.M * g.lda1 < (1LL << 31) && (int64_t)g.N * g.ldw < (1LL << 31);
+// Launches of tm_gemm.
+template <int DT, int TILE, int ALAY, int WLAY, bool DOTS, bool KEEPZ>
+void launch_tiles(const TmLaunch& L, int64_t blocks, hipStream_t s) {
+  constexpr int bytes = TmTile<TILE>::kLdsBytes;
+  auto kernel = tm_gemm<DT, TILE, ALAY, WLAY, DOTS, KEEPZ>;
+  static const hipError_t configured =
+      hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  (void)configured;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TmTile<TILE>::kThreads), bytes, s, L);
 }
 
-template <int DT>
-void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t s,
-                   bool dots = false, int kid = DMT_K_TM_GEMM) {
+inline int64_t tiles_of(const TmGroup& g, int tile) {
+  return (int64_t)((g.M + tile - 1) / tile) * ((g.N + tile - 1) / tile) * tm_slices(g);
+}
+
+// Whether a launch takes 256 x 256 tiles: when there are at least kBigTiles of them (three for every
+// four CUs) and no group is so narrow that half of every tile would be empty.  (A short K makes no
+// difference: data gradients of K = 128 and 256, 720 against 715 and 108 against 102 us.)
+constexpr int kBigTiles = 192;
+inline bool take_big(const dmt_plan* p, const TmGroup* g, int n) {
+  if (p->sw.tm_big == 0) return false;
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    if (g[i].M <= 128 || g[i].N <= 128) return false;
+    tiles += tiles_of(g[i], 256);
+  }
+  return tiles >= kBigTiles || p->sw.tm_big == 2;
+}
+
+// All groups of the list, kMaxGroups to a launch.  dots: every group computes its dot terms itself.
+template <int DT, int ALAY = OP_ROW, int WLAY = OP_ROW>
+void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t s, bool dots = false,
+                   int kid = DMT_K_TM_GEMM) {
   for (size_t first = 0; first < groups.size(); first += kMaxGroups) {
     TmLaunch L;
     L.ngroups = (int32_t)std::min<size_t>(kMaxGroups, groups.size() - first);
-    int32_t tiles = 0;
+    bool keepz = false;                           // a training forward keeps the dot terms
     for (int i = 0; i < L.ngroups; ++i) {
-      const TmGroup& g = groups[first + i];
-      L.g[i] = g;
-      L.tile_start[i] = tiles;
-      tiles += ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * tm_slices(g);
+      L.g[i] = groups[first + i];
+      keepz = keepz || (dots && L.g[i].U != nullptr);
     }
-    L.tile_start[L.ngroups] = tiles;
-    if (tiles == 0) continue;
-    {
-      // wide outputs take the 256 x 256 kernel
-      bool big = dots || p->sw.tm_big != 0;
-      for (int i = 0; i < L.ngroups; ++i) big = big && big_ok(L.g[i], dots);
-      if (big) {
-        static bool configured = false;
-        if (!configured) {
-          (void)hipFuncSetAttribute((const void*)tm_gemm_mfma_256<DT, false>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kBigLdsBytes);
-          (void)hipFuncSetAttribute((const void*)tm_gemm_mfma_256<DT, true>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kBigLdsBytes);
-          (void)hipFuncSetAttribute((const void*)tm_gemm_mfma_256<DT, true, DMT_TM_TAG, true>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kBigLdsBytes);
-          (void)hipFuncSetAttribute((const void*)tm_gemm_mfma_256<DT, false, DMT_TM_TAG, false, true>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kBigLdsBytes);
-          configured = true;
-        }
-        int32_t nst = 0;                                      // super-tiles of the launch
-        for (int i = 0; i < L.ngroups; ++i) {
-          L.tile_start[i] = nst;
-          const int tn = (L.g[i].N + LBN - 1) / LBN;
-          const int tm = (L.g[i].M + LBM - 1) / LBM * tm_slices(L.g[i]);
-          const int sm = tn >= kSuper ? 1 : kSuper / tn;
-          nst += (tm + sm - 1) / sm;
-        }
-        L.tile_start[L.ngroups] = nst;
-        const int32_t big_tiles = (nst + 7) / 8 * 8 * kSuper;
-        DmtScope sc_(p, kid, s);
-        // every tile interior and every operand row 16-byte aligned: tiles go straight to LDS
-        bool direct = !dots && p->sw.tm_direct != 0;
-        for (int i = 0; i < L.ngroups; ++i) {
-          const TmGroup& g = L.g[i];
-          const int kk = g.ksplit > 1 ? g.klen : g.K1;
-          direct = direct && g.M % LBM == 0 && g.N % LBN == 0 && kk >= BK && kk % BK == 0 && g.K1 % BK == 0 &&
-                   g.lda1 % 8 == 0 && g.ldw % 8 == 0 &&
-                   (((uintptr_t)g.A1 | (uintptr_t)g.W) & 15) == 0;
-        }
-        bool keepz = false;                   // a training forward keeps the dot terms
-        for (int i = 0; i < L.ngroups; ++i) keepz = keepz || (dots && L.g[i].U != nullptr);
-        if (keepz)
-          hipLaunchKernelGGL((tm_gemm_mfma_256<DT, true, DMT_TM_TAG, true>), dim3(big_tiles),
-                             dim3(kBigThreads), kBigLdsBytes, s, L);
-        else if (dots)
-          hipLaunchKernelGGL((tm_gemm_mfma_256<DT, true>), dim3(big_tiles), dim3(kBigThreads),
-                             kBigLdsBytes, s, L);
-        else if (direct)
-          hipLaunchKernelGGL((tm_gemm_mfma_256<DT, false, DMT_TM_TAG, false, true>), dim3(big_tiles),
-                             dim3(kBigThreads), kBigLdsBytes, s, L);
-        else
-          hipLaunchKernelGGL((tm_gemm_mfma_256<DT, false>), dim3(big_tiles), dim3(kBigThreads),
-                             kBigLdsBytes, s, L);
-      } else {
-        bool keepu = false;
-        for (int i = 0; i < L.ngroups; ++i) keepu = keepu || L.g[i].U != nullptr;
-        DmtScope sc_(p, kid, s);
-        if (keepu)
-          hipLaunchKernelGGL((tm_gemm_mfma<DT, true>), dim3(tiles), dim3(kBlock), 0, s, L);
-        else
-          hipLaunchKernelGGL((tm_gemm_mfma<DT, false>), dim3(tiles), dim3(kBlock), 0, s, L);
-      }
+    const bool big = take_big(p, L.g, L.ngroups);
+    const int tile = big ? 256 : 128;
+    int64_t tiles = 0;
+    for (int i = 0; i < L.ngroups; ++i) tiles += tiles_of(L.g[i], tile);
+    // super-tiles as large as an XCD's resident blocks, or an eighth of the launch where that is less
+    const int resident = big ? 32 : 64;
+    L.super = (int32_t)std::max<int64_t>(1, std::min<int64_t>(resident, (tiles + 7) / 8));
+    L.cap = 1;
+    int64_t nst = 0;
+    for (int i = 0; i < L.ngroups; ++i) {
+      L.tile_start[i] = (int32_t)nst;
+      const int64_t tn = (L.g[i].N + tile - 1) / tile, tm = (int64_t)((L.g[i].M + tile - 1) / tile) * tm_slices(L.g[i]);
+      const int64_t sm = tn >= L.super ? 1 : L.super / tn;
+      L.cap = (int32_t)std::max<int64_t>(L.cap, sm * tn);
+      nst += (tm + sm - 1) / sm;
     }
+    L.tile_start[L.ngroups] = (int32_t)nst;
+    const int64_t blocks = (nst + 7) / 8 * 8 * L.cap;
+    if (blocks == 0) continue;
+    DmtScope scope(p, kid, s);
+    if constexpr (ALAY == OP_ROW && WLAY == OP_ROW && DMT_TM_TAG == 0) {
+      if (dots && big && keepz) { launch_tiles<DT, 256, ALAY, WLAY, true, true>(L, blocks, s); continue; }
+      if (dots && big) { launch_tiles<DT, 256, ALAY, WLAY, true, false>(L, blocks, s); continue; }
+      if (dots && keepz) { launch_tiles<DT, 128, ALAY, WLAY, true, true>(L, blocks, s); continue; }
+      if (dots) { launch_tiles<DT, 128, ALAY, WLAY, true, false>(L, blocks, s); continue; }
+    }
+    if (big) launch_tiles<DT, 256, ALAY, WLAY, false, false>(L, blocks, s);
+    else launch_tiles<DT, 128, ALAY, WLAY, false, false>(L, blocks, s);
   }
   groups.clear();
 }
+
 // Grouped launch of the dot-term (which = 0: Gram tiles on MFMA, 1: plain FMA) or weight-repack
 // (which = 2) kernels over `items`; nblocks[i] blocks serve items[i].
 template <int DT>

@@ -189,3 +189,21 @@ def test_dot_terms_of_any_feature_count(nf, dt):
     w.tm_out = [40]
     w.tm_dtype = w.pooled_dtype = dt
     check_tm(w)
+
+
+@pytest.mark.parametrize("big", ["0", "2"])
+@pytest.mark.parametrize("batch,out", [(129, 130), (255, 264), (256, 256), (257, 129), (520, 513)])
+@pytest.mark.parametrize("kind", ["linear_relu", "dot_linear", "cross_linear"])
+def test_contraction_tiles_of_both_sizes(kind, batch, out, big, monkeypatch):
+    """Rows and columns just below, at and just above a 128 x 128 / 256 x 256 tile, K of a whole number of
+    steps and with a remainder (4 and 6 features of 72: 288 and 432 columns), widths that do and do not
+    split into 16-byte pieces; 6 features: 15 dot terms, repacked weights; 4: 6 terms, read as they
+    are."""
+    monkeypatch.setenv("DMT_TM_BIG", big)
+    w = wl.scaled(wl.mid(), max_rows=300, batch=batch, num_tables=10)
+    w.dims = [72] * 10
+    w.table_to_tower = [0] * 4 + [1] * 6
+    w.tm_kind = kind
+    w.tm_out = [out, out]
+    w.tm_cross_layers = 1 if kind == "cross_linear" else 0
+    check_tm(w)

@@ -512,3 +512,27 @@ def test_float32_operands_read_where_they_lie(kind, batch, out, dim):
         w.tm_out = [out + 7 * 5, out + 2 * 5]
     w.tm_dtype = w.pooled_dtype = "f32"
     check_tm_bwd(w, rtol=1e-4)
+
+
+@pytest.mark.parametrize("big", ["0", "2"])
+@pytest.mark.parametrize("batch,out", [(129, 130), (255, 264), (256, 256), (257, 129), (520, 513)])
+@pytest.mark.parametrize("kind", ["linear_relu", "dot_linear", "cross_linear"])
+def test_contraction_tiles_of_both_sizes_and_operand_layouts(kind, batch, out, big, monkeypatch):
+    """Data and weight gradients, operands along K and across it, at the edges of both tile sizes; the
+    cross towers' elementwise steps in the contraction's epilogue with one, two and four layers."""
+    monkeypatch.setenv("DMT_TM_BIG", big)
+    w = wl.scaled(wl.mid(), max_rows=300, batch=batch, num_tables=10)
+    w.dims = [72] * 10
+    w.table_to_tower = [0] * 4 + [1] * 6
+    w.tm_kind = kind
+    w.tm_out = [out, out]
+    if kind == "cross_linear":
+        w.tm_cross_layers = {129: 1, 255: 2, 256: 4, 257: 2, 520: 1}[batch]
+    check_tm_bwd(w, rtol=4e-2, keep=out % 2 == 0)
+
+
+@pytest.mark.parametrize("seed", range(10))
+def test_random_medium_configurations_on_large_tiles(seed, monkeypatch):
+    monkeypatch.setenv("DMT_TM_BIG", "2")
+    w = _random_medium_config(seed)
+    check_tm_bwd(w, rtol=4e-2 if w.tm_cross_layers > 0 else 2e-2, keep=bool(seed & 1))
