@@ -126,6 +126,22 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
     for (int32_t t = 0; t < p->T; ++t)
       fused[t] = tp[t].kind == DMT_TM_DOT_LINEAR && p->tower_ntab[t] >= 2 && p->tower_uniform_dim[t] % 8 == 0 &&
                  ws[t].np_pad <= BK;
+  // ... which, in a small launch, reads its weights at any alignment (a training forward still leaves
+  // the backward its repacked copy)
+  bool dots_any = false;
+  if (!keptp) {
+    std::vector<TmGroup> g;
+    for (int32_t t = 0; t < p->T; ++t)
+      if (fused[t]) {
+        g.push_back(TmGroup{});
+        g.back().M = (int32_t)B;
+        g.back().N = tp[t].out_dim;
+      }
+    dots_any = !g.empty() && take_small(p, g.data(), (int)g.size());
+  }
+  auto as_is = [&](int t) {
+    return DT == DMT_F32 || (dots_any && fused[t]) || dot_weights_as_is(tp[t].w_proj, ws[t].np);
+  };
 
   // stage 0: dot terms and repacked projection weights, one grouped launch per kind
   std::vector<TmAuxItem> dots_mfma, dots_simple, packs;
@@ -149,7 +165,7 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
       dots_simple.push_back(it);
       nb_simple.push_back((B * w.np_pad + kBlock - 1) / kBlock);
     }
-    if (DT == DMT_F32 || dot_weights_as_is(q.w_proj, w.np)) continue;
+    if (as_is(t)) continue;
     it.src = q.w_proj;
     it.dst = wp_of(t);
     packs.push_back(it);
@@ -214,10 +230,9 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
     g.A1 = x; g.lda1 = wt; g.K1 = wt;
     g.W1 = q.w_proj; g.ldw1 = wt;
     if (q.kind == DMT_TM_DOT_LINEAR) {
-      const bool as_is = DT == DMT_F32 || dot_weights_as_is(q.w_proj, ws[t].np);
-      const int skip = as_is ? ws[t].np : ws[t].np_pad;    // columns of the dot terms in a weight row
+      const int skip = as_is(t) ? ws[t].np : ws[t].np_pad;    // columns of the dot terms in a weight row
       g.A0 = z_of(t); g.lda0 = ws[t].np_pad; g.K0 = DT == DMT_F32 ? ws[t].np : ws[t].np_pad;
-      g.W0 = as_is ? (const char*)q.w_proj : wp_of(t); g.ldw0 = skip + wt;
+      g.W0 = as_is(t) ? (const char*)q.w_proj : wp_of(t); g.ldw0 = skip + wt;
       g.W1 = (const char*)g.W0 + (size_t)skip * eb; g.ldw1 = skip + wt;
     } else if (q.kind == DMT_TM_CROSS_LINEAR || q.kind == DMT_TM_CROSS_LOWRANK_LINEAR) {
       g.A1 = x_layer(t, q.num_cross_layers - 1);

@@ -651,6 +651,139 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
   }
 }
 
+// ------------------------------------------------ MFMA grouped GEMM, small launches
+//
+// For forward launches of few tiles (a serving batch): a 128 x 128 tile per block would leave most
+// CUs idle and walk all of K in one block.  A block takes a 32 x 32 tile and its eight waves an
+// eighth of K each; operands go from global memory straight into registers (a lane feeds the matrix
+// core 8 consecutive k of one row), the waves' sums are added in wave order through LDS.  Bound by
+// the latencies of one load batch, the exchange and, with in-kernel dot terms (DOTS, as in tm_gemm:
+// every block computes its 32 samples' terms itself), the Gram tiles before them.  Batch 61, 8 towers
+// of 8 x 128 + 28 terms to 256 outputs: 27 -> 10.5 us (25 -> 9.2 back to back).
+constexpr int kSmallWaves = 8;
+
+// 8 elements at p; VEC: p is 16-byte aligned (else the rows of unpacked weights: any even address).
+template <bool VEC> __device__ __forceinline__ uint4 small_load(const uint16_t* p) {
+  if constexpr (VEC) return *(const uint4*)p;
+  uint4 v;
+  __builtin_memcpy(&v, p, 16);
+  return v;
+}
+
+template <int DT, bool DOTS, int TAG = DMT_TM_TAG>
+__global__ __launch_bounds__(kSmallWaves * 64, 4) void tm_gemm_small(const TmLaunch L) {
+  __shared__ __attribute__((aligned(16))) float red[kSmallWaves][16][64];
+  constexpr int kZPitch = BK + 8;
+  __shared__ __attribute__((aligned(16))) uint16_t z[DOTS ? 32 * kZPitch : 8];
+  int gi = 0;
+  while (gi + 1 < L.ngroups && (int)blockIdx.x >= L.tile_start[gi + 1]) ++gi;
+  const TmGroup& G = L.g[gi];
+  const int tile = blockIdx.x - L.tile_start[gi], tiles_n = (G.N + 31) / 32;
+  const int m0 = tile / tiles_n * 32, n0 = tile % tiles_n * 32;
+  const int M = G.M, N = G.N;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 31, h8 = (lane >> 5) * 8;
+  const int m = min(m0 + r, M - 1), n = min(n0 + r, N - 1);     // rows past the edge: the last row, not stored
+  const uint16_t* A1 = (const uint16_t*)G.A1 + (int64_t)m * G.lda1 + h8;
+  const uint16_t* W1 = (const uint16_t*)G.W1 + (int64_t)n * G.ldw1 + h8;
+  // this wave's steps of 16 k (K1 is a multiple of 8: the last step may be half empty)
+  const int S = (G.K1 + 15) / 16, lo = S * wave / kSmallWaves, hi = S * (wave + 1) / kSmallWaves;
+  const bool vec = (((uintptr_t)G.W1 & 15) | (G.ldw1 & 7)) == 0;
+  floatx16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  constexpr int U = 4;
+  uint4 a[U], w[U];
+  auto load = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = (s + u) * 16;
+      a[u] = w[u] = make_uint4(0, 0, 0, 0);
+      if (s + u < hi && k + h8 < G.K1) {
+        a[u] = *(const uint4*)(A1 + k);
+        w[u] = vec ? small_load<true>(W1 + k) : small_load<false>(W1 + k);
+      }
+    }
+  };
+  if constexpr (!DOTS) load(lo);
+  if constexpr (DOTS) {
+    const int nf = G.nf, fd = G.fdim, spg = 32 / nf, K0 = G.K0, np = nf * (nf - 1) / 2;
+    for (int e = threadIdx.x; e < 32 * kZPitch / 8; e += kSmallWaves * 64) ((uint4*)z)[e] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    const uint16_t* A = (const uint16_t*)G.A1;
+    const int sc = r / nf, j = r % nf;
+    for (int s0 = wave * spg; s0 < 32; s0 += kSmallWaves * spg) {
+      const int s = s0 + sc;
+      const bool on = sc < spg && s < 32 && m0 + s < M;
+      const uint16_t* xp = A + (on ? (int64_t)(m0 + s) * G.lda1 + j * fd + h8 : 0);
+      floatx16 d;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) d[v] = 0.f;
+      for (int k = 0; k < fd; k += 128) {
+        uint4 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          x[u] = make_uint4(0, 0, 0, 0);
+          if (on && k + u * 16 + h8 < fd) x[u] = *(const uint4*)(xp + k + u * 16);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (k + u * 16 < fd) d = mfma32<DT>(x[u], x[u], d);
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int rr = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), i = rr % nf;
+        if (rr / nf == sc && i < j && on) store_elt<DT>(z, s * kZPitch + i * (2 * nf - i - 1) / 2 + (j - i - 1), d[v]);
+      }
+    }
+    load(lo);
+    __syncthreads();
+    // the dot terms' own steps, one per wave from the last
+    const int s0 = kSmallWaves - 1 - wave;
+    if (s0 * 16 < K0) {
+      const int k = s0 * 16 + h8;
+      uint4 wz = make_uint4(0, 0, 0, 0);
+      if (k < K0) wz = small_load<false>((const uint16_t*)G.W0 + (int64_t)n * G.ldw0 + k);
+      acc = mfma32<DT>(*(const uint4*)(z + r * kZPitch + k), wz, acc);
+    }
+    if (G.U && n0 == 0)                            // a training forward keeps the terms, zeros behind them
+      for (int e = threadIdx.x; e < 32 * K0; e += kSmallWaves * 64)
+        if (m0 + e / K0 < M) ((uint16_t*)G.U)[(int64_t)(m0 + e / K0) * K0 + e % K0] = z[e / K0 * kZPitch + e % K0];
+  }
+  for (int s = lo; s < hi; s += U) {
+    uint4 ca[U], cw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) { ca[u] = a[u]; cw[u] = w[u]; }
+    load(s + U);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (s + u < hi) acc = mfma32<DT>(ca[u], cw[u], acc);
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[v];
+  __syncthreads();
+  // lane holds column n0 + lane % 32 of rows (v / 4) * 8 + (lane / 32) * 4 + v % 4; two v a wave
+  const int nn = n0 + r;
+  if (nn >= N) return;
+  const float bias = G.bias ? load_elt<DT>(G.bias, nn) : 0.f;
+#pragma unroll
+  for (int q = 0; q < 16 / kSmallWaves; ++q) {
+    const int v = wave * (16 / kSmallWaves) + q, mm = m0 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+    if (mm >= M) continue;
+    float y = red[0][v][lane];
+#pragma unroll
+    for (int p = 1; p < kSmallWaves; ++p) y += red[p][v][lane];
+    y += bias;
+    const int64_t row = G.rdiv > 0 ? (int64_t)(mm / G.rdiv) * G.ldc + (int64_t)(mm % G.rdiv) * G.ldc2 : (int64_t)mm * G.ldc;
+    if (G.epi == EPI_BIAS_RELU) y = y > 0.f ? y : 0.f;
+    if (G.epi == EPI_CROSS) {
+      if (G.U) store_elt<DT>(G.U, row + nn, y);
+      y = load_elt<DT>(G.X0, (int64_t)mm * G.ldx + nn) * y + load_elt<DT>(G.XL, (int64_t)mm * G.ldxl + nn);
+    }
+    store_elt<DT>(G.C, row + nn, y);
+  }
+}
+
 // ------------------------------------------------------------ pairwise dot terms
 
 // Per-tower work of a grouped auxiliary launch (dot terms or weight repack).
@@ -854,6 +987,17 @@ inline bool take_big(const dmt_plan* p, const TmGroup* g, int n) {
   return tiles >= kBigTiles || p->sw.tm_big == 2;
 }
 
+// Whether a forward launch goes to tm_gemm_small: up to 768 tiles of 32 x 32, one and a half rounds of
+// the blocks that are resident together.  Both sides measured (128 x 128 / 32 x 32 tiles, us): dots and
+// K = 1052, 512 tiles 28.6 / 19.2, 832 tiles 28.0 / 30.3; K = 832, 704 tiles 31.9 / 27.2, 1024 tiles
+// 31.5 / 34.1; two cross layers of 2048 columns, 1024 tiles each 85.8 / 84.2, 2048 tiles 87.8 / 149.
+inline bool take_small(const dmt_plan* p, const TmGroup* g, int n) {
+  if (p->sw.tm_big != 1) return p->sw.tm_big == 3;
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) tiles += tiles_of(g[i], 32);
+  return tiles <= 768;
+}
+
 // All groups of the list, kMaxGroups to a launch.  dots: every group computes its dot terms itself.
 template <int DT, int ALAY = OP_ROW, int WLAY = OP_ROW>
 void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t s, bool dots = false,
@@ -865,6 +1009,23 @@ void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t 
     for (int i = 0; i < L.ngroups; ++i) {
       L.g[i] = groups[first + i];
       keepz = keepz || (dots && L.g[i].U != nullptr);
+    }
+    if constexpr (ALAY == OP_ROW && WLAY == OP_ROW && DMT_TM_TAG == 0) {
+      // (in-kernel dot terms, or one K segment)
+      bool small = take_small(p, L.g, L.ngroups);
+      for (int i = 0; i < L.ngroups; ++i) small = small && (dots || L.g[i].K0 == 0);
+      if (small) {
+        int64_t blocks = 0;
+        for (int i = 0; i < L.ngroups; ++i) {
+          L.tile_start[i] = (int32_t)blocks;
+          blocks += tiles_of(L.g[i], 32);
+        }
+        L.tile_start[L.ngroups] = (int32_t)blocks;
+        DmtScope scope(p, kid, s);
+        if (dots) hipLaunchKernelGGL((tm_gemm_small<DT, true>), dim3((unsigned)blocks), dim3(kSmallWaves * 64), 0, s, L);
+        else hipLaunchKernelGGL((tm_gemm_small<DT, false>), dim3((unsigned)blocks), dim3(kSmallWaves * 64), 0, s, L);
+        continue;
+      }
     }
     const bool big = take_big(p, L.g, L.ngroups);
     const int tile = big ? 256 : 128;

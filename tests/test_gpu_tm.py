@@ -191,11 +191,11 @@ def test_dot_terms_of_any_feature_count(nf, dt):
     check_tm(w)
 
 
-@pytest.mark.parametrize("big", ["0", "2"])
-@pytest.mark.parametrize("batch,out", [(129, 130), (255, 264), (256, 256), (257, 129), (520, 513)])
+@pytest.mark.parametrize("big", ["0", "2", "3"])
+@pytest.mark.parametrize("batch,out", [(129, 130), (255, 264), (256, 256), (257, 129), (520, 513), (31, 33), (1, 7)])
 @pytest.mark.parametrize("kind", ["linear_relu", "dot_linear", "cross_linear"])
 def test_contraction_tiles_of_both_sizes(kind, batch, out, big, monkeypatch):
-    """Rows and columns just below, at and just above a 128 x 128 / 256 x 256 tile, K of a whole number of
+    """Rows and columns just below, at and just above a 128 x 128 / 256 x 256 / (3) 32 x 32 tile, K of a whole number of
     steps and with a remainder (4 and 6 features of 72: 288 and 432 columns), widths that do and do not
     split into 16-byte pieces; 6 features: 15 dot terms, repacked weights; 4: 6 terms, read as they
     are."""
