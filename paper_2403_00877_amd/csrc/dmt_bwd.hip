@@ -37,7 +37,13 @@ constexpr int kBlock = 256;
 constexpr int kSortItems = DMT_SORT_ITEMS;
 constexpr int kMaxRadixBits = DMT_RADIX_BITS;      // digit width of one sort pass
 constexpr int kMaxRadix = 1 << kMaxRadixBits;
-constexpr int kDigitsPerThread = (kMaxRadix + kBlock - 1) / kBlock;
+// A call of up to kWideNnz lookups is bound by its launches, not by bytes: it sorts in digits of up to
+// 10 bits, and the scatter's blocks add up the digit counts of their table's other blocks themselves, so
+// a pass is two launches instead of three and there are fewer passes (18 bits of row id: 4 launches
+// instead of 9).  The counts a block reads grow with its table's blocks, which is what the limit is for:
+// at kWideNnz lookups, all in one table, a block reads 256 lines of 4 KB.
+constexpr int kWideRadixBits = 10;
+constexpr int64_t kWideNnz = 1 << 19;
 constexpr int kSortTile = kBlock * kSortItems;   // records per sort block
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kBlock * kScanItems;   // records per head-scan block
@@ -64,7 +70,7 @@ constexpr int kScanBatch = 16;                   // sort blocks whose counts it 
 struct BwdWs {
   uint64_t* pk_a;
   uint64_t* pk_b;
-  uint32_t* hist;         // [nblk_sort][kMaxRadix]
+  uint32_t* hist;         // [nblk_sort][kMaxRadix], or [nblk_sort][1 << kWideRadixBits]
   uint32_t* seg_begin;    // [F + 1] first record of each table (seg_begin[F] = nnz)
   uint32_t* seg_blk;      // [F + 1] first sort block of each table
   uint32_t* blk_table;    // [nblk_sort] table of each sort block
@@ -75,6 +81,7 @@ struct BwdWs {
   size_t bytes;
   int64_t nblk_sort, nblk_scan, ntiles;
   int tile;               // records per reduce tile
+  bool wide;              // sort in wide digits
 };
 
 BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
@@ -96,15 +103,24 @@ BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
   };
   w.pk_a = (uint64_t*)take(sizeof(uint64_t) * n);
   w.pk_b = (uint64_t*)take(sizeof(uint64_t) * n);
-  w.hist = (uint32_t*)take(sizeof(uint32_t) * kMaxRadix * w.nblk_sort);
   w.seg_begin = (uint32_t*)take(sizeof(uint32_t) * (p->F + 1));
   w.seg_blk = (uint32_t*)take(sizeof(uint32_t) * (p->F + 1));
   w.blk_table = (uint32_t*)take(sizeof(uint32_t) * w.nblk_sort);
   w.blk_heads = (uint32_t*)take(sizeof(uint32_t) * (w.nblk_scan + 1));
-  w.seg_off = (uint32_t*)take(sizeof(uint32_t) * (n + 1));
   w.num_unique = (uint32_t*)take(sizeof(uint32_t) * 64);
+  // The sort is done with its counts before seg_off and partials are written, so wide counts may lie
+  // over them.  That is room enough but for few lookups in narrow rows, whose counts get room of their
+  // own unless the tables are many (then the digits stay narrow).  Never less room for more lookups: a
+  // workspace sized for the largest call serves all of them.
+  const size_t hist_at = off;
+  int64_t counts = (int64_t)kMaxRadix * w.nblk_sort;
+  if (p->F <= 64)
+    counts = std::max(counts, (std::min<int64_t>(n, 8 * kSortTile) / kSortTile + 1 + p->F) << kWideRadixBits);
+  w.hist = (uint32_t*)take(sizeof(uint32_t) * counts);
+  w.seg_off = (uint32_t*)take(sizeof(uint32_t) * (n + 1));
   w.partials = (float*)take(sizeof(float) * 2 * slots * p->max_dim);
   w.bytes = off;
+  w.wide = n <= kWideNnz && (sizeof(uint32_t) << kWideRadixBits) * w.nblk_sort <= off - hist_at;
   return w;
 }
 
@@ -209,15 +225,19 @@ __global__ __launch_bounds__(kBlock) void bwd_build_keys(
 // A sort block's share of its table's records, and the table's first global row id.
 struct SortBlock {
   uint32_t base, n, row_base, valid;
+  uint32_t table_base, at, nb;   // first record of the table; which of its nb sort blocks this is
 };
 __device__ __forceinline__ SortBlock sort_block(const DmtTableMeta* __restrict__ meta,
                                                 const uint32_t* __restrict__ seg_begin,
                                                 const uint32_t* __restrict__ seg_blk,
                                                 const uint32_t* __restrict__ blk_table, int F) {
-  SortBlock sb{0, 0, 0, 0};
+  SortBlock sb{0, 0, 0, 0, 0, 0, 0};
   if (blockIdx.x >= seg_blk[F]) return sb;
   const uint32_t f = blk_table[blockIdx.x];
-  sb.base = seg_begin[f] + (blockIdx.x - seg_blk[f]) * (uint32_t)kSortTile;
+  sb.table_base = seg_begin[f];
+  sb.at = blockIdx.x - seg_blk[f];
+  sb.nb = seg_blk[f + 1] - seg_blk[f];
+  sb.base = sb.table_base + sb.at * (uint32_t)kSortTile;
   const uint32_t end = seg_begin[f + 1];
   sb.n = end - sb.base < (uint32_t)kSortTile ? end - sb.base : (uint32_t)kSortTile;
   sb.row_base = (uint32_t)meta[f].row_base;
@@ -231,14 +251,16 @@ __device__ __forceinline__ uint32_t sort_digit(uint64_t rec, uint32_t row_base, 
   return ((((uint32_t)(rec >> 32) & ~kInertBit) - row_base) >> shift) & mask;
 }
 
+template <int MaxBits>
 __global__ __launch_bounds__(kBlock) void radix_hist(
     const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ pk, int shift, int bits,
     uint32_t* __restrict__ hist, const uint32_t* __restrict__ seg_begin,
     const uint32_t* __restrict__ seg_blk, const uint32_t* __restrict__ blk_table, int F) {
-  __shared__ uint32_t h[kMaxRadix];
+  constexpr int MaxRadix = 1 << MaxBits;
+  __shared__ uint32_t h[MaxRadix];
   const SortBlock sb = sort_block(meta, seg_begin, seg_blk, blk_table, F);
   if (!sb.valid) return;
-  for (int d = threadIdx.x; d < kMaxRadix; d += kBlock) h[d] = 0;
+  for (int d = threadIdx.x; d < MaxRadix; d += kBlock) h[d] = 0;
   __syncthreads();
   const uint32_t mask = (1u << bits) - 1;
 #pragma unroll
@@ -248,7 +270,7 @@ __global__ __launch_bounds__(kBlock) void radix_hist(
   }
   __syncthreads();
   for (int d = threadIdx.x; d < (1 << bits); d += kBlock)
-    hist[(int64_t)blockIdx.x * kMaxRadix + d] = h[d];
+    hist[(int64_t)blockIdx.x * MaxRadix + d] = h[d];
 }
 
 // One block per table: turns the per-block digit counts of the table's sort blocks into the
@@ -306,15 +328,19 @@ __global__ __launch_bounds__(kScanThreads) void radix_scan(uint32_t* __restrict_
   }
 }
 
+// Stable scatter of a sort block's records.  `hist` holds where the block's first record of each digit
+// goes or, with OwnScan, the digit counts radix_hist left.
+template <int MaxBits, bool OwnScan>
 __global__ __launch_bounds__(kBlock) void radix_scatter(
     const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ in,
     uint64_t* __restrict__ out, int shift, int bits, const uint32_t* __restrict__ hist,
     const uint32_t* __restrict__ seg_begin, const uint32_t* __restrict__ seg_blk,
     const uint32_t* __restrict__ blk_table, int F) {
   __shared__ uint64_t buf[kSortTile];
-  __shared__ uint32_t cnt[kBlock / 64][kMaxRadix];
-  __shared__ uint32_t tile_start[kMaxRadix];
-  __shared__ uint32_t gbase[kMaxRadix];
+  constexpr int MaxRadix = 1 << MaxBits, DPT = (MaxRadix + kBlock - 1) / kBlock;
+  __shared__ uint32_t cnt[kBlock / 64][MaxRadix];
+  __shared__ uint32_t tile_start[MaxRadix];
+  __shared__ uint32_t gbase[MaxRadix];
   __shared__ uint32_t sm[8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int radix = 1 << bits;
@@ -322,7 +348,7 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
   const SortBlock sb = sort_block(meta, seg_begin, seg_blk, blk_table, F);
   if (!sb.valid) return;
   for (int w = 0; w < kBlock / 64; ++w)
-    for (int d = tid; d < kMaxRadix; d += kBlock) cnt[w][d] = 0;
+    for (int d = tid; d < MaxRadix; d += kBlock) cnt[w][d] = 0;
   __syncthreads();
   const uint32_t tile_base = sb.base;
   const int n_tile = (int)sb.n;
@@ -360,11 +386,11 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
   __syncthreads();
   // thread t owns digits t*DPT .. t*DPT+DPT-1: totals over the waves; cnt becomes each
   // wave's offset inside the digit
-  uint32_t tot[kDigitsPerThread];
+  uint32_t tot[DPT];
   uint32_t tsum = 0;
 #pragma unroll
-  for (int j = 0; j < kDigitsPerThread; ++j) {
-    const int d = tid * kDigitsPerThread + j;
+  for (int j = 0; j < DPT; ++j) {
+    const int d = tid * DPT + j;
     tot[j] = 0;
     if (d < radix) {
       uint32_t run = 0;
@@ -378,14 +404,45 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
     tsum += tot[j];
   }
   uint32_t total;
+  uint32_t goes[DPT];                              // where this block's first record of a digit goes
+  if constexpr (OwnScan) {
+    // records of the table with a smaller digit, and with this digit in earlier blocks
+    static_assert(DPT == 4, "a thread reads its digits' counts as one uint4");
+    uint4 all = make_uint4(0, 0, 0, 0), before = make_uint4(0, 0, 0, 0);
+    if (tid * DPT < radix) {
+      const uint4* __restrict__ h = (const uint4*)(hist + (int64_t)(blockIdx.x - sb.at) * MaxRadix) + tid;
+      for (uint32_t b = 0; b < sb.nb; b += kScanBatch) {
+        uint4 v[kScanBatch];
+#pragma unroll
+        for (int q = 0; q < kScanBatch; ++q)
+          v[q] = b + q < sb.nb ? h[(int64_t)(b + q) * (MaxRadix / 4)] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < kScanBatch; ++q) {
+          if (b + q == sb.at) before = all;
+          all.x += v[q].x; all.y += v[q].y; all.z += v[q].z; all.w += v[q].w;
+        }
+      }
+    }
+    const uint32_t a[DPT] = {all.x, all.y, all.z, all.w};
+    const uint32_t bef[DPT] = {before.x, before.y, before.z, before.w};
+    uint32_t sum = 0;
+#pragma unroll
+    for (int j = 0; j < DPT; ++j) sum += tid * DPT + j < radix ? a[j] : 0u;
+    uint32_t at = sb.table_base + dmt::block_exclusive_scan<kBlock / 64>(sum, sm, total);
+#pragma unroll
+    for (int j = 0; j < DPT; ++j) {
+      goes[j] = at + bef[j];
+      at += a[j];
+    }
+  }
   uint32_t ex = dmt::block_exclusive_scan<kBlock / 64>(tsum, sm, total);
 #pragma unroll
-  for (int j = 0; j < kDigitsPerThread; ++j) {
-    const int d = tid * kDigitsPerThread + j;
+  for (int j = 0; j < DPT; ++j) {
+    const int d = tid * DPT + j;
     if (d < radix) {
       tile_start[d] = ex;
-      // hist holds where this block's first record of digit d goes
-      gbase[d] = hist[(int64_t)blockIdx.x * kMaxRadix + d] - ex;
+      if constexpr (OwnScan) gbase[d] = goes[j] - ex;
+      else gbase[d] = hist[(int64_t)blockIdx.x * MaxRadix + d] - ex;
     }
     ex += tot[j];
   }
@@ -1569,19 +1626,24 @@ static dmt_status bwd_update_run(const dmt_plan* plan, const int32_t* indices,
     int64_t max_rows = 0;
     for (int32_t f = 0; f < plan->F; ++f) max_rows = std::max<int64_t>(max_rows, plan->meta[f].rows);
     const int key_bits = ilog2_ceil(max_rows + 1);
-    const int passes = (key_bits + kMaxRadixBits - 1) / kMaxRadixBits;
+    const int most_bits = w.wide ? kWideRadixBits : kMaxRadixBits;
+    const int passes = (key_bits + most_bits - 1) / most_bits;
     const int bits_per = (key_bits + passes - 1) / passes;
     uint64_t* src = w.pk_a;
     uint64_t* dst = w.pk_b;
     for (int p = 0; p < passes; ++p) {
       const int shift = p * bits_per;
       const int bits = std::min(bits_per, key_bits - shift);
-      timed_launch(plan, DMT_K_BWD_SORT_HIST, s, radix_hist, w.nblk_sort, kBlock, plan->d_meta, src,
-                   shift, bits, w.hist, w.seg_begin, w.seg_blk, w.blk_table, (int)plan->F);
-      timed_launch(plan, DMT_K_BWD_SORT_SCAN, s, radix_scan, plan->F, kScanThreads, w.hist, bits,
-                   w.seg_begin, w.seg_blk);
-      timed_launch(plan, DMT_K_BWD_SORT_SCATTER, s, radix_scatter, w.nblk_sort, kBlock, plan->d_meta,
-                   src, dst, shift, bits, w.hist, w.seg_begin, w.seg_blk, w.blk_table, (int)plan->F);
+      timed_launch(plan, DMT_K_BWD_SORT_HIST, s, w.wide ? radix_hist<kWideRadixBits> : radix_hist<kMaxRadixBits>,
+                   w.nblk_sort, kBlock, plan->d_meta, src, shift, bits, w.hist, w.seg_begin, w.seg_blk,
+                   w.blk_table, (int)plan->F);
+      if (!w.wide)
+        timed_launch(plan, DMT_K_BWD_SORT_SCAN, s, radix_scan, plan->F, kScanThreads, w.hist, bits,
+                     w.seg_begin, w.seg_blk);
+      timed_launch(plan, DMT_K_BWD_SORT_SCATTER, s,
+                   w.wide ? radix_scatter<kWideRadixBits, true> : radix_scatter<kMaxRadixBits, false>,
+                   w.nblk_sort, kBlock, plan->d_meta, src, dst, shift, bits, w.hist, w.seg_begin, w.seg_blk,
+                   w.blk_table, (int)plan->F);
       std::swap(src, dst);
     }
     sorted = src;

@@ -131,6 +131,35 @@ def test_every_reduce_tile_size(batch):
     check_bwd(w)
 
 
+@pytest.mark.parametrize("rows,lens", [
+    ([1, 1], [900, 2]),                             # one bit of row id
+    ([1022, 3], [1000, 1]),                         # 10 bits: one pass
+    ([1024, 5, 1023], [2049, 0, 1]),                # 11 bits: two passes; a block of one record
+    ([1 << 20, 40], [40000, 3]),                    # 21 bits: three passes; 20 blocks in one table
+    ([3000, 70000, 9], [(1 << 18), 1, (1 << 18) - 1]),   # as many lookups as wide digits take
+    ([3000, 70000, 9], [(1 << 18), 1, 1 << 18]),    # one more: narrow digits
+])
+def test_sort_digit_widths(rows, lens):
+    """Two bags a table, the first with two thirds of the table's lookups: the sorted order is the
+    stable order of (table, row), whatever the digits' width and the tables' share."""
+    F = len(rows)
+    w = wl.dataclasses.replace(
+        wl.scaled(wl.mid(True), max_rows=10, batch=2, num_tables=F), table_dtype="f32", rows=rows,
+        dims=[16] * F, table_to_tower=[0] * F, tm_out=[32])
+    per_bag = np.array([c for n in lens for c in (n - n // 3, n // 3)], dtype=np.int64)
+    off = np.concatenate([[0], np.cumsum(per_bag)])
+    rng = np.random.default_rng(7)
+    idx = np.concatenate([(r * rng.random(n) ** 3).astype(np.int32) for r, n in zip(rows, lens)])
+    dw = DeviceWorkload(w, with_state=True, max_nnz=sum(lens))
+    dbg = run_bwd(dw, idx, off, wl.grad_pooled(w), w.lr, w.eps)
+    assert dw.dmt.dmt_last_device_error(dw.plan) == -1
+    key = (np.repeat(np.arange(F, dtype=np.int64), lens) << 32) | idx
+    order = np.argsort(key, kind="stable")
+    bag = np.repeat(np.arange(2 * F), per_bag)
+    assert np.array_equal(dbg["sorted_keys"].cpu().numpy(), key[order])
+    assert np.array_equal(dbg["sorted_bag"].cpu().numpy(), bag[order])
+
+
 @pytest.mark.parametrize("dims", [[32, 64], [64], [32], [256]])
 def test_narrow_and_wide_rows(dims):
     """Dims up to 128 run the lean walk, 256 the wave-per-tile kernel."""
