@@ -30,6 +30,7 @@ constexpr int kStagedBags = kBlock * 8;  // most bags of one block whose offsets
 #define DMT_LOOKUP_UNROLL 4
 #endif
 constexpr int kUnroll = DMT_LOOKUP_UNROLL;
+constexpr int64_t kResidentWaves = 256 * 32;
 
 template <int TD, int OD>
 __global__ __launch_bounds__(kBlock) void lookup_fwd_kernel(
@@ -197,6 +198,13 @@ extern "C" dmt_status dmt_tower_lookup_fwd(const dmt_plan* plan, const int32_t* 
     // slot's serial chain would get long.
     int r = 1;
     while (r * 2 * 16 * kUnroll <= mean_len && ((r * 2) << log2_lpr) <= 64) r *= 2;
+    // A call that leaves wave slots empty (8192 are resident) spreads its bags over more lanes while a
+    // slot keeps a full unroll of rows: 61 x 64 bags of 20 ids 8.5 -> 7.4 us (four slots), 250 x 64
+    // 13.4 -> 11.9 (two); already at 13 000 waves, or at 5 ids a bag, a second slot costs more than it gives
+    // (26 x 2003 bags of 5 ids: 12.6 -> 15.7).
+    const int64_t bags = c.num_tables * B;
+    while (r * 2 * kUnroll <= mean_len && ((r * 2) << log2_lpr) <= 64 &&
+           (bags * 2 * r << log2_lpr) <= kResidentWaves * 64) r *= 2;
     if (tuned_r > 0) {
       r = 1;
       while (r * 2 <= tuned_r && ((r * 2) << log2_lpr) <= 64) r *= 2;
@@ -204,9 +212,12 @@ extern "C" dmt_status dmt_tower_lookup_fwd(const dmt_plan* plan, const int32_t* 
     const int log2_gl = log2_lpr + ilog2_ceil(r);
     const int ngroups = kBlock >> log2_gl;
     // bags one lane group pools in turn: short bags are batched so that a block has a few
-    // dozen ids per group to work on (measured on MI355X: 8 bags at mean length 2.6, 1 at 20)
+    // dozen ids per group to work on (measured on MI355X: 8 bags at mean length 2.6, 1 at 20),
+    // as long as two rounds of resident waves remain: bags in turn are latencies in turn (26 x 2003
+    // bags of 5 ids, 256-byte rows: 4 bags 16.6 us, 1 bag 12.6; 128 x 1000 of 2.6, three launches: 8 bags
+    // 105, 1 bag 62; 26 x 16384 of 1 id, 128-byte rows: 8 bags 26.4, 2 bags 24.0, 1 bag 25.8).
     int bpg = 1;
-    while (bpg < 8 && bpg * 2 * mean_len <= 24.0) bpg *= 2;
+    while (bpg < 8 && bpg * 2 * mean_len <= 24.0 && bags >= 2 * kResidentWaves * ngroups * bpg * 2) bpg *= 2;
     if (tuned_bpg > 0) bpg = tuned_bpg;
     // bags several times longer than the mean are pooled by whole waves (0: never)
     int long_thr = 4 * (int)(mean_len + 1.0);

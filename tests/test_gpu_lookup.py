@@ -99,6 +99,14 @@ def test_row_width_limits(dtype, dim):
     _check(w, dtype)
 
 
+@pytest.mark.parametrize("batch,mean", [(1024, 20), (1025, 20), (2049, 20), (16383, 2), (16384, 2)])
+def test_both_sides_of_the_launch_shape_rules(batch, mean):
+    """8 tables of 256-byte rows: four, two and one row slots a bag; one bag a lane group and two in turn."""
+    w = wl.scaled(wl.mid(), max_rows=500, batch=batch, num_tables=8)
+    w.len_dist, w.len_param, w.len_cap = "poisson", mean, 100
+    _check(w, "f32")
+
+
 def test_one_very_long_bag_among_empty_ones():
     w = wl.scaled(wl.mid(), max_rows=1000, batch=5, num_tables=2)
     dw = DeviceWorkload(w, max_nnz=5000)
