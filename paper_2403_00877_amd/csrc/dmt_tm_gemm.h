@@ -341,41 +341,66 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
       const uint16_t* A = (const uint16_t*)G.A1;
       const int c = lane & 31, sc = c / nf, j = c % nf, h8 = (lane >> 5) * 8;
       const int np = nf * (nf - 1) / 2, npad = K0 - np;
-      for (int s0 = wave * spg; s0 < TILE; s0 += T::kWaves * spg) {
-        const int s = s0 + sc;
-        const bool on = sc < spg && s < TILE && m0 + s < M;
-        const uint16_t* xp = A + (on ? (int64_t)(m0 + s) * G.lda1 + j * fd + h8 : 0);
-        floatx16 d;
+      // the term each of this lane's 16 sums is (a byte each), kNoTerm: none
+      constexpr int kNoTerm = 255;
+      uint32_t terms[4] = {0, 0, 0, 0};
 #pragma clang loop unroll(full)
-        for (int v = 0; v < 16; ++v) d[v] = 0.f;
-        for (int k = 0; k < fd; k += 64) {
-          uint4 a[4];
+      for (int v = 0; v < 16; ++v) {
+        const int rr = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), i = rr - sc * nf;
+        terms[v >> 2] |= (uint32_t)(i >= 0 && i < j ? i * (2 * nf - i - 1) / 2 + (j - i - 1) : kNoTerm) << (v & 3) * 8;
+      }
+      // Sample groups a wave has under way together, and 16-column pieces of each it requests at once.  A
+      // launch of 128 x 128 tiles leaves CUs short of blocks, and the terms take one load latency per step
+      // (26 features of 128 columns on 4 towers, batch 2003: launch 38.5 -> 35.8 us); with 256 x 256 tiles
+      // the loads of all CUs are at the memory's rate already, and more of them in flight is slower
+      // (the phase 25.4 us on 64 features at batch 8192, 27.9 with two groups).
+      constexpr int kGroups = TILE == 128 ? 2 : 1, kPieces = TILE == 128 ? 8 : 4;
+      for (int s0 = wave * spg; s0 < TILE; s0 += kGroups * T::kWaves * spg) {
+        bool on[kGroups];
+        const uint16_t* xp[kGroups];
+        floatx16 d[kGroups];
 #pragma clang loop unroll(full)
-          for (int u = 0; u < 4; ++u)               // (never past the tensor: what is not wanted reads its start)
-            a[u] = *(const uint4*)(on && k + u * 16 + h8 < fd ? xp + k + u * 16 : A);
+        for (int g = 0; g < kGroups; ++g) {
+          const int s = s0 + g * T::kWaves * spg + sc;
+          on[g] = sc < spg && s < TILE && m0 + s < M;
+          xp[g] = A + (on[g] ? (int64_t)(m0 + s) * G.lda1 + j * fd + h8 : 0);
 #pragma clang loop unroll(full)
-          for (int u = 0; u < 4; ++u) {
-            if (!(on && k + u * 16 + h8 < fd)) a[u] = make_uint4(0, 0, 0, 0);
-            d = mfma32<DT>(a[u], a[u], d);
-          }
+          for (int v = 0; v < 16; ++v) d[g][v] = 0.f;
         }
+        for (int k = 0; k < fd; k += kPieces * 16) {
+          uint4 a[kGroups][kPieces];
 #pragma clang loop unroll(full)
-        for (int v = 0; v < 16; ++v) {
-          const int rr = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-          const int i = rr % nf;
-          if (rr / nf == sc && i < j && on) {
-            const int term = i * (2 * nf - i - 1) / 2 + (j - i - 1);
-            store_elt<DT>(lds, s * BK + (((term >> 3) ^ ((s >> 1) & 7)) << 3) + (term & 7), d[v]);
-            if constexpr (KEEPZ)
-              if (G.U) store_elt<DT>(G.U, (int64_t)(m0 + s) * K0 + term, d[v]);
-          }
-        }
-        if constexpr (KEEPZ) {
-          if (G.U)
-            for (int e = lane; e < spg * npad; e += 64) {
-              const int row = s0 + e / npad;
-              if (row < TILE && m0 + row < M) store_elt<DT>(G.U, (int64_t)(m0 + row) * K0 + np + e % npad, 0.f);
+          for (int g = 0; g < kGroups; ++g)
+#pragma clang loop unroll(full)
+            for (int u = 0; u < kPieces; ++u)       // (never past the tensor: what is not wanted reads its start)
+              a[g][u] = *(const uint4*)(on[g] && k + u * 16 + h8 < fd ? xp[g] + k + u * 16 : A);
+#pragma clang loop unroll(full)
+          for (int g = 0; g < kGroups; ++g)
+#pragma clang loop unroll(full)
+            for (int u = 0; u < kPieces; ++u) {
+              if (!(on[g] && k + u * 16 + h8 < fd)) a[g][u] = make_uint4(0, 0, 0, 0);
+              d[g] = mfma32<DT>(a[g][u], a[g][u], d[g]);
             }
+        }
+#pragma clang loop unroll(full)
+        for (int g = 0; g < kGroups; ++g) {
+          const int sg = s0 + g * T::kWaves * spg, s = sg + sc;
+#pragma clang loop unroll(full)
+          for (int v = 0; v < 16; ++v) {
+            const int term = (terms[v >> 2] >> (v & 3) * 8) & 255;
+            if (on[g] && term < kNoTerm) {
+              store_elt<DT>(lds, s * BK + (((term >> 3) ^ ((s >> 1) & 7)) << 3) + (term & 7), d[g][v]);
+              if constexpr (KEEPZ)
+                if (G.U) store_elt<DT>(G.U, (int64_t)(m0 + s) * K0 + term, d[g][v]);
+            }
+          }
+          if constexpr (KEEPZ) {
+            if (G.U)
+              for (int e = lane; e < spg * npad; e += 64) {
+                const int row = sg + e / npad;
+                if (row < TILE && m0 + row < M) store_elt<DT>(G.U, (int64_t)(m0 + row) * K0 + np + e % npad, 0.f);
+              }
+          }
         }
       }
     }
@@ -732,8 +757,8 @@ __global__ __launch_bounds__(kSmallWaves * 64, 4) void tm_gemm_small(const TmLau
       }
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int rr = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), i = rr % nf;
-        if (rr / nf == sc && i < j && on) store_elt<DT>(z, s * kZPitch + i * (2 * nf - i - 1) / 2 + (j - i - 1), d[v]);
+        const int rr = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), i = rr - sc * nf;
+        if (i >= 0 && i < j && on) store_elt<DT>(z, s * kZPitch + i * (2 * nf - i - 1) / 2 + (j - i - 1), d[v]);
       }
     }
     load(lo);
@@ -858,9 +883,8 @@ __global__ __launch_bounds__(kBlock) void tm_dots_mfma(const TmAuxLaunch L) {
   }
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
-    const int rr = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-    const int i = rr % nf;
-    if (rr / nf == sc && i < j && on)
+    const int rr = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), i = rr - sc * nf;
+    if (i >= 0 && i < j && on)
       store_elt<DT>(z, (s0 + sc) * np_pad + (i * (2 * nf - i - 1) / 2 + (j - i - 1)), acc[v]);
   }
   // zeros behind the terms of the wave's samples (2 features: 16 samples x 7 columns, more than
