@@ -29,7 +29,9 @@ constexpr int kMaxGroups = 16;
 //   g_l = acc + g_{l+1}                       (float32; the sum without GN for the projection)
 //   C = g_l                                   (where C is set: layers below need it)
 //   DU = du_{l-1} = g_l * x0                  (rounded), DBP its column sums
-//   ACC (+)= g_{l+1} * u_l [+ g_1 * u_0 + g_1 where U0 is set, l = 1]
+//   ACC (+)= g_{l+1} * u_l [+ (g_1 * u_0 + g_1) where U0 is set, l = 1]
+// (each product rounded to float32 before it is added, as in tmb_cross_prep: how the steps are shared
+// out over kernels leaves grad_pooled as it is, to the last bit)
 enum { EPI_BIAS = 0, EPI_BIAS_RELU = 1, EPI_CROSS = 2, EPI_F32 = 3, EPI_F32_ADD = 4, EPI_CROSS_GRAD = 5 };
 
 // How an operand lies in memory: OP_ROW with its K columns contiguous ([M][ld], k in a row), or
@@ -104,6 +106,12 @@ template <int DT> __device__ __forceinline__ void store_elt(void* p, int64_t i, 
   if constexpr (DT == DMT_F32) ((float*)p)[i] = v;
   else if constexpr (DT == DMT_F16) ((uint16_t*)p)[i] = (uint16_t)dmt::f32_to_f16_bits(v);
   else ((uint16_t*)p)[i] = (uint16_t)dmt::f32_to_bf16_bits(v);
+}
+
+// a * b rounded to float32: never fused into an addition.
+__device__ __forceinline__ float mul_rounded(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
 }
 
 // ------------------------------------------------------------- MFMA grouped GEMM
@@ -550,12 +558,14 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
                   const float4 n = pg[buf][u];
                   dmt::unpack2<DT>(pu[buf][u].x, v0, v1);
                   dmt::unpack2<DT>(pu[buf][u].y, v2, v3);
-                  t.x += n.x * v0; t.y += n.y * v1; t.z += n.z * v2; t.w += n.w * v3;
+                  t.x += mul_rounded(n.x, v0); t.y += mul_rounded(n.y, v1);
+                  t.z += mul_rounded(n.z, v2); t.w += mul_rounded(n.w, v3);
                 }
                 if (has_u0) {
                   dmt::unpack2<DT>(pv[buf][u].x, v0, v1);
                   dmt::unpack2<DT>(pv[buf][u].y, v2, v3);
-                  t.x += g.x * v0 + g.x; t.y += g.y * v1 + g.y; t.z += g.z * v2 + g.z; t.w += g.w * v3 + g.w;
+                  t.x += mul_rounded(g.x, v0) + g.x; t.y += mul_rounded(g.y, v1) + g.y;
+                  t.z += mul_rounded(g.z, v2) + g.z; t.w += mul_rounded(g.w, v3) + g.w;
                 }
                 *(float4*)(a0 + e * 4u) = t;
               }

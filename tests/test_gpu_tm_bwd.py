@@ -536,3 +536,42 @@ def test_random_medium_configurations_on_large_tiles(seed, monkeypatch):
     monkeypatch.setenv("DMT_TM_BIG", "2")
     w = _random_medium_config(seed)
     check_tm_bwd(w, rtol=4e-2 if w.tm_cross_layers > 0 else 2e-2, keep=bool(seed & 1))
+
+
+@pytest.mark.parametrize("big", ["0", "2"])
+@pytest.mark.parametrize("layers", [1, 2, 3, 4])
+def test_cross_gradient_rounds_its_products_first(layers, big, monkeypatch):
+    """grad_pooled of a cross tower bit for bit: with all cross weights zero g_l = dy W at every layer
+    and u_l = b_l, so it is the float32 sum, last layer first, of the rounded products g b_l, then of
+    the rounded g b_0 plus g.  g is exact (18 bits: one 8-bit weight plus another 2^10 times smaller),
+    g b has 26 bits, so a product fused into its addition shows."""
+    import paper_2403_00877_amd as dmt
+    monkeypatch.setenv("DMT_TM_BIG", big)
+    B, wt, O = 70, 136, 8
+    rng = np.random.default_rng(layers)
+    bits8 = lambda *shape: ((128 + rng.integers(0, 128, shape)) / 128.0 * rng.choice([-1, 1], shape)).astype(np.float32)
+    w, b = bits8(O, wt), bits8(layers, wt)
+    dy = np.zeros((B, O), dtype=np.float32)
+    dy[np.arange(B), rng.integers(0, 4, B)] = 1.0
+    dy[np.arange(B), rng.integers(4, 8, B)] = 2.0 ** -10
+    bf = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(torch.bfloat16).cuda()
+    nan = lambda *shape: torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+    table = torch.zeros(4, wt, dtype=torch.bfloat16, device="cuda")
+    plan = dmt.dmt_plan_create([4], [wt], "bf16", 1, [0], B, B)
+    dmt.dmt_plan_bind(plan, [table], None)
+    p = dict(kind="cross_linear", out_dim=O, w_proj=bf(w), b_proj=bf(np.zeros(O)),
+             w_cross=[bf(np.zeros((wt, wt))) for _ in range(layers)], b_cross=[bf(b[l]) for l in range(layers)])
+    params = dmt.make_tm_params([p])
+    grads = dmt.make_tm_grads([dict(dw_proj=nan(O, wt), db_proj=nan(O), dw_cross=[nan(wt, wt) for _ in range(layers)],
+                                    db_cross=[nan(wt) for _ in range(layers)])])
+    x = bf(bits8(B, wt)).reshape(-1)
+    ws = torch.empty(dmt.dmt_tm_bwd_workspace_bytes(plan, params, B), dtype=torch.uint8, device="cuda")
+    dx = nan(B * wt)
+    dmt.dmt_tower_module_bwd(plan, params, x, None, B, torch.from_numpy(dy.reshape(-1)).cuda(), dx, grads, ws)
+    g = dy @ w
+    assert np.array_equal(g.astype(np.float64), dy.astype(np.float64) @ w)
+    want = np.zeros((B, wt), dtype=np.float32)
+    for l in reversed(range(layers)):
+        want += g * b[l] + g if l == 0 else g * b[l]
+    got = dx.cpu().numpy().reshape(B, wt)
+    assert np.array_equal(got.view(np.int32), want.view(np.int32))
