@@ -562,8 +562,9 @@ def test_cross_gradient_rounds_its_products_first(layers, big, monkeypatch):
     p = dict(kind="cross_linear", out_dim=O, w_proj=bf(w), b_proj=bf(np.zeros(O)),
              w_cross=[bf(np.zeros((wt, wt))) for _ in range(layers)], b_cross=[bf(b[l]) for l in range(layers)])
     params = dmt.make_tm_params([p])
-    grads = dmt.make_tm_grads([dict(dw_proj=nan(O, wt), db_proj=nan(O), dw_cross=[nan(wt, wt) for _ in range(layers)],
-                                    db_cross=[nan(wt) for _ in range(layers)])])
+    held = dict(dw_proj=nan(O, wt), db_proj=nan(O), dw_cross=[nan(wt, wt) for _ in range(layers)],
+                db_cross=[nan(wt) for _ in range(layers)])
+    grads = dmt.make_tm_grads([held])
     x = bf(bits8(B, wt)).reshape(-1)
     ws = torch.empty(dmt.dmt_tm_bwd_workspace_bytes(plan, params, B), dtype=torch.uint8, device="cuda")
     dx = nan(B * wt)
