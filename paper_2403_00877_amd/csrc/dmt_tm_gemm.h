@@ -196,11 +196,13 @@ struct TmStage {
   // values that stay in registers.  Read and clamped from the group on every K step, it held up
   // the requests by a scalar load's latency: DCN training step 14.33 -> 13.94 ms, mid forward 308 -> 302 us.
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(int k, int kn) const {
-    // (the last row counts to the end of its last chunk, which its pitch has room for: the bounds
-    // check is by 4 bytes and would drop an odd last element)
+    // (The bounds check is by 4 bytes.  OP_ROW: the last row counts to the end of its last chunk, which
+    // its pitch has room for.  OP_COL: to the end of the last element's 4 bytes and no further, since
+    // the pitch may be less than whole chunks: with rows = ld = 12 the next k's first elements would
+    // count as in bounds, and what lies past the tensor would meet the other operand's zeros.)
     kn = min(kn, BK);
     return LAY == OP_ROW ? tm_buffer(base + k, ((uint32_t)(rows - 1) * (uint32_t)ld + ((kn + 7) & ~7)) * 2u)
-                         : tm_buffer(base + (int64_t)k * ld, ((uint32_t)(kn - 1) * (uint32_t)ld + ((rows + 7) & ~7)) * 2u);
+                         : tm_buffer(base + (int64_t)k * ld, ((uint32_t)(kn - 1) * (uint32_t)ld + ((rows + 1) & ~1)) * 2u);
   }
   // This wave's j-th request: of a whole step, or with kn columns left in the segment.
   __device__ __forceinline__ void request(uint32_t lds, __amdgpu_buffer_rsrc_t rsrc, int j, int wave) const {

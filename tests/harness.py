@@ -20,6 +20,13 @@ def to_device(a: np.ndarray, dtype: str = None) -> torch.Tensor:
     return t.cuda()
 
 
+def nan_behind(t: torch.Tensor) -> torch.Tensor:
+    """The same values with NaN right behind them in memory (64 elements)."""
+    buf = torch.full((t.numel() + 64,), float("nan"), dtype=t.dtype, device=t.device)
+    buf[:t.numel()] = t.reshape(-1)
+    return buf[:t.numel()].view(t.shape)
+
+
 def to_f64(t: torch.Tensor) -> np.ndarray:
     return t.detach().to(torch.float64).cpu().numpy()
 
@@ -125,9 +132,10 @@ class DeviceWorkload:
 
 class TowerModules:
     """A workload's Tower-Module weights: encoded once to w.tm_dtype, held on the
-    device for the library and decoded back to float64 for the oracle."""
+    device for the library and decoded back to float64 for the oracle.  guard: with NaN
+    behind every weight and bias."""
 
-    def __init__(self, dw: "DeviceWorkload", dtype: str = None):
+    def __init__(self, dw: "DeviceWorkload", dtype: str = None, guard: bool = False):
         w = dw.w
         self.dw = dw
         self.dtype = dtype or w.tm_dtype
@@ -137,7 +145,7 @@ class TowerModules:
         self.dec = []
         for t, hw in enumerate(self.host):
             enc = lambda a: wl.encode(a, self.dtype)
-            dev = lambda a: to_device(enc(a), self.dtype)
+            dev = lambda a: (nan_behind if guard else lambda v: v)(to_device(enc(a), self.dtype))
             d = dict(kind=w.tm_kind, out_dim=w.tm_out[t], w_proj=dev(hw["w_proj"]), b_proj=dev(hw["b_proj"]),
                      w_cross=[dev(a) for a in hw["w_cross"]], b_cross=[dev(a) for a in hw["b_cross"]],
                      feat_out=w.tm_feat_out)

@@ -12,8 +12,8 @@ import torch
 import oracle
 from oracle import tm_bwd
 import workloads as wl
-from harness import (RTOL, DeviceWorkload, TowerModules, assert_close, assert_grad_close, to_device,
-                     to_f64)
+from harness import (RTOL, DeviceWorkload, TowerModules, assert_close, assert_grad_close, nan_behind,
+                     to_device, to_f64)
 
 pytestmark = pytest.mark.gpu
 
@@ -70,9 +70,10 @@ def forward_keep(dw, tm, x_dev):
     return kept
 
 
-def check_tm_bwd(w, rtol=None, keep=False):
+def check_tm_bwd(w, rtol=None, keep=False, guard=False):
+    """guard: what lies behind the pooled values, the weights and the output gradient is NaN."""
     dw = DeviceWorkload(w)
-    tm = TowerModules(dw)
+    tm = TowerModules(dw, guard=guard)
     idx, off = wl.lookup_batch(w)
     pooled = oracle.lookup_towered(dw.host_tables, w.table_dtype, w.dims, w.table_to_tower, idx, off, w.batch)
     enc = [oracle.round_to(p, tm.dtype) for p in pooled]
@@ -90,6 +91,8 @@ def check_tm_bwd(w, rtol=None, keep=False):
             pre = oracle.tm_linear(x64[t], tm.dec[t]["w_proj"], tm.dec[t]["b_proj"])
             dys[t][np.abs(pre) < 1e-3 * np.sqrt(np.mean(pre * pre))] = 0.0
     dy_dev = torch.from_numpy(np.concatenate([d.reshape(-1) for d in dys])).cuda()
+    if guard:
+        x_dev, dy_dev = nan_behind(x_dev), nan_behind(dy_dev)
     y_dev = tm.run(x_dev) if w.tm_kind == wl.TM_LINEAR_RELU else None
     kept = forward_keep(dw, tm, x_dev) if keep else None
     got_dx, got = run_bwd(dw, tm, x_dev, y_dev, dy_dev, kept)
@@ -239,6 +242,24 @@ def test_dlrm_module_odd_widths():
     w.tm_feat_out = 5
     w.tm_out = [20 + 3 * 5] * 2
     check_tm_bwd(w)
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("dim,nf,batch,feat_out,big", [(12, 2, 77, 5, "1"), (12, 4, 301, 24, "2"), (4, 6, 65, 8, "0"),
+                                                       (20, 2, 1, 1, "1"), (132, 2, 300, 136, "2")])
+def test_dlrm_module_rows_that_end_inside_a_chunk(dim, nf, batch, feat_out, big, dt, monkeypatch):
+    """Features of 4 mod 8 columns (float32 tables) under a 16-bit module: the rows of the per-feature
+    layer's operands end halfway through a 16-byte piece, and what follows the last one is NaN."""
+    monkeypatch.setenv("DMT_TM_BIG", big)
+    w = wl.scaled(wl.mid(), max_rows=300, batch=batch, num_tables=2 * nf)
+    w.table_dtype = "f32"
+    w.dims = [dim] * (2 * nf)
+    w.table_to_tower = [0] * nf + [1] * nf
+    w.tm_kind = wl.TM_DLRM
+    w.tm_feat_out = feat_out
+    w.tm_out = [20 + nf * feat_out, 3 + nf * feat_out]
+    w.tm_dtype = w.pooled_dtype = dt
+    check_tm_bwd(w, guard=True)
 
 
 @pytest.mark.parametrize("kind", ["linear_relu", "dot_linear", "cross_linear", "dlrm"])
