@@ -27,6 +27,9 @@ namespace {
 struct TowerWs {
   size_t z_off = 0, wp_off = 0, x_off[2] = {0, 0};
   size_t t_off = 0;            // low-rank cross layers: t = V_l x_l, [B][r]
+  // DLRM towers of the 16-bit types whose features are no multiple of 8 columns: the shared layer's
+  // operands with their rows padded to one (np_pad columns, np of them real)
+  size_t xf_off = 0, wf_off = 0;
   int np = 0, np_pad = 0;
 };
 
@@ -82,6 +85,12 @@ dmt_status plan_tm(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, int eb
         if (q.feat_out < 1 || (int64_t)q.out_dim - (int64_t)nf * q.feat_out < 1) return DMT_EINVAL;
         if (!q.w_cross[0] || !q.b_cross[0] || ((uintptr_t)q.w_cross[0] & 15)) return DMT_EINVAL;
         if (B * nf >= (1LL << 31)) return DMT_ENOTSUP;
+        w.np = p->tower_uniform_dim[t];
+        w.np_pad = (w.np + 7) / 8 * 8;
+        if (eb == 2 && w.np_pad != w.np) {
+          w.xf_off = take((size_t)B * nf * w.np_pad * eb);
+          w.wf_off = take((size_t)q.feat_out * w.np_pad * eb);
+        }
         break;
       }
       default:
@@ -143,6 +152,10 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
     return DT == DMT_F32 || (dots_any && fused[t]) || dot_weights_as_is(tp[t].w_proj, ws[t].np);
   };
 
+  // Whether a DLRM tower's shared layer reads padded copies: a row that ends inside a 16-byte piece would
+  // bring the next row's first columns into its sum.
+  auto padded_feat = [&](int t) { return DT != DMT_F32 && tp[t].kind == DMT_TM_DLRM && ws[t].np_pad != ws[t].np; };
+
   // stage 0: dot terms and repacked projection weights, one grouped launch per kind
   std::vector<TmAuxItem> dots_mfma, dots_simple, packs;
   std::vector<int64_t> nb_mfma, nb_simple, nb_pack;
@@ -150,8 +163,19 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
     const dmt_tm_params& q = tp[t];
     if (q.kind == DMT_TM_CROSS_LINEAR || q.kind == DMT_TM_CROSS_LOWRANK_LINEAR)
       max_layers = std::max(max_layers, q.num_cross_layers);
-    if (q.kind != DMT_TM_DOT_LINEAR) continue;
     const TowerWs& w = ws[t];
+    if (padded_feat(t)) {
+      auto pad_rows = [&](const void* src, int64_t rows, size_t dst) {
+        TmAuxItem it{};
+        it.src = src; it.dst = wsp + dst;
+        it.O = (int32_t)rows; it.np = w.np; it.np_pad = w.np_pad;
+        packs.push_back(it);
+        nb_pack.push_back((rows * w.np_pad + kBlock - 1) / kBlock);
+      };
+      pad_rows(x_all + (size_t)B * p->width_prefix[t] * eb, B * p->tower_ntab[t], w.xf_off);
+      pad_rows(q.w_cross[0], q.feat_out, w.wf_off);
+    }
+    if (q.kind != DMT_TM_DOT_LINEAR) continue;
     TmAuxItem it{};
     it.nf = p->tower_ntab[t]; it.n = p->tower_uniform_dim[t]; it.np = w.np; it.np_pad = w.np_pad;
     it.O = q.out_dim; it.wt = p->tower_width[t];
@@ -248,8 +272,10 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
       const int nf = p->tower_ntab[t], n = p->tower_uniform_dim[t];
       g.N = q.out_dim - nf * q.feat_out;
       TmGroup h{};
-      h.A1 = x; h.lda1 = n; h.K1 = n;
-      h.W1 = q.w_cross[0]; h.ldw1 = n; h.bias = q.b_cross[0];
+      const bool pad = padded_feat(t);
+      const int k = pad ? ws[t].np_pad : n;
+      h.A1 = pad ? (const void*)(wsp + ws[t].xf_off) : x; h.lda1 = k; h.K1 = k;
+      h.W1 = pad ? (const void*)(wsp + ws[t].wf_off) : q.w_cross[0]; h.ldw1 = k; h.bias = q.b_cross[0];
       h.C = y_all + ((size_t)B * out_prefix[t] + g.N) * eb;
       h.ldc = q.out_dim; h.rdiv = nf; h.ldc2 = q.feat_out;
       h.M = (int32_t)(B * nf); h.N = q.feat_out; h.epi = EPI_BIAS;
@@ -281,10 +307,11 @@ extern "C" size_t dmt_tm_workspace_bytes(const dmt_plan* plan, const dmt_tm_para
   if (!plan || !per_tower || B <= 0) return 0;
   return dmt_guard_size([&]() -> size_t {
     std::vector<TowerWs> ws;
-    size_t bytes = 0;
-    // sized for the wider element type so one figure serves every dtype
-    if (plan_tm(plan, per_tower, B, 4, &ws, &bytes) != DMT_OK) return 0;
-    return bytes;
+    size_t b4 = 0, b2 = 0;
+    // enough for every dtype: the 16-bit layouts have smaller operands but may pad some
+    if (plan_tm(plan, per_tower, B, 4, &ws, &b4) != DMT_OK) return 0;
+    if (plan_tm(plan, per_tower, B, 2, &ws, &b2) != DMT_OK) b2 = 0;   // e.g. a rank no multiple of 8
+    return std::max(b4, b2);
   });
 }
 

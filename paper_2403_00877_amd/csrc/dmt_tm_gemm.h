@@ -958,7 +958,7 @@ __global__ __launch_bounds__(kBlock) void tm_dots_simple(const TmAuxLaunch L) {
 }
 
 // Projection weights [O][np + Wt] -> [O][np_pad + Wt] with zero columns after the
-// dot terms, so both K segments start 16-byte aligned.
+// dot terms, so both K segments start 16-byte aligned.  (Wt = 0: rows of np elements padded to np_pad.)
 template <int DT>
 __global__ __launch_bounds__(kBlock) void tm_pack_w(const TmAuxLaunch L) {
   const int gi = aux_group(L);

@@ -4,20 +4,23 @@ import torch
 
 import oracle
 import workloads as wl
-from harness import RTOL, DeviceWorkload, TowerModules, assert_close, to_device, to_f64
+from harness import RTOL, DeviceWorkload, TowerModules, assert_close, nan_behind, to_device, to_f64
 
 pytestmark = pytest.mark.gpu
 
 
-def check_tm(w, chained=False):
+def check_tm(w, chained=False, guard=False):
     """TM on the oracle's pooled values (rounded to the pooled dtype), then
-    optionally also the GPU lookup -> GPU TM chain."""
+    optionally also the GPU lookup -> GPU TM chain.  guard: what lies behind the pooled values and
+    the weights is NaN."""
     dw = DeviceWorkload(w)
-    tm = TowerModules(dw)
+    tm = TowerModules(dw, guard=guard)
     idx, off = wl.lookup_batch(w)
     pooled = oracle.lookup_towered(dw.host_tables, w.table_dtype, w.dims, w.table_to_tower, idx, off, w.batch)
     enc = [oracle.round_to(p, tm.dtype) for p in pooled]
     x_dev = torch.cat([to_device(e, tm.dtype).reshape(-1) for e in enc])
+    if guard:
+        x_dev = nan_behind(x_dev)
     got = to_f64(tm.run(x_dev))
     x64 = [wl.decode(e, tm.dtype) for e in enc]
     ref = tm.oracle(x64)
@@ -144,6 +147,25 @@ def test_dlrm_module_odd_widths():
     w.tm_feat_out = 5
     w.tm_out = [20 + 3 * 5] * 2
     check_tm(w)
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("dim,nf,batch,feat_out,big", [(12, 2, 77, 5, "0"), (12, 4, 301, 24, "2"), (4, 6, 65, 8, "3"),
+                                                       (20, 2, 1, 1, "1"), (132, 2, 300, 136, "1")])
+def test_dlrm_module_rows_that_end_inside_a_chunk(dim, nf, batch, feat_out, big, dt, monkeypatch):
+    """Features of 4 mod 8 columns (float32 tables) under a 16-bit module: a row of the per-feature
+    layer's operands ends halfway through a 16-byte piece, whose other half is the next row (behind
+    the last one: NaN)."""
+    monkeypatch.setenv("DMT_TM_BIG", big)
+    w = wl.scaled(wl.mid(), max_rows=300, batch=batch, num_tables=2 * nf)
+    w.table_dtype = "f32"
+    w.dims = [dim] * (2 * nf)
+    w.table_to_tower = [0] * nf + [1] * nf
+    w.tm_kind = wl.TM_DLRM
+    w.tm_feat_out = feat_out
+    w.tm_out = [20 + nf * feat_out, 3 + nf * feat_out]
+    w.tm_dtype = w.pooled_dtype = dt
+    check_tm(w, guard=True)
 
 
 @pytest.mark.parametrize("dt,rank", [("bf16", 64), ("bf16", 256), ("f16", 32), ("f32", 5)])
