@@ -148,8 +148,12 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
       }
     dots_any = !g.empty() && take_small(p, g.data(), (int)g.size());
   }
+  // (Only the kernel with in-kernel dot terms clears the weights that meet the zeros behind the terms: the
+  // pooled values' first ones, where the terms are no multiple of 8.  The others read zeros in the
+  // repacked copy.)
   auto as_is = [&](int t) {
-    return DT == DMT_F32 || (dots_any && fused[t]) || dot_weights_as_is(tp[t].w_proj, ws[t].np);
+    return DT == DMT_F32 || (dots_any && fused[t]) ||
+           (dot_weights_as_is(tp[t].w_proj, ws[t].np) && (fused[t] || ws[t].np == ws[t].np_pad));
   };
 
   // Whether a DLRM tower's shared layer reads padded copies: a row that ends inside a 16-byte piece would

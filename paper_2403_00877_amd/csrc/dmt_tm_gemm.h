@@ -204,6 +204,14 @@ struct TmStage {
     return LAY == OP_ROW ? tm_buffer(base + k, ((uint32_t)(rows - 1) * (uint32_t)ld + ((kn + 7) & ~7)) * 2u)
                          : tm_buffer(base + (int64_t)k * ld, ((uint32_t)(kn - 1) * (uint32_t)ld + ((rows + 1) & ~1)) * 2u);
   }
+  // OP_ROW: zeros in columns k .. of the pieces of a landed tile that also hold columns before k (each
+  // lane its own pieces).
+  __device__ __forceinline__ void zero_from(uint16_t* tile, int k, int wave, int lane) const {
+    if (!(k & 7) || chunk != k >> 3) return;
+#pragma clang loop unroll(full)
+    for (int j = 0; j < kInstr; ++j)
+      for (int e = k & 7; e < 8; ++e) tile[((j * NW + wave) * 64 + lane) * 8 + e] = 0;
+  }
   // This wave's j-th request: of a whole step, or with kn columns left in the segment.
   __device__ __forceinline__ void request(uint32_t lds, __amdgpu_buffer_rsrc_t rsrc, int j, int wave) const {
     tm_request(lds + (j * NW + wave) * 1024, rsrc, off[j]);
@@ -435,7 +443,14 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
         }
       }
     }
-    __builtin_amdgcn_s_waitcnt(0x0f70);            // vmcnt(0): this wave's requests have landed
+    if constexpr (DOTS) {
+      // Weights that are read as they are: the pooled values' weights stand behind the terms' and
+      // meet the zeros behind the terms.  They count as zeros (an infinite one would make NaN).
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      sw.zero_from(lds + TILE * BK, G.nf * (G.nf - 1) / 2, wave, lane);
+    } else {
+      __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): this wave's requests have landed
+    }
     __syncthreads();
     if (!DOTS && nk > 1) request_tile(1, 1);
     read_frag(0, 0, 0);
@@ -801,7 +816,13 @@ __global__ __launch_bounds__(kSmallWaves * 64, 4) void tm_gemm_small(const TmLau
     if (s0 * 16 < K0) {
       const int k = s0 * 16 + h8;
       uint4 wz = make_uint4(0, 0, 0, 0);
-      if (k < K0) wz = small_load<false>((const uint16_t*)G.W0 + (int64_t)n * G.ldw0 + k);
+      if (k < np) {
+        wz = small_load<false>((const uint16_t*)G.W0 + (int64_t)n * G.ldw0 + k);
+        // (behind the terms' weights stand the pooled values': zeros, as the terms there are)
+        uint32_t* const q = (uint32_t*)&wz;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[i] = k + 2 * i + 1 < np ? q[i] : k + 2 * i < np ? q[i] & 0xffffu : 0u;
+      }
       acc = mfma32<DT>(*(const uint4*)(z + r * kZPitch + k), wz, acc);
     }
     if (G.U && n0 == 0)                            // a training forward keeps the terms, zeros behind them

@@ -213,6 +213,37 @@ def test_dot_terms_of_any_feature_count(nf, dt):
     check_tm(w)
 
 
+@pytest.mark.parametrize("big,fuse", [("0", "1"), ("2", "1"), ("3", "1"), ("0", "0"), ("2", "0")])
+@pytest.mark.parametrize("nf", [2, 4, 5, 8, 9, 12])
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+def test_an_infinite_weight_reaches_only_its_own_products(nf, dt, big, fuse, monkeypatch):
+    """The flat weights that stand where a row's dot terms are padded to a whole 16-byte piece: an
+    infinite one makes its output infinite, with the sign of the value it multiplies, and no NaN.
+    1, 6, 10, 28, 36 and 66 terms; in-kernel terms on all three tilings, and terms of their own."""
+    monkeypatch.setenv("DMT_TM_BIG", big)
+    monkeypatch.setenv("DMT_TM_FUSE", fuse)
+    w = wl.scaled(wl.mid(), max_rows=100, batch=261, num_tables=nf)
+    w.dims = [24] * nf
+    w.table_to_tower = [0] * nf
+    w.tm_out = [264]
+    w.tm_dtype = w.pooled_dtype = dt
+    dw = DeviceWorkload(w)
+    tm = TowerModules(dw)
+    np_, pad = nf * (nf - 1) // 2, -(nf * (nf - 1) // 2) % 8
+    weights = tm.keep[0]["w_proj"]
+    x = torch.randn(w.batch, nf * 24, device="cuda", generator=torch.Generator("cuda").manual_seed(nf)).to(weights.dtype)
+    plain = tm.run(x.reshape(-1)).view(w.batch, 264)
+    assert torch.isfinite(plain).all()
+    planted = {o: j for o, j in zip((0, 31, 130, 263), (0, 1, pad // 2, max(pad - 1, 0)))}
+    for o, j in planted.items():
+        weights[o, np_ + j] = float("inf")
+    got = tm.run(x.reshape(-1)).view(w.batch, 264)
+    others = [o for o in range(264) if o not in planted]
+    assert torch.equal(got[:, others], plain[:, others])
+    for o, j in planted.items():
+        assert torch.equal(got[:, o], torch.sign(x[:, j]) * float("inf")), (o, j)
+
+
 @pytest.mark.parametrize("big", ["0", "2", "3"])
 @pytest.mark.parametrize("batch,out", [(129, 130), (255, 264), (256, 256), (257, 129), (520, 513), (31, 33), (1, 7)])
 @pytest.mark.parametrize("kind", ["linear_relu", "dot_linear", "cross_linear"])
