@@ -519,9 +519,13 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
   auto z_of = [&](int t) -> const char* {           // dot terms: kept by the forward, or recomputed
     return keptp && kept[t].has_z ? keptp + kept[t].z : (const char*)(wsp + ws[t].p);
   };
-  auto wp_of = [&](int t) -> const char* {          // the projection's weights, repacked where they must be
+  // The projection's weights, repacked where they must be.  The forward has kept a repacked copy if the
+  // terms are odd; otherwise only if ITS weights were not 4-byte aligned, which the weights at hand
+  // do not tell.
+  auto kept_wp = [&](int t) { return keptp && kept[t].has_z && ws[t].np % 2 == 1; };
+  auto wp_of = [&](int t) -> const char* {
     if (!ws[t].packed) return (const char*)tp[t].w_proj;
-    return keptp && kept[t].has_z ? keptp + kept[t].wp : (const char*)(wsp + ws[t].wp);
+    return kept_wp(t) ? keptp + kept[t].wp : (const char*)(wsp + ws[t].wp);
   };
   // ---- recompute what the forward did not keep: dot terms (and the repacked weights)
   std::vector<TmAuxItem> dots_mfma, dots_simple, packs;
@@ -529,14 +533,14 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
   for (int32_t t = 0; t < p->T; ++t) {
     const dmt_tm_params& q = tp[t];
     if (is_cross(q)) max_layers = std::max(max_layers, q.num_cross_layers);
-    if (q.kind != DMT_TM_DOT_LINEAR || (keptp && kept[t].has_z)) continue;
+    if (q.kind != DMT_TM_DOT_LINEAR) continue;
     const TowerBwdWs& w = ws[t];
     TmAuxItem it{};
     it.nf = p->tower_ntab[t]; it.n = p->tower_uniform_dim[t]; it.np = w.np; it.np_pad = w.np_pad;
     it.O = q.out_dim; it.wt = p->tower_width[t];
     it.src = x_of(t);
     it.dst = wsp + w.p;
-    if (w.np_pad > 0) {
+    if (w.np_pad > 0 && !(keptp && kept[t].has_z)) {
       if (dots_mfma_ok(it.nf, it.n)) {
         dots_mfma.push_back(it);
         nb_mfma.push_back(dots_mfma_blocks(B, it.nf));
@@ -545,7 +549,7 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
         nb_simple.push_back((B * w.np_pad + kBlock - 1) / kBlock);
       }
     }
-    if (!w.packed) continue;
+    if (!w.packed || kept_wp(t)) continue;
     it.src = q.w_proj;
     it.dst = wsp + w.wp;
     packs.push_back(it);

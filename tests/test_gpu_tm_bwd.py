@@ -223,6 +223,43 @@ def test_kept_dot_terms_on_every_dot_path(dt, fuse, monkeypatch):
     check_tm_bwd(w5, rtol=1e-4 if dt == "f32" else 4e-2, keep=True)
 
 
+@pytest.mark.parametrize("fuse", ["0", "1"])
+@pytest.mark.parametrize("nf,forward_at,backward_at", [(4, 0, 1), (4, 1, 0), (8, 0, 1), (3, 0, 1), (3, 1, 0), (2, 1, 1)])
+def test_kept_activations_serve_weights_at_any_address(nf, forward_at, backward_at, fuse, monkeypatch):
+    """The same dot-tower weights at an aligned address and 2 bytes behind one (weights there are read
+    from a repacked copy; 4 and 8 features: an even number of dot terms, whose aligned weights are read
+    as they are), given to the training forward and to the backward in either order."""
+    monkeypatch.setenv("DMT_TM_FUSE", fuse)
+    w = wl.scaled(wl.mid(), max_rows=100, batch=70, num_tables=nf)
+    w.dims = [24] * nf
+    w.table_to_tower = [0] * nf
+    w.tm_out = [40]
+    w.tm_dtype = w.pooled_dtype = "bf16"
+    dw = DeviceWorkload(w)
+    tm = TowerModules(dw)
+    p = tm.keep[0]
+    x = torch.randn(w.batch * nf * 24, device="cuda").to(torch.bfloat16)
+    dy = torch.randn(w.batch * 40, device="cuda")
+
+    def weights_at(odd):
+        buf = torch.full((p["w_proj"].numel() + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        buf[odd:odd + p["w_proj"].numel()] = p["w_proj"].reshape(-1)
+        moved = buf[odd:odd + p["w_proj"].numel()].view(p["w_proj"].shape)
+        tm.moved.append(moved)
+        return dw.dmt.make_tm_params([dict(p, w_proj=moved)])
+
+    tm.moved = []
+    tm.params = weights_at(0)
+    want_dx, want = run_bwd(dw, tm, x, None, dy, None)
+    tm.params = weights_at(forward_at)
+    kept = forward_keep(dw, tm, x)
+    tm.params = weights_at(backward_at)
+    got_dx, got = run_bwd(dw, tm, x, None, dy, kept)
+    np.testing.assert_array_equal(got_dx, want_dx)
+    for k in ("dw_proj", "db_proj"):
+        np.testing.assert_array_equal(got[0][k], want[0][k])
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f16", "f32"])
 def test_dlrm_module_flat_and_shared_per_feature_projection(dt):
     # 2 towers x 8 features x 128: flat 1024 -> 200 next to the shared 128 -> 24 (392 outputs)
