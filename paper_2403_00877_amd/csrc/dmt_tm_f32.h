@@ -143,6 +143,12 @@ __device__ __forceinline__ void f32_segment(const F32Seg& g, int64_t m, int64_t 
   }
 }
 
+// First of a tile's `steps` that the wave `part` of 2^log2_ks takes.  (64 bits: a per-feature layer's weight
+// gradient has up to 2^28 steps, times sixteen waves.)
+__host__ __device__ inline int f32_first_step(int steps, int part, int log2_ks) {
+  return (int)((int64_t)steps * part >> log2_ks);
+}
+
 template <int TAG = DMT_TM_TAG>
 __global__ __launch_bounds__(kF32Waves * 64) void tm_gemm_f32(const TmF32Launch L) {
   __shared__ float red[kF32Waves][16][64];
@@ -161,7 +167,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void tm_gemm_f32(const TmF32Launch 
   const int m = min(m0 + r, M - 1), n = min(n0 + r, N - 1);   // rows past the edge: the last row, not stored
   // this wave's share of the steps, cut into the two segments
   const int S0 = (G.K0 + 7) / 8, S = S0 + (G.K1 + 7) / 8;
-  const int lo = live ? S * part >> G.log2_ks : 0, hi = live ? S * (part + 1) >> G.log2_ks : 0;
+  const int lo = live ? f32_first_step(S, part, G.log2_ks) : 0, hi = live ? f32_first_step(S, part + 1, G.log2_ks) : 0;
   floatx16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
