@@ -51,7 +51,7 @@ constexpr int kScanTile = kBlock * kScanItems;   // records per head-scan block
 // to fill the chip with tiles of 128.  A wave takes about 0.25 us per record, so 2300 records in
 // tiles of 128 are 18 waves of 30 us (tiles of 16: 7.7); but every run that crosses a tile
 // boundary costs a partial sum and a share of the fix-up, so tiles shrink only until there are
-// kFillTiles of them (four waves per SIMD at 4096, eight at 8192).
+// fill_tiles of them (four waves per SIMD at 4096, eight at 8192).
 constexpr int kReduceTile = 128, kMinReduceTile = 16;
 inline int64_t fill_tiles(int max_dim) { return max_dim <= 128 ? 8192 : 4096; }
 inline int reduce_tile(int64_t nnz, int max_dim) {
@@ -1392,30 +1392,99 @@ __device__ __forceinline__ uint32_t table_of(const int64_t* __restrict__ row_bas
 // starts adds the pieces in tile order and applies the update.
 // one wave per block: groups are independent, and the group at the head of a long run works
 // far longer than its neighbours (50.7 -> 47.4 us on Mid)
-constexpr int kFixBlock = 64;
-template <int TD>
-__global__ __launch_bounds__(kFixBlock) void bwd_fixup_update(
+//
+// Small calls (Small): their tiles are smaller, so a row of many lookups has up to eight times the
+// pieces, and one group would take eight times the memory latencies (eight pieces each).  A run of
+// more than kLongRun tiles there is left to a block of its own, kLongGroups groups that share the
+// pieces and add their sums in group order: no more latencies than tiles of 128 records have.  One
+// such block stands ready for every kLongRun tiles and ends after two records if no long run
+// has its first multiple of kLongRun tiles there.  Whole call, us, with tiles of 128 / smaller tiles
+// and one group / now: one row of 131072 lookups, 128 columns 148 / 700 / 131; of 16384 64 / 110 / 36; two
+// rows of 65536, 64 columns 93 / 367 / 80; 26 tables, half of them of 2 to 24 rows, 104156 lookups 114 / 67 / 61.
+constexpr int kFixBlock = 64, kLongRun = 64, kLongGroups = 8, kLongBlock = kLongGroups * 64;
+template <int TD, bool Small>
+__global__ __launch_bounds__(Small ? kLongBlock : kFixBlock) void bwd_fixup_update(
     const DmtTableMeta* __restrict__ meta, uint32_t B, uint32_t nbags,
     const uint64_t* __restrict__ pk, int64_t nnz, uint32_t total_rows,
-    const float* __restrict__ partials, int Dmax, int log2_gl, int tile, int64_t ntiles, float lr, float eps,
-    const unsigned long long* __restrict__ err_offsets) {
+    const float* __restrict__ partials, int Dmax, int log2_gl, int tile, int64_t ntiles, int nlong, float lr,
+    float eps, const unsigned long long* __restrict__ err_offsets) {
   if (*err_offsets != ~0ULL) return;
-  const int GL = 1 << log2_gl;
-  const int64_t t0 = (int64_t)blockIdx.x * (kFixBlock >> log2_gl) + (threadIdx.x >> log2_gl);
+  const int GL = 1 << log2_gl, NG = (int)(blockDim.x >> log2_gl);
+  const int grp = threadIdx.x >> log2_gl, gl = threadIdx.x & (GL - 1);
+  const bool on = gl * 4 < Dmax;
+  auto head_piece = [&](int64_t t0) -> float4 {
+    return on ? *((const float4*)(partials + (2 * t0 + 1) * Dmax) + gl) : make_float4(0.f, 0.f, 0.f, 0.f);
+  };
+  // acc + the pieces of tiles first .. first + 7, of the eight `stride` tiles on, ... up to t1
+  auto add_pieces = [&](float4 acc, int64_t first, int64_t t1, int stride) -> float4 {
+    for (int64_t tt = first; tt <= t1; tt += stride) {
+      float4 g[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        g[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (on && tt + q <= t1) g[q] = *((const float4*)(partials + 2 * (tt + q) * Dmax) + gl);
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        acc.x += g[q].x; acc.y += g[q].y; acc.z += g[q].z; acc.w += g[q].w;
+      }
+    }
+    return acc;
+  };
+  // The row of a run, from its key and (no search through the row bases) the bag of any of its records.
+  uint32_t f = 0;
+  int64_t row = 0;
+  auto find_row = [&](uint64_t rec) -> bool {
+    const uint32_t key = (uint32_t)(rec >> 32), bag = (uint32_t)rec;
+    if (key >= total_rows || bag >= nbags) return false;
+    f = bag / B;
+    row = (int64_t)key - meta[f].row_base;
+    return row >= 0 && row < meta[f].rows;         // key and bag disagree: not a row to touch
+  };
+  if constexpr (Small) {
+    if ((int)blockIdx.x < nlong) {
+      // (every wave finds the same: the block stays together)
+      const int64_t m = ((int64_t)blockIdx.x + 1) * kLongRun;
+      const int lane = threadIdx.x & 63;
+      const uint64_t rec = pk[m * tile], before = pk[m * tile - 1];
+      const uint32_t key = (uint32_t)(rec >> 32);
+      if (key != (uint32_t)(before >> 32) || !find_row(rec)) return;
+      // tiles m, m - 1, ... that start with the key (the keys are sorted), up to kLongRun of them
+      const int back = __popcll(__ballot((uint32_t)(pk[(m - lane) * tile] >> 32) == key));
+      const int64_t first = m - back + 1;
+      const int64_t t0 = (uint32_t)(pk[first * tile - 1] >> 32) == key ? first - 1 : first;
+      if (t0 > 0 && t0 == m - kLongRun && (uint32_t)(pk[t0 * tile] >> 32) == key &&
+          (uint32_t)(pk[t0 * tile - 1] >> 32) == key)
+        return;                                    // starts further back: another block's
+      int64_t t1 = m, hi = ntiles;                 // holds at t1, fails at hi
+      while (hi - t1 > 1) {
+        const int64_t step = (hi - t1 + 63) / 64, at = t1 + (lane + 1) * step;
+        const int n = __popcll(__ballot(at < hi && (uint32_t)(pk[min(at, ntiles - 1) * tile] >> 32) == key));
+        hi = min(hi, t1 + (n + 1) * step);
+        t1 += n * step;
+      }
+      if (t1 - t0 <= kLongRun) return;             // its group adds it up
+      __shared__ float4 sums[kLongBlock];
+      sums[threadIdx.x] = add_pieces(make_float4(0.f, 0.f, 0.f, 0.f), t0 + 1 + grp * 8, t1, NG * 8);
+      __syncthreads();
+      if (grp > 0) return;
+      float4 acc = head_piece(t0);
+      for (int q = 0; q < NG; ++q) {
+        const float4 g = sums[(q << log2_gl) + gl];
+        acc.x += g.x; acc.y += g.y; acc.z += g.z; acc.w += g.w;
+      }
+      apply_row_update<TD, false>(meta, f, (uint32_t)row, acc, gl, GL, lr, eps);
+      return;
+    }
+  }
+  const int64_t t0 = (int64_t)(blockIdx.x - (Small ? nlong : 0)) * NG + grp;
   if (t0 >= ntiles - 1) return;
-  const int gl = threadIdx.x & (GL - 1);
   const int64_t p0 = t0 * tile, p1 = p0 + tile;    // p1 < nnz here
   // (the four records the decisions below look at are requested together: their latencies
   // would otherwise follow one another in every group)
   const uint64_t r_last = pk[p1 - 1], r_next = pk[p1], r_first = pk[p0], r_before = pk[p0 > 0 ? p0 - 1 : 0];
   const uint32_t k_last = (uint32_t)(r_last >> 32);
-  if (k_last != (uint32_t)(r_next >> 32) || k_last >= total_rows) return;
-  // the run's table follows from the bag of any of its records (no search through the row bases)
-  const uint32_t bag = (uint32_t)r_last;
-  if (bag >= nbags) return;
-  const uint32_t f = bag / B;
-  const int64_t row = (int64_t)k_last - meta[f].row_base;
-  if (row < 0 || row >= meta[f].rows) return;      // key and bag disagree: not a row to touch
+  if (k_last != (uint32_t)(r_next >> 32) || !find_row(r_last)) return;
   const uint32_t k_first = (uint32_t)(r_first >> 32);
   if (k_first == k_last && p0 > 0 && (uint32_t)(r_before >> 32) == k_first) return;
   // last tile the run reaches: the largest t with the run's key at the tile's first record
@@ -1424,27 +1493,14 @@ __global__ __launch_bounds__(kFixBlock) void bwd_fixup_update(
   for (int64_t step = 1; t1 + step < hi; step <<= 1) {
     if ((uint32_t)(pk[(t1 + step) * tile] >> 32) == k_last) t1 += step;
     else { hi = t1 + step; break; }
+    if (Small && t1 - t0 > kLongRun) return;
   }
   while (hi - t1 > 1) {
     const int64_t mid = (t1 + hi) >> 1;
     if ((uint32_t)(pk[mid * tile] >> 32) == k_last) t1 = mid; else hi = mid;
   }
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  const bool on = gl * 4 < Dmax;
-  if (on) acc = *((const float4*)(partials + (2 * t0 + 1) * Dmax) + gl);
-  for (int64_t tt = t0 + 1; tt <= t1; tt += 8) {
-    float4 g[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      g[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (on && tt + q <= t1) g[q] = *((const float4*)(partials + 2 * (tt + q) * Dmax) + gl);
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      acc.x += g[q].x; acc.y += g[q].y; acc.z += g[q].z; acc.w += g[q].w;
-    }
-  }
-  apply_row_update<TD, false>(meta, f, (uint32_t)row, acc, gl, GL, lr, eps);
+  if (Small && t1 - t0 > kLongRun) return;
+  apply_row_update<TD, false>(meta, f, (uint32_t)row, add_pieces(head_piece(t0), t0 + 1, t1, 8), gl, GL, lr, eps);
 }
 
 // ------------------------------------------------------------- parity exports
@@ -1572,10 +1628,13 @@ void launch_reduce_and_fixup(const ReduceCall& c) {
       default: launch_reduce_grouped<TD, 6>(c); break;
     }
   }
-  const int64_t blocks = (c.w->ntiles + (kFixBlock >> log2_gl) - 1) / (kFixBlock >> log2_gl);
-  timed_launch(c.plan, DMT_K_BWD_FIXUP, c.s, bwd_fixup_update<TD>, blocks, kFixBlock, c.plan->d_meta,
-               (uint32_t)c.B, c.nbags, c.sorted, c.nnz, c.total_rows, c.w->partials, max_dim,
-               log2_gl, c.w->tile, c.w->ntiles, c.lr, c.eps, c.plan->d_error + 1);
+  const bool small = c.w->tile < kReduceTile;
+  const int threads = small ? std::max(64, kLongGroups << log2_gl) : kFixBlock, groups = threads >> log2_gl;
+  const int nlong = small ? (int)((c.w->ntiles - 1) / kLongRun) : 0;      // tiles 64, 128, ... < ntiles
+  const int64_t blocks = nlong + (c.w->ntiles + groups - 1) / groups;
+  timed_launch(c.plan, DMT_K_BWD_FIXUP, c.s, small ? bwd_fixup_update<TD, true> : bwd_fixup_update<TD, false>, blocks,
+               threads, c.plan->d_meta, (uint32_t)c.B, c.nbags, c.sorted, c.nnz, c.total_rows, c.w->partials, max_dim,
+               log2_gl, c.w->tile, c.w->ntiles, nlong, c.lr, c.eps, c.plan->d_error + 1);
 }
 
 }  // namespace

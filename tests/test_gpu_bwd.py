@@ -131,6 +131,38 @@ def test_every_reduce_tile_size(batch):
     check_bwd(w)
 
 
+@pytest.mark.parametrize("dim", [4, 16, 32, 64, 128, 256])
+@pytest.mark.parametrize("counts", [
+    [5, 16 * 64], [0, 16 * 64 + 1], [7, 16 * 64 + 10],        # 63 to 65 tiles further than it starts
+    [0, 16 * 65 + 1], [15, 16 * 65 + 2], [16, 16 * 66], [16 * 63, 16 * 65 + 1], [16 * 63 + 1, 16 * 66],
+    [16 * 64 - 1, 16 * 129 + 2], [16 * 64, 16 * 66], [16 * 64 + 1, 16 * 64 + 15], [3, 16 * 65, 16 * 130 + 1, 4, 16 * 71],
+    [16 * 200 + 9, 2, 2],
+])
+def test_rows_of_many_lookups_in_small_calls(dim, counts):
+    """Tiles of 16 records: runs of about as many tiles as a group adds up by itself and of several times
+    as many, starting at, behind and in front of a tile's and of a 64th tile's first record, one behind
+    the other and up to the last record; the second table holds one run as long as its share."""
+    n = sum(counts)
+    w = wl.dataclasses.replace(
+        wl.scaled(wl.mid(True), max_rows=10, batch=n, num_tables=2), table_dtype="f32", rows=[9, 2],
+        dims=[dim] * 2, table_to_tower=[0] * 2, tm_out=[32])
+    rng = np.random.default_rng(dim)
+    off = np.arange(2 * n + 1, dtype=np.int64)
+    idx = np.concatenate([rng.permutation(np.repeat(np.arange(len(counts)), counts)), np.ones(n)]).astype(np.int32)
+    dw = DeviceWorkload(w, with_state=True, max_nnz=2 * n)
+    grad = wl.grad_pooled(w)
+    run_bwd(dw, idx, off, grad, w.lr, w.eps, debug=False)
+    assert dw.dmt.dmt_last_device_error(dw.plan) == -1
+    ref = oracle.bwd_update(dw.host_tables, "f32", [np.zeros(r, np.float32) for r in w.rows], w.dims, w.table_to_tower,
+                            idx, off, n, grad, w.lr, w.eps)
+    for f in range(2):
+        m = ref["key_table"] == f
+        rows = torch.from_numpy(ref["key_row"][m]).cuda()
+        assert_close(to_f64(dw.tables[f][rows]), ref["new_rows"][m][:, :dim], 1e-5, "rows")
+        # (a sum of n terms of either sign: its float32 error is a few units of the terms' root sum of squares)
+        assert_close(to_f64(dw.states[f][rows]), ref["new_state"][m], 2e-5, "state")
+
+
 @pytest.mark.parametrize("rows,lens", [
     ([1, 1], [900, 2]),                             # one bit of row id
     ([1022, 3], [1000, 1]),                         # 10 bits: one pass
