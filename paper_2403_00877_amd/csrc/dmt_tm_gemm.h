@@ -204,13 +204,16 @@ struct TmStage {
     return LAY == OP_ROW ? tm_buffer(base + k, ((uint32_t)(rows - 1) * (uint32_t)ld + ((kn + 7) & ~7)) * 2u)
                          : tm_buffer(base + (int64_t)k * ld, ((uint32_t)(kn - 1) * (uint32_t)ld + ((rows + 1) & ~1)) * 2u);
   }
-  // OP_ROW: zeros in columns k .. of the pieces of a landed tile that also hold columns before k (each
-  // lane its own pieces).
+  // OP_ROW: zeros in columns k .. (k even) of the pieces of a landed tile that also hold columns before k
+  // (each lane its own pieces).
   __device__ __forceinline__ void zero_from(uint16_t* tile, int k, int wave, int lane) const {
     if (!(k & 7) || chunk != k >> 3) return;
+    uint4* const p = (uint4*)tile + wave * 64 + lane;
 #pragma clang loop unroll(full)
-    for (int j = 0; j < kInstr; ++j)
-      for (int e = k & 7; e < 8; ++e) tile[((j * NW + wave) * 64 + lane) * 8 + e] = 0;
+    for (int j = 0; j < kInstr; ++j) {
+      const uint4 v = p[j * NW * 64];
+      p[j * NW * 64] = make_uint4(v.x, (k & 7) > 2 ? v.y : 0u, (k & 7) > 4 ? v.z : 0u, 0u);
+    }
   }
   // This wave's j-th request: of a whole step, or with kn columns left in the segment.
   __device__ __forceinline__ void request(uint32_t lds, __amdgpu_buffer_rsrc_t rsrc, int j, int wave) const {
@@ -447,7 +450,8 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
       // Weights that are read as they are: the pooled values' weights stand behind the terms' and
       // meet the zeros behind the terms.  They count as zeros (an infinite one would make NaN).
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      sw.zero_from(lds + TILE * BK, G.nf * (G.nf - 1) / 2, wave, lane);
+      const int np = G.nf * (G.nf - 1) / 2;
+      if ((const uint16_t*)G.W0 + np == G.W1) sw.zero_from(lds + TILE * BK, np, wave, lane);
     } else {
       __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): this wave's requests have landed
     }
