@@ -57,13 +57,12 @@ def test_large_scaled_cross_linear_bf16():
     check_tm(w, chained=True)
 
 
-@pytest.mark.parametrize("direct", ["1", "0"])
+@pytest.mark.parametrize("big", ["2", "0"])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-def test_cross_linear_on_interior_tiles(direct, dtype, monkeypatch):
-    """A batch and widths that are multiples of the 256 x 256 tile: such launches load their
-    operand tiles straight into LDS (DMT_TM_DIRECT=0 keeps the register-staged loop); two 1024
-    x 1024 cross layers and a 1024 -> 256 projection on two towers, B = 512."""
-    monkeypatch.setenv("DMT_TM_DIRECT", direct)
+def test_cross_linear_on_interior_tiles(big, dtype, monkeypatch):
+    """A batch and widths that are multiples of the 256 x 256 and of the 128 x 128 tile, each in turn;
+    two 1024 x 1024 cross layers and a 1024 -> 256 projection on two towers, B = 512."""
+    monkeypatch.setenv("DMT_TM_BIG", big)
     w = wl.scaled(wl.large(), max_rows=3000, batch=512)
     sel = [f for f in range(256) if w.table_to_tower[f] in (0, 1)][:16]
     w.rows = [w.rows[f] for f in sel]
@@ -79,8 +78,11 @@ def test_imbalanced_scaled_linear_f16():
     check_tm(wl.scaled(wl.imbalanced(), max_rows=2000, batch=777, num_tables=26), chained=True)
 
 
-def test_dot_linear_odd_feature_count_falls_back():
-    # 3 features per tower do not tile a 32-row MFMA block: plain-FMA dot kernel
+@pytest.mark.parametrize("fuse", ["1", "0"])
+def test_dot_linear_odd_feature_count(fuse, monkeypatch):
+    # 3 features per tower: ten samples and two idle rows in a Gram tile, in the projection kernel
+    # and in the dot kernel
+    monkeypatch.setenv("DMT_TM_FUSE", fuse)
     w = wl.scaled(wl.mid(), max_rows=500, batch=50, num_tables=6)
     w.table_to_tower = [0, 0, 0, 1, 1, 1]
     w.tm_out = [40, 24]
@@ -97,11 +99,11 @@ def test_dot_linear_f32_and_f16():
 
 def test_dot_linear_fused_and_separate_towers_in_one_call():
     """Tower 0 (4 features x 64, 6 dots padded to 8, 300 outputs) takes the GEMM that computes
-    its dot terms in-kernel; tower 1 (8 features, 96 outputs) the separate dot kernel and the
-    128 x 128 GEMM; batch 519 leaves ragged row tiles in both."""
-    w = wl.scaled(wl.mid(), max_rows=400, batch=519, num_tables=12)
-    w.dims = [64] * 4 + [128] * 8
-    w.table_to_tower = [0] * 4 + [1] * 8
+    its dot terms in-kernel; tower 1 (12 features of 128, 66 terms: more than one K step, 96 outputs)
+    the separate dot kernel and a plain GEMM; batch 519 leaves ragged row tiles in both."""
+    w = wl.scaled(wl.mid(), max_rows=400, batch=519, num_tables=16)
+    w.dims = [64] * 4 + [128] * 12
+    w.table_to_tower = [0] * 4 + [1] * 12
     w.tm_out = [300, 96]
     for dt in ("bf16", "f16"):
         w.tm_dtype = dt
@@ -109,10 +111,12 @@ def test_dot_linear_fused_and_separate_towers_in_one_call():
         check_tm(w)
 
 
+@pytest.mark.parametrize("big", ["0", "1", "2"])
 @pytest.mark.parametrize("out_dim,batch", [(100, 77), (300, 333), (257, 512)])
-def test_linear_odd_output_widths_and_ragged_batches(out_dim, batch):
+def test_linear_odd_output_widths_and_ragged_batches(out_dim, batch, big, monkeypatch):
     """Output widths that are no multiple of 8 or of a tile (scalar epilogue, partial
-    column tiles) on both GEMM kernels (<= 128 columns: 128 x 128; wider: 256 x 256)."""
+    column tiles) on both tilings of the grouped GEMM and on the one these sizes take (32 x 32)."""
+    monkeypatch.setenv("DMT_TM_BIG", big)
     w = wl.scaled(wl.imbalanced(), max_rows=500, batch=batch, num_tables=9)
     w.tm_out = [out_dim] * w.num_towers
     check_tm(w)
@@ -170,8 +174,7 @@ def test_dlrm_module_rows_that_end_inside_a_chunk(dim, nf, batch, feat_out, big,
 
 @pytest.mark.parametrize("dt,rank", [("bf16", 64), ("bf16", 256), ("f16", 32), ("f32", 5)])
 def test_lowrank_cross_module(dt, rank):
-    """Two low-rank DCN-v2 cross layers on 512-wide towers (rank 256 takes the 256 x 256 GEMM for
-    the second contraction, the smaller ranks the 128 x 128 one), then 512 -> 96; batch 150."""
+    """Two low-rank DCN-v2 cross layers on 512-wide towers, then 512 -> 96; batch 150."""
     w = wl.scaled(wl.large(), max_rows=300, batch=150, num_tables=8)
     w.table_to_tower = [0, 0, 0, 0, 1, 1, 1, 1]
     w.tm_out = [96, 96]

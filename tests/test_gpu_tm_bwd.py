@@ -137,7 +137,7 @@ def test_tiny_linear_relu_f32():
 
 
 def test_linear_bf16_and_f16_ragged():
-    # towers of unequal width, batch 777 (not a multiple of 8: padded transposed operands),
+    # towers of unequal width, batch 777 (a last, partial K step of the weight gradients),
     # output width 100 (padded gradient operand, partial column tiles)
     w = wl.scaled(wl.imbalanced(), max_rows=2000, batch=777, num_tables=26)
     w.tm_out = [100] * w.num_towers
@@ -193,9 +193,11 @@ def test_cross_three_layers_narrow_tower_f32_and_bf16(keep):
         check_tm_bwd(w, rtol, keep=keep)
 
 
-def test_kept_activations_wide_cross_tower_and_dot_towers():
-    # two 2048-wide towers (256 x 256 GEMM path), 2 layers; then dot towers, whose training forward
-    # keeps the dot terms it computes inside the projection kernel
+@pytest.mark.parametrize("big", ["1", "2"])
+def test_kept_activations_wide_cross_tower_and_dot_towers(big, monkeypatch):
+    # two 2048-wide towers, 2 layers; then dot towers, whose training forward keeps the dot terms it
+    # computes inside the projection kernel; on the tiling these sizes take and on 256 x 256 tiles
+    monkeypatch.setenv("DMT_TM_BIG", big)
     w = wl.scaled(wl.large(), max_rows=3000, batch=200)
     sel = [f for f in range(256) if w.table_to_tower[f] in (0, 1)]
     w.rows = [w.rows[f] for f in sel]; w.dims = [128] * 32
@@ -207,9 +209,9 @@ def test_kept_activations_wide_cross_tower_and_dot_towers():
 
 @pytest.mark.parametrize("dt,fuse", [("f32", "1"), ("f16", "1"), ("bf16", "0")])
 def test_kept_dot_terms_on_every_dot_path(dt, fuse, monkeypatch):
-    """The dot terms a training forward keeps, from the one-thread-per-term kernel (float32), the
-    fused projection kernel, and the separate Gram-tile kernel (fusion switched off); 5 features
-    per tower leave padding columns behind the 10 terms."""
+    """The dot terms a training forward keeps, from the float32 Gram-tile kernel, the fused projection
+    kernel, and the separate Gram-tile kernel (fusion switched off); 5 features per tower leave
+    padding columns behind the 10 terms."""
     monkeypatch.setenv("DMT_TM_FUSE", fuse)
     w = wl.scaled(wl.mid(), max_rows=3000, batch=257, num_tables=16)
     w.tm_dtype = dt
@@ -405,8 +407,7 @@ def test_random_small_configurations(seed):
 
 def _random_medium_config(seed):
     """Larger arbitrary towers: 2-16 features of 32-128 columns, batches and widths that are
-    sometimes whole multiples of the 256 x 256 tile (the contraction then loads its operand
-    tiles straight into LDS) and sometimes ragged."""
+    sometimes whole multiples of the 256 x 256 tile and sometimes ragged."""
     rng = np.random.default_rng(5000 + seed)
     kinds = [wl.TM_LINEAR_RELU, wl.TM_DOT_LINEAR, wl.TM_CROSS_LINEAR, wl.TM_DLRM, wl.TM_CROSS_LOWRANK_LINEAR]
     kind = kinds[seed % len(kinds)]
@@ -431,8 +432,8 @@ def _random_medium_config(seed):
 
 @pytest.mark.parametrize("seed", range(20))
 def test_random_medium_configurations(seed):
-    """Forward and backward of arbitrary towers wide and long enough for the 256 x 256 kernel,
-    the in-kernel dot terms, split-K weight gradients and the straight-to-LDS operand loads."""
+    """Forward and backward of arbitrary towers of several tiles each way: in-kernel and separate dot
+    terms, split-K weight gradients, on the tiling the sizes choose."""
     w = _random_medium_config(seed)
     dw = DeviceWorkload(w)
     tm = TowerModules(dw)
@@ -449,7 +450,7 @@ def test_random_medium_configurations(seed):
     check_tm_bwd(w, rtol=ftol, keep=bool(seed & 1))
 
 
-@pytest.mark.parametrize("switch", ["DMT_TM_BIG=0", "DMT_TM_FUSE=0", "DMT_TMB_KSPLIT=3", "DMT_TM_DIRECT=0"])
+@pytest.mark.parametrize("switch", ["DMT_TM_BIG=0", "DMT_TM_FUSE=0", "DMT_TMB_KSPLIT=3", "DMT_TM_BIG=3"])
 @pytest.mark.parametrize("seed", range(10))
 def test_random_medium_configurations_on_the_other_kernel_choices(seed, switch, monkeypatch):
     """The same towers with one of the plan's kernel choices turned the other way."""
