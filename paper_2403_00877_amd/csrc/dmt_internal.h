@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <vector>
 
 #include "dmt.h"
@@ -35,6 +36,16 @@ static inline size_t dmt_guard_size(Body body) {
     return 0;
   }
 }
+
+// What has to be done once per GPU of the process (kernel attributes belong to a device).  Two threads may
+// both be told to do it.
+struct DmtPerDevice {
+  std::atomic<uint64_t> done{0};
+  bool needed(int dev) const { return dev < 0 || dev >= 64 || !(done.load(std::memory_order_acquire) >> dev & 1); }
+  void set(int dev) {
+    if (dev >= 0 && dev < 64) done.fetch_or(1ULL << dev, std::memory_order_release);
+  }
+};
 
 // Per-table record the kernels read (device copy lives in the plan).
 struct DmtTableMeta {

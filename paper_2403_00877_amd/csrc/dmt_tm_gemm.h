@@ -1045,9 +1045,12 @@ template <int DT, int TILE, int ALAY, int WLAY, bool DOTS, bool KEEPZ>
 void launch_tiles(const TmLaunch& L, int64_t blocks, hipStream_t s) {
   constexpr int bytes = TmTile<TILE>::kLdsBytes;
   auto kernel = tm_gemm<DT, TILE, ALAY, WLAY, DOTS, KEEPZ>;
-  static const hipError_t configured =
-      hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  (void)configured;
+  static DmtPerDevice configured;
+  int dev = -1;
+  (void)hipGetDevice(&dev);
+  if (configured.needed(dev) &&
+      hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess)
+    configured.set(dev);
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TmTile<TILE>::kThreads), bytes, s, L);
 }
 

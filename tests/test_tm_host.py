@@ -14,7 +14,9 @@ def lib(tmp_path_factory):
     src, so = str(tmp / "tm_host.hip"), str(tmp / "libtm_host.so")
     with open(src, "w") as f:
         f.write('#include "dmt_tm_f32.h"\n'
-                'extern "C" int first_step(int steps, int part, int log2_ks) { return f32_first_step(steps, part, log2_ks); }\n')
+                'extern "C" int first_step(int steps, int part, int log2_ks) { return f32_first_step(steps, part, log2_ks); }\n'
+                'static DmtPerDevice once;\n'
+                'extern "C" int needed(int dev) { const bool n = once.needed(dev); once.set(dev); return n; }\n')
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + hip_build.FLAGS + ["-O0", "--cuda-host-only", "-shared", "-o", so, src],
                    check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
     return ctypes.CDLL(so)
@@ -28,3 +30,8 @@ def test_waves_share_all_steps_of_a_float32_tile(lib, steps, log2_ks):
     first = [lib.first_step(steps, q, log2_ks) for q in range(parts + 1)]
     assert first == [steps * q // parts for q in range(parts + 1)]
     assert first[0] == 0 and first[-1] == steps
+
+
+def test_kernel_attributes_are_set_on_every_device(lib):
+    assert [lib.needed(d) for d in (0, 0, 1, 1, 0, 7, 63, 7, 63, 1)] == [1, 0, 1, 0, 0, 1, 1, 0, 0, 0]
+    assert [lib.needed(d) for d in (-1, -1, 64, 64)] == [1, 1, 1, 1]        # unknown: every time
