@@ -77,6 +77,11 @@ struct TmGroup {
 };
 
 __host__ __device__ inline int tm_slices(const TmGroup& g) { return g.ksplit > 1 ? g.ksplit : 1; }
+// The first k behind the slice that starts at kofs < K1.  (kofs + klen may lie up to a K step per slice past
+// K1, which itself may be next to 2^31.)
+__host__ __device__ inline int tm_slice_end(int K1, int kofs, int klen) {
+  return klen < K1 - kofs ? kofs + klen : K1;
+}
 
 struct TmLaunch {
   int32_t ngroups;
@@ -301,7 +306,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
   const int slice = tmv / tiles_m, tm = tmv - slice * tiles_m;
   const int m0 = tm * TILE, n0 = tn * TILE;
   const int M = G.M, N = G.N, K0 = G.K0;
-  const int kofs = G.ksplit > 1 ? slice * G.klen : 0, kend = G.ksplit > 1 ? min(G.K1, kofs + G.klen) : G.K1;
+  const int kofs = G.ksplit > 1 ? slice * G.klen : 0, kend = G.ksplit > 1 ? tm_slice_end(G.K1, kofs, G.klen) : G.K1;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / T::WN, wn = wave % T::WN;

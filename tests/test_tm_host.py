@@ -15,6 +15,7 @@ def lib(tmp_path_factory):
     with open(src, "w") as f:
         f.write('#include "dmt_tm_f32.h"\n'
                 'extern "C" int first_step(int steps, int part, int log2_ks) { return f32_first_step(steps, part, log2_ks); }\n'
+                'extern "C" int slice_end(int K1, int kofs, int klen) { return tm_slice_end(K1, kofs, klen); }\n'
                 'static DmtPerDevice once;\n'
                 'extern "C" int needed(int dev) { const bool n = once.needed(dev); once.set(dev); return n; }\n')
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + hip_build.FLAGS + ["-O0", "--cuda-host-only", "-shared", "-o", so, src],
@@ -30,6 +31,18 @@ def test_waves_share_all_steps_of_a_float32_tile(lib, steps, log2_ks):
     first = [lib.first_step(steps, q, log2_ks) for q in range(parts + 1)]
     assert first == [steps * q // parts for q in range(parts + 1)]
     assert first[0] == 0 and first[-1] == steps
+
+
+@pytest.mark.parametrize("K", [1, 64, 1000, 8192, 2 ** 30 + 5, 2 ** 31 - 129, 2 ** 31 - 1])
+@pytest.mark.parametrize("slices", [2, 3, 16])
+def test_slices_cover_all_rows_of_a_16_bit_weight_gradient(lib, K, slices):
+    klen = -(-(-(-K // slices)) // 64) * 64
+    at, ends = 0, []
+    while at < K:
+        ends.append(lib.slice_end(K, at, klen))
+        assert ends[-1] == min(K, at + klen)
+        at += klen
+    assert ends[-1] == K and len(ends) <= slices
 
 
 def test_kernel_attributes_are_set_on_every_device(lib):
