@@ -158,6 +158,10 @@ __device__ __forceinline__ uint4 gload(const uint4* p) {
   const dmt_u32x4 v = *(const DMT_GLOBAL dmt_u32x4*)p;
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+__device__ __forceinline__ void gstore(uint4 v, uint4* p) {
+  dmt_u32x4 t = {v.x, v.y, v.z, v.w};
+  *(DMT_GLOBAL dmt_u32x4*)p = t;
+}
 __device__ __forceinline__ uint2 gload(const uint2* p) {
   const dmt_u32x2 v = *(const DMT_GLOBAL dmt_u32x2*)p;
   return make_uint2(v.x, v.y);

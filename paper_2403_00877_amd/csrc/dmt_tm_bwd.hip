@@ -381,7 +381,7 @@ dmt_status plan_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, in
         w.dxn = take((size_t)B * wt * 4);
         w.du[0] = take((size_t)B * wt * eb);
         w.du[1] = take((size_t)B * wt * eb);
-        w.dbc = take((size_t)((B + 127) / 128) * wt * 4);
+        w.dbc = take((size_t)((B + 63) / 64) * wt * 4);
         if (low) {
           w.dtf = take((size_t)B * r * 4);
           w.dtq = take((size_t)B * r * eb);
@@ -616,7 +616,7 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
     g.DU = wsp + w.du[(l - 1) & 1];
     g.DBP = (float*)(wsp + w.dbc);
   };
-  const int64_t cross_parts = (B + 127) / 128;
+  const int64_t cross_parts = (B + 63) / 64;
 
   // ---- projections: gradient operands, then both contractions for all towers
   std::vector<TmGroup> dgrad, dgrad2, wgrad, wgrad2;

@@ -1,7 +1,7 @@
 // Grouped contractions of the Tower Module, shared by its forward and backward:
 //   C = epilogue(A . W^T [+ b]), either operand contiguous along the reduction dimension or along
 // its own, one launch for all towers of a stage (block id -> tower, tile).
-// 16-bit types run on MFMA (v_mfma_f32_32x32x16, float32 accumulate); float32 has its own kernel
+// 16-bit types run on MFMA (v_mfma_f32_16x16x32, float32 accumulate); float32 has its own kernel
 // (dmt_tm_f32.h).  Also the pairwise-dot (Gram tile) kernels and the projection-weight
 // repack of the dot-product form.  Everything lives in an unnamed namespace: each
 // translation unit that includes this header gets its own copy.
@@ -16,6 +16,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kBlock = 256;              // threads of the small kernels' blocks
@@ -62,14 +63,14 @@ struct TmGroup {
   // C + s * cstride floats, and the caller adds the slices up in a fixed order.
   int32_t ksplit, klen;
   int64_t cstride;
-  // EPI_CROSS_GRAD: [M][ldc] float32 / 16-bit tensors, and the column sums of du, one row per 128 rows
+  // EPI_CROSS_GRAD: [M][ldc] float32 / 16-bit tensors, and the column sums of du, one row per 64 rows
   // of C
   const float* GN;        // g_{l+1} or NULL
   const void* UL;         // u_l (with GN)
   const void* U0;         // u_0 or NULL
   float* ACC;
   void* DU;
-  float* DBP;             // [(M + 127) / 128][N]
+  float* DBP;             // [(M + 63) / 64][N]
   int32_t acc_first;      // ACC holds nothing yet
   // Two-level output rows: with rdiv > 0 row m of C starts at (m / rdiv) * ldc + (m % rdiv) * ldc2,
   // i.e. rdiv consecutive rows of the contraction share one row of the output tensor.
@@ -87,6 +88,8 @@ struct TmLaunch {
   int32_t ngroups;
   int32_t super;                       // tiles of a super-tile (dealt to one XCD), at most
   int32_t cap;                         // block slots of a super-tile
+  int32_t stream;                      // more output than the caches keep
+  int32_t stagger;                     // how far apart the XCDs start, in sleeps of 4096 cycles
   int32_t tile_start[kMaxGroups + 1];  // first super-tile of each group
   TmGroup g[kMaxGroups];
 };
@@ -98,6 +101,16 @@ __device__ __forceinline__ floatx16 mfma32(uint4 a, uint4 b, floatx16 c) {
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   else
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a),
+                                                  __builtin_bit_cast(halfx8, b), c, 0, 0, 0);
+}
+
+template <int DT>
+__device__ __forceinline__ floatx4 mfma16(uint4 a, uint4 b, floatx4 c) {
+  if constexpr (DT == DMT_BF16)
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(halfx8, a),
                                                   __builtin_bit_cast(halfx8, b), c, 0, 0, 0);
 }
 
@@ -127,27 +140,37 @@ __device__ __forceinline__ float mul_rounded(float a, float b) {
 // CU: for launches that would leave CUs without a 256 x 256 tile, and for outputs of at most 128
 // rows or columns.
 //
+// 16 x 16 x 32 instructions rather than 32 x 32 x 16: the chip is power-limited on real data, and they
+// take less of it for the same product (registers only, normal random operands: 1990 against 1730
+// TFLOP/s; on zeros both reach 2430).  Within a row of them the W fragments go back and forth, so
+// that neighbouring instructions share an operand (1990 against 1952).
+//
 // Operand tiles go from global memory straight into LDS (buffer_load_dwordx4 ... lds: a wave's 64
 // lanes fill 1 KB of consecutive LDS, 16 bytes a lane), two stages deep: tile kt + 2 is requested
-// into the stage tile kt is being read from, behind the barrier inside step kt, and every wave waits
-// for its own requests before the next step's barrier.  The buffer's bounds stand in for all edges:
-// rows past the operand's last, and chunks past the last k (their lanes ask for an offset that is
-// never in bounds), arrive as zeros.  (The requests are inline assembly: told about them, the
-// compiler makes every LDS read of the current tile wait for the next tile's requests, since it
-// cannot tell the two stages apart.)
+// into the stage tile kt is being read from, behind the barrier inside step kt, one request per row of
+// MFMAs (in one burst they fill the memory pipe's queue, and the matrix instructions behind them
+// wait), and every wave waits for its own requests before the next step's barrier.  The buffer's
+// bounds stand in for all edges: rows past the operand's last, and chunks past the last k (their lanes
+// ask for an offset that is never in bounds), arrive as zeros.  (The requests are inline assembly:
+// told about them, the compiler makes every LDS read of the current tile wait for the next tile's
+// requests, since it cannot tell the two stages apart.)
+//
+// The K steps of all the tiles a block works through are one stream: behind a tile's last step come the
+// requests for the next tile's first, so that a tile starts with its operands in LDS; the epilogue in
+// between has LDS of its own.
 //
 // OP_ROW tile: 128-byte rows (64 k) without padding; column chunk c (8 elements) of row r sits in
 // slot c ^ (r / 2) % 8.  A fragment read (ds_read_b128, 16 lanes a cycle from 64 banks) touches 16
 // rows: 2 r and 2 r + 1 lie in the two halves of one 256-byte bank row and share a slot, the eight
 // pairs differ in it, so it is conflict-free.
 // OP_COL tile: 64 rows of BM (BN) elements, one per k; chunk c of row k sits in slot
-// c ^ 4 (k % 4).  Fragments come through ds_read_b64_tr_b16, which transposes 4 x 4 blocks among 16
-// lanes: lane p of a group names row k + p / 4, elements 4 (p % 4) ..., and receives column p of the
-// four rows.  The four rows of a group lie on the same banks but for the slot, which spreads them.
+// c ^ 4 (k % 4) ^ 2 (k / 8 % 2).  Fragments come through ds_read_b64_tr_b16, which transposes 4 x 4
+// blocks among 16 lanes: lane p of a group names row k + p / 4, elements 4 (p % 4) ..., and receives
+// column p of the four rows.  The four rows of a group and those of the next (k + 8) lie on the same
+// banks but for the slot, which spreads them.
 //
 // The MFMAs take the W fragment as their first operand, so the accumulators hold the tile
-// transposed: a lane owns one row and four consecutive columns per register quad, which the
-// epilogue parks in LDS with 16-byte stores.
+// transposed: a lane owns one row and four consecutive columns per tile of 16.
 
 // TAG only marks the including source file in the kernel's name, so that a profile tells the
 // forward's launches from the backward's.
@@ -159,11 +182,19 @@ constexpr uint32_t kOobOffset = 0x80000000u;      // beyond any buffer (256 rows
 
 // Buffer descriptor of `bytes` bytes from p (uniform).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tm_buffer(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
+  // (all of it through scalar registers: the requests' assembly takes no others)
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)p), hi = __builtin_amdgcn_readfirstlane((uint32_t)((uintptr_t)p >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)((uintptr_t)hi << 32 | lo), 0, (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 // 64 lanes' 16-byte pieces of a buffer to 1 KB of LDS at byte address lds.
 __device__ __forceinline__ void tm_request(uint32_t lds, __amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(off), "s"(rsrc) : "memory");
+}
+
+// 64 lanes' 4-byte pieces of a buffer to 256 bytes of LDS.
+__device__ __forceinline__ void tm_touch(uint32_t lds, __amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
                :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(off), "s"(rsrc) : "memory");
 }
 
@@ -172,7 +203,7 @@ template <int LAY, int R, int NW>
 struct TmStage {
   static constexpr int kInstr = R * BK * 2 / 1024 / NW;    // requests per wave and K step
   static_assert(NW % 2 == 0 && kInstr * NW * 1024 == R * BK * 2, "");
-  uint32_t off[kInstr];                            // this lane's byte offsets from the tile's first element
+  uint32_t off, step;                              // this lane's byte offset from the tile's first element; a request's from the last
   int chunk;                                       // OP_ROW: this lane's column chunk (the same in every request)
   const uint16_t* base;                            // the tile's first element at the segment's first k
   int ld, rows;                                    // row pitch; operand rows in the tile
@@ -184,16 +215,16 @@ struct TmStage {
     rows = min(rows_all - row0, R);
     base = (const uint16_t*)p + (LAY == OP_ROW ? (int64_t)row0 * ld + k0 : (int64_t)k0 * ld + row0);
     chunk = LAY == OP_ROW ? (lane & 7) ^ (((wave & 1) << 2) | (lane >> 4)) : 0;
-#pragma clang loop unroll(full)
-    for (int j = 0; j < kInstr; ++j) {
-      if constexpr (LAY == OP_ROW) {
-        off[j] = ((uint32_t)((j * NW + wave) * 8 + (lane >> 3)) * (uint32_t)ld + chunk * 8) * 2u;
-      } else {
-        constexpr int kRowLanes = R / 8;           // 16-byte slots of one k row
-        const int k = (j * NW + wave) * (64 / kRowLanes) + lane / kRowLanes;
-        const int c = (lane % kRowLanes) ^ ((k & 3) << 2);
-        off[j] = c * 8 < rows ? ((uint32_t)k * (uint32_t)ld + c * 8) * 2u : kOobOffset;
-      }
+    if constexpr (LAY == OP_ROW) {
+      off = ((uint32_t)(wave * 8 + (lane >> 3)) * (uint32_t)ld + chunk * 8) * 2u;
+      step = NW * 8 * 2u * (uint32_t)ld;
+    } else {
+      constexpr int kRowLanes = R / 8;             // 16-byte slots of one k row
+      static_assert(NW * (64 / kRowLanes) % 16 == 0, "requests 16 k apart share a slot");
+      const int k = wave * (64 / kRowLanes) + lane / kRowLanes;
+      const int c = (lane % kRowLanes) ^ ((k & 3) << 2) ^ ((k >> 2) & 2);
+      off = c * 8 < rows ? ((uint32_t)k * (uint32_t)ld + c * 8) * 2u : kOobOffset;
+      step = NW * (64 / kRowLanes) * 2u * (uint32_t)ld;
     }
   }
   // The segment's columns k .. k + 63 (from its first; kn are left), for request().  The buffer ends with
@@ -205,9 +236,10 @@ struct TmStage {
     // its pitch has room for.  OP_COL: to the end of the last element's 4 bytes and no further, since
     // the pitch may be less than whole chunks: with rows = ld = 12 the next k's first elements would
     // count as in bounds, and what lies past the tensor would meet the other operand's zeros.)
-    kn = min(kn, BK);
-    return LAY == OP_ROW ? tm_buffer(base + k, ((uint32_t)(rows - 1) * (uint32_t)ld + ((kn + 7) & ~7)) * 2u)
-                         : tm_buffer(base + (int64_t)k * ld, ((uint32_t)(kn - 1) * (uint32_t)ld + ((rows + 1) & ~1)) * 2u);
+    const uint32_t left = (uint32_t)min(kn, BK);
+    const uint32_t bytes = (LAY == OP_ROW ? (uint32_t)(rows - 1) * (uint32_t)ld + ((left + 7) & ~7u)
+                                          : (left - 1) * (uint32_t)ld + ((uint32_t)(rows + 1) & ~1u)) * 2u;
+    return tm_buffer(base + (LAY == OP_ROW ? (int64_t)k : (int64_t)k * ld), kn > 0 ? bytes : 0u);
   }
   // OP_ROW: zeros in columns k .. (k even) of the pieces of a landed tile that also hold columns before k
   // (each lane its own pieces).
@@ -220,53 +252,65 @@ struct TmStage {
       p[j * NW * 64] = make_uint4(v.x, (k & 7) > 2 ? v.y : 0u, (k & 7) > 4 ? v.z : 0u, 0u);
     }
   }
-  // This wave's j-th request: of a whole step, or with kn columns left in the segment.
-  __device__ __forceinline__ void request(uint32_t lds, __amdgpu_buffer_rsrc_t rsrc, int j, int wave) const {
-    tm_request(lds + (j * NW + wave) * 1024, rsrc, off[j]);
-  }
-  __device__ __forceinline__ void request_tail(uint32_t lds, __amdgpu_buffer_rsrc_t rsrc, int j, int wave, int kn) const {
-    tm_request(lds + (j * NW + wave) * 1024, rsrc, LAY == OP_COL || chunk * 8 < kn ? off[j] : kOobOffset);
+  // This wave's j-th request of a step with kn columns left in the segment.
+  __device__ __forceinline__ void request(uint32_t lds, __amdgpu_buffer_rsrc_t rsrc, int j, int wave, int kn) const {
+    tm_request(lds + (j * NW + wave) * 1024, rsrc, LAY == OP_COL || chunk * 8 < kn ? off + j * step : kOobOffset);
   }
 };
 
-// One operand's fragment reads: NF fragments of 32 rows from row `first` (a multiple of 32 NF) of a
-// staged tile of R rows.
-template <int LAY, int R, int NF>
+// One operand's fragment reads: fragment i is rows 16 i ... (from row `first`, a multiple of 64) x 32 k of a
+// staged tile of R rows; lane l gets 8 consecutive k (8 (l / 16) ...) of its row l % 16.
+template <int LAY, int R>
 struct TmFrag {
-  static constexpr int kReads = LAY == OP_ROW ? NF : 2 * NF;   // LDS instructions per K slice
-  int at[LAY == OP_ROW ? BK / 16 : NF];
+  int at[LAY == OP_ROW ? BK / 32 : 1];
   __device__ __forceinline__ void init(int first, int lane) {
     if constexpr (LAY == OP_ROW) {
 #pragma clang loop unroll(full)
-      for (int kk = 0; kk < BK / 16; ++kk)
-        at[kk] = (first + (lane & 31)) * BK + ((kk * 2 + (lane >> 5)) ^ ((lane >> 1) & 7)) * 8;
+      for (int kk = 0; kk < BK / 32; ++kk)
+        at[kk] = (first + (lane & 15)) * BK + ((kk * 4 + (lane >> 4)) ^ ((lane >> 1) & 7)) * 8;
     } else {
-      const int p = lane & 15;
-#pragma clang loop unroll(full)
-      for (int i = 0; i < NF; ++i) {
-        const int c = (((first / 32 + i) ^ (p >> 2)) << 2) + ((lane >> 4) & 1) * 2 + ((p & 3) >> 1);
-        at[i] = ((lane >> 5) * 8 + (p >> 2)) * R + c * 8 + (p & 1) * 4;
-      }
+      const int p = lane & 15, k = (lane >> 4) * 8 + (p >> 2);
+      at[0] = k * R + (((first >> 3) + ((p & 3) >> 1)) ^ ((k & 3) << 2) ^ ((k >> 2) & 2)) * 8 + (p & 1) * 4;
     }
   }
-  __device__ __forceinline__ void read(uint4 (&f)[NF], const uint16_t* tile, int kk) const {
+  __device__ __forceinline__ uint4 read(const uint16_t* tile, int kk, int i) const {
     if constexpr (LAY == OP_ROW) {
-#pragma clang loop unroll(full)
-      for (int i = 0; i < NF; ++i) f[i] = *(const uint4*)(tile + at[kk] + i * 32 * BK);
+      return *(const uint4*)(tile + at[kk] + i * 16 * BK);
     } else {
       typedef short short4v __attribute__((ext_vector_type(4)));
       typedef __attribute__((address_space(3))) short4v lds_short4;
-#pragma clang loop unroll(full)
-      for (int i = 0; i < NF; ++i) {
-        const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                                                       (lds_short4*)(tile + at[i] + kk * 16 * R)));
-        const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                                                       (lds_short4*)(tile + at[i] + (kk * 16 + 4) * R)));
-        f[i] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-      }
+      const uint16_t* q = tile + (at[0] ^ (i * 16)) + kk * 32 * R;
+      const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)q));
+      const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(q + 4 * R)));
+      return make_uint4(lo.x, lo.y, hi.x, hi.y);
     }
   }
 };
+
+// Whether a group's outputs, and what its epilogue reads, move in whole pieces of 16 bytes.  (EPI_CROSS_GRAD:
+// N and ldc are a tower's width, the tensors the library's own or blocks of grad_pooled.)
+__device__ __forceinline__ bool tm_whole(const TmGroup& g) {
+  // (no short circuits: the fields are read together)
+  const uint64_t c = (uint64_t)g.C, x = (uint64_t)g.X0 | (uint64_t)g.XL | (uint64_t)g.U;
+  const bool f32 = ((g.N | g.ldc) & 3) == 0 & g.rdiv == 0 & (c & 15) == 0 & (g.ksplit <= 1 | (g.cstride & 3) == 0);
+  const bool b16 = ((g.N | g.ldc | g.ldc2) & 7) == 0 & ((c | (uint64_t)g.bias) & 15) == 0;
+  const bool cross = ((g.ldx | g.ldxl) & 7) == 0 & (x & 15) == 0;
+  return g.epi == EPI_CROSS_GRAD | (g.epi >= EPI_F32 ? f32 : b16 & (g.epi != EPI_CROSS | cross));
+}
+
+// Orders a wave's LDS accesses: lanes read what other lanes wrote.  (A wave's LDS instructions execute in
+// order; to the compiler its lanes are unrelated threads.)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48; every lane gets it.
+__device__ __forceinline__ float quarters_sum(float v) {
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
+}
 
 // TILE: 256 or 128.  DOTS: the operand's first K0 (<= 64) columns are the tower's pairwise dot
 // terms, which the block computes itself (Gram tiles, as in tm_dots_mfma) straight into the first
@@ -274,110 +318,156 @@ struct TmFrag {
 // them).
 template <int TILE> struct TmTile {
   static constexpr int WM = 2, WN = TILE == 256 ? 4 : 2, kWaves = WM * WN, kThreads = kWaves * 64;
-  static constexpr int MT = TILE / WM / 32, NT = TILE / WN / 32;     // MFMA tiles of a wave
+  static constexpr int MT = TILE / WM / 16, NT = TILE / WN / 16;     // MFMA tiles of a wave
   static constexpr int kStageBytes = 2 * TILE * BK * 2;              // A then W
-  static constexpr int kHalf = TILE / WM;                            // rows the epilogue parks at a time
-  static constexpr int kParkStride = TILE + 4;   // floats; rows 4 banks apart: 16 lanes' float4 stores spread over all 64
-  static constexpr int kLdsBytes = 2 * kStageBytes > kHalf * kParkStride * 4 ? 2 * kStageBytes : kHalf * kParkStride * 4;
+  static constexpr int kHalf = TILE / WM;                            // rows a wave covers
+  static constexpr int kLdsBytes = 2 * kStageBytes + kWaves * 4096;  // two stages, 4 KB a wave for the epilogue
+  static_assert(NT == 4, "the epilogue takes 64 columns a wave");
 };
 
-template <int DT, int TILE, int ALAY, int WLAY, bool DOTS = false, bool KEEPZ = false, int TAG = DMT_TM_TAG>
+constexpr int min_int(int a, int b) { return a < b ? a : b; }
+
+// A block's work: one tile of one group (of one slice of its K).
+struct TmWork {
+  int gi, m0, n0, slice;
+};
+
+// What a launch's epilogues are: KIND_READS those that read as much as they write (EPI_CROSS,
+// EPI_CROSS_GRAD), KIND_ADD EPI_F32_ADD, KIND_PLAIN all others.  (Kernels of their own: together they need
+// more registers, and what an epilogue reads ahead behind a run-time condition is slow: data gradients of
+// 16 towers of 2048 columns, batch 8192, added to a tensor 1303 us, in a kernel of their own 1090.)
+enum { KIND_PLAIN = 0, KIND_READS = 1, KIND_ADD = 2 };
+inline int epi_kind(int epi) {
+  return epi == EPI_CROSS || epi == EPI_CROSS_GRAD ? KIND_READS : epi == EPI_F32_ADD ? KIND_ADD : KIND_PLAIN;
+}
+
+template <int DT, int TILE, int ALAY, int WLAY, int KIND = KIND_PLAIN, bool DOTS = false, bool KEEPZ = false, int TAG = DMT_TM_TAG>
 __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void tm_gemm(const TmLaunch L) {
   using T = TmTile<TILE>;
-  static_assert(!DOTS || (ALAY == OP_ROW && WLAY == OP_ROW), "");
+  constexpr bool kForward = ALAY == OP_ROW && WLAY == OP_ROW;        // 16-bit outputs and x0; the others are gradients
+  static_assert(!DOTS || kForward, "");
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   // XCD-aware rasterisation.  Consecutive block ids go to different XCDs, so block b belongs
   // to XCD b % 8 and is that XCD's (b / 8)-th block.  The launch's tiles are cut into
   // super-tiles of up to L.super tiles (a few tile rows x all tile columns of one group) that
   // are dealt to the XCDs in turn: the blocks resident on an XCD then share their A rows
   // and W columns in that XCD's L2 instead of every XCD pulling every A tile over the fabric.
-  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-  const int gs = (idx / L.cap) * 8 + xcd, within = idx % L.cap;
-  if (gs >= L.tile_start[L.ngroups]) return;
-  int gi = 0;
-  while (gi + 1 < L.ngroups && gs >= L.tile_start[gi + 1]) ++gi;
-  const TmGroup& G = L.g[gi];
-  const int tiles_n = (G.N + TILE - 1) / TILE, tiles_m = (G.M + TILE - 1) / TILE;
-  const int sm = tiles_n >= L.super ? 1 : L.super / tiles_n;     // tile rows per super-tile
-  if (within >= sm * tiles_n) return;
-  // a split K multiplies the tile rows: virtual row tmv = slice * tiles_m + tm
-  const int tmv = (gs - L.tile_start[gi]) * sm + within / tiles_n, tn = within % tiles_n;
-  if (tmv >= tiles_m * tm_slices(G)) return;
-  const int slice = tmv / tiles_m, tm = tmv - slice * tiles_m;
-  const int m0 = tm * TILE, n0 = tn * TILE;
-  const int M = G.M, N = G.N, K0 = G.K0;
-  const int kofs = G.ksplit > 1 ? slice * G.klen : 0, kend = G.ksplit > 1 ? tm_slice_end(G.K1, kofs, G.klen) : G.K1;
+  // A grid smaller than the launch's slots works through them a grid at a time, in the same order.
+  int slot = blockIdx.x >> 3;
+  auto locate = [&](TmWork& w) __attribute__((always_inline)) {      // this block's next tile, if there is one
+    for (;; slot += gridDim.x >> 3) {
+      const int gs = (slot / L.cap) * 8 + (blockIdx.x & 7), within = slot % L.cap;
+      if (gs >= L.tile_start[L.ngroups]) return false;
+      int gi = 0;
+      while (gi + 1 < L.ngroups && gs >= L.tile_start[gi + 1]) ++gi;
+      const TmGroup& G = L.g[gi];
+      const int tiles_n = (G.N + TILE - 1) / TILE, tiles_m = (G.M + TILE - 1) / TILE;
+      const int sm = tiles_n >= L.super ? 1 : L.super / tiles_n;     // tile rows per super-tile
+      // a split K multiplies the tile rows: virtual row tmv = slice * tiles_m + tm
+      const int tmv = (gs - L.tile_start[gi]) * sm + within / tiles_n;
+      if (within >= sm * tiles_n || tmv >= tiles_m * tm_slices(G)) continue;
+      w.gi = __builtin_amdgcn_readfirstlane(gi);
+      w.slice = __builtin_amdgcn_readfirstlane(tmv / tiles_m);
+      w.m0 = __builtin_amdgcn_readfirstlane(tmv % tiles_m * TILE);
+      w.n0 = __builtin_amdgcn_readfirstlane(within % tiles_n * TILE);
+      slot += gridDim.x >> 3;
+      return true;
+    }
+  };
+  // Blocks that work through several tiles of cross layers start a little apart, XCD by XCD: their epilogues,
+  // bound by memory, then meet other XCDs' matrix work instead of one another's.  (Cross layer of 2048
+  // columns with u kept, 16 towers, batch 8192: 1155 -> 1131 us, its gradient 1658 -> 1598; plain
+  // epilogues gain nothing.)
+  if constexpr (KIND != KIND_PLAIN)
+    for (int q = (blockIdx.x & 7) * L.stagger; q > 0; --q) __builtin_amdgcn_s_sleep(64);
+  TmWork work, ahead;                              // the tile being computed, the one being requested
+  if (!locate(ahead)) return;
+  work = ahead;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / T::WN, wn = wave % T::WN;
-  floatx16 acc[T::MT][T::NT];
-#pragma clang loop unroll(full)
-  for (int i = 0; i < T::MT; ++i)
-#pragma clang loop unroll(full)
-    for (int j = 0; j < T::NT; ++j)
-#pragma clang loop unroll(full)
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  // ---- K loop
+  // ---- the requests
+  TmStage<ALAY, TILE, T::kWaves> sa;
+  TmStage<WLAY, TILE, T::kWaves> sw;
+  constexpr int kReqs = 2 * TmStage<ALAY, TILE, T::kWaves>::kInstr;  // of a wave and K step: A and W in turn
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint16_t*)lds;
+  __amdgpu_buffer_rsrc_t ba, bw;
+  uint32_t to = 0;
+  int k = 0, left = 0, kn = 0, stage = 0;          // of the next step: first k, columns left; of this one; its stage
+  bool flat = false;                               // the second segment (pooled values) is being requested
+  auto begin = [&](bool second) __attribute__((always_inline)) {
+    const TmGroup& G = L.g[ahead.gi];
+    flat = second;
+    k = 0;
+    if (second) {
+      const int kofs = G.ksplit > 1 ? ahead.slice * G.klen : 0;
+      left = (G.ksplit > 1 ? tm_slice_end(G.K1, kofs, G.klen) : G.K1) - kofs;
+      sa.init(G.A1, G.lda1, ahead.m0, G.M, kofs, wave, lane);
+      sw.init(G.W1, G.ldw1, ahead.n0, G.N, kofs, wave, lane);
+    } else {                                       // (in-kernel dot terms: A comes from the block itself)
+      left = G.K0;
+      if constexpr (!DOTS) sa.init(G.A0, G.lda0, ahead.m0, G.M, 0, wave, lane);
+      sw.init(G.W0, G.ldw0, ahead.n0, G.N, 0, wave, lane);
+    }
+  };
+  // The next K step of the stream.  (The launch makes sure that a block with several tiles is never more
+  // than one of them ahead: their K is two steps or more.)
+  auto aim = [&]() __attribute__((always_inline)) {
+    if (left <= 0) {
+      if (!flat) begin(true);
+      else if (locate(ahead)) begin(L.g[ahead.gi].K0 == 0);
+    }
+    bw = sw.buffer(k, left);
+    ba = DOTS && !flat ? bw : sa.buffer(k, left);
+    kn = left;
+    to = lds0 + stage * T::kStageBytes;
+    stage ^= 1;
+    k += BK;
+    left -= BK;
+  };
+  auto request = [&](int q) __attribute__((always_inline)) {
+    if (q % 2 == 0) sa.request(to, ba, q / 2, wave, kn);
+    else sw.request(to + TILE * BK * 2, bw, q / 2, wave, kn);
+  };
+
+  // ---- fragments: A's of a row of MFMAs are read three rows ahead, W's of a slice of 32 k a slice ahead
+  TmFrag<ALAY, TILE> ra;
+  TmFrag<WLAY, TILE> rw;
+  ra.init(wm * T::MT * 16, lane);
+  rw.init(wn * T::NT * 16, lane);
+  constexpr int kRows = BK / 32 * T::MT, kAhead = 3;                 // rows of MFMAs in a K step
+  // Requests per row, and how many the rows behind the barrier hold: all of them in 128 x 128 tiles, whose K
+  // steps are half as long and whose launches wait for memory (spread further, a projection of 512
+  // outputs on 8 towers, batch 3001, took 69.8 instead of 66.7 us).
+  constexpr int kPerRow = TILE == 256 ? 1 : 4, kEarly = min_int(kReqs, kAhead * kPerRow);
+  static_assert((kReqs - kEarly + kPerRow - 1) / kPerRow < kRows - kAhead - 2, "");
+  uint4 fa[4], fw[2][T::NT];
+
+  // what the K loop and the epilogue need of the tile being computed, read while requests are under way
+  int nk, kl;                                      // K steps; columns of the second segment
+  bool whole;
+  auto measure = [&]() __attribute__((always_inline)) {
+    const TmGroup& G = L.g[work.gi];
+    const int kofs = G.ksplit > 1 ? work.slice * G.klen : 0;
+    kl = (G.ksplit > 1 ? tm_slice_end(G.K1, kofs, G.klen) : G.K1) - kofs;
+    nk = (G.K0 + BK - 1) / BK + (kl + BK - 1) / BK;
+    whole = __builtin_amdgcn_readfirstlane(tm_whole(G));
+  };
+
+  begin(L.g[work.gi].K0 == 0);
+  aim();
+#pragma clang loop unroll(full)
+  for (int q = DOTS ? 1 : 0; q < kReqs; q += DOTS ? 2 : 1) request(q);
+  aim();
+  if (kn > 0)
+#pragma clang loop unroll(full)
+    for (int q = 0; q < kEarly; ++q) request(q);
+  measure();
   {
-    TmStage<ALAY, TILE, T::kWaves> sa;
-    TmStage<WLAY, TILE, T::kWaves> sw;
-    sa.init(G.A1, G.lda1, m0, M, kofs, wave, lane);
-    sw.init(G.W1, G.ldw1, n0, N, kofs, wave, lane);
-    const int nk0 = (K0 + BK - 1) / BK, nk = nk0 + (kend - kofs + BK - 1) / BK;
-    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint16_t*)lds;
-    auto request_tile = [&](int stage, int kt) __attribute__((always_inline)) {
-      const uint32_t la = lds0 + stage * T::kStageBytes, lw = la + TILE * BK * 2;
-      if (kt >= nk0) {
-        const int k = (kt - nk0) * BK, kn = kend - kofs - k;
-        const __amdgpu_buffer_rsrc_t ba = sa.buffer(k, kn), bw = sw.buffer(k, kn);
-        if (kn >= BK) {
-#pragma clang loop unroll(full)
-          for (int j = 0; j < sa.kInstr; ++j) {
-            sa.request(la, ba, j, wave);
-            sw.request(lw, bw, j, wave);
-          }
-        } else {                                   // the segment's last, partial step
-#pragma clang loop unroll(full)
-          for (int j = 0; j < sa.kInstr; ++j) {
-            sa.request_tail(la, ba, j, wave, kn);
-            sw.request_tail(lw, bw, j, wave, kn);
-          }
-        }
-      } else {                                     // (few steps: their offsets are not kept in registers)
-        const int k = kt * BK;
-        if constexpr (!DOTS) {
-          TmStage<ALAY, TILE, T::kWaves> sa0;      // segment 0 has pitches of its own
-          sa0.init(G.A0, G.lda0, m0, M, 0, wave, lane);
-          const __amdgpu_buffer_rsrc_t b0 = sa0.buffer(k, K0 - k);
-#pragma clang loop unroll(full)
-          for (int j = 0; j < sa0.kInstr; ++j) sa0.request_tail(la, b0, j, wave, K0 - k);
-        }
-        TmStage<WLAY, TILE, T::kWaves> sw0;
-        sw0.init(G.W0, G.ldw0, n0, N, 0, wave, lane);
-        const __amdgpu_buffer_rsrc_t b0 = sw0.buffer(k, K0 - k);
-#pragma clang loop unroll(full)
-        for (int j = 0; j < sw0.kInstr; ++j) sw0.request_tail(lw, b0, j, wave, K0 - k);
-      }
-    };
-    TmFrag<ALAY, TILE, T::MT> ra;
-    TmFrag<WLAY, TILE, T::NT> rw;
-    ra.init(wm * T::MT * 32, lane);
-    rw.init(wn * T::NT * 32, lane);
-    // Fragments are double-buffered in registers: the reads of K slice kk + 1 are issued before the
-    // MFMAs of slice kk, so LDS latency hides behind matrix work of the same wave.  The barrier of
-    // a K step sits in front of its last slice's MFMAs: behind it come the requests for tile
-    // kt + 2 (every wave has read the whole current stage by then) and the first reads of tile
-    // kt + 1, and the last slice's MFMAs cover both.
-    uint4 fa[2][T::MT], fw[2][T::NT];
-    auto read_frag = [&](int buf, int stage, int kk) __attribute__((always_inline)) {
-      const uint16_t* t = lds + stage * (T::kStageBytes / 2);
-      ra.read(fa[buf], t, kk);
-      rw.read(fw[buf], t + TILE * BK, kk);
-    };
-    request_tile(0, 0);
     if constexpr (DOTS) {
-      if (nk > 1) request_tile(1, 1);
+      const TmGroup& G = L.g[work.gi];
+      const int m0 = work.m0, M = G.M, K0 = G.K0;
       // pairwise dots of this block's samples into the first stage's A tile, zeros behind them: a
       // wave takes 32 / nf samples at a time, whose (sample, feature) rows are one Gram tile
 #pragma clang loop unroll(full)
@@ -420,7 +510,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
           for (int g = 0; g < kGroups; ++g)
 #pragma clang loop unroll(full)
             for (int u = 0; u < kPieces; ++u)       // (never past the tensor: what is not wanted reads its start)
-              a[g][u] = *(const uint4*)(on[g] && k + u * 16 + h8 < fd ? xp[g] + k + u * 16 : A);
+              a[g][u] = dmt::gload((const uint4*)(on[g] && k + u * 16 + h8 < fd ? xp[g] + k + u * 16 : A));
 #pragma clang loop unroll(full)
           for (int g = 0; g < kGroups; ++g)
 #pragma clang loop unroll(full)
@@ -454,282 +544,316 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
     if constexpr (DOTS) {
       // Weights that are read as they are: the pooled values' weights stand behind the terms' and
       // meet the zeros behind the terms.  They count as zeros (an infinite one would make NaN).
+      const TmGroup& G = L.g[work.gi];
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       const int np = G.nf * (G.nf - 1) / 2;
       if ((const uint16_t*)G.W0 + np == G.W1) sw.zero_from(lds + TILE * BK, np, wave, lane);
     } else {
-      __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): this wave's requests have landed
+      // vmcnt: this wave's requests of the first step have landed
+      if (kn > 0) __builtin_amdgcn_s_waitcnt(0x0f70 + kEarly);
+      else __builtin_amdgcn_s_waitcnt(0x0f70);
     }
     __syncthreads();
-    if (!DOTS && nk > 1) request_tile(1, 1);
-    read_frag(0, 0, 0);
-    for (int kt = 0; kt < nk; ++kt) {
-      const int cur = kt & 1;
-#pragma clang loop unroll(full)
-      for (int kk = 0; kk < BK / 16; ++kk) {
-        if (kk + 1 < BK / 16) {
-          read_frag((kk + 1) & 1, cur, kk + 1);
-        } else {
-          __builtin_amdgcn_s_waitcnt(0x0f70);
-          __syncthreads();
-          if (kt + 2 < nk) request_tile(cur, kt + 2);
-          if (kt + 1 < nk) read_frag(0, cur ^ 1, 0);
-        }
-#pragma clang loop unroll(full)
-        for (int i = 0; i < T::MT; ++i)
-#pragma clang loop unroll(full)
-          for (int j = 0; j < T::NT; ++j) acc[i][j] = mfma32<DT>(fw[kk & 1][j], fa[kk & 1][i], acc[i][j]);
-        // LDS reads and MFMAs alternately: left alone, the scheduler puts each read right in front
-        // of the MFMA that needs it, to save registers
-        if (kk + 1 < BK / 16) {
-          constexpr int kReads = TmFrag<ALAY, TILE, T::MT>::kReads + TmFrag<WLAY, TILE, T::NT>::kReads;
-          constexpr int kMfma = T::MT * T::NT, kPer = (kReads + kMfma - 1) / kMfma, kPairs = kReads / kPer;
-#pragma clang loop unroll(full)
-          for (int q = 0; q < kPairs; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x100, kPer, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          }
-          if (kMfma > kPairs) __builtin_amdgcn_sched_group_barrier(0x008, kMfma - kPairs, 0);
-        }
-      }
-    }
   }
+  const uint16_t* tile = lds;                      // the stage being read, and the other one
+  const uint16_t* next = lds + T::kStageBytes / 2;
 
-  // ---- epilogue through LDS, the rows of one wave row at a time: the waves that own them park their
-  // float32 accumulators (a lane holds four consecutive columns of one row per register quad: too
-  // narrow for global memory), then all threads walk them in 8-column pieces, so bias, x0, x_l
-  // and the output move as 16-byte accesses.
-  const int epi = G.epi;
-  float* park = (float*)lds;
-  auto park_half = [&]() __attribute__((always_inline)) {
+  for (;;) {
+    // (a tile's first fragments: the last step of the one before has read them too, but they would take
+    // registers from its epilogue)
 #pragma clang loop unroll(full)
-    for (int j = 0; j < T::NT; ++j)
+    for (int i = 0; i < kAhead; ++i) fa[i] = ra.read(tile, 0, i);
 #pragma clang loop unroll(full)
-      for (int i = 0; i < T::MT; ++i)
+    for (int j = 0; j < T::NT; ++j) fw[0][j] = rw.read(tile + TILE * BK, 0, j);
+    floatx4 acc[T::MT][T::NT];
 #pragma clang loop unroll(full)
-        for (int g = 0; g < 4; ++g)
-          *(float4*)(park + (i * 32 + (lane & 31)) * T::kParkStride + wn * T::NT * 32 + j * 32 + g * 8 + (lane >> 5) * 4) =
-              make_float4(acc[i][j][g * 4], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
-  };
-  constexpr int kRowThreads = TILE / 8, kRowStep = T::kThreads / kRowThreads, kChunks = T::kHalf / kRowStep;
-  constexpr int kAhead = 2, kBufs = TILE == 256 ? 3 : 4;     // pieces whose operands are requested together, batches of them
-  static_assert(kChunks % kAhead == 0, "");
-  const int r0 = tid / kRowThreads, cc = (tid % kRowThreads) * 8;
-  constexpr bool kForward = ALAY == OP_ROW && WLAY == OP_ROW;        // 16-bit outputs and x0; the others are gradients
-  if constexpr (!kForward) {
-    // Float32 outputs, four columns a lane, so that a wave's store covers whole lines (eight columns a
-    // lane, two stores of every other 16 bytes: 2.5 GB of data gradients took 715 us, now 644).
-    constexpr int kRow4 = T::kThreads / (TILE / 4), kPieces = T::kHalf / kRow4;
-    constexpr int kBatch = TILE == 256 ? 2 : 4, kBatchesHalf = kPieces / kBatch, kBatchesAll = T::WM * kBatchesHalf, kDeep = 2;
-    const int r4 = tid / (TILE / 4), c4 = (tid % (TILE / 4)) * 4;
-    const bool on = n0 + c4 < N;
-    const int64_t corner = (int64_t)m0 * G.ldc + n0;
-    char* const c = (char*)((float*)G.C + slice * G.cstride + corner);
-    const bool grad = ALAY == OP_ROW && epi == EPI_CROSS_GRAD, add = epi == EPI_F32_ADD;
-    if (grad || (epi >= EPI_F32 && N % 4 == 0 && G.ldc % 4 == 0 && G.rdiv == 0 && ((uintptr_t)c & 15) == 0)) {
-      // What a piece reads is requested a batch of pieces ahead, the first before the accumulators are
-      // parked: with one block per CU nothing else hides that latency.  EPI_CROSS_GRAD: whole
-      // pieces only (N and ldc are a tower's width, the tensors the library's own or blocks of
-      // grad_pooled).
-      const char *gn = add ? c : (const char*)(G.GN + corner), *ul = (const char*)G.UL + corner * 2;
-      const char *x0 = (const char*)G.X0 + corner * 2, *u0 = (const char*)G.U0 + corner * 2;
-      char *a0 = (char*)(G.ACC + corner), *du = (char*)G.DU + corner * 2;
-      const bool has_gn = add || (grad && G.GN), has_u0 = grad && G.U0, acc_old = grad && !G.acc_first && (G.GN || G.U0);
-      float4 pg[kDeep][kBatch], po[kDeep][kBatch];
-      uint2 px[kDeep][kBatch], pu[kDeep][kBatch], pv[kDeep][kBatch];
-      auto request = [&](int buf, int b) __attribute__((always_inline)) {
+    for (int i = 0; i < T::MT; ++i)
 #pragma clang loop unroll(full)
-        for (int u = 0; u < kBatch; ++u) {
-          // (rows and columns past the edge read in bounds and are not stored)
-          const uint32_t m = (uint32_t)min(b / kBatchesHalf * T::kHalf + r4 + (b % kBatchesHalf * kBatch + u) * kRow4, M - 1 - m0);
-          const uint32_t e = m * (uint32_t)G.ldc + (on ? (uint32_t)c4 : 0u);
-          if (has_gn) pg[buf][u] = *(const float4*)(gn + e * 4u);
-          if constexpr (ALAY == OP_ROW) {
-            if (grad) {
-              px[buf][u] = *(const uint2*)(x0 + e * 2u);
-              if (G.GN) pu[buf][u] = *(const uint2*)(ul + e * 2u);
-              if (has_u0) pv[buf][u] = *(const uint2*)(u0 + e * 2u);
-              if (acc_old) po[buf][u] = *(const float4*)(a0 + e * 4u);
-            }
+      for (int j = 0; j < T::NT; ++j)
+#pragma clang loop unroll(full)
+        for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
+
+    // ---- K loop
+    // Lines of the tile's operands kTouch steps ahead that this block brings to the XCD's L2 for itself and
+    // the blocks it shares them with, a wave up to 64: an epilogue's traffic on other CUs makes misses too
+    // slow for the two stages.  (The cross layer above 1304 -> 1246 us, others 1 %; weight gradients,
+    // whose epilogues are few, lose 2 %.)
+    constexpr bool kTouches = TILE == 256 && ALAY == OP_ROW && !DOTS;
+    constexpr int kTouch = 4;
+    uint32_t touch = kOobOffset;
+    bool touches = false;
+    if constexpr (kTouches) {
+      const TmGroup& G = L.g[work.gi];
+      const int tiles_n = (G.N + TILE - 1) / TILE, sm = tiles_n >= L.super ? 1 : L.super / tiles_n;
+      const int line = (wave & 3) * 64 + lane;
+      const bool a = wave < 4;                     // four waves A's lines, four W's
+      const int part = a ? work.n0 / TILE : work.m0 / TILE % sm, parts = a ? tiles_n : sm;
+      if (line >= part * TILE / parts && line < (part + 1) * TILE / parts) {
+        if (a || WLAY == OP_ROW) touch = line < (a ? sa.rows : sw.rows) ? (uint32_t)line * (uint32_t)(a ? sa.ld : sw.ld) * 2u : kOobOffset;
+        else if ((line & 3) * 64 < sw.rows) touch = ((uint32_t)(line >> 2) * (uint32_t)sw.ld + (line & 3) * 64) * 2u;
+      }
+      touches = __builtin_amdgcn_readfirstlane(G.K0 == 0 && __any(touch != kOobOffset));
+    }
+    for (int kt = 0; kt < nk; ++kt) {
+      // The barrier of a K step sits in front of its last three rows of MFMAs, by when every wave has
+      // read all it needs of the stage: behind it come the first requests for tile kt + 2 and
+      // the first reads of tile kt + 1, and those rows cover both.
+#pragma clang loop unroll(full)
+      for (int r = 0; r < kRows; ++r) {
+        const int kk = r / T::MT, i = r % T::MT;
+        if (r == kRows - kAhead) {
+          if (kTouches && touches && kt + kTouch < nk) {
+            const int k1 = (kt + kTouch) * BK;
+            tm_touch(lds0 + 2 * T::kStageBytes + wave * 4096, wave < 4 ? sa.buffer(k1, kl - k1) : sw.buffer(k1, kl - k1), touch);
+            __builtin_amdgcn_s_waitcnt(0x0f71);    // vmcnt: all but the touch
+          } else {
+            __builtin_amdgcn_s_waitcnt(0x0f70);
           }
-        }
-      };
-      float4 sums = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (has_gn || grad) request(0, 0);
-#pragma clang loop unroll(full)
-      for (int b = 0; b < kBatchesAll; ++b) {
-        const int h = b / kBatchesHalf, buf = b % kDeep;
-        if (b % kBatchesHalf == 0) {
-          if (wm == h) park_half();
           __syncthreads();
         }
-        if ((has_gn || grad) && b + 1 < kBatchesAll) request((b + 1) % kDeep, b + 1);
+        if (r == kRows - kAhead - 2) aim();
+        if (r + kAhead < kRows) {
+          fa[(r + kAhead) % 4] = ra.read(tile, (r + kAhead) / T::MT, (r + kAhead) % T::MT);
+        } else {
+          fa[(r + kAhead) % 4] = ra.read(next, 0, r + kAhead - kRows);
 #pragma clang loop unroll(full)
-        for (int u = 0; u < kBatch; ++u) {
-          const int r = r4 + (b % kBatchesHalf * kBatch + u) * kRow4;
-          if (m0 + h * T::kHalf + r >= M || !on) continue;
-          const uint32_t e = (uint32_t)(h * T::kHalf + r) * (uint32_t)G.ldc + (uint32_t)c4;
-          float4 g = *(const float4*)(park + r * T::kParkStride + c4);
-          if (has_gn) {
-            const float4 n = pg[buf][u];
-            g.x += n.x; g.y += n.y; g.z += n.z; g.w += n.w;
-          }
-          if constexpr (ALAY == OP_ROW) {
-            if (grad) {
-              float v0, v1, v2, v3;
-              if (G.GN || has_u0) {
-                float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (acc_old) t = po[buf][u];
-                if (G.GN) {
-                  const float4 n = pg[buf][u];
-                  dmt::unpack2<DT>(pu[buf][u].x, v0, v1);
-                  dmt::unpack2<DT>(pu[buf][u].y, v2, v3);
-                  t.x += mul_rounded(n.x, v0); t.y += mul_rounded(n.y, v1);
-                  t.z += mul_rounded(n.z, v2); t.w += mul_rounded(n.w, v3);
-                }
-                if (has_u0) {
-                  dmt::unpack2<DT>(pv[buf][u].x, v0, v1);
-                  dmt::unpack2<DT>(pv[buf][u].y, v2, v3);
-                  t.x += mul_rounded(g.x, v0) + g.x; t.y += mul_rounded(g.y, v1) + g.y;
-                  t.z += mul_rounded(g.z, v2) + g.z; t.w += mul_rounded(g.w, v3) + g.w;
-                }
-                *(float4*)(a0 + e * 4u) = t;
-              }
-              dmt::unpack2<DT>(px[buf][u].x, v0, v1);
-              dmt::unpack2<DT>(px[buf][u].y, v2, v3);
-              const uint2 d = make_uint2(dmt::pack2<DT>(g.x * v0, g.y * v1), dmt::pack2<DT>(g.z * v2, g.w * v3));
-              *(uint2*)(du + e * 2u) = d;
-              dmt::unpack2<DT>(d.x, v0, v1);       // the bias gradient sums the rounded values
-              dmt::unpack2<DT>(d.y, v2, v3);
-              sums.x += v0; sums.y += v1; sums.z += v2; sums.w += v3;
-              if (!G.C) continue;
-            }
-          }
-          *(float4*)(c + e * 4u) = g;
+          for (int j = 0; j < T::NT; ++j)
+            if (j * kAhead / T::NT == r + kAhead - kRows) fw[0][j] = rw.read(next + TILE * BK, 0, j);
         }
-        if (b % kBatchesHalf == kBatchesHalf - 1) {
-          __syncthreads();                         // the parked rows have been read
-          if (grad && (TILE == 256 || h == T::WM - 1)) {
-            // column sums of 128 rows: the row steps' sums, added in order
-            *(float4*)(park + r4 * TILE + c4) = sums;
-            sums = make_float4(0.f, 0.f, 0.f, 0.f);
-            __syncthreads();
-            const int block = (m0 + (TILE == 256 ? h * T::kHalf : 0)) / 128;
-            if (tid < TILE && n0 + tid < N && block * 128 < M) {
-              float y = 0.f;
 #pragma clang loop unroll(full)
-              for (int q = 0; q < kRow4; ++q) y += park[q * TILE + tid];
-              G.DBP[(int64_t)block * N + n0 + tid] = y;
-            }
-            __syncthreads();
-          }
+        for (int j = 0; j < T::NT; ++j)
+          if ((TILE == 256 ? j + 1 : j / 2) == r) fw[1][j] = rw.read(tile + TILE * BK, 1, j);
+        if (kn > 0)
+#pragma clang loop unroll(full)
+          for (int q = 0; q < kReqs; ++q)
+            if ((q < kEarly ? kRows - kAhead + q / kPerRow : (q - kEarly) / kPerRow) == r) request(q);
+#pragma clang loop unroll(full)
+        for (int jj = 0; jj < T::NT; ++jj) {
+          const int j = i & 1 ? T::NT - 1 - jj : jj;
+          acc[i][j] = mfma16<DT>(fw[kk][j], fa[r % 4], acc[i][j]);
         }
+        __builtin_amdgcn_sched_barrier(0);         // (left alone, reads end up right in front of their use)
       }
-      return;
+      const uint16_t* const was = tile;
+      tile = next;
+      next = was;
     }
-  }
-  const bool f32out = epi >= EPI_F32;
-  // byte addresses of the 16-bit tensors: the tile's corner (uniform, 64 bits) + an offset inside the tile
-  char* const cbase = (char*)G.C + ((int64_t)m0 * G.ldc + n0) * 2;
-  char* const ubase = (char*)G.U + ((int64_t)m0 * G.ldc + n0) * 2;
-  const char* const xbase = (const char*)G.X0 + ((int64_t)m0 * G.ldx + n0) * 2;
-  const char* const lbase = (const char*)G.XL + ((int64_t)m0 * G.ldxl + n0) * 2;
-  // whole 16-byte pieces everywhere (all tiles of a group alike): N and the pitches multiples of 8
-  bool fast = !f32out && G.N % 8 == 0 && G.ldc % 8 == 0 && G.ldc2 % 8 == 0 && (((uintptr_t)cbase | (uintptr_t)G.bias) & 15) == 0;
-  if (epi == EPI_CROSS)
-    fast = fast && G.ldx % 8 == 0 && G.ldxl % 8 == 0 && (((uintptr_t)xbase | (uintptr_t)lbase | (uintptr_t)ubase) & 15) == 0;
-  const bool cols_on = n0 + cc < N;
-  if (fast) {
-    const bool pre_cross = kForward && epi == EPI_CROSS;
-    const uint32_t la = (uint32_t)G.ldx * 2u, lb = (uint32_t)G.ldxl * 2u, col = cols_on ? (uint32_t)cc * 2u : 0u;
-    // a thread's chunks all lie in one 8-column piece of the tile: one bias load serves them
-    uint4 bias_raw = make_uint4(0, 0, 0, 0);
-    if (G.bias && cols_on) bias_raw = *(const uint4*)((const uint16_t*)G.bias + n0 + cc);
-    // The cross epilogue requests its operands (x0 and x_l) for two pieces together, kBufs - 1
-    // batches ahead of the one being walked and the first before the accumulators are parked: with
-    // one block per CU nothing else hides that latency, and more is more registers than a wave
-    // has beside its accumulators.
-    uint4 pa[kBufs][kAhead], pb[kBufs][kAhead];
-    auto request = [&](int buf, int batch) __attribute__((always_inline)) {
-      const int h = batch / (kChunks / kAhead), u1 = batch % (kChunks / kAhead) * kAhead;
+
+    // ---- epilogue, 16 rows x 64 columns of the wave's accumulators at a time: they go through 4 KB of
+    // LDS of its own, so that its loads and stores of global memory cover whole lines (straight from the
+    // registers, 64 bytes of 16 rows each: data gradients 1257 against 1066 us).  Chunk c (four columns)
+    // of row r lies in slot c ^ r: 16 lanes that write one chunk of 16 rows or read 16 chunks of one
+    // touch all banks once.  No barrier: the next tile's operands are landing beside it.
+    const TmGroup& G = L.g[work.gi];
+    const int m0 = work.m0, n0 = work.n0, slice = work.slice, M = G.M, N = G.N, epi = G.epi;
+    // (opaque: what the branches below work out from either would otherwise be worked out ahead of the
+    // loop over tiles, and kept in registers)
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    floatx4* const turn = (floatx4*)(lds + T::kStageBytes) + wave * 256;
+    auto put = [&](int i) __attribute__((always_inline)) {
+      wave_sync();
 #pragma clang loop unroll(full)
-      for (int u = 0; u < kAhead; ++u) {
-        const uint32_t m = (uint32_t)min(h * T::kHalf + r0 + (u1 + u) * kRowStep, M - 1 - m0);
-        pa[buf][u] = *(const uint4*)(xbase + (m * la + col));
-        pb[buf][u] = *(const uint4*)(lbase + (m * lb + col));
-      }
+      for (int j = 0; j < T::NT; ++j) turn[(ln & 15) * 16 + ((j * 4 + (ln >> 4)) ^ (ln & 15))] = acc[i][j];
+      wave_sync();
     };
-    constexpr int kBatches = T::WM * (kChunks / kAhead);
-    if (pre_cross)
+    auto get = [&](int r, int c) __attribute__((always_inline)) { return turn[r * 16 + (c ^ r)]; };
+    // (outputs that the caches will not keep until they are read do not push the operands out)
+    const bool stream = L.stream;
+    auto put_out = [&](auto v, auto* p) __attribute__((always_inline)) {
+      if (stream) dmt::nt_store(v, p);
+      else dmt::gstore(v, p);
+    };
+    const int wrow = wm * T::kHalf, wcol = wn * 64;
+    if (whole && epi < EPI_F32 && (kForward || KIND == KIND_PLAIN)) {
+      // 16-bit outputs: eight rows at a time, eight columns a lane.  What the cross epilogue reads (x0 and
+      // x_l) is requested kDeep pieces ahead: more is more registers than a wave has beside its
+      // accumulators.
+      constexpr int kAll = T::MT * 2, kDeep = 8;
+      const int r8 = ln >> 3, c = wcol + (ln & 7) * 8;
+      const bool on = n0 + c < N;
+      // byte addresses: the tile's corner (uniform, 64 bits) + an offset inside the tile
+      char* const cbase = (char*)G.C + ((int64_t)m0 * G.ldc + n0) * 2;
+      char* const ubase = (char*)G.U + ((int64_t)m0 * G.ldc + n0) * 2;
+      const char* const xbase = (const char*)G.X0 + ((int64_t)m0 * G.ldx + n0) * 2;
+      const char* const lbase = (const char*)G.XL + ((int64_t)m0 * G.ldxl + n0) * 2;
+      constexpr bool cross = KIND == KIND_READS;
+      uint4 bias_raw = make_uint4(0, 0, 0, 0), pa[kDeep], pb[kDeep];
+      if (G.bias && on) bias_raw = dmt::gload((const uint4*)((const uint16_t*)G.bias + n0 + c));
+      auto pack8 = [](const float (&y)[8]) __attribute__((always_inline)) {
+        return make_uint4(dmt::pack2<DT>(y[0], y[1]), dmt::pack2<DT>(y[2], y[3]), dmt::pack2<DT>(y[4], y[5]), dmt::pack2<DT>(y[6], y[7]));
+      };
+      auto fetch = [&](int e) __attribute__((always_inline)) {
+        // (rows and columns past the edge read in bounds and are not stored)
+        const uint32_t m = (uint32_t)min(wrow + e * 8 + r8, M - 1 - m0), cc = on ? (uint32_t)c : 0u;
+        pa[e % kDeep] = dmt::nt_load((const uint4*)(xbase + (m * (uint32_t)G.ldx + cc) * 2u));
+        pb[e % kDeep] = dmt::nt_load((const uint4*)(lbase + (m * (uint32_t)G.ldxl + cc) * 2u));
+      };
+      if (cross)
 #pragma clang loop unroll(full)
-      for (int q = 0; q < kBufs - 1 && q < kBatches; ++q) request(q, q);
+        for (int e = 0; e < kDeep - 1; ++e) fetch(e);
 #pragma clang loop unroll(full)
-    for (int batch = 0; batch < kBatches; ++batch) {
-      const int h = batch / (kChunks / kAhead), u1 = batch % (kChunks / kAhead) * kAhead, buf = batch % kBufs;
-      if (u1 == 0) {
-        if (wm == h) park_half();
-        __syncthreads();
-      }
-      if (pre_cross && batch + kBufs - 1 < kBatches) request((batch + kBufs - 1) % kBufs, batch + kBufs - 1);
-#pragma clang loop unroll(full)
-      for (int u = 0; u < kAhead; ++u) {
-        const int r = r0 + (u1 + u) * kRowStep;
-        if (m0 + h * T::kHalf + r >= M || !cols_on) continue;
-        const float4 s0 = *(const float4*)(park + r * T::kParkStride + cc);
-        const float4 s1 = *(const float4*)(park + r * T::kParkStride + cc + 4);
-        char* c = cbase + ((uint32_t)(h * T::kHalf + r) * (uint32_t)G.ldc + (uint32_t)cc) * 2u;
-        if (G.rdiv > 0) {
-          const int m = m0 + h * T::kHalf + r;
-          c = (char*)G.C + ((int64_t)(m / G.rdiv) * G.ldc + (int64_t)(m % G.rdiv) * G.ldc2 + n0 + cc) * 2;
-        }
-        float y[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
-        float bv[8];
+      for (int e = 0; e < kAll; ++e) {
+        const int r = wrow + e * 8 + r8;
+        if (cross && e + kDeep - 1 < kAll) fetch(e + kDeep - 1);
+        if (e % 2 == 0) put(e / 2);
+        const floatx4 s0 = get(e % 2 * 8 + r8, (ln & 7) * 2), s1 = get(e % 2 * 8 + r8, (ln & 7) * 2 + 1);
+        float y[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]}, bv[8];
         dmt::decode_chunk<DT>(bv, bias_raw);
 #pragma clang loop unroll(full)
         for (int q = 0; q < 8; ++q) y[q] += bv[q];
-        if (epi == EPI_BIAS_RELU) {
+        if (m0 + r < M && on) {
+          const uint32_t off = ((uint32_t)r * (uint32_t)G.ldc + (uint32_t)c) * 2u;
+          char* out = cbase + off;
+          if (G.rdiv > 0) {
+            const int m = m0 + r;
+            out = (char*)G.C + ((int64_t)(m / G.rdiv) * G.ldc + (int64_t)(m % G.rdiv) * G.ldc2 + n0 + c) * 2;
+          }
+          if (epi == EPI_BIAS_RELU) {
 #pragma clang loop unroll(full)
-          for (int q = 0; q < 8; ++q) y[q] = y[q] > 0.f ? y[q] : 0.f;
-        } else if (kForward && epi == EPI_CROSS) {
-          float xv[8], lv[8];
-          if (G.U) dmt::store_chunk<DT, 8>(ubase + ((uint32_t)(h * T::kHalf + r) * (uint32_t)G.ldc + (uint32_t)cc) * 2u, 0, y);
-          dmt::decode_chunk<DT>(xv, pa[buf][u]);
-          dmt::decode_chunk<DT>(lv, pb[buf][u]);
+            for (int q = 0; q < 8; ++q) y[q] = y[q] > 0.f ? y[q] : 0.f;
+          } else if constexpr (cross) {
+            float xv[8], lv[8];
+            if (G.U) put_out(pack8(y), (uint4*)(ubase + off));
+            dmt::decode_chunk<DT>(xv, pa[e % kDeep]);
+            dmt::decode_chunk<DT>(lv, pb[e % kDeep]);
 #pragma clang loop unroll(full)
-          for (int q = 0; q < 8; ++q) y[q] = xv[q] * y[q] + lv[q];
+            for (int q = 0; q < 8; ++q) y[q] = xv[q] * y[q] + lv[q];
+          }
+          put_out(pack8(y), (uint4*)out);
         }
-        dmt::store_chunk<DT, 8>(c, 0, y);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if (u1 + kAhead == kChunks && h + 1 < T::WM) __syncthreads();
-    }
-    return;
-  }
-  // odd widths, unaligned rows: the same, element by element
-  for (int h = 0; h < T::WM; ++h) {
-    if (wm == h) park_half();
-    __syncthreads();
-    for (int r = r0; r < T::kHalf; r += kRowStep) {
-      const int m = m0 + h * T::kHalf + r;
-      if (m >= M) break;
-      const int64_t row = G.rdiv > 0 ? (int64_t)(m / G.rdiv) * G.ldc + (int64_t)(m % G.rdiv) * G.ldc2 : (int64_t)m * G.ldc;
-      for (int q = 0; q < 8 && n0 + cc + q < N; ++q) {
-        const int n = n0 + cc + q;
-        float y = park[r * T::kParkStride + cc + q];
-        if (f32out) {
-          float* c = (float*)G.C + slice * G.cstride + row + n;
-          *c = epi == EPI_F32_ADD ? *c + y : y;
-          continue;
+    } else if (!kForward && whole) {
+      // float32 outputs: four rows at a time, four columns a lane.  What a piece reads is requested kDeep
+      // pieces ahead.
+      constexpr int kAll = T::MT * 4;
+      const int r4 = ln >> 4, c = wcol + (ln & 15) * 4;
+      const bool on = n0 + c < N;
+      const int64_t corner = (int64_t)m0 * G.ldc + n0;
+      char* const cbase = (char*)((float*)G.C + slice * G.cstride + corner);
+      // (rows and columns past the edge read in bounds and are not stored)
+      auto place = [&](int e) __attribute__((always_inline)) {
+        return (uint32_t)min(wrow + e * 4 + r4, M - 1 - m0) * (uint32_t)G.ldc + (on ? (uint32_t)c : 0u);
+      };
+      if constexpr (KIND != KIND_READS) {
+        constexpr int kDeep = 4;
+        constexpr bool add = KIND == KIND_ADD;
+        float4 old[kDeep];
+        if (add)
+#pragma clang loop unroll(full)
+          for (int e = 0; e < kDeep - 1; ++e) old[e] = dmt::nt_load((const float4*)(cbase + place(e) * 4u));
+#pragma clang loop unroll(full)
+        for (int e = 0; e < kAll; ++e) {
+          if (add && e + kDeep - 1 < kAll) old[(e + kDeep - 1) % kDeep] = dmt::nt_load((const float4*)(cbase + place(e + kDeep - 1) * 4u));
+          if (e % 4 == 0) put(e / 4);
+          const floatx4 s = get(e % 4 * 4 + r4, ln & 15);
+          float4 g = make_float4(s[0], s[1], s[2], s[3]);
+          if (add) {
+            const float4 o = old[e % kDeep];
+            g.x += o.x; g.y += o.y; g.z += o.z; g.w += o.w;
+          }
+          if (m0 + wrow + e * 4 + r4 < M && on) put_out(g, (float4*)(cbase + place(e) * 4u));
+          __builtin_amdgcn_sched_barrier(0);
         }
-        if (G.bias) y += load_elt<DT>(G.bias, n);
-        if (epi == EPI_BIAS_RELU) y = y > 0.f ? y : 0.f;
-        if (epi == EPI_CROSS) {
-          if (G.U) store_elt<DT>(G.U, row + n, y);
-          y = load_elt<DT>(G.X0, (int64_t)m * G.ldx + n) * y + load_elt<DT>(G.XL, (int64_t)m * G.ldxl + n);
+      } else {
+        constexpr int kDeep = 5;
+        const char *gn = (const char*)(G.GN + corner), *ul = (const char*)G.UL + corner * 2;
+        const char *x0 = (const char*)G.X0 + corner * 2, *u0 = (const char*)G.U0 + corner * 2;
+        char *a0 = (char*)(G.ACC + corner), *du = (char*)G.DU + corner * 2;
+        const bool has_gn = G.GN, has_u0 = G.U0, has_c = G.C, acc_old = !G.acc_first;
+        float4 pg[kDeep];
+        uint2 px[kDeep], pu[kDeep], pv[kDeep];
+        auto fetch = [&](int e) __attribute__((always_inline)) {
+          const uint32_t at = place(e);
+          px[e % kDeep] = dmt::nt_load((const uint2*)(x0 + at * 2u));
+          if (has_gn) {
+            pg[e % kDeep] = dmt::nt_load((const float4*)(gn + at * 4u));
+            pu[e % kDeep] = dmt::nt_load((const uint2*)(ul + at * 2u));
+          }
+          if (has_u0) pv[e % kDeep] = dmt::nt_load((const uint2*)(u0 + at * 2u));
+        };
+        float4 sums = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma clang loop unroll(full)
+        for (int e = 0; e < kDeep - 1; ++e) fetch(e);
+#pragma clang loop unroll(full)
+        for (int e = 0; e < kAll; ++e) {
+          const int b = e % kDeep;
+          if (e + kDeep - 1 < kAll) fetch(e + kDeep - 1);
+          if (e % 4 == 0) put(e / 4);
+          const floatx4 s = get(e % 4 * 4 + r4, ln & 15);
+          if (m0 + wrow + e * 4 + r4 < M && on) {
+            const uint32_t at = place(e);
+            float4 g = make_float4(s[0], s[1], s[2], s[3]);
+            float v0, v1, v2, v3;
+            if (has_gn || has_u0) {
+              float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+              if (acc_old) t = dmt::nt_load((const float4*)(a0 + at * 4u));      // (three layers and more)
+              if (has_gn) {
+                const float4 n = pg[b];
+                g.x += n.x; g.y += n.y; g.z += n.z; g.w += n.w;
+                dmt::unpack2<DT>(pu[b].x, v0, v1);
+                dmt::unpack2<DT>(pu[b].y, v2, v3);
+                t.x += mul_rounded(n.x, v0); t.y += mul_rounded(n.y, v1);
+                t.z += mul_rounded(n.z, v2); t.w += mul_rounded(n.w, v3);
+              }
+              if (has_u0) {
+                dmt::unpack2<DT>(pv[b].x, v0, v1);
+                dmt::unpack2<DT>(pv[b].y, v2, v3);
+                t.x += mul_rounded(g.x, v0) + g.x; t.y += mul_rounded(g.y, v1) + g.y;
+                t.z += mul_rounded(g.z, v2) + g.z; t.w += mul_rounded(g.w, v3) + g.w;
+              }
+              put_out(t, (float4*)(a0 + at * 4u));
+            }
+            dmt::unpack2<DT>(px[b].x, v0, v1);
+            dmt::unpack2<DT>(px[b].y, v2, v3);
+            const uint2 d = make_uint2(dmt::pack2<DT>(g.x * v0, g.y * v1), dmt::pack2<DT>(g.z * v2, g.w * v3));
+            put_out(d, (uint2*)(du + at * 2u));
+            dmt::unpack2<DT>(d.x, v0, v1);         // the bias gradient sums the rounded values
+            dmt::unpack2<DT>(d.y, v2, v3);
+            sums.x += v0; sums.y += v1; sums.z += v2; sums.w += v3;
+            if (has_c) put_out(g, (float4*)(cbase + at * 4u));
+          }
+          if (e % 16 == 15) {
+            // column sums of 64 rows: 16 of a lane, then the four lanes of its columns
+            sums = make_float4(quarters_sum(sums.x), quarters_sum(sums.y), quarters_sum(sums.z), quarters_sum(sums.w));
+            const int block = (m0 + wrow) / 64 + e / 16;
+            if (r4 == 0 && block * 64 < M && on) dmt::gstore(sums, (float4*)(G.DBP + (int64_t)block * N + n0 + c));
+            sums = make_float4(0.f, 0.f, 0.f, 0.f);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
-        store_elt<DT>(G.C, row + n, y);
+      }
+    } else {
+      // odd widths, unaligned rows: a column a lane, element by element
+      const int n = n0 + wcol + ln;
+#pragma clang loop unroll(full)
+      for (int i = 0; i < T::MT; ++i) {
+        put(i);
+        for (int r = 0; r < 16; ++r) {
+          const int m = m0 + wrow + i * 16 + r;
+          if (m >= M || n >= N) break;
+          const int64_t row = G.rdiv > 0 ? (int64_t)(m / G.rdiv) * G.ldc + (int64_t)(m % G.rdiv) * G.ldc2 : (int64_t)m * G.ldc;
+          float y = ((const float*)(turn + r * 16 + ((ln >> 2) ^ r)))[ln & 3];
+          if (epi >= EPI_F32) {
+            float* c = (float*)G.C + slice * G.cstride + row + n;
+            *c = epi == EPI_F32_ADD ? *c + y : y;
+            continue;
+          }
+          if (G.bias) y += load_elt<DT>(G.bias, n);
+          if (epi == EPI_BIAS_RELU) y = y > 0.f ? y : 0.f;
+          if (epi == EPI_CROSS) {
+            if (G.U) store_elt<DT>(G.U, row + n, y);
+            y = load_elt<DT>(G.X0, (int64_t)m * G.ldx + n) * y + load_elt<DT>(G.XL, (int64_t)m * G.ldxl + n);
+          }
+          store_elt<DT>(G.C, row + n, y);
+        }
       }
     }
-    __syncthreads();
+    // the requests are at the next tile's second step, if there is one
+    if (kn <= 0) return;
+    work = ahead;
+    measure();
   }
 }
 
@@ -1046,10 +1170,10 @@ inline size_t plan_tm_kept(const dmt_plan* p, const dmt_tm_params* tp, int64_t B
 }
 
 // Launches of tm_gemm.
-template <int DT, int TILE, int ALAY, int WLAY, bool DOTS, bool KEEPZ>
+template <int DT, int TILE, int ALAY, int WLAY, int KIND, bool DOTS, bool KEEPZ>
 void launch_tiles(const TmLaunch& L, int64_t blocks, hipStream_t s) {
   constexpr int bytes = TmTile<TILE>::kLdsBytes;
-  auto kernel = tm_gemm<DT, TILE, ALAY, WLAY, DOTS, KEEPZ>;
+  auto kernel = tm_gemm<DT, TILE, ALAY, WLAY, KIND, DOTS, KEEPZ>;
   static DmtPerDevice configured;
   int dev = -1;
   (void)hipGetDevice(&dev);
@@ -1088,13 +1212,33 @@ inline bool take_small(const dmt_plan* p, const TmGroup* g, int n) {
   return tiles <= 768;
 }
 
+// Whether a launch's 256 x 256 tiles may be worked through by one block per CU: every tile has the same number
+// of K steps (blocks that are handed out a tile at a time even differences out), and two at least, so
+// that the requests are never more than one tile ahead.
+constexpr int kCUs = 256;
+inline bool same_steps(const TmGroup* g, int n) {
+  int64_t steps = 0;
+  for (int i = 0; i < n; ++i) {
+    const bool split = g[i].ksplit > 1;
+    const int64_t first = split ? g[i].klen : g[i].K1, last = split ? g[i].K1 - (int64_t)(g[i].ksplit - 1) * g[i].klen : first;
+    const int64_t k0 = (g[i].K0 + BK - 1) / BK, s = k0 + (first + BK - 1) / BK;
+    if (k0 + (last + BK - 1) / BK < 2 || (steps != 0 && s != steps)) return false;
+    steps = s;
+  }
+  return true;
+}
+
 // All groups of the list, kMaxGroups to a launch.  dots: every group computes its dot terms itself.
 template <int DT, int ALAY = OP_ROW, int WLAY = OP_ROW>
 void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t s, bool dots = false,
                    int kid = DMT_K_TM_GEMM) {
-  for (size_t first = 0; first < groups.size(); first += kMaxGroups) {
+  // (towers of several forms may share a stage; their epilogues are kernels of their own)
+  std::stable_sort(groups.begin(), groups.end(), [](const TmGroup& a, const TmGroup& b) { return epi_kind(a.epi) < epi_kind(b.epi); });
+  for (size_t first = 0, end; first < groups.size(); first = end) {
+    const int kind = epi_kind(groups[first].epi);
+    for (end = first + 1; end < groups.size() && end < first + kMaxGroups && epi_kind(groups[end].epi) == kind; ++end) {}
     TmLaunch L;
-    L.ngroups = (int32_t)std::min<size_t>(kMaxGroups, groups.size() - first);
+    L.ngroups = (int32_t)(end - first);
     bool keepz = false;                           // a training forward keeps the dot terms
     for (int i = 0; i < L.ngroups; ++i) {
       L.g[i] = groups[first + i];
@@ -1130,21 +1274,43 @@ void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t 
       L.tile_start[i] = (int32_t)nst;
       const int64_t tn = (L.g[i].N + tile - 1) / tile, tm = (int64_t)((L.g[i].M + tile - 1) / tile) * tm_slices(L.g[i]);
       const int64_t sm = tn >= L.super ? 1 : L.super / tn;
-      L.cap = (int32_t)std::max<int64_t>(L.cap, sm * tn);
+      L.cap = (int32_t)std::max<int64_t>(L.cap, std::min(sm, tm) * tn);
       nst += (tm + sm - 1) / sm;
     }
     L.tile_start[L.ngroups] = (int32_t)nst;
-    const int64_t blocks = (nst + 7) / 8 * 8 * L.cap;
+    int64_t blocks = (nst + 7) / 8 * 8 * L.cap;
     if (blocks == 0) continue;
+    // 128 MB of outputs: half of what the Infinity Cache holds.  (Streamed, the 34 MB of a split weight
+    // gradient's slices took 41 instead of 31 us to add up; kept, 1.1 GB of data gradients take 1042
+    // instead of 1026 us.)
+    int64_t out = 0;
+    for (int i = 0; i < L.ngroups; ++i)
+      out += (int64_t)L.g[i].M * L.g[i].N * tm_slices(L.g[i]) * (L.g[i].epi >= EPI_F32 || L.g[i].U ? 4 : 2);
+    L.stream = out > (128 << 20);
+    L.stagger = 0;
+    // (and few slots without a tile: they would leave their blocks idle)
+    if (big && !dots && tiles > kCUs && nst * L.cap <= tiles + tiles / 16 && same_steps(L.g, L.ngroups)) {
+      // (the last XCD starts a quarter of a tile late: eight rounds and more make up for that)
+      if (kind != KIND_PLAIN && tiles >= 8 * kCUs) L.stagger = 2;
+      blocks = kCUs;
+    }
     DmtScope scope(p, kid, s);
     if constexpr (ALAY == OP_ROW && WLAY == OP_ROW && DMT_TM_TAG == 0) {
-      if (dots && big && keepz) { launch_tiles<DT, 256, ALAY, WLAY, true, true>(L, blocks, s); continue; }
-      if (dots && big) { launch_tiles<DT, 256, ALAY, WLAY, true, false>(L, blocks, s); continue; }
-      if (dots && keepz) { launch_tiles<DT, 128, ALAY, WLAY, true, true>(L, blocks, s); continue; }
-      if (dots) { launch_tiles<DT, 128, ALAY, WLAY, true, false>(L, blocks, s); continue; }
+      if (dots && big && keepz) { launch_tiles<DT, 256, ALAY, WLAY, KIND_PLAIN, true, true>(L, blocks, s); continue; }
+      if (dots && big) { launch_tiles<DT, 256, ALAY, WLAY, KIND_PLAIN, true, false>(L, blocks, s); continue; }
+      if (dots && keepz) { launch_tiles<DT, 128, ALAY, WLAY, KIND_PLAIN, true, true>(L, blocks, s); continue; }
+      if (dots) { launch_tiles<DT, 128, ALAY, WLAY, KIND_PLAIN, true, false>(L, blocks, s); continue; }
     }
-    if (big) launch_tiles<DT, 256, ALAY, WLAY, false, false>(L, blocks, s);
-    else launch_tiles<DT, 128, ALAY, WLAY, false, false>(L, blocks, s);
+    if constexpr (ALAY == OP_ROW) {
+      if (kind == KIND_READS && big) { launch_tiles<DT, 256, ALAY, WLAY, KIND_READS, false, false>(L, blocks, s); continue; }
+      if (kind == KIND_READS) { launch_tiles<DT, 128, ALAY, WLAY, KIND_READS, false, false>(L, blocks, s); continue; }
+    }
+    if constexpr (ALAY == OP_ROW && WLAY == OP_COL) {
+      if (kind == KIND_ADD && big) { launch_tiles<DT, 256, ALAY, WLAY, KIND_ADD, false, false>(L, blocks, s); continue; }
+      if (kind == KIND_ADD) { launch_tiles<DT, 128, ALAY, WLAY, KIND_ADD, false, false>(L, blocks, s); continue; }
+    }
+    if (big) launch_tiles<DT, 256, ALAY, WLAY, KIND_PLAIN, false, false>(L, blocks, s);
+    else launch_tiles<DT, 128, ALAY, WLAY, KIND_PLAIN, false, false>(L, blocks, s);
   }
   groups.clear();
 }

@@ -635,3 +635,66 @@ def test_cross_gradient_rounds_its_products_first(layers, big, monkeypatch):
         want += g * b[l] + g if l == 0 else g * b[l]
     got = dx.cpu().numpy().reshape(B, wt)
     assert np.array_equal(got.view(np.int32), want.view(np.int32))
+
+
+@pytest.mark.parametrize("kind", ["linear", "cross_linear"])
+@pytest.mark.parametrize("widths,out,batch", [((1024, 1024, 1024), 1288, 5900), ((128, 128, 128), 2056, 8200),
+                                              ((64, 128, 256), 2056, 8200), ((1024,) * 4, 256, 33000)])
+def test_launches_of_more_tiles_than_cus(kind, widths, out, batch):
+    """Blocks that work through several 256 x 256 tiles (K of two steps and more, equal in all towers), and
+    launches that must not (unequal towers, one K step), forward and backward, against float32 torch.
+    16-bit operands and outputs are rounded once (2^-9 relative per term), through two cross layers twice:
+    the rms bounds of the other tests, a quarter of their elementwise 2e-2 and 4e-2."""
+    import paper_2403_00877_amd as dmt
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    dims = [64 if w == 64 else 128 for w in widths for _ in range(max(1, w // 128))]
+    tower = [t for t, w in enumerate(widths) for _ in range(max(1, w // 128))]
+    F, T, L = len(dims), len(widths), 2 if kind == "cross_linear" else 0
+    plan = dmt.dmt_plan_create([16] * F, dims, "bf16", T, tower, batch, 1)
+    dmt.dmt_plan_bind(plan, [torch.zeros(16, d, dtype=torch.bfloat16, device="cuda") for d in dims], None)
+    rand = lambda scale, *shape: (torch.randn(*shape, generator=g, device="cuda") * scale).to(torch.bfloat16)
+    f32 = lambda *shape: torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+    xs = [rand(1.0, batch, w) for w in widths]
+    params = [dict(kind=kind, out_dim=out, w_proj=rand(w ** -0.5, out, w), b_proj=rand(0.1, out),
+                   w_cross=[rand(w ** -0.5, w, w) for _ in range(L)], b_cross=[rand(0.1, w) for _ in range(L)],
+                   feat_out=0) for w in widths]
+    grads = [dict(dw_proj=f32(out, w), db_proj=f32(out), dw_cross=[f32(w, w) for _ in range(L)],
+                  db_cross=[f32(w) for _ in range(L)]) for w in widths]
+    tp, tg = dmt.make_tm_params(params), dmt.make_tm_grads(grads)
+    buf = lambda n: torch.full((max(256, n),), 255, dtype=torch.uint8, device="cuda")
+    pooled = torch.cat([x.reshape(-1) for x in xs])
+    y = torch.full((batch * out * T,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    nkept = dmt.dmt_tm_kept_bytes(plan, tp, batch, "bf16")
+    kept = buf(nkept) if nkept else None
+    dmt.dmt_tower_module_fwd_keep(plan, tp, pooled, batch, y, kept, buf(dmt.dmt_tm_workspace_bytes(plan, tp, batch)))
+    dy = torch.randn(batch * out * T, generator=g, device="cuda")
+    dx = f32(pooled.numel())
+    dmt.dmt_tower_module_bwd(plan, tp, pooled, y, batch, dy, dx, tg,
+                             buf(dmt.dmt_tm_bwd_workspace_bytes(plan, tp, batch)), kept=kept)
+    bound = 1e-2 if L else 5e-3
+
+    def check(got, ref, what):
+        err = (got.float() - ref).square().mean().sqrt() / ref.square().mean().sqrt()
+        assert err <= bound, "%s: rms error %.2e" % (what, err)      # (NaN fails)
+
+    at = 0
+    for t, w in enumerate(widths):
+        p = params[t]
+        x = xs[t].float().requires_grad_()
+        leaf = lambda a: a.float().requires_grad_()
+        wp, bp = leaf(p["w_proj"]), leaf(p["b_proj"])
+        wc, bc = [leaf(a) for a in p["w_cross"]], [leaf(a) for a in p["b_cross"]]
+        h = x
+        for l in range(L):
+            h = x * (h @ wc[l].t() + bc[l]) + h
+        ref = h @ wp.t() + bp
+        ref.backward(dy[t * batch * out:(t + 1) * batch * out].view(batch, out))
+        check(y[t * batch * out:(t + 1) * batch * out].view(batch, out), ref.detach(), "output %d" % t)
+        check(dx[at:at + batch * w].view(batch, w), x.grad, "grad_pooled %d" % t)
+        check(grads[t]["dw_proj"], wp.grad, "dw_proj %d" % t)
+        check(grads[t]["db_proj"], bp.grad, "db_proj %d" % t)
+        for l in range(L):
+            check(grads[t]["dw_cross"][l], wc[l].grad, "dw_cross %d %d" % (t, l))
+            check(grads[t]["db_cross"][l], bc[l].grad, "db_cross %d %d" % (t, l))
+        at += batch * w
