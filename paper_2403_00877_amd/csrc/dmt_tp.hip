@@ -305,6 +305,10 @@ __global__ __launch_bounds__(kBlock) void tp_gram(const DmtTableMeta* __restrict
 // exactly once, and its waves share out the 32 x 32 sub-tiles of the upper triangle of the
 // Gram matrix (at most 36, three per wave).  A sub-tile (r, c), r <= c, is stored like a tile
 // pair of 32-feature tiles, which is what tp_finish reads.  One block per CU; block = batch slice.
+// Two sample buffers: a wave that is done with a sample commits its share of the next one's rows, which
+// were under way meanwhile, and requests the one after, so that a sample costs one barrier and loads are
+// under way all the time but while they are committed (one buffer, two barriers: 263.1 us for 256
+// features of 128 columns, batch 16384; now 259.6: it reads 576 KB of fragments from LDS a sample).
 constexpr int kWideThreads = 1024, kWideRows = 256, kWideSub = 3;
 template <int DT, int NP>
 __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
@@ -315,7 +319,7 @@ __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   __shared__ int64_t s_base[kWideRows];
   __shared__ int32_t s_pitch[kWideRows];
-  __shared__ __attribute__((aligned(16))) float s_inv[kWideRows];
+  __shared__ __attribute__((aligned(16))) float s_inv[2][kWideRows];
   __shared__ uint8_t s_r[36], s_c[36];
   const int npad = (N + 15) & ~15, ldx = npad + 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -367,15 +371,17 @@ __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
       }
     }
   };
-  auto commit = [&]() __attribute__((always_inline)) {
+  const int stage = kWideRows * ldx;         // elements of a sample's buffer
+  auto commit = [&](int buf) __attribute__((always_inline)) {
+    uint16_t* const rows = lds + buf * stage;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const int row = p * RP + row0;
       if constexpr (kRaw) {
         const uint4 r = raw[p].v[0];
         const float ss = row_group_sum<LPR>(sumsq8<DT>(r));
-        if (chunk * 8 < npad) *(uint4*)(lds + row * ldx + chunk * 8) = r;
-        if (chunk == 0) s_inv[row] = ss > 0.f ? __builtin_amdgcn_rsqf(ss) : 0.f;
+        if (chunk * 8 < npad) *(uint4*)(rows + row * ldx + chunk * 8) = r;
+        if (chunk == 0) s_inv[buf][row] = ss > 0.f ? __builtin_amdgcn_rsqf(ss) : 0.f;
       } else {
         float x[8];
         decode8<DT>(raw[p], x);
@@ -385,24 +391,29 @@ __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
         ss = row_group_sum<LPR>(ss);
         const float inv = ss > 0.f ? __builtin_amdgcn_rsqf(ss) : 0.f;
         if (chunk * 8 < npad) {
-          *(uint4*)(lds + row * ldx + chunk * 8) =
+          *(uint4*)(rows + row * ldx + chunk * 8) =
               make_uint4(dmt::pack2<DMT_F16>(x[0] * inv, x[1] * inv),
                          dmt::pack2<DMT_F16>(x[2] * inv, x[3] * inv),
                          dmt::pack2<DMT_F16>(x[4] * inv, x[5] * inv),
                          dmt::pack2<DMT_F16>(x[6] * inv, x[7] * inv));
         }
-        if (chunk == 0) s_inv[row] = 1.0f;
+        if (chunk == 0) s_inv[buf][row] = 1.0f;
       }
     }
   };
 
   const int64_t b_begin = blockIdx.x * per, b_end = b_begin + per < B ? b_begin + per : B;
-  if (b_begin < b_end) fetch(b_begin);
-  for (int64_t b = b_begin; b < b_end; ++b) {
-    __syncthreads();                         // the previous sample's rows have been consumed
-    commit();
+  if (b_begin < b_end) {
+    fetch(b_begin);
+    commit(0);
+    if (b_begin + 1 < b_end) fetch(b_begin + 1);
+  }
+  int buf = 0;
+  for (int64_t b = b_begin; b < b_end; ++b, buf ^= 1) {
+    // (this sample's rows are in LDS, and every wave is done with the other buffer's)
     __syncthreads();
-    if (b + 1 < b_end) fetch(b + 1);
+    const uint16_t* const rows = lds + buf * stage;
+    const float* const inv = s_inv[buf];
 #pragma unroll
     for (int q = 0; q < kWideSub; ++q) {
       if (wave + 16 * q < nsub) {            // uniform over the wave
@@ -410,8 +421,8 @@ __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
         for (int k = 0; k < npad; k += 16) {
-          const uint4 a = *(const uint4*)(lds + oa[q] + k);
-          const uint4 c = *(const uint4*)(lds + ob[q] + k);
+          const uint4 a = *(const uint4*)(rows + oa[q] + k);
+          const uint4 c = *(const uint4*)(rows + ob[q] + k);
           if constexpr (DT == DMT_BF16)
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
                                                           __builtin_bit_cast(bf16x8, c), acc, 0, 0, 0);
@@ -419,16 +430,20 @@ __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
             acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a),
                                                          __builtin_bit_cast(halfx8, c), acc, 0, 0, 0);
         }
-        const float ic = s_inv[ic_off[q]];
+        const float ic = inv[ic_off[q]];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float4 ir = *(const float4*)(s_inv + ir_off[q] + j * 8);
+          const float4 ir = *(const float4*)(inv + ir_off[q] + j * 8);
           total[q][4 * j + 0] += acc[4 * j + 0] * (ir.x * ic);
           total[q][4 * j + 1] += acc[4 * j + 1] * (ir.y * ic);
           total[q][4 * j + 2] += acc[4 * j + 2] * (ir.z * ic);
           total[q][4 * j + 3] += acc[4 * j + 3] * (ir.w * ic);
         }
       }
+    }
+    if (b + 1 < b_end) {
+      commit(buf ^ 1);
+      if (b + 2 < b_end) fetch(b + 2);
     }
   }
 
@@ -551,14 +566,14 @@ template <int DT, int NP>
 void launch_gram_wide(const dmt_plan* p, const void* pooled, int64_t B, const TpShape& sh,
                       float* partial, hipStream_t s) {
   const int npad = (sh.N + 15) & ~15;
-  const size_t lds = sizeof(uint16_t) * kWideRows * (npad + 8);
-  static bool configured = false;
-  if (!configured) {
-    (void)hipFuncSetAttribute((const void*)tp_gram_wide<DT, NP>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)(sizeof(uint16_t) * kWideRows * (NP * 32 + 8)));
-    configured = true;
-  }
+  const size_t lds = 2 * sizeof(uint16_t) * kWideRows * (npad + 8);
+  static DmtPerDevice configured;
+  int dev = -1;
+  (void)hipGetDevice(&dev);
+  if (configured.needed(dev) &&
+      hipFuncSetAttribute((const void*)tp_gram_wide<DT, NP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)(2 * sizeof(uint16_t) * kWideRows * (NP * 32 + 8))) == hipSuccess)
+    configured.set(dev);
   hipLaunchKernelGGL((tp_gram_wide<DT, NP>), dim3((unsigned)sh.nslices), dim3(kWideThreads), lds, s,
                      p->d_meta, pooled, B, p->F, sh.N, sh.nt, sh.npairs, sh.per, partial);
 }
