@@ -75,9 +75,12 @@ struct TmGroup {
   // Two-level output rows: with rdiv > 0 row m of C starts at (m / rdiv) * ldc + (m % rdiv) * ldc2,
   // i.e. rdiv consecutive rows of the contraction share one row of the output tensor.
   int32_t rdiv, ldc2;
+  // reps > 1 (no split K): so many contractions that differ in where A1, W0 (elements) and C (cstride
+  // floats) start: a per-feature layer's.  They take the place of the slices.
+  int32_t reps, a1_step, w0_step;
 };
 
-__host__ __device__ inline int tm_slices(const TmGroup& g) { return g.ksplit > 1 ? g.ksplit : 1; }
+__host__ __device__ inline int tm_slices(const TmGroup& g) { return g.ksplit > 1 ? g.ksplit : g.reps > 1 ? g.reps : 1; }
 // The first k behind the slice that starts at kofs < K1.  (kofs + klen may lie up to a K step per slice past
 // K1, which itself may be next to 2^31.)
 __host__ __device__ inline int tm_slice_end(int K1, int kofs, int klen) {
@@ -292,7 +295,7 @@ struct TmFrag {
 __device__ __forceinline__ bool tm_whole(const TmGroup& g) {
   // (no short circuits: the fields are read together)
   const uint64_t c = (uint64_t)g.C, x = (uint64_t)g.X0 | (uint64_t)g.XL | (uint64_t)g.U;
-  const bool f32 = ((g.N | g.ldc) & 3) == 0 & g.rdiv == 0 & (c & 15) == 0 & (g.ksplit <= 1 | (g.cstride & 3) == 0);
+  const bool f32 = ((g.N | g.ldc) & 3) == 0 & g.rdiv == 0 & (c & 15) == 0 & (tm_slices(g) <= 1 | (g.cstride & 3) == 0);
   const bool b16 = ((g.N | g.ldc | g.ldc2) & 7) == 0 & ((c | (uint64_t)g.bias) & 15) == 0;
   const bool cross = ((g.ldx | g.ldxl) & 7) == 0 & (x & 15) == 0;
   return g.epi == EPI_CROSS_GRAD | (g.epi >= EPI_F32 ? f32 : b16 & (g.epi != EPI_CROSS | cross));
@@ -403,12 +406,12 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
     if (second) {
       const int kofs = G.ksplit > 1 ? ahead.slice * G.klen : 0;
       left = (G.ksplit > 1 ? tm_slice_end(G.K1, kofs, G.klen) : G.K1) - kofs;
-      sa.init(G.A1, G.lda1, ahead.m0, G.M, kofs, wave, lane);
+      sa.init((const uint16_t*)G.A1 + (int64_t)ahead.slice * G.a1_step, G.lda1, ahead.m0, G.M, kofs, wave, lane);
       sw.init(G.W1, G.ldw1, ahead.n0, G.N, kofs, wave, lane);
     } else {                                       // (in-kernel dot terms: A comes from the block itself)
       left = G.K0;
       if constexpr (!DOTS) sa.init(G.A0, G.lda0, ahead.m0, G.M, 0, wave, lane);
-      sw.init(G.W0, G.ldw0, ahead.n0, G.N, 0, wave, lane);
+      sw.init((const uint16_t*)G.W0 + (int64_t)ahead.slice * G.w0_step, G.ldw0, ahead.n0, G.N, 0, wave, lane);
     }
   };
   // The next K step of the stream.  (The launch makes sure that a block with several tiles is never more
