@@ -45,6 +45,20 @@ constexpr int kMaxRadix = 1 << kMaxRadixBits;
 constexpr int kWideRadixBits = 10;
 constexpr int64_t kWideNnz = 1 << 19;
 constexpr int kSortTile = kBlock * kSortItems;   // records per sort block
+// Records a thread of a sort block ranks, one after another, in calls that sort in wide digits.  Such a call
+// does not fill the chip and is bound by that chain of ballots, so blocks are as small as two records a
+// thread while a table has 64 blocks on average and a call 256 of full tables: a block reads the digit
+// counts of all of its table's.  Whole update, us, blocks of 2048 / smaller ones: 8 tables of 16 K
+// lookups 115.8 / 110.5 (1024 records), one of 32 K 50.2 / 45.4 (512), 4 of 32 K 112.3 / 111.6; past the line 2 of
+// 123 K 119.3 / 123.1, one of 127 K 80.6 / 98.9.
+constexpr int kTableBlocks = 64;
+constexpr int64_t kWideBlocks = kWideNnz / kSortTile;
+inline int wide_items(int64_t nnz, int F) {
+  const int64_t per_table = (nnz + F - 1) / F;
+  const int64_t items = std::max((nnz + kBlock * kWideBlocks - 1) / (kBlock * kWideBlocks),
+                                 (per_table + kBlock * kTableBlocks - 1) / (kBlock * kTableBlocks));
+  return (int)std::min<int64_t>(kSortItems, std::max<int64_t>(2, items));
+}
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kBlock * kScanItems;   // records per head-scan block
 // Sorted records per reduce tile (one wave walks one): 128, or down to 16 where a call is too small
@@ -82,6 +96,7 @@ struct BwdWs {
   int64_t nblk_sort, nblk_scan, ntiles;
   int tile;               // records per reduce tile
   bool wide;              // sort in wide digits
+  int sort_items;         // records per thread of a sort block
 };
 
 BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
@@ -105,7 +120,8 @@ BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
   w.pk_b = (uint64_t*)take(sizeof(uint64_t) * n);
   w.seg_begin = (uint32_t*)take(sizeof(uint32_t) * (p->F + 1));
   w.seg_blk = (uint32_t*)take(sizeof(uint32_t) * (p->F + 1));
-  w.blk_table = (uint32_t*)take(sizeof(uint32_t) * w.nblk_sort);
+  // (never less room for more lookups: a workspace sized for the largest call serves all of them)
+  w.blk_table = (uint32_t*)take(sizeof(uint32_t) * std::max(w.nblk_sort, std::min((n + 2 * kBlock - 1) / (2 * kBlock), kWideBlocks + 1) + p->F));
   w.blk_heads = (uint32_t*)take(sizeof(uint32_t) * (w.nblk_scan + 1));
   w.num_unique = (uint32_t*)take(sizeof(uint32_t) * 64);
   // The sort is done with its counts before seg_off and partials are written, so wide counts may lie
@@ -121,6 +137,15 @@ BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
   w.partials = (float*)take(sizeof(float) * 2 * slots * p->max_dim);
   w.bytes = off;
   w.wide = n <= kWideNnz && (sizeof(uint32_t) << kWideRadixBits) * w.nblk_sort <= off - hist_at;
+  // smaller sort blocks as far as their counts have room
+  w.sort_items = kSortItems;
+  for (int items = wide_items(n, p->F); w.wide && items < kSortItems; ++items) {
+    const int64_t nblk = (n + items * kBlock - 1) / (items * kBlock) + p->F;
+    if ((sizeof(uint32_t) << kWideRadixBits) * nblk > off - hist_at) continue;
+    w.sort_items = items;
+    w.nblk_sort = nblk;
+    break;
+  }
   return w;
 }
 
@@ -130,8 +155,8 @@ BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
 // The starts come from the offsets of every table's first bag, made ascending and clamped to
 // [0, nnz], so that blocks stay inside the record array whatever `offsets` holds.
 __device__ void build_sort_map(const int64_t* __restrict__ offsets, uint32_t B, int F, int64_t nnz,
-                               uint32_t* __restrict__ seg_begin, uint32_t* __restrict__ seg_blk,
-                               uint32_t* __restrict__ blk_table) {
+                               uint32_t sort_tile, uint32_t* __restrict__ seg_begin,
+                               uint32_t* __restrict__ seg_blk, uint32_t* __restrict__ blk_table) {
   __shared__ uint32_t sm[kBlock / 64];
   __shared__ uint32_t s_first[kBlock], s_nb[kBlock];
   uint32_t rec_run = 0, blk_run = 0;
@@ -149,7 +174,7 @@ __device__ void build_sort_map(const int64_t* __restrict__ offsets, uint32_t B, 
     rec_run += total;
     begin = begin > (uint32_t)nnz ? (uint32_t)nnz : begin;
     const uint32_t end = begin + len > (uint32_t)nnz ? (uint32_t)nnz : begin + len;
-    const uint32_t nb = (end - begin + kSortTile - 1) / kSortTile;
+    const uint32_t nb = (end - begin + sort_tile - 1) / sort_tile;
     const uint32_t first = blk_run + dmt::block_exclusive_scan<kBlock / 64>(nb, sm, total);
     blk_run += total;
     if (f < F) {
@@ -178,11 +203,11 @@ constexpr int kKeysMaxBags = 1024;
 __global__ __launch_bounds__(kBlock) void bwd_build_keys(
     const DmtTableMeta* __restrict__ meta, const int32_t* __restrict__ indices,
     const int64_t* __restrict__ offsets, uint32_t B, uint32_t nbags, int64_t nnz, int F,
-    uint64_t* __restrict__ pk, int log2_bpb, uint32_t* __restrict__ seg_begin,
+    uint64_t* __restrict__ pk, int log2_bpb, uint32_t sort_tile, uint32_t* __restrict__ seg_begin,
     uint32_t* __restrict__ seg_blk, uint32_t* __restrict__ blk_table,
     unsigned long long* __restrict__ err, unsigned long long* __restrict__ err_offsets) {
   __shared__ int64_t offs[kKeysMaxBags + 1];
-  if (blockIdx.x == 0) build_sort_map(offsets, B, F, nnz, seg_begin, seg_blk, blk_table);
+  if (blockIdx.x == 0) build_sort_map(offsets, B, F, nnz, sort_tile, seg_begin, seg_blk, blk_table);
   const uint32_t g0 = blockIdx.x << log2_bpb;
   if (g0 >= nbags) return;
   const int nb = (int)min((uint32_t)(1 << log2_bpb), nbags - g0);
@@ -230,16 +255,17 @@ struct SortBlock {
 __device__ __forceinline__ SortBlock sort_block(const DmtTableMeta* __restrict__ meta,
                                                 const uint32_t* __restrict__ seg_begin,
                                                 const uint32_t* __restrict__ seg_blk,
-                                                const uint32_t* __restrict__ blk_table, int F) {
+                                                const uint32_t* __restrict__ blk_table, int F,
+                                                uint32_t sort_tile) {
   SortBlock sb{0, 0, 0, 0, 0, 0, 0};
   if (blockIdx.x >= seg_blk[F]) return sb;
   const uint32_t f = blk_table[blockIdx.x];
   sb.table_base = seg_begin[f];
   sb.at = blockIdx.x - seg_blk[f];
   sb.nb = seg_blk[f + 1] - seg_blk[f];
-  sb.base = sb.table_base + sb.at * (uint32_t)kSortTile;
+  sb.base = sb.table_base + sb.at * sort_tile;
   const uint32_t end = seg_begin[f + 1];
-  sb.n = end - sb.base < (uint32_t)kSortTile ? end - sb.base : (uint32_t)kSortTile;
+  sb.n = end - sb.base < sort_tile ? end - sb.base : sort_tile;
   sb.row_base = (uint32_t)meta[f].row_base;
   sb.valid = 1;
   return sb;
@@ -255,10 +281,10 @@ template <int MaxBits>
 __global__ __launch_bounds__(kBlock) void radix_hist(
     const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ pk, int shift, int bits,
     uint32_t* __restrict__ hist, const uint32_t* __restrict__ seg_begin,
-    const uint32_t* __restrict__ seg_blk, const uint32_t* __restrict__ blk_table, int F) {
+    const uint32_t* __restrict__ seg_blk, const uint32_t* __restrict__ blk_table, int F, int sort_items) {
   constexpr int MaxRadix = 1 << MaxBits;
   __shared__ uint32_t h[MaxRadix];
-  const SortBlock sb = sort_block(meta, seg_begin, seg_blk, blk_table, F);
+  const SortBlock sb = sort_block(meta, seg_begin, seg_blk, blk_table, F, (uint32_t)(sort_items * kBlock));
   if (!sb.valid) return;
   for (int d = threadIdx.x; d < MaxRadix; d += kBlock) h[d] = 0;
   __syncthreads();
@@ -335,7 +361,7 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
     const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ in,
     uint64_t* __restrict__ out, int shift, int bits, const uint32_t* __restrict__ hist,
     const uint32_t* __restrict__ seg_begin, const uint32_t* __restrict__ seg_blk,
-    const uint32_t* __restrict__ blk_table, int F) {
+    const uint32_t* __restrict__ blk_table, int F, int sort_items) {
   __shared__ uint64_t buf[kSortTile];
   constexpr int MaxRadix = 1 << MaxBits, DPT = (MaxRadix + kBlock - 1) / kBlock;
   __shared__ uint32_t cnt[kBlock / 64][MaxRadix];
@@ -345,7 +371,8 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int radix = 1 << bits;
   const uint32_t mask = (uint32_t)radix - 1;
-  const SortBlock sb = sort_block(meta, seg_begin, seg_blk, blk_table, F);
+  const int items = OwnScan ? sort_items : kSortItems;   // (narrow digits: full blocks)
+  const SortBlock sb = sort_block(meta, seg_begin, seg_blk, blk_table, F, (uint32_t)(items * kBlock));
   if (!sb.valid) return;
   for (int w = 0; w < kBlock / 64; ++w)
     for (int d = tid; d < MaxRadix; d += kBlock) cnt[w][d] = 0;
@@ -360,7 +387,8 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
   uint32_t rank[kSortItems];
 #pragma unroll
   for (int i = 0; i < kSortItems; ++i) {
-    const int q = wave * (kSortItems * 64) + i * 64 + lane;
+    if (i >= items) break;
+    const int q = wave * (items * 64) + i * 64 + lane;
     const bool valid = q < n_tile;
     rec[i] = valid ? in[tile_base + q] : ~0ULL;
     const uint32_t d = sort_digit(rec[i], sb.row_base, shift, mask);
@@ -449,7 +477,8 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kSortItems; ++i) {
-    const int q = wave * (kSortItems * 64) + i * 64 + lane;
+    if (i >= items) break;
+    const int q = wave * (items * 64) + i * 64 + lane;
     if (q < n_tile) {
       const uint32_t d = sort_digit(rec[i], sb.row_base, shift, mask);
       buf[tile_start[d] + cnt[wave][d] + rank[i]] = rec[i];
@@ -1677,7 +1706,7 @@ static dmt_status bwd_update_run(const dmt_plan* plan, const int32_t* indices,
     log2_bpb = log2_bpb < 4 ? 4 : (log2_bpb > 10 ? 10 : log2_bpb);
     const int64_t key_blocks = ((int64_t)nbags + (1 << log2_bpb) - 1) >> log2_bpb;
     timed_launch(plan, DMT_K_BWD_KEYS, s, bwd_build_keys, key_blocks, kBlock, plan->d_meta, indices,
-                 offsets, (uint32_t)B, nbags, nnz, (int)plan->F, w.pk_a, log2_bpb, w.seg_begin,
+                 offsets, (uint32_t)B, nbags, nnz, (int)plan->F, w.pk_a, log2_bpb, (uint32_t)(w.sort_items * kBlock), w.seg_begin,
                  w.seg_blk, w.blk_table, plan->row_shards ? nullptr : plan->d_error, plan->d_error + 1);
 
     // stable LSD radix sort inside every table over the bits a row id of the largest table
@@ -1695,14 +1724,14 @@ static dmt_status bwd_update_run(const dmt_plan* plan, const int32_t* indices,
       const int bits = std::min(bits_per, key_bits - shift);
       timed_launch(plan, DMT_K_BWD_SORT_HIST, s, w.wide ? radix_hist<kWideRadixBits> : radix_hist<kMaxRadixBits>,
                    w.nblk_sort, kBlock, plan->d_meta, src, shift, bits, w.hist, w.seg_begin, w.seg_blk,
-                   w.blk_table, (int)plan->F);
+                   w.blk_table, (int)plan->F, w.sort_items);
       if (!w.wide)
         timed_launch(plan, DMT_K_BWD_SORT_SCAN, s, radix_scan, plan->F, kScanThreads, w.hist, bits,
                      w.seg_begin, w.seg_blk);
       timed_launch(plan, DMT_K_BWD_SORT_SCATTER, s,
                    w.wide ? radix_scatter<kWideRadixBits, true> : radix_scatter<kMaxRadixBits, false>,
                    w.nblk_sort, kBlock, plan->d_meta, src, dst, shift, bits, w.hist, w.seg_begin, w.seg_blk,
-                   w.blk_table, (int)plan->F);
+                   w.blk_table, (int)plan->F, w.sort_items);
       std::swap(src, dst);
     }
     sorted = src;

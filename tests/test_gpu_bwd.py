@@ -325,3 +325,30 @@ def test_every_lookup_hits_the_same_row():
 def test_every_lookup_hits_a_different_row():
     # no duplicates at all: every run has length one
     _degenerate(lambda n: np.arange(n) % 1920 + (np.arange(n) // 1920) * 0)
+
+
+@pytest.mark.parametrize("tables,batch,length", [(1, 64, 9), (1, 520, 63), (3, 129, 16), (3, 511, 33), (8, 257, 8),
+                                                 (2, 1030, 64), (26, 300, 13)])
+def test_sort_blocks_of_every_size(tables, batch, length):
+    """Sort blocks of 512 to 2048 records (two to eight a thread), tables that end inside, at and past a block's
+    edge: the sorted order against a stable sort of the ids."""
+    import paper_2403_00877_amd as dmt
+    rows, dim, nnz = [5000 + 37 * f for f in range(tables)], 8, tables * batch * length
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tables)
+    idx = torch.cat([torch.randint(0, r, (batch * length,), generator=g, device="cuda") for r in rows]).to(torch.int32)
+    off = torch.arange(tables * batch + 1, device="cuda") * length
+    tabs = [torch.zeros(r, dim, device="cuda") for r in rows]
+    states = [torch.zeros(r, device="cuda") for r in rows]
+    plan = dmt.dmt_plan_create(rows, [dim] * tables, "f32", 1, [0] * tables, batch, nnz)
+    dmt.dmt_plan_bind(plan, tabs, states)
+    grad = torch.randn(batch * tables * dim, generator=g, device="cuda")
+    ws = torch.empty(dmt.dmt_bwd_workspace_bytes(plan, batch, nnz), dtype=torch.uint8, device="cuda")
+    keys = torch.empty(nnz, dtype=torch.int64, device="cuda")
+    bags = torch.empty(nnz, dtype=torch.int32, device="cuda")
+    dmt.dmt_tower_lookup_bwd_update(plan, idx, off, batch, grad, 0.01, 1e-8, ws,
+                                    debug=dict(sorted_keys=keys, sorted_bag=bags))
+    table = torch.arange(tables, device="cuda").repeat_interleave(batch * length)
+    ref, order = torch.sort((table << 32) | idx.to(torch.int64), stable=True)
+    assert torch.equal(keys, ref)
+    assert torch.equal(bags.to(torch.int64), order // length)
