@@ -91,6 +91,7 @@ struct TmLaunch {
   int32_t ngroups;
   int32_t super;                       // tiles of a super-tile (dealt to one XCD), at most
   int32_t cap;                         // block slots of a super-tile
+  int32_t slots;                       // of an XCD
   int32_t stream;                      // more output than the caches keep
   int32_t stagger;                     // how far apart the XCDs start, in sleeps of 4096 cycles
   int32_t tile_start[kMaxGroups + 1];  // first super-tile of each group
@@ -358,9 +359,9 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
   // A grid smaller than the launch's slots works through them a grid at a time, in the same order.
   int slot = blockIdx.x >> 3;
   auto locate = [&](TmWork& w) __attribute__((always_inline)) {      // this block's next tile, if there is one
-    for (;; slot += gridDim.x >> 3) {
+    for (; slot < L.slots; slot += gridDim.x >> 3) {
       const int gs = (slot / L.cap) * 8 + (blockIdx.x & 7), within = slot % L.cap;
-      if (gs >= L.tile_start[L.ngroups]) return false;
+      if (gs >= L.tile_start[L.ngroups]) continue;
       int gi = 0;
       while (gi + 1 < L.ngroups && gs >= L.tile_start[gi + 1]) ++gi;
       const TmGroup& G = L.g[gi];
@@ -376,6 +377,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
       slot += gridDim.x >> 3;
       return true;
     }
+    return false;
   };
   // Blocks that work through several tiles of cross layers start a little apart, XCD by XCD: their epilogues,
   // bound by memory, then meet other XCDs' matrix work instead of one another's.  (Cross layer of 2048
@@ -466,7 +468,6 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
   if (kn > 0)
 #pragma clang loop unroll(full)
     for (int q = 0; q < kEarly; ++q) request(q);
-  measure();
   {
     if constexpr (DOTS) {
       const TmGroup& G = L.g[work.gi];
@@ -551,7 +552,9 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       const int np = G.nf * (G.nf - 1) / 2;
       if ((const uint16_t*)G.W0 + np == G.W1) sw.zero_from(lds + TILE * BK, np, wave, lane);
+      measure();
     } else {
+      measure();
       // vmcnt: this wave's requests of the first step have landed
       if (kn > 0) __builtin_amdgcn_s_waitcnt(0x0f70 + kEarly);
       else __builtin_amdgcn_s_waitcnt(0x0f70);
@@ -1283,6 +1286,7 @@ void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t 
     L.tile_start[L.ngroups] = (int32_t)nst;
     int64_t blocks = (nst + 7) / 8 * 8 * L.cap;
     if (blocks == 0) continue;
+    L.slots = (int32_t)(blocks / 8);
     // 128 MB of outputs: half of what the Infinity Cache holds.  (Streamed, the 34 MB of a split weight
     // gradient's slices took 41 instead of 31 us to add up; kept, 1.1 GB of data gradients take 1042
     // instead of 1026 us.)
