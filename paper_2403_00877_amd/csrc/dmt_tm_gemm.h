@@ -419,7 +419,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
   // The next K step of the stream.  (The launch makes sure that a block with several tiles is never more
   // than one of them ahead: their K is two steps or more.)
   auto aim = [&]() __attribute__((always_inline)) {
-    if (left <= 0) {
+    if (__builtin_expect(left <= 0, 0)) {        // (out of the loop's way: 23.7 -> 23.0 us where a K step waits for memory)
       if (!flat) begin(true);
       else if (locate(ahead)) begin(L.g[ahead.gi].K0 == 0);
     }
@@ -442,10 +442,11 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
   ra.init(wm * T::MT * 16, lane);
   rw.init(wn * T::NT * 16, lane);
   constexpr int kRows = BK / 32 * T::MT, kAhead = 3;                 // rows of MFMAs in a K step
-  // Requests per row, and how many the rows behind the barrier hold: all of them in 128 x 128 tiles, whose K
-  // steps are half as long and whose launches wait for memory (spread further, a projection of 512
-  // outputs on 8 towers, batch 3001, took 69.8 instead of 66.7 us).
-  constexpr int kPerRow = TILE == 256 ? 1 : 4, kEarly = min_int(kReqs, kAhead * kPerRow);
+  // Requests per row, and how many the rows behind the barrier hold.  128 x 128 tiles: all of them right behind
+  // it, ahead of the row's LDS reads.  Their K steps are half as long and their launches wait for memory: two per row,
+  // a projection of 512 outputs on 8 towers, batch 3001, took 69.8 instead of 66.7 us.
+  constexpr bool kBurst = TILE != 256;
+  constexpr int kPerRow = kBurst ? kReqs : 1, kEarly = min_int(kReqs, kAhead * kPerRow);
   static_assert((kReqs - kEarly + kPerRow - 1) / kPerRow < kRows - kAhead - 2, "");
   uint4 fa[4], fw[2][T::NT];
 
@@ -618,6 +619,13 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
           __syncthreads();
         }
         if (r == kRows - kAhead - 2) aim();
+        auto requests = [&]() __attribute__((always_inline)) {
+          if (kn > 0)
+#pragma clang loop unroll(full)
+            for (int q = 0; q < kReqs; ++q)
+              if ((q < kEarly ? kRows - kAhead + q / kPerRow : (q - kEarly) / kPerRow) == r) request(q);
+        };
+        if (kBurst) requests();
         if (r + kAhead < kRows) {
           fa[(r + kAhead) % 4] = ra.read(tile, (r + kAhead) / T::MT, (r + kAhead) % T::MT);
         } else {
@@ -629,10 +637,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
 #pragma clang loop unroll(full)
         for (int j = 0; j < T::NT; ++j)
           if ((TILE == 256 ? j + 1 : j / 2) == r) fw[1][j] = rw.read(tile + TILE * BK, 1, j);
-        if (kn > 0)
-#pragma clang loop unroll(full)
-          for (int q = 0; q < kReqs; ++q)
-            if ((q < kEarly ? kRows - kAhead + q / kPerRow : (q - kEarly) / kPerRow) == r) request(q);
+        if (!kBurst) requests();
 #pragma clang loop unroll(full)
         for (int jj = 0; jj < T::NT; ++jj) {
           const int j = i & 1 ? T::NT - 1 - jj : jj;
@@ -664,8 +669,14 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
       wave_sync();
     };
     auto get = [&](int r, int c) __attribute__((always_inline)) { return turn[r * 16 + (c ^ r)]; };
-    // (outputs that the caches will not keep until they are read do not push the operands out)
+    // (what the caches would not keep until it is used again does not push the operands out; what they would
+    // keep must not be streamed: a backward of 500 samples found its pooled values gone, and took 27 -> 34 us
+    // for its first contractions)
     const bool stream = L.stream;
+    auto take = [&](auto* p) __attribute__((always_inline)) {
+      if (stream) return dmt::nt_load(p);
+      return dmt::gload(p);
+    };
     auto put_out = [&](auto v, auto* p) __attribute__((always_inline)) {
       if (stream) dmt::nt_store(v, p);
       else dmt::gstore(v, p);
@@ -692,8 +703,8 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
       auto fetch = [&](int e) __attribute__((always_inline)) {
         // (rows and columns past the edge read in bounds and are not stored)
         const uint32_t m = (uint32_t)min(wrow + e * 8 + r8, M - 1 - m0), cc = on ? (uint32_t)c : 0u;
-        pa[e % kDeep] = dmt::nt_load((const uint4*)(xbase + (m * (uint32_t)G.ldx + cc) * 2u));
-        pb[e % kDeep] = dmt::nt_load((const uint4*)(lbase + (m * (uint32_t)G.ldxl + cc) * 2u));
+        pa[e % kDeep] = take((const uint4*)(xbase + (m * (uint32_t)G.ldx + cc) * 2u));
+        pb[e % kDeep] = take((const uint4*)(lbase + (m * (uint32_t)G.ldxl + cc) * 2u));
       };
       if (cross)
 #pragma clang loop unroll(full)
@@ -748,10 +759,10 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
         float4 old[kDeep];
         if (add)
 #pragma clang loop unroll(full)
-          for (int e = 0; e < kDeep - 1; ++e) old[e] = dmt::nt_load((const float4*)(cbase + place(e) * 4u));
+          for (int e = 0; e < kDeep - 1; ++e) old[e] = take((const float4*)(cbase + place(e) * 4u));
 #pragma clang loop unroll(full)
         for (int e = 0; e < kAll; ++e) {
-          if (add && e + kDeep - 1 < kAll) old[(e + kDeep - 1) % kDeep] = dmt::nt_load((const float4*)(cbase + place(e + kDeep - 1) * 4u));
+          if (add && e + kDeep - 1 < kAll) old[(e + kDeep - 1) % kDeep] = take((const float4*)(cbase + place(e + kDeep - 1) * 4u));
           if (e % 4 == 0) put(e / 4);
           const floatx4 s = get(e % 4 * 4 + r4, ln & 15);
           float4 g = make_float4(s[0], s[1], s[2], s[3]);
@@ -772,12 +783,12 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
         uint2 px[kDeep], pu[kDeep], pv[kDeep];
         auto fetch = [&](int e) __attribute__((always_inline)) {
           const uint32_t at = place(e);
-          px[e % kDeep] = dmt::nt_load((const uint2*)(x0 + at * 2u));
+          px[e % kDeep] = take((const uint2*)(x0 + at * 2u));
           if (has_gn) {
-            pg[e % kDeep] = dmt::nt_load((const float4*)(gn + at * 4u));
-            pu[e % kDeep] = dmt::nt_load((const uint2*)(ul + at * 2u));
+            pg[e % kDeep] = take((const float4*)(gn + at * 4u));
+            pu[e % kDeep] = take((const uint2*)(ul + at * 2u));
           }
-          if (has_u0) pv[e % kDeep] = dmt::nt_load((const uint2*)(u0 + at * 2u));
+          if (has_u0) pv[e % kDeep] = take((const uint2*)(u0 + at * 2u));
         };
         float4 sums = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma clang loop unroll(full)
@@ -794,7 +805,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
             float v0, v1, v2, v3;
             if (has_gn || has_u0) {
               float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-              if (acc_old) t = dmt::nt_load((const float4*)(a0 + at * 4u));      // (three layers and more)
+              if (acc_old) t = take((const float4*)(a0 + at * 4u));      // (three layers and more)
               if (has_gn) {
                 const float4 n = pg[b];
                 g.x += n.x; g.y += n.y; g.z += n.z; g.w += n.w;
