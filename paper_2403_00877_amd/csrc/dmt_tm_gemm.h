@@ -419,7 +419,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
   // The next K step of the stream.  (The launch makes sure that a block with several tiles is never more
   // than one of them ahead: their K is two steps or more.)
   auto aim = [&]() __attribute__((always_inline)) {
-    if (__builtin_expect(left <= 0, 0)) {        // (out of the loop's way: 23.7 -> 23.0 us where a K step waits for memory)
+    if (left <= 0) {
       if (!flat) begin(true);
       else if (locate(ahead)) begin(L.g[ahead.gi].K0 == 0);
     }
@@ -781,14 +781,15 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
         const bool has_gn = G.GN, has_u0 = G.U0, has_c = G.C, acc_old = !G.acc_first;
         float4 pg[kDeep];
         uint2 px[kDeep], pu[kDeep], pv[kDeep];
+        // (plain loads at every size: the choice of take() costs the 256 x 256 instance 20 bytes of scratch a lane)
         auto fetch = [&](int e) __attribute__((always_inline)) {
           const uint32_t at = place(e);
-          px[e % kDeep] = take((const uint2*)(x0 + at * 2u));
+          px[e % kDeep] = dmt::gload((const uint2*)(x0 + at * 2u));
           if (has_gn) {
-            pg[e % kDeep] = take((const float4*)(gn + at * 4u));
-            pu[e % kDeep] = take((const uint2*)(ul + at * 2u));
+            pg[e % kDeep] = dmt::gload((const float4*)(gn + at * 4u));
+            pu[e % kDeep] = dmt::gload((const uint2*)(ul + at * 2u));
           }
-          if (has_u0) pv[e % kDeep] = take((const uint2*)(u0 + at * 2u));
+          if (has_u0) pv[e % kDeep] = dmt::gload((const uint2*)(u0 + at * 2u));
         };
         float4 sums = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma clang loop unroll(full)
@@ -805,7 +806,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
             float v0, v1, v2, v3;
             if (has_gn || has_u0) {
               float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-              if (acc_old) t = take((const float4*)(a0 + at * 4u));      // (three layers and more)
+              if (acc_old) t = dmt::gload((const float4*)(a0 + at * 4u));      // (three layers and more)
               if (has_gn) {
                 const float4 n = pg[b];
                 g.x += n.x; g.y += n.y; g.z += n.z; g.w += n.w;
