@@ -24,130 +24,9 @@
 
 #include "dmt_internal.h"
 #include "dmt_device_utils.h"
+#include "dmt_bwd_plan.h"
 
 namespace {
-
-constexpr int kBlock = 256;
-#ifndef DMT_SORT_ITEMS
-#define DMT_SORT_ITEMS 8
-#endif
-#ifndef DMT_RADIX_BITS
-#define DMT_RADIX_BITS 8
-#endif
-constexpr int kSortItems = DMT_SORT_ITEMS;
-constexpr int kMaxRadixBits = DMT_RADIX_BITS;      // digit width of one sort pass
-constexpr int kMaxRadix = 1 << kMaxRadixBits;
-// A call of up to kWideNnz lookups is bound by its launches, not by bytes: it sorts in digits of up to
-// 10 bits, and the scatter's blocks add up the digit counts of their table's other blocks themselves, so
-// a pass is two launches instead of three and there are fewer passes (18 bits of row id: 4 launches
-// instead of 9).  The counts a block reads grow with its table's blocks, which is what the limit is for:
-// at kWideNnz lookups, all in one table, a block reads 256 lines of 4 KB.
-constexpr int kWideRadixBits = 10;
-constexpr int64_t kWideNnz = 1 << 19;
-constexpr int kSortTile = kBlock * kSortItems;   // records per sort block
-// Records a thread of a sort block ranks, one after another, in calls that sort in wide digits.  Such a call
-// does not fill the chip and is bound by that chain of ballots, so blocks are as small as two records a
-// thread while a table has 64 blocks on average and a call 256 of full tables: a block reads the digit
-// counts of all of its table's.  Whole update, us, blocks of 2048 / smaller ones: 8 tables of 16 K
-// lookups 115.8 / 110.5 (1024 records), one of 32 K 50.2 / 45.4 (512), 4 of 32 K 112.3 / 111.6; past the line 2 of
-// 123 K 119.3 / 123.1, one of 127 K 80.6 / 98.9.
-constexpr int kTableBlocks = 64;
-constexpr int64_t kWideBlocks = kWideNnz / kSortTile;
-inline int wide_items(int64_t nnz, int F) {
-  const int64_t per_table = (nnz + F - 1) / F;
-  const int64_t items = std::max((nnz + kBlock * kWideBlocks - 1) / (kBlock * kWideBlocks),
-                                 (per_table + kBlock * kTableBlocks - 1) / (kBlock * kTableBlocks));
-  return (int)std::min<int64_t>(kSortItems, std::max<int64_t>(2, items));
-}
-constexpr int kScanItems = 16;
-constexpr int kScanTile = kBlock * kScanItems;   // records per head-scan block
-// Sorted records per reduce tile (one wave walks one): 128, or down to 16 where a call is too small
-// to fill the chip with tiles of 128.  A wave takes about 0.25 us per record, so 2300 records in
-// tiles of 128 are 18 waves of 30 us (tiles of 16: 7.7); but every run that crosses a tile
-// boundary costs a partial sum and a share of the fix-up, so tiles shrink only until there are
-// fill_tiles of them (four waves per SIMD at 4096, eight at 8192).
-constexpr int kReduceTile = 128, kMinReduceTile = 16;
-inline int64_t fill_tiles(int max_dim) { return max_dim <= 128 ? 8192 : 4096; }
-inline int reduce_tile(int64_t nnz, int max_dim) {
-  int tile = kReduceTile;
-  while (tile > kMinReduceTile && (nnz + tile / 2 - 1) / (tile / 2) <= fill_tiles(max_dim)) tile /= 2;
-  return tile;
-}
-#ifndef DMT_RU
-#define DMT_RU 4
-#endif
-constexpr int kReduceUnroll = DMT_RU;
-constexpr uint32_t kInertBit = 0x80000000u;      // key flag of an id outside its table
-constexpr int kScanThreads = 1024;               // block of the per-table offset scan
-constexpr int kScanBatch = 16;                   // sort blocks whose counts it reads together
-
-struct BwdWs {
-  uint64_t* pk_a;
-  uint64_t* pk_b;
-  uint32_t* hist;         // [nblk_sort][kMaxRadix], or [nblk_sort][1 << kWideRadixBits]
-  uint32_t* seg_begin;    // [F + 1] first record of each table (seg_begin[F] = nnz)
-  uint32_t* seg_blk;      // [F + 1] first sort block of each table
-  uint32_t* blk_table;    // [nblk_sort] table of each sort block
-  uint32_t* blk_heads;    // [nblk_scan]
-  uint32_t* seg_off;      // [nnz + 1]
-  uint32_t* num_unique;   // [1]
-  float* partials;        // [2 * tiles][Dmax]
-  size_t bytes;
-  int64_t nblk_sort, nblk_scan, ntiles;
-  int tile;               // records per reduce tile
-  bool wide;              // sort in wide digits
-  int sort_items;         // records per thread of a sort block
-};
-
-BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
-  BwdWs w;
-  const int64_t n = nnz > 0 ? nnz : 1;
-  w.nblk_sort = (n + kSortTile - 1) / kSortTile + p->F;   // every table may end in a partial block
-  w.nblk_scan = (n + kScanTile - 1) / kScanTile;
-  w.tile = reduce_tile(n, p->max_dim);
-  w.ntiles = (n + w.tile - 1) / w.tile;
-  // partial slots for the tiles of this and of every smaller call (a workspace sized for the largest
-  // serves all of them)
-  const int64_t slots = std::max((n + kReduceTile - 1) / kReduceTile,
-                                 std::min((n + kMinReduceTile - 1) / kMinReduceTile, fill_tiles(p->max_dim)));
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    size_t o = off;
-    off = dmt_align_up(off + bytes, 256);
-    return (char*)((uintptr_t)base + o);          // (base is null when only the size is wanted)
-  };
-  w.pk_a = (uint64_t*)take(sizeof(uint64_t) * n);
-  w.pk_b = (uint64_t*)take(sizeof(uint64_t) * n);
-  w.seg_begin = (uint32_t*)take(sizeof(uint32_t) * (p->F + 1));
-  w.seg_blk = (uint32_t*)take(sizeof(uint32_t) * (p->F + 1));
-  // (never less room for more lookups: a workspace sized for the largest call serves all of them)
-  w.blk_table = (uint32_t*)take(sizeof(uint32_t) * std::max(w.nblk_sort, std::min((n + 2 * kBlock - 1) / (2 * kBlock), kWideBlocks + 1) + p->F));
-  w.blk_heads = (uint32_t*)take(sizeof(uint32_t) * (w.nblk_scan + 1));
-  w.num_unique = (uint32_t*)take(sizeof(uint32_t) * 64);
-  // The sort is done with its counts before seg_off and partials are written, so wide counts may lie
-  // over them.  That is room enough but for few lookups in narrow rows, whose counts get room of their
-  // own unless the tables are many (then the digits stay narrow).  Never less room for more lookups: a
-  // workspace sized for the largest call serves all of them.
-  const size_t hist_at = off;
-  int64_t counts = (int64_t)kMaxRadix * w.nblk_sort;
-  if (p->F <= 64)
-    counts = std::max(counts, (std::min<int64_t>(n, 8 * kSortTile) / kSortTile + 1 + p->F) << kWideRadixBits);
-  w.hist = (uint32_t*)take(sizeof(uint32_t) * counts);
-  w.seg_off = (uint32_t*)take(sizeof(uint32_t) * (n + 1));
-  w.partials = (float*)take(sizeof(float) * 2 * slots * p->max_dim);
-  w.bytes = off;
-  w.wide = n <= kWideNnz && (sizeof(uint32_t) << kWideRadixBits) * w.nblk_sort <= off - hist_at;
-  // smaller sort blocks as far as their counts have room
-  w.sort_items = kSortItems;
-  for (int items = wide_items(n, p->F); w.wide && items < kSortItems; ++items) {
-    const int64_t nblk = (n + items * kBlock - 1) / (items * kBlock) + p->F;
-    if ((sizeof(uint32_t) << kWideRadixBits) * nblk > off - hist_at) continue;
-    w.sort_items = items;
-    w.nblk_sort = nblk;
-    break;
-  }
-  return w;
-}
 
 // ------------------------------------------------------------------ key build
 
@@ -155,7 +34,7 @@ BwdWs carve(const dmt_plan* p, int64_t nnz, void* base) {
 // The starts come from the offsets of every table's first bag, made ascending and clamped to
 // [0, nnz], so that blocks stay inside the record array whatever `offsets` holds.
 __device__ void build_sort_map(const int64_t* __restrict__ offsets, uint32_t B, int F, int64_t nnz,
-                               uint32_t sort_tile, uint32_t* __restrict__ seg_begin,
+                               int least_items, uint32_t* __restrict__ seg_begin,
                                uint32_t* __restrict__ seg_blk, uint32_t* __restrict__ blk_table) {
   __shared__ uint32_t sm[kBlock / 64];
   __shared__ uint32_t s_first[kBlock], s_nb[kBlock];
@@ -174,7 +53,8 @@ __device__ void build_sort_map(const int64_t* __restrict__ offsets, uint32_t B, 
     rec_run += total;
     begin = begin > (uint32_t)nnz ? (uint32_t)nnz : begin;
     const uint32_t end = begin + len > (uint32_t)nnz ? (uint32_t)nnz : begin + len;
-    const uint32_t nb = (end - begin + sort_tile - 1) / sort_tile;
+    const uint32_t items = (uint32_t)table_items(end - begin, least_items);
+    const uint32_t nb = (end - begin + items * kBlock - 1) / (items * kBlock);
     const uint32_t first = blk_run + dmt::block_exclusive_scan<kBlock / 64>(nb, sm, total);
     blk_run += total;
     if (f < F) {
@@ -183,10 +63,11 @@ __device__ void build_sort_map(const int64_t* __restrict__ offsets, uint32_t B, 
     }
     // the tables' block lists are written a wave per table, a block per lane
     s_first[threadIdx.x] = first;
-    s_nb[threadIdx.x] = f < F ? nb : 0u;
+    s_nb[threadIdx.x] = f < F ? nb << 4 | items : 0u;
     __syncthreads();
     for (int q = threadIdx.x >> 6; q < kBlock && f0 + q < F; q += kBlock / 64)
-      for (uint32_t j = threadIdx.x & 63; j < s_nb[q]; j += 64) blk_table[s_first[q] + j] = (uint32_t)(f0 + q);
+      for (uint32_t j = threadIdx.x & 63; j < s_nb[q] >> 4; j += 64)
+        blk_table[s_first[q] + j] = (uint32_t)(f0 + q) << 4 | (s_nb[q] & 15);
     __syncthreads();
   }
   if (threadIdx.x == 0) {
@@ -203,11 +84,11 @@ constexpr int kKeysMaxBags = 1024;
 __global__ __launch_bounds__(kBlock) void bwd_build_keys(
     const DmtTableMeta* __restrict__ meta, const int32_t* __restrict__ indices,
     const int64_t* __restrict__ offsets, uint32_t B, uint32_t nbags, int64_t nnz, int F,
-    uint64_t* __restrict__ pk, int log2_bpb, uint32_t sort_tile, uint32_t* __restrict__ seg_begin,
+    uint64_t* __restrict__ pk, int log2_bpb, int least_items, uint32_t* __restrict__ seg_begin,
     uint32_t* __restrict__ seg_blk, uint32_t* __restrict__ blk_table,
     unsigned long long* __restrict__ err, unsigned long long* __restrict__ err_offsets) {
   __shared__ int64_t offs[kKeysMaxBags + 1];
-  if (blockIdx.x == 0) build_sort_map(offsets, B, F, nnz, sort_tile, seg_begin, seg_blk, blk_table);
+  if (blockIdx.x == 0) build_sort_map(offsets, B, F, nnz, least_items, seg_begin, seg_blk, blk_table);
   const uint32_t g0 = blockIdx.x << log2_bpb;
   if (g0 >= nbags) return;
   const int nb = (int)min((uint32_t)(1 << log2_bpb), nbags - g0);
@@ -251,15 +132,18 @@ __global__ __launch_bounds__(kBlock) void bwd_build_keys(
 struct SortBlock {
   uint32_t base, n, row_base, valid;
   uint32_t table_base, at, nb;   // first record of the table; which of its nb sort blocks this is
+  int items;                     // records per thread (narrow digits: kSortItems)
 };
+template <bool Wide>
 __device__ __forceinline__ SortBlock sort_block(const DmtTableMeta* __restrict__ meta,
                                                 const uint32_t* __restrict__ seg_begin,
                                                 const uint32_t* __restrict__ seg_blk,
-                                                const uint32_t* __restrict__ blk_table, int F,
-                                                uint32_t sort_tile) {
-  SortBlock sb{0, 0, 0, 0, 0, 0, 0};
+                                                const uint32_t* __restrict__ blk_table, int F) {
+  SortBlock sb{0, 0, 0, 0, 0, 0, 0, 0};
   if (blockIdx.x >= seg_blk[F]) return sb;
-  const uint32_t f = blk_table[blockIdx.x];
+  const uint32_t packed = blk_table[blockIdx.x], f = packed >> 4;
+  sb.items = Wide ? (int)(packed & 15) : kSortItems;
+  const uint32_t sort_tile = (uint32_t)(sb.items * kBlock);
   sb.table_base = seg_begin[f];
   sb.at = blockIdx.x - seg_blk[f];
   sb.nb = seg_blk[f + 1] - seg_blk[f];
@@ -281,10 +165,10 @@ template <int MaxBits>
 __global__ __launch_bounds__(kBlock) void radix_hist(
     const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ pk, int shift, int bits,
     uint32_t* __restrict__ hist, const uint32_t* __restrict__ seg_begin,
-    const uint32_t* __restrict__ seg_blk, const uint32_t* __restrict__ blk_table, int F, int sort_items) {
+    const uint32_t* __restrict__ seg_blk, const uint32_t* __restrict__ blk_table, int F) {
   constexpr int MaxRadix = 1 << MaxBits;
   __shared__ uint32_t h[MaxRadix];
-  const SortBlock sb = sort_block(meta, seg_begin, seg_blk, blk_table, F, (uint32_t)(sort_items * kBlock));
+  const SortBlock sb = sort_block<MaxBits == kWideRadixBits>(meta, seg_begin, seg_blk, blk_table, F);
   if (!sb.valid) return;
   for (int d = threadIdx.x; d < MaxRadix; d += kBlock) h[d] = 0;
   __syncthreads();
@@ -361,7 +245,7 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
     const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ in,
     uint64_t* __restrict__ out, int shift, int bits, const uint32_t* __restrict__ hist,
     const uint32_t* __restrict__ seg_begin, const uint32_t* __restrict__ seg_blk,
-    const uint32_t* __restrict__ blk_table, int F, int sort_items) {
+    const uint32_t* __restrict__ blk_table, int F) {
   __shared__ uint64_t buf[kSortTile];
   constexpr int MaxRadix = 1 << MaxBits, DPT = (MaxRadix + kBlock - 1) / kBlock;
   __shared__ uint32_t cnt[kBlock / 64][MaxRadix];
@@ -371,9 +255,9 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int radix = 1 << bits;
   const uint32_t mask = (uint32_t)radix - 1;
-  const int items = OwnScan ? sort_items : kSortItems;   // (narrow digits: full blocks)
-  const SortBlock sb = sort_block(meta, seg_begin, seg_blk, blk_table, F, (uint32_t)(items * kBlock));
+  const SortBlock sb = sort_block<OwnScan>(meta, seg_begin, seg_blk, blk_table, F);
   if (!sb.valid) return;
+  const int items = sb.items;
   for (int w = 0; w < kBlock / 64; ++w)
     for (int d = tid; d < MaxRadix; d += kBlock) cnt[w][d] = 0;
   __syncthreads();
@@ -1706,7 +1590,7 @@ static dmt_status bwd_update_run(const dmt_plan* plan, const int32_t* indices,
     log2_bpb = log2_bpb < 4 ? 4 : (log2_bpb > 10 ? 10 : log2_bpb);
     const int64_t key_blocks = ((int64_t)nbags + (1 << log2_bpb) - 1) >> log2_bpb;
     timed_launch(plan, DMT_K_BWD_KEYS, s, bwd_build_keys, key_blocks, kBlock, plan->d_meta, indices,
-                 offsets, (uint32_t)B, nbags, nnz, (int)plan->F, w.pk_a, log2_bpb, (uint32_t)(w.sort_items * kBlock), w.seg_begin,
+                 offsets, (uint32_t)B, nbags, nnz, (int)plan->F, w.pk_a, log2_bpb, w.least_items, w.seg_begin,
                  w.seg_blk, w.blk_table, plan->row_shards ? nullptr : plan->d_error, plan->d_error + 1);
 
     // stable LSD radix sort inside every table over the bits a row id of the largest table
@@ -1724,14 +1608,14 @@ static dmt_status bwd_update_run(const dmt_plan* plan, const int32_t* indices,
       const int bits = std::min(bits_per, key_bits - shift);
       timed_launch(plan, DMT_K_BWD_SORT_HIST, s, w.wide ? radix_hist<kWideRadixBits> : radix_hist<kMaxRadixBits>,
                    w.nblk_sort, kBlock, plan->d_meta, src, shift, bits, w.hist, w.seg_begin, w.seg_blk,
-                   w.blk_table, (int)plan->F, w.sort_items);
+                   w.blk_table, (int)plan->F);
       if (!w.wide)
         timed_launch(plan, DMT_K_BWD_SORT_SCAN, s, radix_scan, plan->F, kScanThreads, w.hist, bits,
                      w.seg_begin, w.seg_blk);
       timed_launch(plan, DMT_K_BWD_SORT_SCATTER, s,
                    w.wide ? radix_scatter<kWideRadixBits, true> : radix_scatter<kMaxRadixBits, false>,
                    w.nblk_sort, kBlock, plan->d_meta, src, dst, shift, bits, w.hist, w.seg_begin, w.seg_blk,
-                   w.blk_table, (int)plan->F, w.sort_items);
+                   w.blk_table, (int)plan->F);
       std::swap(src, dst);
     }
     sorted = src;

@@ -330,14 +330,44 @@ def test_every_lookup_hits_a_different_row():
 @pytest.mark.parametrize("tables,batch,length", [(1, 64, 9), (1, 520, 63), (3, 129, 16), (3, 511, 33), (8, 257, 8),
                                                  (2, 1030, 64), (26, 300, 13)])
 def test_sort_blocks_of_every_size(tables, batch, length):
-    """Sort blocks of 512 to 2048 records (two to eight a thread), tables that end inside, at and past a block's
-    edge: the sorted order against a stable sort of the ids."""
+    """Sort blocks of 512 records (two a thread; five in the last but one case), tables that end inside, at and
+    past a block's edge: the sorted order against a stable sort of the ids."""
+    _sorted_order([batch * length] * tables, batch, [length] * tables)
+
+
+# records a thread by table (of at least the call's least): a table of L lookups gets ceil(L / 16384), 2 to 8
+@pytest.mark.parametrize("lens", [
+    [40_000], [60_000], [90_000], [100_000], [110_000], [130_000],           # 3, 4, 6, 7, 7 and 8
+    [16_384 * 2], [16_384 * 2 + 1], [16_384 * 5], [16_384 * 5 + 1],          # the lines between two sizes
+    [500, 126_000, 0, 511, 513, 1, 2000, 4096],                              # nearly all of a call in one table
+    [1, 1, 300_000, 33_000, 70_000, 7],                                      # several sizes in one call
+    [5] * 40 + [130_001] + [1500] * 23,
+    [262_144, 262_144], [524_288], [524_289],                                # least of 8; the last wide digits, narrow ones
+])
+def test_sort_blocks_follow_each_table(lens):
+    _sorted_order(lens, 64)
+
+
+@pytest.mark.parametrize("tables,each", [(60, 90), (64, 400), (200, 40), (300, 433)])
+def test_sort_blocks_where_counts_are_short_of_room(tables, each):
+    """Many tables of narrow rows: fewer and larger sort blocks, or narrow digits."""
+    _sorted_order([each] * tables, 32)
+
+
+def _sorted_order(lens, batch, bag=None):
+    """Table t has lens[t] lookups, spread over its bags as evenly as they go (or bag[t] each)."""
     import paper_2403_00877_amd as dmt
-    rows, dim, nnz = [5000 + 37 * f for f in range(tables)], 8, tables * batch * length
+    tables, nnz, dim = len(lens), sum(lens), 8
+    rows = [5000 + 37 * f for f in range(tables)]
     g = torch.Generator(device="cuda")
     g.manual_seed(tables)
-    idx = torch.cat([torch.randint(0, r, (batch * length,), generator=g, device="cuda") for r in rows]).to(torch.int32)
-    off = torch.arange(tables * batch + 1, device="cuda") * length
+    idx = torch.cat([torch.randint(0, r, (n,), generator=g, device="cuda") for r, n in zip(rows, lens)]).to(torch.int32)
+    per = torch.tensor(lens, device="cuda").repeat_interleave(batch)
+    b = torch.arange(batch, device="cuda").repeat(tables)
+    counts = per // batch + (b < per % batch)
+    off = torch.zeros(tables * batch + 1, dtype=torch.int64, device="cuda")
+    off[1:] = torch.cumsum(counts, 0)
+    assert bag is None or torch.equal(counts, torch.tensor(bag, device="cuda").repeat_interleave(batch))
     tabs = [torch.zeros(r, dim, device="cuda") for r in rows]
     states = [torch.zeros(r, device="cuda") for r in rows]
     plan = dmt.dmt_plan_create(rows, [dim] * tables, "f32", 1, [0] * tables, batch, nnz)
@@ -348,7 +378,8 @@ def test_sort_blocks_of_every_size(tables, batch, length):
     bags = torch.empty(nnz, dtype=torch.int32, device="cuda")
     dmt.dmt_tower_lookup_bwd_update(plan, idx, off, batch, grad, 0.01, 1e-8, ws,
                                     debug=dict(sorted_keys=keys, sorted_bag=bags))
-    table = torch.arange(tables, device="cuda").repeat_interleave(batch * length)
+    table = torch.arange(tables, device="cuda").repeat_interleave(torch.tensor(lens, device="cuda"))
     ref, order = torch.sort((table << 32) | idx.to(torch.int64), stable=True)
     assert torch.equal(keys, ref)
-    assert torch.equal(bags.to(torch.int64), order // length)
+    which = torch.arange(tables * batch, device="cuda").repeat_interleave(counts)
+    assert torch.equal(bags.to(torch.int64), which[order])
