@@ -31,8 +31,8 @@ namespace {
 // ------------------------------------------------------------------ key build
 
 // Where each table's records start and which sort blocks cover them.  Run by one block.
-// The starts come from the offsets of every table's first bag, made ascending and clamped to
-// [0, nnz], so that blocks stay inside the record array whatever `offsets` holds.
+// The starts come from the offsets of every table's first bag, clamped to [0, nnz] and made ascending (each at
+// least the largest before it), so that records and blocks stay inside their arrays whatever `offsets` holds.
 __device__ void build_sort_map(const int64_t* __restrict__ offsets, uint32_t B, int F, int64_t nnz,
                                int least_items, uint32_t* __restrict__ seg_begin,
                                uint32_t* __restrict__ seg_blk, uint32_t* __restrict__ blk_table) {
@@ -41,18 +41,16 @@ __device__ void build_sort_map(const int64_t* __restrict__ offsets, uint32_t B, 
   uint32_t rec_run = 0, blk_run = 0;
   for (int f0 = 0; f0 < F; f0 += kBlock) {
     const int f = f0 + (int)threadIdx.x;
-    uint32_t len = 0;
+    int64_t a = 0, b = 0;
     if (f < F) {
-      int64_t a = offsets[(int64_t)f * B], b = offsets[(int64_t)(f + 1) * B];
+      a = offsets[(int64_t)f * B], b = offsets[(int64_t)(f + 1) * B];
       a = a < 0 ? 0 : (a > nnz ? nnz : a);
       b = b < 0 ? 0 : (b > nnz ? nnz : b);
-      len = b > a ? (uint32_t)(b - a) : 0u;
     }
     uint32_t total;
-    uint32_t begin = rec_run + dmt::block_exclusive_scan<kBlock / 64>(len, sm, total);
-    rec_run += total;
-    begin = begin > (uint32_t)nnz ? (uint32_t)nnz : begin;
-    const uint32_t end = begin + len > (uint32_t)nnz ? (uint32_t)nnz : begin + len;
+    const uint32_t begin = max(rec_run, dmt::block_inclusive_max<kBlock / 64>((uint32_t)a, sm, total));
+    const uint32_t end = max(begin, (uint32_t)b);          // (the next table's begin)
+    rec_run = max(rec_run, total);
     const uint32_t items = (uint32_t)table_items(end - begin, least_items);
     const uint32_t nb = (end - begin + items * kBlock - 1) / (items * kBlock);
     const uint32_t first = blk_run + dmt::block_exclusive_scan<kBlock / 64>(nb, sm, total);
@@ -60,6 +58,7 @@ __device__ void build_sort_map(const int64_t* __restrict__ offsets, uint32_t B, 
     if (f < F) {
       seg_begin[f] = begin;
       seg_blk[f] = first;
+      if (f == F - 1) seg_begin[F] = end;
     }
     // the tables' block lists are written a wave per table, a block per lane
     s_first[threadIdx.x] = first;
@@ -70,10 +69,7 @@ __device__ void build_sort_map(const int64_t* __restrict__ offsets, uint32_t B, 
         blk_table[s_first[q] + j] = (uint32_t)(f0 + q) << 4 | (s_nb[q] & 15);
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    seg_begin[F] = rec_run > (uint32_t)nnz ? (uint32_t)nnz : rec_run;
-    seg_blk[F] = blk_run;
-  }
+  if (threadIdx.x == 0) seg_blk[F] = blk_run;
 }
 
 // One block takes 2^log2_bpb consecutive bags and walks their lookups id by id, so the work per

@@ -214,4 +214,27 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
   return before + incl - v;
 }
 
+// Inclusive prefix maximum over a block of NW waves, as above.
+template <int NW>
+__device__ __forceinline__ uint32_t block_inclusive_max(uint32_t v, uint32_t* smem, uint32_t& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t t = __shfl_up(v, o);
+    if (lane >= o && t > v) v = t;
+  }
+  if (lane == 63) smem[wave] = v;
+  __syncthreads();
+  uint32_t all = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const uint32_t s = smem[w];
+    if (w < wave && s > v) v = s;
+    if (s > all) all = s;
+  }
+  __syncthreads();
+  total = all;
+  return v;
+}
+
 }  // namespace dmt

@@ -295,6 +295,29 @@ def test_malformed_offsets_update_nothing_and_are_reported(case):
     assert sum(int((s != 0).sum()) for s in dw.states) > 0
 
 
+def test_malformed_offsets_of_many_tables_stay_inside_the_workspace():
+    """Tables whose first bags start at 0, nnz, 0, nnz ...: added up, the tables' lengths pass 2^32, and blocks that
+    start from such a sum would list 16384 sort blocks where the launch has 9216.  Nothing is touched, inside the
+    tables or behind the workspace."""
+    import paper_2403_00877_amd as dmt
+    F, nnz, dim, rows = 1024, 1 << 24, 4, 16
+    off = torch.zeros(F + 1, dtype=torch.int64)
+    off[1::2] = nnz
+    tabs = torch.ones(F, rows, dim, device="cuda")
+    states = torch.zeros(F, rows, device="cuda")
+    plan = dmt.dmt_plan_create([rows] * F, [dim] * F, "f32", 1, [0] * F, 1, nnz)
+    dmt.dmt_plan_bind(plan, list(tabs), list(states))
+    need = dmt.dmt_bwd_workspace_bytes(plan, 1, nnz)
+    ws = torch.full((need + 4096,), 171, dtype=torch.uint8, device="cuda")
+    idx = torch.zeros(nnz, dtype=torch.int32, device="cuda")
+    grad = torch.ones(F * dim, device="cuda")
+    dmt.dmt_tower_lookup_bwd_update(plan, idx, off.cuda(), 1, grad, 0.01, 1e-8, ws[:need])
+    with pytest.raises(dmt.DmtError) as e:
+        dmt.dmt_last_device_error(plan)
+    assert e.value.code == 1 and e.value.position == 1               # DMT_EINVAL, first bad bag
+    assert bool((ws[need:] == 171).all()) and bool((tabs == 1).all()) and bool((states == 0).all())
+
+
 def _degenerate(ids_of):
     w = wl.scaled(wl.mid(True), max_rows=5000, batch=64, num_tables=2)
     w.table_to_tower = [0, 0]
