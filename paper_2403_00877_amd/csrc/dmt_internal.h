@@ -47,6 +47,16 @@ struct DmtPerDevice {
   }
 };
 
+// Lets `kernel` use `bytes` of dynamic LDS on the current device: more than the default limit, which is set
+// device by device.  `done` belongs to the kernel.  (A failure is tried again at the next launch.)
+inline void dmt_allow_lds(DmtPerDevice& done, const void* kernel, int bytes) {
+  int dev = -1;
+  (void)hipGetDevice(&dev);
+  if (done.needed(dev) &&
+      hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess)
+    done.set(dev);
+}
+
 // Per-table record the kernels read (device copy lives in the plan).
 struct DmtTableMeta {
   const void* table;     // row-major [rows][D]

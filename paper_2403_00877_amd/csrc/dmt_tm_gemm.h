@@ -1193,11 +1193,7 @@ void launch_tiles(const TmLaunch& L, int64_t blocks, hipStream_t s) {
   constexpr int bytes = TmTile<TILE>::kLdsBytes;
   auto kernel = tm_gemm<DT, TILE, ALAY, WLAY, KIND, DOTS, KEEPZ>;
   static DmtPerDevice configured;
-  int dev = -1;
-  (void)hipGetDevice(&dev);
-  if (configured.needed(dev) &&
-      hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess)
-    configured.set(dev);
+  dmt_allow_lds(configured, (const void*)kernel, bytes);
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TmTile<TILE>::kThreads), bytes, s, L);
 }
 

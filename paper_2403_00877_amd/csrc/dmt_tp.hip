@@ -550,13 +550,8 @@ void launch_gram(const dmt_plan* p, const void* pooled, int64_t B, const TpShape
                  float* partial, hipStream_t s) {
   const int npad = (sh.N + 15) & ~15;
   const size_t lds = sizeof(uint16_t) * 2 * TF * (npad + 8);
-  static bool configured = false;           // wide rows need more than the default LDS limit
-  if (!configured) {
-    (void)hipFuncSetAttribute((const void*)tp_gram<DT, NP, TF>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)(sizeof(uint16_t) * 2 * TF * (NP * 32 + 8)));
-    configured = true;
-  }
+  static DmtPerDevice configured;           // wide rows need more than the default LDS limit
+  dmt_allow_lds(configured, (const void*)tp_gram<DT, NP, TF>, (int)(sizeof(uint16_t) * 2 * TF * (NP * 32 + 8)));
   const int64_t blocks = (sh.nslices + 7) / 8 * 8 * sh.npairs;
   hipLaunchKernelGGL((tp_gram<DT, NP, TF>), dim3((unsigned)blocks), dim3(kBlock), lds, s, p->d_meta,
                      pooled, B, p->F, sh.N, sh.nt, sh.npairs, sh.per, sh.nslices, partial);
@@ -568,12 +563,7 @@ void launch_gram_wide(const dmt_plan* p, const void* pooled, int64_t B, const Tp
   const int npad = (sh.N + 15) & ~15;
   const size_t lds = 2 * sizeof(uint16_t) * kWideRows * (npad + 8);
   static DmtPerDevice configured;
-  int dev = -1;
-  (void)hipGetDevice(&dev);
-  if (configured.needed(dev) &&
-      hipFuncSetAttribute((const void*)tp_gram_wide<DT, NP>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)(2 * sizeof(uint16_t) * kWideRows * (NP * 32 + 8))) == hipSuccess)
-    configured.set(dev);
+  dmt_allow_lds(configured, (const void*)tp_gram_wide<DT, NP>, (int)(2 * sizeof(uint16_t) * kWideRows * (NP * 32 + 8)));
   hipLaunchKernelGGL((tp_gram_wide<DT, NP>), dim3((unsigned)sh.nslices), dim3(kWideThreads), lds, s,
                      p->d_meta, pooled, B, p->F, sh.N, sh.nt, sh.npairs, sh.per, partial);
 }

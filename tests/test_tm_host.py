@@ -13,7 +13,16 @@ def lib(tmp_path_factory):
     tmp = tmp_path_factory.mktemp("tm_host")
     src, so = str(tmp / "tm_host.hip"), str(tmp / "libtm_host.so")
     with open(src, "w") as f:
-        f.write('#include "dmt_tm_f32.h"\n'
+        # (the two runtime calls of dmt_allow_lds, so that it can be watched on devices that are not there)
+        f.write('#include <hip/hip_runtime.h>\n'
+                'static int g_dev, g_sets, g_fail;\n'
+                'static hipError_t fake_get(int* d) { *d = g_dev; return hipSuccess; }\n'
+                'static hipError_t fake_set(const void*, hipFuncAttribute, int) { ++g_sets; return g_fail ? hipErrorInvalidValue : hipSuccess; }\n'
+                '#define hipGetDevice fake_get\n'
+                '#define hipFuncSetAttribute fake_set\n'
+                '#include "dmt_tm_f32.h"\n'
+                'static DmtPerDevice lds;\n'
+                'extern "C" int allow_lds(int dev, int fail) { g_dev = dev; g_fail = fail; g_sets = 0; dmt_allow_lds(lds, &lds, 1); return g_sets; }\n'
                 'extern "C" int first_step(int steps, int part, int log2_ks) { return f32_first_step(steps, part, log2_ks); }\n'
                 'extern "C" int slice_end(int K1, int kofs, int klen) { return tm_slice_end(K1, kofs, klen); }\n'
                 'static DmtPerDevice once;\n'
@@ -48,3 +57,16 @@ def test_slices_cover_all_rows_of_a_16_bit_weight_gradient(lib, K, slices):
 def test_kernel_attributes_are_set_on_every_device(lib):
     assert [lib.needed(d) for d in (0, 0, 1, 1, 0, 7, 63, 7, 63, 1)] == [1, 0, 1, 0, 0, 1, 1, 0, 0, 0]
     assert [lib.needed(d) for d in (-1, -1, 64, 64)] == [1, 1, 1, 1]        # unknown: every time
+
+
+def test_lds_beyond_the_default_is_asked_for_on_every_device(lib):
+    """All kernels with more dynamic LDS than a device grants by itself go through dmt_allow_lds."""
+    assert [lib.allow_lds(d, 0) for d in (0, 0, 1, 0, 1, 5)] == [1, 0, 1, 0, 0, 1]
+    assert [lib.allow_lds(3, 1), lib.allow_lds(3, 0), lib.allow_lds(3, 0)] == [1, 1, 0]      # a failure is tried again
+    uses = {}
+    for name in sorted(os.listdir(hip_build.CSRC)):
+        with open(os.path.join(hip_build.CSRC, name)) as f:
+            n = f.read().count("hipFuncSetAttribute(")
+        if n:
+            uses[name] = n
+    assert uses == {"dmt_internal.h": 1}
