@@ -315,7 +315,7 @@ __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
     const DmtTableMeta* __restrict__ meta, const void* __restrict__ pooled, int64_t B, int F, int N,
     int gt, int nsub, int64_t per, float* __restrict__ partial) {
   constexpr int LPR = 4 * NP, RP = kWideThreads / LPR;     // NP passes cover the 256 rows
-  constexpr bool kRaw = DT != DMT_F32;
+  static_assert(DT != DMT_F32, "float32 rows, staged, need more registers than a 16-wave block has");
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   __shared__ int64_t s_base[kWideRows];
   __shared__ int32_t s_pitch[kWideRows];
@@ -366,8 +366,7 @@ __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
       if (cin && row < F) {
         raw[p] = fetch8<DT, true>(pooled, s_base[row] + b * s_pitch[row] + chunk * 8);
       } else {
-#pragma unroll
-        for (int q = 0; q < (DT == DMT_F32 ? 2 : 1); ++q) raw[p].v[q] = make_uint4(0, 0, 0, 0);
+        raw[p].v[0] = make_uint4(0, 0, 0, 0);
       }
     }
   };
@@ -377,28 +376,10 @@ __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const int row = p * RP + row0;
-      if constexpr (kRaw) {
-        const uint4 r = raw[p].v[0];
-        const float ss = row_group_sum<LPR>(sumsq8<DT>(r));
-        if (chunk * 8 < npad) *(uint4*)(rows + row * ldx + chunk * 8) = r;
-        if (chunk == 0) s_inv[buf][row] = ss > 0.f ? __builtin_amdgcn_rsqf(ss) : 0.f;
-      } else {
-        float x[8];
-        decode8<DT>(raw[p], x);
-        float ss = 0.f;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) ss += x[q] * x[q];
-        ss = row_group_sum<LPR>(ss);
-        const float inv = ss > 0.f ? __builtin_amdgcn_rsqf(ss) : 0.f;
-        if (chunk * 8 < npad) {
-          *(uint4*)(rows + row * ldx + chunk * 8) =
-              make_uint4(dmt::pack2<DMT_F16>(x[0] * inv, x[1] * inv),
-                         dmt::pack2<DMT_F16>(x[2] * inv, x[3] * inv),
-                         dmt::pack2<DMT_F16>(x[4] * inv, x[5] * inv),
-                         dmt::pack2<DMT_F16>(x[6] * inv, x[7] * inv));
-        }
-        if (chunk == 0) s_inv[buf][row] = 1.0f;
-      }
+      const uint4 r = raw[p].v[0];
+      const float ss = row_group_sum<LPR>(sumsq8<DT>(r));
+      if (chunk * 8 < npad) *(uint4*)(rows + row * ldx + chunk * 8) = r;
+      if (chunk == 0) s_inv[buf][row] = ss > 0.f ? __builtin_amdgcn_rsqf(ss) : 0.f;
     }
   };
 
