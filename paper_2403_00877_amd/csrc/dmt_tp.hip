@@ -301,14 +301,16 @@ __global__ __launch_bounds__(kBlock) void tp_gram(const DmtTableMeta* __restrict
 }
 
 // The same contraction for 65 ... 256 features of dim N <= 128: one block of 16 waves stages ALL
-// features of a sample (up to 256 rows, 68 KB of LDS at N = 128), so the pooled tensor is read
+// features of a sample (up to 256 rows, 68 KB at N = 128), so the pooled tensor is read
 // exactly once, and its waves share out the 32 x 32 sub-tiles of the upper triangle of the
 // Gram matrix (at most 36, three per wave).  A sub-tile (r, c), r <= c, is stored like a tile
 // pair of 32-feature tiles, which is what tp_finish reads.  One block per CU; block = batch slice.
-// Two sample buffers: a wave that is done with a sample commits its share of the next one's rows, which
-// were under way meanwhile, and requests the one after, so that a sample costs one barrier and loads are
-// under way all the time but while they are committed (one buffer, two barriers: 263.1 us for 256
-// features of 128 columns, batch 16384; now 259.6: it reads 576 KB of fragments from LDS a sample).
+// Two sample buffers (139 KB of LDS at N = 128): a wave that is done with a sample commits its share of the next
+// one's rows, which were under way meanwhile, and requests the one after, so that a sample costs one barrier and
+// loads are under way all the time but while they are committed.  One buffer, two barriers / this, us, batch 16384:
+// 256 features of 128 columns 267.8 / 263.0 (it reads 576 KB of fragments from LDS a sample), 128 of 64
+// 83.6 / 74, 128 of 16 60.8 / 49; only narrow rows of more than 224 features lose (256 of 16: 88.3 / 90.3).  Batch
+// 100, one sample a block, 256 of 128: 18.5 / 18.7.
 constexpr int kWideThreads = 1024, kWideRows = 256, kWideSub = 3;
 template <int DT, int NP>
 __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
@@ -358,15 +360,33 @@ __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
     for (int v = 0; v < 16; ++v) total[q][v] = 0.f;
   }
 
+  const int64_t b_begin = blockIdx.x * per, b_end = b_begin + per < B ? b_begin + per : B;
+  // This thread's pieces of the rows: zeros of rows past the last feature and columns past the last.  Their addresses
+  // walk from sample to sample, which saves narrow rows a tenth of their instructions; four of them would be
+  // more registers than a 16-wave block has (up to 128 columns, batch 16384: 284 instead of 261 us).
+  constexpr bool kWalk = NP <= 2;
+  const uint16_t* src[kWalk ? NP : 1];
+  int step[kWalk ? NP : 1];
   Raw8<DT> raw[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    raw[p].v[0] = make_uint4(0, 0, 0, 0);
+    if constexpr (kWalk) {
+      const int row = p * RP + row0;
+      src[p] = (const uint16_t*)pooled + s_base[row] + b_begin * s_pitch[row] + chunk * 8;
+      step[p] = s_pitch[row];
+    }
+  }
   auto fetch = [&](int64_t b) __attribute__((always_inline)) {
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const int row = p * RP + row0;
-      if (cin && row < F) {
-        raw[p] = fetch8<DT, true>(pooled, s_base[row] + b * s_pitch[row] + chunk * 8);
+      if (!cin || row >= F) continue;
+      if constexpr (kWalk) {
+        raw[p] = fetch8<DT, true>(src[p], 0);
+        src[p] += step[p];
       } else {
-        raw[p].v[0] = make_uint4(0, 0, 0, 0);
+        raw[p] = fetch8<DT, true>(pooled, s_base[row] + b * s_pitch[row] + chunk * 8);
       }
     }
   };
@@ -383,49 +403,45 @@ __global__ __launch_bounds__(kWideThreads) void tp_gram_wide(
     }
   };
 
-  const int64_t b_begin = blockIdx.x * per, b_end = b_begin + per < B ? b_begin + per : B;
-  if (b_begin < b_end) {
-    fetch(b_begin);
-    commit(0);
-    if (b_begin + 1 < b_end) fetch(b_begin + 1);
-  }
+  // (from two rounds ahead of the first sample, so that each part's code is there once: a batch of 100, one sample
+  // a block, took 19.4 us with a copy of fetch and commit in front of the loop)
   int buf = 0;
-  for (int64_t b = b_begin; b < b_end; ++b, buf ^= 1) {
-    // (this sample's rows are in LDS, and every wave is done with the other buffer's)
-    __syncthreads();
-    const uint16_t* const rows = lds + buf * stage;
-    const float* const inv = s_inv[buf];
+  for (int64_t b = b_begin - 2; b < b_end; ++b, buf ^= 1) {
+    if (b >= b_begin) {
+      // (this sample's rows are in LDS, and every wave is done with the other buffer's)
+      __syncthreads();
+      const uint16_t* const rows = lds + buf * stage;
+      const float* const inv = s_inv[buf];
 #pragma unroll
-    for (int q = 0; q < kWideSub; ++q) {
-      if (wave + 16 * q < nsub) {            // uniform over the wave
-        floatx16 acc;
+      for (int q = 0; q < kWideSub; ++q) {
+        if (wave + 16 * q < nsub) {            // uniform over the wave
+          floatx16 acc;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-        for (int k = 0; k < npad; k += 16) {
-          const uint4 a = *(const uint4*)(rows + oa[q] + k);
-          const uint4 c = *(const uint4*)(rows + ob[q] + k);
-          if constexpr (DT == DMT_BF16)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                          __builtin_bit_cast(bf16x8, c), acc, 0, 0, 0);
-          else
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a),
-                                                         __builtin_bit_cast(halfx8, c), acc, 0, 0, 0);
-        }
-        const float ic = inv[ic_off[q]];
+          for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+          for (int k = 0; k < npad; k += 16) {
+            const uint4 a = *(const uint4*)(rows + oa[q] + k);
+            const uint4 c = *(const uint4*)(rows + ob[q] + k);
+            if constexpr (DT == DMT_BF16)
+              acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                            __builtin_bit_cast(bf16x8, c), acc, 0, 0, 0);
+            else
+              acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a),
+                                                           __builtin_bit_cast(halfx8, c), acc, 0, 0, 0);
+          }
+          const float ic = inv[ic_off[q]];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float4 ir = *(const float4*)(inv + ir_off[q] + j * 8);
-          total[q][4 * j + 0] += acc[4 * j + 0] * (ir.x * ic);
-          total[q][4 * j + 1] += acc[4 * j + 1] * (ir.y * ic);
-          total[q][4 * j + 2] += acc[4 * j + 2] * (ir.z * ic);
-          total[q][4 * j + 3] += acc[4 * j + 3] * (ir.w * ic);
+          for (int j = 0; j < 4; ++j) {
+            const float4 ir = *(const float4*)(inv + ir_off[q] + j * 8);
+            total[q][4 * j + 0] += acc[4 * j + 0] * (ir.x * ic);
+            total[q][4 * j + 1] += acc[4 * j + 1] * (ir.y * ic);
+            total[q][4 * j + 2] += acc[4 * j + 2] * (ir.z * ic);
+            total[q][4 * j + 3] += acc[4 * j + 3] * (ir.w * ic);
+          }
         }
       }
     }
-    if (b + 1 < b_end) {
-      commit(buf ^ 1);
-      if (b + 2 < b_end) fetch(b + 2);
-    }
+    if (b + 1 >= b_begin && b + 1 < b_end) commit(buf ^ 1);
+    if (b + 2 < b_end) fetch(b + 2);
   }
 
 #pragma unroll

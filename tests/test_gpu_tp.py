@@ -116,6 +116,19 @@ def test_interaction_on_random_shapes(seed):
     _check(I, tp.tp_interaction(wl.decode(enc, dtype)), "seed %d F=%d N=%d B=%d T=%d %s" % (seed, F, N, B, T, dtype), dtype)
 
 
+@pytest.mark.parametrize("F,N,sizes", [(65, 8, [1, 64]), (100, 24, [60, 40]), (225, 32, [224, 1]), (129, 40, [2, 127]),
+                                       (256, 64, [256]), (90, 72, [30, 59, 1]), (256, 128, [100, 156])])
+@pytest.mark.parametrize("B", [255, 257, 600])
+def test_one_to_three_samples_a_block(F, N, sizes, B):
+    """The all-features kernel: blocks of one, two and three samples (one buffer, both, and back to the first), row
+    addresses that walk (up to 64 columns) and that do not, towers of unequal pitch."""
+    w = _workload(F, N, len(sizes), B, "bf16", sizes)
+    dw = DeviceWorkload(w)
+    enc = wl.encode(wl.tp_embeddings(F + B, B, F, N, groups=max(1, F // 4)).astype(np.float32), "bf16")
+    I = _interaction(dw, to_device(_tower_major(w, enc), "bf16"))
+    _check(I, tp.tp_interaction(wl.decode(enc, "bf16")), "F=%d N=%d B=%d" % (F, N, B), "bf16")
+
+
 def test_zero_embeddings_count_as_cosine_zero_and_signs_cancel():
     F, N, B = 6, 16, 8
     w = _workload(F, N, 2, B, "f32")
