@@ -337,11 +337,13 @@ struct TmWork {
 };
 
 // What a launch's epilogues are: KIND_READS those that read as much as they write (EPI_CROSS,
-// EPI_CROSS_GRAD), KIND_ADD EPI_F32_ADD, KIND_PLAIN all others.  (Kernels of their own: together they need
+// EPI_CROSS_GRAD), KIND_SUMS EPI_CROSS_GRAD of towers of three layers and more, whose gradients add to what the
+// layers behind left in ACC, KIND_ADD EPI_F32_ADD, KIND_PLAIN all others.  (Kernels of their own: together they need
 // more registers, and what an epilogue reads ahead behind a run-time condition is slow: data gradients of
 // 16 towers of 2048 columns, batch 8192, added to a tensor 1303 us, in a kernel of their own 1090.)
-enum { KIND_PLAIN = 0, KIND_READS = 1, KIND_ADD = 2 };
-inline int epi_kind(int epi) {
+enum { KIND_PLAIN = 0, KIND_READS = 1, KIND_ADD = 2, KIND_SUMS = 3 };
+inline bool epi_sums(const TmGroup& g) { return g.epi == EPI_CROSS_GRAD && !g.acc_first && (g.GN || g.U0); }
+inline int epi_kind(int epi) {           // (KIND_SUMS: a launch of KIND_READS of which any group is one)
   return epi == EPI_CROSS || epi == EPI_CROSS_GRAD ? KIND_READS : epi == EPI_F32_ADD ? KIND_ADD : KIND_PLAIN;
 }
 
@@ -753,7 +755,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
       auto place = [&](int e) __attribute__((always_inline)) {
         return (uint32_t)min(wrow + e * 4 + r4, M - 1 - m0) * (uint32_t)G.ldc + (on ? (uint32_t)c : 0u);
       };
-      if constexpr (KIND != KIND_READS) {
+      if constexpr (KIND != KIND_READS && KIND != KIND_SUMS) {
         constexpr int kDeep = 4;
         constexpr bool add = KIND == KIND_ADD;
         float4 old[kDeep];
@@ -774,12 +776,14 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
           __builtin_amdgcn_sched_barrier(0);
         }
       } else {
-        constexpr int kDeep = 5;
+        // (ACC is 16 bytes a lane and piece more; at five pieces ahead the 256 x 256 instance would spill.  Read
+        // where it is added instead, a tower of four layers of 2048 columns, batch 500, took 266 us, now 259.)
+        constexpr int kDeep = KIND == KIND_SUMS && TILE == 256 ? 4 : 5;
         const char *gn = (const char*)(G.GN + corner), *ul = (const char*)G.UL + corner * 2;
         const char *x0 = (const char*)G.X0 + corner * 2, *u0 = (const char*)G.U0 + corner * 2;
         char *a0 = (char*)(G.ACC + corner), *du = (char*)G.DU + corner * 2;
-        const bool has_gn = G.GN, has_u0 = G.U0, has_c = G.C, acc_old = !G.acc_first;
-        float4 pg[kDeep];
+        const bool has_gn = G.GN, has_u0 = G.U0, has_c = G.C, acc_old = KIND == KIND_SUMS && !G.acc_first;
+        float4 pg[kDeep], po[kDeep];
         uint2 px[kDeep], pu[kDeep], pv[kDeep];
         // (plain loads at every size: the choice of take() costs the 256 x 256 instance 20 bytes of scratch a lane)
         auto fetch = [&](int e) __attribute__((always_inline)) {
@@ -790,6 +794,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
             pu[e % kDeep] = dmt::gload((const uint2*)(ul + at * 2u));
           }
           if (has_u0) pv[e % kDeep] = dmt::gload((const uint2*)(u0 + at * 2u));
+          if (acc_old) po[e % kDeep] = dmt::gload((const float4*)(a0 + at * 4u));
         };
         float4 sums = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma clang loop unroll(full)
@@ -806,7 +811,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
             float v0, v1, v2, v3;
             if (has_gn || has_u0) {
               float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-              if (acc_old) t = dmt::gload((const float4*)(a0 + at * 4u));      // (three layers and more)
+              if (acc_old) t = po[b];
               if (has_gn) {
                 const float4 n = pg[b];
                 g.x += n.x; g.y += n.y; g.z += n.z; g.w += n.w;
@@ -1316,13 +1321,17 @@ void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t 
       if (dots && keepz) { launch_tiles<DT, 128, ALAY, WLAY, KIND_PLAIN, true, true>(L, blocks, s); continue; }
       if (dots) { launch_tiles<DT, 128, ALAY, WLAY, KIND_PLAIN, true, false>(L, blocks, s); continue; }
     }
+    if constexpr (ALAY == OP_ROW && WLAY == OP_COL) {
+      bool sums = false;
+      for (int i = 0; i < L.ngroups; ++i) sums = sums || epi_sums(L.g[i]);
+      if (sums && big) { launch_tiles<DT, 256, ALAY, WLAY, KIND_SUMS, false, false>(L, blocks, s); continue; }
+      if (sums) { launch_tiles<DT, 128, ALAY, WLAY, KIND_SUMS, false, false>(L, blocks, s); continue; }
+      if (kind == KIND_ADD && big) { launch_tiles<DT, 256, ALAY, WLAY, KIND_ADD, false, false>(L, blocks, s); continue; }
+      if (kind == KIND_ADD) { launch_tiles<DT, 128, ALAY, WLAY, KIND_ADD, false, false>(L, blocks, s); continue; }
+    }
     if constexpr (ALAY == OP_ROW) {
       if (kind == KIND_READS && big) { launch_tiles<DT, 256, ALAY, WLAY, KIND_READS, false, false>(L, blocks, s); continue; }
       if (kind == KIND_READS) { launch_tiles<DT, 128, ALAY, WLAY, KIND_READS, false, false>(L, blocks, s); continue; }
-    }
-    if constexpr (ALAY == OP_ROW && WLAY == OP_COL) {
-      if (kind == KIND_ADD && big) { launch_tiles<DT, 256, ALAY, WLAY, KIND_ADD, false, false>(L, blocks, s); continue; }
-      if (kind == KIND_ADD) { launch_tiles<DT, 128, ALAY, WLAY, KIND_ADD, false, false>(L, blocks, s); continue; }
     }
     if (big) launch_tiles<DT, 256, ALAY, WLAY, KIND_PLAIN, false, false>(L, blocks, s);
     else launch_tiles<DT, 128, ALAY, WLAY, KIND_PLAIN, false, false>(L, blocks, s);
