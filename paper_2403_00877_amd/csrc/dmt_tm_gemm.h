@@ -593,7 +593,9 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
     // Lines of the tile's operands kTouch steps ahead that this block brings to the XCD's L2 for itself and
     // the blocks it shares them with, a wave up to 64: an epilogue's traffic on other CUs makes misses too
     // slow for the two stages.  (The cross layer above 1304 -> 1246 us, others 1 %; weight gradients,
-    // whose epilogues are few, lose 2 %.)
+    // whose epilogues are few, lose 2 %.)  Not where the tile is as wide as the output: nobody shares its rows of A
+    // then, and asking for them twice is all it does (4 towers of 6 and 7 features to 256 outputs, batch 20000,
+    // 54.9 against 64.9 us; 4 towers of 1024 columns, batch 16384, 37.5 against 45.8).
     constexpr bool kTouches = TILE == 256 && ALAY == OP_ROW && !DOTS;
     constexpr int kTouch = 4;
     uint32_t touch = kOobOffset;
@@ -608,7 +610,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
         if (a || WLAY == OP_ROW) touch = line < (a ? sa.rows : sw.rows) ? (uint32_t)line * (uint32_t)(a ? sa.ld : sw.ld) * 2u : kOobOffset;
         else if ((line & 3) * 64 < sw.rows) touch = ((uint32_t)(line >> 2) * (uint32_t)sw.ld + (line & 3) * 64) * 2u;
       }
-      touches = __builtin_amdgcn_readfirstlane(G.K0 == 0 && __any(touch != kOobOffset));
+      touches = __builtin_amdgcn_readfirstlane(G.K0 == 0 && tiles_n > 1 && __any(touch != kOobOffset));
     }
     for (int kt = 0; kt < nk; ++kt) {
       // The barrier of a K step sits in front of its last three rows of MFMAs, by when every wave has
@@ -1317,7 +1319,9 @@ void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t 
     L.stagger = 0;
     // (and few slots without a tile: they would leave their blocks idle)
     if (big && !dots && tiles > kCUs && nst * L.cap <= tiles + tiles / 16 && same_steps(L.g, L.ngroups)) {
-      // (the last XCD starts a quarter of a tile late: eight rounds and more make up for that)
+      // (The last XCD starts 57 K cycles late: a third of a tile of 32 K steps, about a whole one of four.  Eight
+      // rounds and more make up for that: cross layers of rank 256 and 128, 12 rounds, 1088 against 1082 us and 971
+      // against 951 with none, 16 rounds 1284 / 1305 and 1148 / 1161, rank 512 and 1024 1 % less.)
       if (kind != KIND_PLAIN && tiles >= 8 * kCUs) L.stagger = 2;
       blocks = kCUs;
     }
