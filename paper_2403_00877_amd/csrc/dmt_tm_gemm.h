@@ -93,7 +93,6 @@ struct TmLaunch {
   int32_t cap;                         // block slots of a super-tile
   int32_t slots;                       // of an XCD
   int32_t step;                        // blocks of an XCD
-  int32_t stream;                      // more output than the caches keep
   int32_t stagger;                     // how far apart the XCDs start, in sleeps of 4096 cycles
   int32_t tile_start[kMaxGroups + 1];  // first super-tile of each group
   TmGroup g[kMaxGroups];
@@ -680,18 +679,6 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
       wave_sync();
     };
     auto get = [&](int r, int c) __attribute__((always_inline)) { return turn[r * 16 + (c ^ r)]; };
-    // (what the caches would not keep until it is used again does not push the operands out; what they would
-    // keep must not be streamed: a backward of 500 samples found its pooled values gone, and took 27 -> 34 us
-    // for its first contractions)
-    const bool stream = L.stream;
-    auto take = [&](auto* p) __attribute__((always_inline)) {
-      if (stream) return dmt::nt_load(p);
-      return dmt::gload(p);
-    };
-    auto put_out = [&](auto v, auto* p) __attribute__((always_inline)) {
-      if (stream) dmt::nt_store(v, p);
-      else dmt::gstore(v, p);
-    };
     const int wrow = wm * T::kHalf, wcol = wn * 64;
     if (whole && epi < EPI_F32 && (kForward || KIND == KIND_PLAIN)) {
       // 16-bit outputs: eight rows at a time, eight columns a lane.  What the cross epilogue reads (x0 and
@@ -714,8 +701,8 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
       auto fetch = [&](int e) __attribute__((always_inline)) {
         // (rows and columns past the edge read in bounds and are not stored)
         const uint32_t m = (uint32_t)min(wrow + e * 8 + r8, M - 1 - m0), cc = on ? (uint32_t)c : 0u;
-        pa[e % kDeep] = take((const uint4*)(xbase + (m * (uint32_t)G.ldx + cc) * 2u));
-        pb[e % kDeep] = take((const uint4*)(lbase + (m * (uint32_t)G.ldxl + cc) * 2u));
+        pa[e % kDeep] = dmt::gload((const uint4*)(xbase + (m * (uint32_t)G.ldx + cc) * 2u));
+        pb[e % kDeep] = dmt::gload((const uint4*)(lbase + (m * (uint32_t)G.ldxl + cc) * 2u));
       };
       if (cross)
 #pragma clang loop unroll(full)
@@ -742,13 +729,13 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
             for (int q = 0; q < 8; ++q) y[q] = y[q] > 0.f ? y[q] : 0.f;
           } else if constexpr (cross) {
             float xv[8], lv[8];
-            if (G.U) put_out(pack8(y), (uint4*)(ubase + off));
+            if (G.U) dmt::gstore(pack8(y), (uint4*)(ubase + off));
             dmt::decode_chunk<DT>(xv, pa[e % kDeep]);
             dmt::decode_chunk<DT>(lv, pb[e % kDeep]);
 #pragma clang loop unroll(full)
             for (int q = 0; q < 8; ++q) y[q] = xv[q] * y[q] + lv[q];
           }
-          put_out(pack8(y), (uint4*)out);
+          dmt::gstore(pack8(y), (uint4*)out);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -770,10 +757,10 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
         float4 old[kDeep];
         if (add)
 #pragma clang loop unroll(full)
-          for (int e = 0; e < kDeep - 1; ++e) old[e] = take((const float4*)(cbase + place(e) * 4u));
+          for (int e = 0; e < kDeep - 1; ++e) old[e] = dmt::gload((const float4*)(cbase + place(e) * 4u));
 #pragma clang loop unroll(full)
         for (int e = 0; e < kAll; ++e) {
-          if (add && e + kDeep - 1 < kAll) old[(e + kDeep - 1) % kDeep] = take((const float4*)(cbase + place(e + kDeep - 1) * 4u));
+          if (add && e + kDeep - 1 < kAll) old[(e + kDeep - 1) % kDeep] = dmt::gload((const float4*)(cbase + place(e + kDeep - 1) * 4u));
           if (e % 4 == 0) put(e / 4);
           const floatx4 s = get(e % 4 * 4 + r4, ln & 15);
           float4 g = make_float4(s[0], s[1], s[2], s[3]);
@@ -781,7 +768,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
             const float4 o = old[e % kDeep];
             g.x += o.x; g.y += o.y; g.z += o.z; g.w += o.w;
           }
-          if (m0 + wrow + e * 4 + r4 < M && on) put_out(g, (float4*)(cbase + place(e) * 4u));
+          if (m0 + wrow + e * 4 + r4 < M && on) dmt::gstore(g, (float4*)(cbase + place(e) * 4u));
           __builtin_amdgcn_sched_barrier(0);
         }
       } else {
@@ -794,7 +781,6 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
         const bool has_gn = G.GN, has_u0 = G.U0, has_c = G.C, acc_old = KIND == KIND_SUMS && !G.acc_first;
         float4 pg[kDeep], po[kDeep];
         uint2 px[kDeep], pu[kDeep], pv[kDeep];
-        // (plain loads at every size: the choice of take() costs the 256 x 256 instance 20 bytes of scratch a lane)
         auto fetch = [&](int e) __attribute__((always_inline)) {
           const uint32_t at = place(e);
           px[e % kDeep] = dmt::gload((const uint2*)(x0 + at * 2u));
@@ -835,16 +821,16 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
                 t.x += mul_rounded(g.x, v0) + g.x; t.y += mul_rounded(g.y, v1) + g.y;
                 t.z += mul_rounded(g.z, v2) + g.z; t.w += mul_rounded(g.w, v3) + g.w;
               }
-              put_out(t, (float4*)(a0 + at * 4u));
+              dmt::gstore(t, (float4*)(a0 + at * 4u));
             }
             dmt::unpack2<DT>(px[b].x, v0, v1);
             dmt::unpack2<DT>(px[b].y, v2, v3);
             const uint2 d = make_uint2(dmt::pack2<DT>(g.x * v0, g.y * v1), dmt::pack2<DT>(g.z * v2, g.w * v3));
-            put_out(d, (uint2*)(du + at * 2u));
+            dmt::gstore(d, (uint2*)(du + at * 2u));
             dmt::unpack2<DT>(d.x, v0, v1);         // the bias gradient sums the rounded values
             dmt::unpack2<DT>(d.y, v2, v3);
             sums.x += v0; sums.y += v1; sums.z += v2; sums.w += v3;
-            if (has_c) put_out(g, (float4*)(cbase + at * 4u));
+            if (has_c) dmt::gstore(g, (float4*)(cbase + at * 4u));
           }
           if (e % 16 == 15) {
             // column sums of 64 rows: 16 of a lane, then the four lanes of its columns
@@ -1318,13 +1304,6 @@ void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t 
     int64_t blocks = (nst + 7) / 8 * 8 * L.cap;
     if (blocks == 0) continue;
     L.slots = (int32_t)(blocks / 8);
-    // 128 MB of outputs: half of what the Infinity Cache holds.  (Streamed, the 34 MB of a split weight
-    // gradient's slices took 41 instead of 31 us to add up; kept, 1.1 GB of data gradients take 1042
-    // instead of 1026 us.)
-    int64_t out = 0;
-    for (int i = 0; i < L.ngroups; ++i)
-      out += (int64_t)L.g[i].M * L.g[i].N * tm_slices(L.g[i]) * (L.g[i].epi >= EPI_F32 || L.g[i].U ? 4 : 2);
-    L.stream = out > (128 << 20);
     L.stagger = 0;
     // (and few slots without a tile: they would leave their blocks idle)
     if (big && !dots && tiles > kCUs && nst * L.cap <= tiles + tiles / 16 && same_steps(L.g, L.ngroups)) {
