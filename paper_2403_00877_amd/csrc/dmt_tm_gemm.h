@@ -1251,6 +1251,41 @@ inline bool same_steps(const TmGroup* g, int n) {
   return true;
 }
 
+// Cuts a launch's groups into tiles and deals them out; how many blocks it takes.
+inline int64_t tile_launch(const dmt_plan* p, TmLaunch& L, bool dots, int kind, bool* big_tiles) {
+  const bool big = *big_tiles = take_big(p, L.g, L.ngroups);
+  const int tile = big ? 256 : 128;
+  int64_t tiles = 0;
+  for (int i = 0; i < L.ngroups; ++i) tiles += tiles_of(L.g[i], tile);
+  // super-tiles as large as an XCD's resident blocks, or an eighth of the launch where that is less
+  const int resident = big ? 32 : 64;
+  L.super = (int32_t)std::max<int64_t>(1, std::min<int64_t>(resident, (tiles + 7) / 8));
+  L.cap = 1;
+  int64_t nst = 0;
+  for (int i = 0; i < L.ngroups; ++i) {
+    L.tile_start[i] = (int32_t)nst;
+    const int64_t tn = (L.g[i].N + tile - 1) / tile, tm = (int64_t)((L.g[i].M + tile - 1) / tile) * tm_slices(L.g[i]);
+    const int64_t sm = tn >= L.super ? 1 : L.super / tn;
+    L.cap = (int32_t)std::max<int64_t>(L.cap, std::min(sm, tm) * tn);
+    nst += (tm + sm - 1) / sm;
+  }
+  L.tile_start[L.ngroups] = (int32_t)nst;
+  int64_t blocks = (nst + 7) / 8 * 8 * L.cap;
+  if (blocks == 0) return 0;
+  L.slots = (int32_t)(blocks / 8);
+  L.stagger = 0;
+  // (and few slots without a tile: they would leave their blocks idle)
+  if (big && !dots && tiles > kCUs && nst * L.cap <= tiles + tiles / 16 && same_steps(L.g, L.ngroups)) {
+    // (The last XCD starts 57 K cycles late: a third of a tile of 32 K steps, about a whole one of four.  Eight
+    // rounds and more make up for that: cross layers of rank 256 and 128, 12 rounds, 1088 against 1082 us and 971
+    // against 951 with none, 16 rounds 1284 / 1305 and 1148 / 1161, rank 512 and 1024 1 % less.)
+    if (kind != KIND_PLAIN && tiles >= 8 * kCUs) L.stagger = 2;
+    blocks = kCUs;
+  }
+  L.step = (int32_t)(blocks / 8);
+  return blocks;
+}
+
 // All groups of the list, kMaxGroups to a launch.  dots: every group computes its dot terms itself.
 template <int DT, int ALAY = OP_ROW, int WLAY = OP_ROW>
 void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t s, bool dots = false,
@@ -1284,36 +1319,9 @@ void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t 
         continue;
       }
     }
-    const bool big = take_big(p, L.g, L.ngroups);
-    const int tile = big ? 256 : 128;
-    int64_t tiles = 0;
-    for (int i = 0; i < L.ngroups; ++i) tiles += tiles_of(L.g[i], tile);
-    // super-tiles as large as an XCD's resident blocks, or an eighth of the launch where that is less
-    const int resident = big ? 32 : 64;
-    L.super = (int32_t)std::max<int64_t>(1, std::min<int64_t>(resident, (tiles + 7) / 8));
-    L.cap = 1;
-    int64_t nst = 0;
-    for (int i = 0; i < L.ngroups; ++i) {
-      L.tile_start[i] = (int32_t)nst;
-      const int64_t tn = (L.g[i].N + tile - 1) / tile, tm = (int64_t)((L.g[i].M + tile - 1) / tile) * tm_slices(L.g[i]);
-      const int64_t sm = tn >= L.super ? 1 : L.super / tn;
-      L.cap = (int32_t)std::max<int64_t>(L.cap, std::min(sm, tm) * tn);
-      nst += (tm + sm - 1) / sm;
-    }
-    L.tile_start[L.ngroups] = (int32_t)nst;
-    int64_t blocks = (nst + 7) / 8 * 8 * L.cap;
+    bool big;
+    const int64_t blocks = tile_launch(p, L, dots, kind, &big);
     if (blocks == 0) continue;
-    L.slots = (int32_t)(blocks / 8);
-    L.stagger = 0;
-    // (and few slots without a tile: they would leave their blocks idle)
-    if (big && !dots && tiles > kCUs && nst * L.cap <= tiles + tiles / 16 && same_steps(L.g, L.ngroups)) {
-      // (The last XCD starts 57 K cycles late: a third of a tile of 32 K steps, about a whole one of four.  Eight
-      // rounds and more make up for that: cross layers of rank 256 and 128, 12 rounds, 1088 against 1082 us and 971
-      // against 951 with none, 16 rounds 1284 / 1305 and 1148 / 1161, rank 512 and 1024 1 % less.)
-      if (kind != KIND_PLAIN && tiles >= 8 * kCUs) L.stagger = 2;
-      blocks = kCUs;
-    }
-    L.step = (int32_t)(blocks / 8);
     DmtScope scope(p, kid, s);
     if constexpr (ALAY == OP_ROW && WLAY == OP_ROW && DMT_TM_TAG == 0) {
       if (dots && big && keepz) { launch_tiles<DT, 256, ALAY, WLAY, KIND_PLAIN, true, true>(L, blocks, s); continue; }

@@ -152,3 +152,23 @@ def test_wide_towers_of_several_forms_in_one_plan(keep):
     wide = [_tower("cross_linear", 4, 128, 264, layers=3), _tower("linear", 4, 128, 520), _tower("cross_linear", 4, 128, 264, layers=2),
             _tower("cross_lowrank_linear", 4, 128, 264, layers=2, r=136), _tower("dot_linear", 4, 128, 264)]
     _check(wide, 12345, "bf16", keep)
+
+
+# Blocks that work through several 256 x 256 tiles whose K has two segments, which every tile starts over: dot terms
+# beside pooled values (12 features and more) in the forward, a per-feature layer beside the flat one in the backward
+# (tests/test_tm_host.py checks that these sizes are such launches).  Ragged rows and columns, a last K step that
+# is cut off in either segment.
+@pytest.mark.parametrize("nf,dim,out", [(16, 64, 520), (16, 64, 516), (12, 64, 520)])
+def test_many_tiles_of_dot_towers(nf, dim, out):
+    _check([_tower("dot_linear", nf, dim, out)] * 4, 10233, "bf16", False)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("r", [64, 24])
+def test_many_tiles_of_per_feature_layers(r, dtype):
+    _check([_tower("dlrm", 4, 256, 4 * r + 264, r=r)] * 4, 10233, dtype, False)
+
+
+def test_many_tiles_as_wide_as_the_output():
+    """Tiles that share no rows of their first operand with another."""
+    _check([_tower("linear", 8, 128, 256)] * 4, 32760, "bf16", False)

@@ -25,6 +25,13 @@ def lib(tmp_path_factory):
                 'extern "C" int allow_lds(int dev, int fail) { g_dev = dev; g_fail = fail; g_sets = 0; dmt_allow_lds(lds, &lds, 1); return g_sets; }\n'
                 'extern "C" int first_step(int steps, int part, int log2_ks) { return f32_first_step(steps, part, log2_ks); }\n'
                 'extern "C" int slice_end(int K1, int kofs, int klen) { return tm_slice_end(K1, kofs, klen); }\n'
+                '// blocks of a launch of n like groups; *tiles its tiles\n'
+                'extern "C" long blocks_of(int n, int M, int N, int K0, int K1, int reps, long* tiles) {\n'
+                '  dmt_plan p; TmLaunch L; L.ngroups = n; bool big;\n'
+                '  for (int i = 0; i < n; ++i) { TmGroup g{}; g.M = M; g.N = N; g.K0 = K0; g.K1 = K1; g.reps = reps; L.g[i] = g; }\n'
+                '  const long b = tile_launch(&p, L, false, KIND_PLAIN, &big);\n'
+                '  *tiles = 0; for (int i = 0; i < n; ++i) *tiles += tiles_of(L.g[i], big ? 256 : 128);\n'
+                '  return big ? b : -b; }\n'
                 'static DmtPerDevice once;\n'
                 'extern "C" int needed(int dev) { const bool n = once.needed(dev); once.set(dev); return n; }\n')
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + hip_build.FLAGS + ["-O0", "--cuda-host-only", "-shared", "-o", so, src],
@@ -70,3 +77,27 @@ def test_lds_beyond_the_default_is_asked_for_on_every_device(lib):
         if n:
             uses[name] = n
     assert uses == {"dmt_internal.h": 1}
+
+
+# (towers, rows, columns, K of the first segment, of the second, contractions a group stands for) of launches that one
+# block per CU works through; tests/test_gpu_tm_forms.py runs them
+ONE_BLOCK_PER_CU = [
+    (4, 10233, 520, 120, 1024, 0), (4, 10233, 516, 120, 1024, 0), (4, 10233, 520, 66, 768, 0),    # dot terms | pooled values
+    (4, 10233, 256, 264, 64, 4), (4, 10233, 256, 264, 24, 4),                                     # a per-feature layer's
+    (3, 5900, 1288, 0, 1024, 0), (3, 8200, 2056, 0, 128, 0), (4, 32760, 256, 0, 1024, 0),         # one segment
+]
+
+
+@pytest.mark.parametrize("n,M,N,K0,K1,reps", ONE_BLOCK_PER_CU)
+def test_launches_that_one_block_per_cu_works_through(lib, n, M, N, K0, K1, reps):
+    tiles = ctypes.c_long()
+    assert lib.blocks_of(n, M, N, K0, K1, reps, ctypes.byref(tiles)) == 256 and tiles.value > 256
+
+
+@pytest.mark.parametrize("n,M,N,K0,K1,reps", [(4, 8192, 512, 0, 1024, 0),                     # a tile a block
+                                              (3, 8200, 2056, 0, 64, 0),                      # one K step
+                                              (4, 8205, 520, 120, 1024, 0)])                  # many slots without a tile
+def test_launches_that_get_a_block_for_every_tile(lib, n, M, N, K0, K1, reps):
+    tiles = ctypes.c_long()
+    blocks = lib.blocks_of(n, M, N, K0, K1, reps, ctypes.byref(tiles))
+    assert blocks >= tiles.value and blocks % 8 == 0
