@@ -845,7 +845,7 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
     } else {
       // odd widths, unaligned rows: a column a lane, element by element; four rows' values are read before the first
       // is stored, and the column's bias once.  (Row by row, bias and all, 4 towers of 2048 columns to 257 outputs, batch
-      // 4999, took 54.0 us, now 45.6; to 100 43.6, now 36.1.)
+      // 4999, took 54.8 us, now 43.8; to 100 44.3, now 33.5.)
       const int n = n0 + wcol + ln;
       const float bias = epi < EPI_F32 && G.bias && n < N ? load_elt<DT>(G.bias, n) : 0.f;
 #pragma clang loop unroll(full)
@@ -859,16 +859,16 @@ __global__ __launch_bounds__(TmTile<TILE>::kThreads, TILE == 256 ? 1 : 2) void t
           for (int q = 0; q < 4; ++q) {
             const int m = m0 + wrow + i * 16 + r0 + q;
             if (m >= M || n >= N) continue;
-            const int64_t row = G.rdiv > 0 ? (int64_t)(m / G.rdiv) * G.ldc + (int64_t)(m % G.rdiv) * G.ldc2 : (int64_t)m * G.ldc;
+            const int64_t row = !DOTS && G.rdiv > 0 ? (int64_t)(m / G.rdiv) * G.ldc + (int64_t)(m % G.rdiv) * G.ldc2 : (int64_t)m * G.ldc;
             float y = v[q];
-            if (epi >= EPI_F32) {
+            if (!kForward && epi >= EPI_F32) {
               float* c = (float*)G.C + slice * G.cstride + row + n;
-              *c = epi == EPI_F32_ADD ? *c + y : y;
+              *c = KIND == KIND_ADD ? *c + y : y;
               continue;
             }
             if (G.bias) y += bias;
             if (epi == EPI_BIAS_RELU) y = y > 0.f ? y : 0.f;
-            if (epi == EPI_CROSS) {
+            if (kForward && KIND == KIND_READS) {
               if (G.U) store_elt<DT>(G.U, row + n, y);
               y = load_elt<DT>(G.X0, (int64_t)m * G.ldx + n) * y + load_elt<DT>(G.XL, (int64_t)m * G.ldxl + n);
             }
