@@ -146,7 +146,7 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
         g.back().M = (int32_t)B;
         g.back().N = tp[t].out_dim;
       }
-    dots_any = !g.empty() && take_small(p, g.data(), (int)g.size());
+    dots_any = !g.empty() && take_small(p, g.data(), (int)g.size(), true);
   }
   // (Only the kernel with in-kernel dot terms clears the weights that meet the zeros behind the terms: the
   // pooled values' first ones, where the terms are no multiple of 8.  The others read zeros in the

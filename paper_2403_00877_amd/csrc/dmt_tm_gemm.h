@@ -1210,34 +1210,7 @@ inline int64_t tiles_of(const TmGroup& g, int tile) {
   return (int64_t)((g.M + tile - 1) / tile) * ((g.N + tile - 1) / tile) * tm_slices(g);
 }
 
-// Whether a launch takes 256 x 256 tiles: when there are at least kBigTiles of them (three for every
-// four CUs) and no group is so narrow that half of every tile would be empty.  (A short K makes no
-// difference: data gradients of K = 128 and 256, 720 against 715 and 108 against 102 us.)
-constexpr int kBigTiles = 192;
-inline bool take_big(const dmt_plan* p, const TmGroup* g, int n) {
-  if (p->sw.tm_big == 0) return false;
-  int64_t tiles = 0;
-  for (int i = 0; i < n; ++i) {
-    if (g[i].M <= 128 || g[i].N <= 128) return false;
-    tiles += tiles_of(g[i], 256);
-  }
-  return tiles >= kBigTiles || p->sw.tm_big == 2;
-}
-
-// Whether a forward launch goes to tm_gemm_small: up to 768 tiles of 32 x 32, one and a half rounds of
-// the blocks that are resident together.  Both sides measured (128 x 128 / 32 x 32 tiles, us): dots and
-// K = 1052, 512 tiles 28.6 / 19.2, 832 tiles 28.0 / 30.3; K = 832, 704 tiles 31.9 / 27.2, 1024 tiles
-// 31.5 / 34.1; two cross layers of 2048 columns, 1024 tiles each 85.8 / 84.2, 2048 tiles 87.8 / 149.
-inline bool take_small(const dmt_plan* p, const TmGroup* g, int n) {
-  if (p->sw.tm_big != 1) return p->sw.tm_big == 3;
-  int64_t tiles = 0;
-  for (int i = 0; i < n; ++i) tiles += tiles_of(g[i], 32);
-  return tiles <= 768;
-}
-
-// Whether a launch's 256 x 256 tiles may be worked through by one block per CU: every tile has the same number
-// of K steps (blocks that are handed out a tile at a time even differences out), and two at least, so
-// that the requests are never more than one tile ahead.
+// Whether every tile of a launch has the same number of K steps, and two at least.
 constexpr int kCUs = 256;
 inline bool same_steps(const TmGroup* g, int n) {
   int64_t steps = 0;
@@ -1249,6 +1222,45 @@ inline bool same_steps(const TmGroup* g, int n) {
     steps = s;
   }
   return true;
+}
+
+// Whether a launch takes 256 x 256 tiles: when there are at least kBigTiles of them (three for every four CUs), or
+// when 128 x 128 tiles of equal K would be more than the kMidSlots blocks that are resident together, and no group is
+// so narrow that half of every tile would be empty.  Both sides measured (forward, 128 x 128 / 256 x 256 tiles, us): 4
+// linear towers of 1024 columns, 448 mid tiles 22.1 / 30.9, 528 (132 big ones) 37.1 / 31.2, of 256 columns 11.3 / 16.5
+// and 19.4 / 16.9; dots and K = 1052, 512 mid tiles 40.2 / 48.4, 528 77.2 / 49.1.  Cross layers' second round is
+// short beside their epilogues: 4 towers of 2048 columns, 640 mid tiles (160 big ones) 156.3 / 162.9, from 192 big
+// ones on 164.6 / 139.8; towers of unequal K even out better in the smaller tiles (3 to 20 tables, 576 mid tiles
+// 30.2 / 38.0).
+constexpr int kBigTiles = 192, kMidSlots = 512;
+inline bool take_big(const dmt_plan* p, const TmGroup* g, int n) {
+  if (p->sw.tm_big == 0) return false;
+  int64_t tiles = 0, mid = 0;
+  bool plain = true;
+  for (int i = 0; i < n; ++i) {
+    if (g[i].M <= 128 || g[i].N <= 128) return false;
+    tiles += tiles_of(g[i], 256);
+    mid += tiles_of(g[i], 128);
+    plain = plain && (g[i].epi == EPI_BIAS || g[i].epi == EPI_BIAS_RELU);
+  }
+  return tiles >= kBigTiles || (plain && mid > kMidSlots && same_steps(g, n)) || p->sw.tm_big == 2;
+}
+
+// Whether a forward launch goes to tm_gemm_small: up to 512 tiles of 32 x 32, two for every CU; 768 of cross layers,
+// 1024 with dot terms, which a 128 x 128 tile takes longer over.  Both sides measured (128 x 128 / 32 x 32 tiles, us):
+// one segment, K = 1024, 512 tiles 13.7 / 12.0, 576 tiles 13.8 / 16.5, K = 2048 21.5 / 21.5 and 21.7 / 29.2, K = 512,
+// 768 tiles 10.1 / 10.2; cross layers of 4 towers of 1024 columns, 768 tiles 46.5 / 42.5, 896 tiles 46.4 / 49.3; dots
+// and K = 1052, 1024 tiles 30.2 / 28.6, 1152 tiles 30.1 / 32.9, 4 features of 32, 1024 tiles 14.4 / 11.5, 1152 tiles
+// 14.4 / 14.4.
+inline bool take_small(const dmt_plan* p, const TmGroup* g, int n, bool dots) {
+  if (p->sw.tm_big != 1) return p->sw.tm_big == 3;
+  int64_t tiles = 0;
+  bool cross = true;
+  for (int i = 0; i < n; ++i) {
+    tiles += tiles_of(g[i], 32);
+    cross = cross && g[i].epi == EPI_CROSS;
+  }
+  return tiles <= (dots ? 1024 : cross ? 768 : 512);
 }
 
 // Cuts a launch's groups into tiles and deals them out; how many blocks it takes.
@@ -1274,7 +1286,9 @@ inline int64_t tile_launch(const dmt_plan* p, TmLaunch& L, bool dots, int kind, 
   if (blocks == 0) return 0;
   L.slots = (int32_t)(blocks / 8);
   L.stagger = 0;
-  // (and few slots without a tile: they would leave their blocks idle)
+  // One block per CU works through a launch's 256 x 256 tiles where their K is equal (blocks that are handed out a
+  // tile at a time even differences out) and two steps at least, so that the requests are never more than one tile
+  // ahead, and where few slots are without a tile: they would leave their blocks idle.
   if (big && !dots && tiles > kCUs && nst * L.cap <= tiles + tiles / 16 && same_steps(L.g, L.ngroups)) {
     // (The last XCD starts 57 K cycles late: a third of a tile of 32 K steps, about a whole one of four.  Eight
     // rounds and more make up for that: cross layers of rank 256 and 128, 12 rounds, 1088 against 1082 us and 971
@@ -1304,7 +1318,7 @@ void launch_groups(const dmt_plan* p, std::vector<TmGroup>& groups, hipStream_t 
     }
     if constexpr (ALAY == OP_ROW && WLAY == OP_ROW && DMT_TM_TAG == 0) {
       // (in-kernel dot terms, or one K segment)
-      bool small = take_small(p, L.g, L.ngroups);
+      bool small = take_small(p, L.g, L.ngroups, dots);
       for (int i = 0; i < L.ngroups; ++i) small = small && (dots || L.g[i].K0 == 0);
       if (small) {
         int64_t blocks = 0;

@@ -32,6 +32,10 @@ def lib(tmp_path_factory):
                 '  const long b = tile_launch(&p, L, false, KIND_PLAIN, &big);\n'
                 '  *tiles = 0; for (int i = 0; i < n; ++i) *tiles += tiles_of(L.g[i], big ? 256 : 128);\n'
                 '  return big ? b : -b; }\n'
+                'extern "C" int forward_tile(int n, int M, int N, int K1, int dK, int epi, int dots) {\n'
+                '  dmt_plan p; TmGroup g[kMaxGroups] = {};\n'
+                '  for (int i = 0; i < n; ++i) { g[i].M = M; g[i].N = N; g[i].K1 = K1 + i * dK; g[i].epi = epi; }\n'
+                '  return take_small(&p, g, n, dots != 0) ? 32 : take_big(&p, g, n) ? 256 : 128; }\n'
                 'static DmtPerDevice once;\n'
                 'extern "C" int needed(int dev) { const bool n = once.needed(dev); once.set(dev); return n; }\n')
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + hip_build.FLAGS + ["-O0", "--cuda-host-only", "-shared", "-o", so, src],
@@ -101,3 +105,20 @@ def test_launches_that_get_a_block_for_every_tile(lib, n, M, N, K0, K1, reps):
     tiles = ctypes.c_long()
     blocks = lib.blocks_of(n, M, N, K0, K1, reps, ctypes.byref(tiles))
     assert blocks >= tiles.value and blocks % 8 == 0
+
+
+BIAS, CROSS, F32 = 0, 2, 3           # what a launch's outputs are (EPI_*)
+
+
+@pytest.mark.parametrize("n,M,N,K,dK,epi,dots,tile", [
+    (4, 512, 256, 1024, 0, BIAS, 0, 32), (4, 513, 256, 1024, 0, BIAS, 0, 128),            # 512 small tiles and more
+    (4, 192, 1024, 1024, 0, CROSS, 0, 32), (4, 193, 1024, 1024, 0, CROSS, 0, 128),        # 768 of cross layers
+    (8, 512, 256, 1024, 0, BIAS, 1, 32), (8, 513, 256, 1024, 0, BIAS, 1, 128),            # 1024 with dot terms
+    (8, 4096, 256, 1024, 0, BIAS, 0, 128), (8, 4097, 256, 1024, 0, BIAS, 0, 256),         # 512 mid tiles and more
+    (8, 4097, 256, 1024, 0, BIAS, 1, 256), (8, 4097, 256, 1024, 64, BIAS, 0, 128),        # ... unequal K
+    (8, 4097, 256, 64, 0, BIAS, 0, 128), (8, 4097, 256, 1024, 0, F32, 0, 128),            # ... one K step, gradients
+    (4, 1280, 2048, 2048, 0, CROSS, 0, 128), (4, 1281, 2048, 2048, 0, CROSS, 0, 256),     # 192 big tiles
+    (8, 6000, 256, 1024, 64, BIAS, 0, 256), (8, 60000, 128, 1024, 0, BIAS, 0, 128),       # ... unless narrow
+])
+def test_which_tiles_a_launch_takes(lib, n, M, N, K, dK, epi, dots, tile):
+    assert lib.forward_tile(n, M, N, K, dK, epi, dots) == tile
