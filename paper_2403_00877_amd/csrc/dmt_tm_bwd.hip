@@ -274,10 +274,14 @@ struct TileCount {
 // fill the CUs once, as nearly as they can without a second, mostly empty round: 256 x 256 tiles
 // (one to a CU) while a slice stays at least 1024 long, else 128 x 128 (two to a CU) and at least 512.
 inline void choose_split(const dmt_plan* p, const TileCount& n, int64_t K, int* ksplit, int* klen) {
-  // (No slices where the 128 x 128 tiles alone are three for every four slots: adding two slices of
-  // 512 x 2048 weights up took longer than the larger tiles saved, 400 against 360 us.)
+  // No slices where the 128 x 128 tiles alone are three for every four slots, but for two of 4096 and more, which
+  // make enough 256 x 256 tiles: what these save then is more than adding the slices up takes.  Backward, 128 x 128 /
+  // two slices, us: 12 towers of 1024 columns to 512 outputs (384 tiles), batch 4096 215.3 / 203.0, 8192 390.3 /
+  // 356.0, 16384 722.8 / 643.7, 22 of them (704) 390.2 / 395.2, 691.4 / 671.4 and 1327 / 1254; 23 of 768 columns to 400 331.1 /
+  // 359.0, 682.5 / 677.9 and 1213 / 1180; rank 512 beside 2048 columns, 8 towers, 737.2 / 745.2 and 1363 / 1323.
   int64_t ks = 1;
   const bool enough = n.wide ? n.t256 >= kBigTiles || n.t128 >= 384 : false;
+  if (enough && n.t256 < kBigTiles && n.t256 * 2 >= kBigTiles && K >= 8192) ks = 2;
   if (n.wide && !enough) ks = std::min<int64_t>(16, 256 / std::max<int64_t>(n.t256, 1));
   if (!enough && (!n.wide || n.t256 * ks < kBigTiles || K / ks < 1024)) {
     ks = std::max<int64_t>(1, std::min<int64_t>(16, 512 / std::max<int64_t>(n.t128, 1)));

@@ -639,7 +639,9 @@ def test_cross_gradient_rounds_its_products_first(layers, big, monkeypatch):
 
 @pytest.mark.parametrize("kind", ["linear", "cross_linear"])
 @pytest.mark.parametrize("widths,out,batch", [((1024, 1024, 1024), 1288, 5900), ((128, 128, 128), 2056, 8200),
-                                              ((64, 128, 256), 2056, 8200), ((1024,) * 4, 256, 33000)])
+                                              ((64, 128, 256), 2056, 8200), ((1024,) * 4, 256, 33000),
+                                              # projections' gradients in two slices of a long batch, the second short
+                                              ((1024,) * 3, 2048, 8195)])
 def test_launches_of_more_tiles_than_cus(kind, widths, out, batch):
     """Blocks that work through several 256 x 256 tiles (K of two steps and more, equal in all towers), and
     launches that must not (unequal towers, one K step), forward and backward, against float32 torch.
