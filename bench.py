@@ -105,7 +105,7 @@ def batch_accounting(torch, w, idx, off):
 
 # kernel (as the profiler names it) -> the family dmt_kernel_name() reports
 FAMILIES = (("lookup_fwd_kernel", "lookup_fwd"), ("bwd_reduce_update", "bwd_reduce_update"),
-            ("bwd_fixup_update", "bwd_fixup_update"), ("bwd_build_keys", "bwd_build_keys"),
+            ("bwd_fixup_update", "bwd_fixup_update"), ("bwd_bag_samples", "bwd_build_keys"),
             ("radix_hist", "radix_hist"), ("radix_scan", "radix_scan"), ("radix_scatter", "radix_scatter"),
             ("tm_gemm", "tm_gemm"), ("tm_pack_w", "tm_pack_w"), ("tm_dots", "tm_dots"),
             ("dmt_copy_kernel", "copy"))
@@ -492,8 +492,8 @@ def run_workload(args, wname, traffic, primary):
         # state read + write; partial sums of rows that span tiles
         "bwd_reduce_update": float((nnz_f * (8 + Df * 4) + U_f * (2 * Df * eb + 8)).sum()
                                    - span * (2 * Dmax * eb + 8) + pslots * Dmax * 4),
-        # one radix pass: records read and written
-        "radix_scatter": nnz * 16,
+        # one radix pass of three: row and sample read and written, 6 bytes; the last writes 8
+        "radix_scatter": nnz * 38 / 3,
     }
     compulsory = {
         # each distinct row once; ids, offsets and the pooled store as they are
@@ -501,7 +501,7 @@ def run_workload(args, wname, traffic, primary):
         # each bag's gradient slice once, every sorted record once, each distinct row read and
         # written once with its state
         "bwd_reduce_update": float((B * Df * 4 + nnz_f * 8 + U_f * (2 * Df * eb + 8)).sum()),
-        "radix_scatter": nnz * 16,
+        "radix_scatter": nnz * 38 / 3,
     }
     kin = w.tm_in_dims()
     tw = w.tower_widths()

@@ -502,7 +502,7 @@ typedef enum {
   DMT_K_TM_DOTS = 1,           /* pairwise dot terms                          */
   DMT_K_TM_PACK = 2,           /* projection-weight repack for the dot TM     */
   DMT_K_TM_GEMM = 3,           /* grouped contraction (cross layers, linears) */
-  DMT_K_BWD_KEYS = 4,          /* key build                                   */
+  DMT_K_BWD_KEYS = 4,          /* each lookup's sample, the sort's blocks     */
   DMT_K_BWD_SORT_HIST = 5,     /* radix pass: per-block digit histogram       */
   DMT_K_BWD_SORT_SCAN = 6,     /* radix pass: digit offsets                   */
   DMT_K_BWD_SORT_SCATTER = 7,  /* radix pass: stable scatter                  */

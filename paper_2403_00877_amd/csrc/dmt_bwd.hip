@@ -1,5 +1,5 @@
 // dmt_tower_lookup_bwd_update: gradients to the activated rows only (paper
-// Sec. 2.2), as  key build -> stable LSD radix sort by row id inside every
+// Sec. 2.2), as  samples of the lookups -> stable LSD radix sort by row id inside every
 // table's records -> tiled segment reduce fused with the rowwise Adagrad row
 // update -> fix-up of rows whose run spans several tiles.
 //
@@ -7,15 +7,16 @@
 // bag order), every row's gradient is summed in a fixed order, and each row has
 // exactly one writer.  No floating-point atomics anywhere.
 //
-// Data in the workspace: 64-bit records (global_row << 32 | bag), where
+// The sort's result: 64-bit records (global_row << 32 | bag), where
 // global_row = (sum of rows of earlier tables) + row and bag = f*B + b.  The
 // lookups arrive grouped by table (bags are table-major), so the sort never moves
 // a record out of its table's range: sort blocks are aligned to the tables and
 // every pass ranks only the bits of the row inside the table, which takes
-// ceil(log2(largest table)) bits instead of ceil(log2(all rows)).  An id outside
+// ceil(log2(largest table)) bits instead of ceil(log2(all rows)), and until its last pass
+// a record is the row inside the table and the sample.  An id outside
 // its table gets the key  kInertBit | (global id one past the table's last row):
 // it sorts behind the table's rows, equals no row's key, and is never touched.
-// `offsets` must tile [0, nnz) (ascending, offsets[0] = 0, last = nnz): the key build
+// `offsets` must tile [0, nnz) (ascending, offsets[0] = 0, last = nnz): bwd_bag_samples
 // checks this, records the first bag that breaks it, and the reduce and fix-up kernels
 // then return without touching a row (dmt_last_device_error reports DMT_EINVAL).
 #include <algorithm>
@@ -28,7 +29,7 @@
 
 namespace {
 
-// ------------------------------------------------------------------ key build
+// ------------------------------------------------------------------ samples of the lookups
 
 // Where each table's records start and which sort blocks cover them.  Run by one block.
 // The starts come from the offsets of every table's first bag, clamped to [0, nnz] and made ascending (each at
@@ -72,18 +73,20 @@ __device__ void build_sort_map(const int64_t* __restrict__ offsets, uint32_t B, 
   if (threadIdx.x == 0) seg_blk[F] = blk_run;
 }
 
-// One block takes 2^log2_bpb consecutive bags and walks their lookups id by id, so the work per
+// Which sample each lookup belongs to: smp[j] = b for the lookups j of bag f*B + b.  The sort's first pass reads
+// it beside `indices`.
+// One block takes 2^log2_bpb consecutive bags and walks their lookups four at a time, so the work per
 // thread does not depend on how the bag lengths are spread (a lane group per bag leaves most lanes
 // idle when a few bags are hundreds of ids long and most hold one or two).  The bags' offsets go
-// to LDS; a thread finds the bag of its position by bisection there.
+// to LDS; a thread finds the bag of its first position by bisection there and goes on from it.
 constexpr int kKeysMaxBags = 1024;
-__global__ __launch_bounds__(kBlock) void bwd_build_keys(
-    const DmtTableMeta* __restrict__ meta, const int32_t* __restrict__ indices,
+template <typename Sample>
+__global__ __launch_bounds__(kBlock) void bwd_bag_samples(
     const int64_t* __restrict__ offsets, uint32_t B, uint32_t nbags, int64_t nnz, int F,
-    uint64_t* __restrict__ pk, int log2_bpb, int least_items, uint32_t* __restrict__ seg_begin,
+    Sample* __restrict__ smp, int log2_bpb, int least_items, uint32_t* __restrict__ seg_begin,
     uint32_t* __restrict__ seg_blk, uint32_t* __restrict__ blk_table,
-    unsigned long long* __restrict__ err, unsigned long long* __restrict__ err_offsets) {
-  __shared__ int64_t offs[kKeysMaxBags + 1];
+    unsigned long long* __restrict__ err_offsets) {
+  __shared__ uint32_t offs[kKeysMaxBags + 1];
   if (blockIdx.x == 0) build_sort_map(offsets, B, F, nnz, least_items, seg_begin, seg_blk, blk_table);
   const uint32_t g0 = blockIdx.x << log2_bpb;
   if (g0 >= nbags) return;
@@ -95,39 +98,70 @@ __global__ __launch_bounds__(kBlock) void bwd_build_keys(
     const bool at_end = g0 + (uint32_t)i == nbags;
     if (o < 0 || o > nnz || (g0 + (uint32_t)i == 0 && o != 0) || (at_end && o != nnz))
       atomicMin(err_offsets, (unsigned long long)(g0 + i - (at_end ? 1 : 0)));
-    offs[i] = o < 0 ? 0 : (o > nnz ? nnz : o);
+    offs[i] = (uint32_t)(o < 0 ? 0 : (o > nnz ? nnz : o));
   }
   __syncthreads();
   for (int i = threadIdx.x; i < nb; i += kBlock)
     if (offs[i] > offs[i + 1]) atomicMin(err_offsets, (unsigned long long)(g0 + i));
-  const int64_t s = offs[0], e = offs[nb];
-  for (int64_t j = s + threadIdx.x; j < e; j += kBlock) {
-    int lo = 0, hi = nb;                           // offs[lo] <= j < offs[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (offs[mid] <= j) lo = mid; else hi = mid;
+  const uint32_t s = offs[0], e = offs[nb], b0 = g0 % B;
+  for (uint32_t j = (s & ~3u) + threadIdx.x * 4; j < e; j += kBlock * 4) {
+    Sample v[4];
+    int lo = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t at = j + u;
+      // offs[lo] <= at < offs[lo + 1]; most lookups lie in the bag of the one before or in the next
+      if (at >= s && at < e && (u == 0 || offs[lo + 1] <= at)) {
+        if (u > 0 && lo + 2 <= nb && offs[lo + 2] > at) {
+          ++lo;
+        } else {
+          int hi = nb;
+          while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (offs[mid] <= at) lo = mid; else hi = mid;
+          }
+        }
+      }
+      uint32_t b = b0 + (uint32_t)lo;
+      if (b >= B) b = B > kKeysMaxBags ? b - B : b % B;
+      v[u] = (Sample)b;
     }
-    const uint32_t g = g0 + (uint32_t)lo;
-    const uint32_t f = g / B;
-    const uint64_t rows = (uint64_t)meta[f].rows;
-    const uint32_t row_base = (uint32_t)meta[f].row_base;
-    // a row-wise shard gives the ids of other shards the inert key silently (err is null then)
-    const int64_t local = (int64_t)indices[j] - meta[f].row_begin;
-    uint32_t gid = row_base + (uint32_t)local;
-    if ((uint64_t)local >= rows) {
-      if (err) atomicMin(err, (unsigned long long)j);
-      gid = kInertBit | (row_base + (uint32_t)rows);
+    if (j >= s && j + 4 <= e) {
+      struct alignas(4 * sizeof(Sample)) Four { Sample v[4]; };
+      *(Four*)(smp + j) = Four{{v[0], v[1], v[2], v[3]}};
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (j + u >= s && j + u < e) smp[j + u] = v[u];
     }
-    pk[j] = ((uint64_t)gid << 32) | g;
   }
 }
 
 // ------------------------------------------------------------------ radix sort
 
-// A sort block's share of its table's records, and the table's first global row id.
+// Between its passes the sort keeps a lookup as a 32-bit row id inside its table and the sample (16 bits up to
+// 65536 samples), in two arrays: the table is known from the position.  The counting kernels then read 4 bytes
+// a lookup and the scatters move 6 each way, and the first pass reads `indices` as they lie.  Only the last pass
+// writes the 64-bit records the reduce kernels walk.  Records of 8 bytes through all passes, built beforehand
+// / now, us: 64 tables of 164 K lookups, 20 bits of row id: build 41 / samples 18, count 22 / 10-13, scatter 43 / 34-46
+// a pass, the whole sort 253 / 188; 256 of 246 K, 20 bits: 1543 / 908; 128 of 170 K, 23 bits: 563 / 374.  The
+// scatters are bound by their instructions (a wave's 64 lanes take four cycles each) as much as by bytes.
+template <typename Sample>
+struct SortIo {
+  const int32_t* ids;            // first pass: the call's indices
+  const uint32_t* key_in;        // other passes
+  const Sample* smp_in;
+  uint32_t* key_out;             // all passes but the last
+  Sample* smp_out;
+  uint64_t* pk_out;              // last pass
+};
+
+// A sort block's share of its table's records, and what its table decides.
 struct SortBlock {
-  uint32_t base, n, row_base, valid;
+  uint32_t id, base, n, valid;   // its number, counted through the tables
   uint32_t table_base, at, nb;   // first record of the table; which of its nb sort blocks this is
+  uint32_t f, rows, row_base;    // the table; its rows; its first global row id
+  int64_t row_begin;             // id of its first row
   int items;                     // records per thread (narrow digits: kSortItems)
 };
 template <bool Wide>
@@ -135,48 +169,78 @@ __device__ __forceinline__ SortBlock sort_block(const DmtTableMeta* __restrict__
                                                 const uint32_t* __restrict__ seg_begin,
                                                 const uint32_t* __restrict__ seg_blk,
                                                 const uint32_t* __restrict__ blk_table, int F) {
-  SortBlock sb{0, 0, 0, 0, 0, 0, 0, 0};
+  SortBlock sb{};
   if (blockIdx.x >= seg_blk[F]) return sb;
-  const uint32_t packed = blk_table[blockIdx.x], f = packed >> 4;
+  sb.id = blockIdx.x;
+  const uint32_t packed = blk_table[sb.id], f = packed >> 4;
   sb.items = Wide ? (int)(packed & 15) : kSortItems;
   const uint32_t sort_tile = (uint32_t)(sb.items * kBlock);
   sb.table_base = seg_begin[f];
-  sb.at = blockIdx.x - seg_blk[f];
+  sb.at = sb.id - seg_blk[f];
   sb.nb = seg_blk[f + 1] - seg_blk[f];
   sb.base = sb.table_base + sb.at * sort_tile;
   const uint32_t end = seg_begin[f + 1];
   sb.n = end - sb.base < sort_tile ? end - sb.base : sort_tile;
+  sb.f = f;
+  sb.rows = (uint32_t)meta[f].rows;
   sb.row_base = (uint32_t)meta[f].row_base;
+  sb.row_begin = meta[f].row_begin;
   sb.valid = 1;
   return sb;
 }
 
-// The pass's digit of a record: bits [shift, shift + bits) of the row id inside the table.
-__device__ __forceinline__ uint32_t sort_digit(uint64_t rec, uint32_t row_base, int shift,
-                                               uint32_t mask) {
-  return ((((uint32_t)(rec >> 32) & ~kInertBit) - row_base) >> shift) & mask;
+// The row inside the table, or one past its last row for an id outside it.
+template <bool First, typename Sample>
+__device__ __forceinline__ uint32_t sort_key(const SortIo<Sample>& io, const SortBlock& sb, uint32_t at) {
+  if constexpr (First) {
+    const int64_t local = (int64_t)io.ids[at] - sb.row_begin;
+    return (uint64_t)local < (uint64_t)sb.rows ? (uint32_t)local : sb.rows;
+  } else {
+    return io.key_in[at];
+  }
 }
 
-template <int MaxBits>
+template <int MaxBits, bool First, typename Sample>
 __global__ __launch_bounds__(kBlock) void radix_hist(
-    const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ pk, int shift, int bits,
+    const DmtTableMeta* __restrict__ meta, SortIo<Sample> io, int shift, int bits,
     uint32_t* __restrict__ hist, const uint32_t* __restrict__ seg_begin,
-    const uint32_t* __restrict__ seg_blk, const uint32_t* __restrict__ blk_table, int F) {
+    const uint32_t* __restrict__ seg_blk, const uint32_t* __restrict__ blk_table, int F,
+    unsigned long long* __restrict__ err) {
   constexpr int MaxRadix = 1 << MaxBits;
   __shared__ uint32_t h[MaxRadix];
   const SortBlock sb = sort_block<MaxBits == kWideRadixBits>(meta, seg_begin, seg_blk, blk_table, F);
   if (!sb.valid) return;
   for (int d = threadIdx.x; d < MaxRadix; d += kBlock) h[d] = 0;
-  __syncthreads();
   const uint32_t mask = (1u << bits) - 1;
+  // (no load is conditional: the compiler would wait for each before the next)
+  uint32_t key[kSortItems];
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i)
+    key[i] = sort_key<First>(io, sb, sb.base + min((uint32_t)(i * kBlock + threadIdx.x), sb.n - 1));
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int i = 0; i < kSortItems; ++i) {
     const uint32_t q = i * kBlock + threadIdx.x;
-    if (q < sb.n) atomicAdd(&h[sort_digit(pk[sb.base + q], sb.row_base, shift, mask)], 1u);
+    const uint32_t d = (key[i] >> shift) & mask;
+    if constexpr (First) {
+      if (q < sb.n) {
+        atomicAdd(&h[d], 1u);
+        // (a row-wise shard passes over the ids of other shards silently: err is null then)
+        if (err && key[i] == sb.rows) atomicMin(err, (unsigned long long)(sb.base + q));
+      }
+    } else {
+      // behind the first pass the lookups of a frequent row lie side by side, and 64 lanes that add to one
+      // counter take 64 turns: a run of equal digits is added by its first lane
+      const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)d, 0x138, 0xf, 0xf, false);   // wave_shr:1
+      const uint64_t valid = __ballot(q < sb.n);
+      const uint64_t ends = (__ballot(d != before) | ~valid) >> 1 >> lane;     // where the lanes behind this one start anew
+      if (q < sb.n && d != before) atomicAdd(&h[d], ends ? (uint32_t)__ffsll((unsigned long long)ends) : 64u - lane);
+    }
   }
   __syncthreads();
   for (int d = threadIdx.x; d < (1 << bits); d += kBlock)
-    hist[(int64_t)blockIdx.x * MaxRadix + d] = h[d];
+    hist[(int64_t)sb.id * MaxRadix + d] = h[d];
 }
 
 // One block per table: turns the per-block digit counts of the table's sort blocks into the
@@ -236,16 +300,15 @@ __global__ __launch_bounds__(kScanThreads) void radix_scan(uint32_t* __restrict_
 
 // Stable scatter of a sort block's records.  `hist` holds where the block's first record of each digit
 // goes or, with OwnScan, the digit counts radix_hist left.
-template <int MaxBits, bool OwnScan>
+template <int MaxBits, bool OwnScan, bool First, bool Last, typename Sample>
 __global__ __launch_bounds__(kBlock) void radix_scatter(
-    const DmtTableMeta* __restrict__ meta, const uint64_t* __restrict__ in,
-    uint64_t* __restrict__ out, int shift, int bits, const uint32_t* __restrict__ hist,
-    const uint32_t* __restrict__ seg_begin, const uint32_t* __restrict__ seg_blk,
-    const uint32_t* __restrict__ blk_table, int F) {
-  __shared__ uint64_t buf[kSortTile];
+    const DmtTableMeta* __restrict__ meta, SortIo<Sample> io, int shift, int bits,
+    const uint32_t* __restrict__ hist, const uint32_t* __restrict__ seg_begin,
+    const uint32_t* __restrict__ seg_blk, const uint32_t* __restrict__ blk_table, int F, uint32_t B) {
+  __shared__ uint32_t kbuf[kSortTile];
+  __shared__ Sample sbuf[kSortTile];
   constexpr int MaxRadix = 1 << MaxBits, DPT = (MaxRadix + kBlock - 1) / kBlock;
   __shared__ uint32_t cnt[kBlock / 64][MaxRadix];
-  __shared__ uint32_t tile_start[MaxRadix];
   __shared__ uint32_t gbase[MaxRadix];
   __shared__ uint32_t sm[8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -254,61 +317,62 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
   const SortBlock sb = sort_block<OwnScan>(meta, seg_begin, seg_blk, blk_table, F);
   if (!sb.valid) return;
   const int items = sb.items;
+  const int n_tile = (int)sb.n;
+  // (no load is conditional: the compiler would wait for each before the next)
+  uint32_t key[kSortItems], smp[kSortItems], rank[kSortItems];
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i) {
+    const uint32_t at = sb.base + (uint32_t)min(wave * (items * 64) + i * 64 + lane, n_tile - 1);
+    key[i] = sort_key<First>(io, sb, at);
+    smp[i] = io.smp_in[at];
+  }
   for (int w = 0; w < kBlock / 64; ++w)
     for (int d = tid; d < MaxRadix; d += kBlock) cnt[w][d] = 0;
   __syncthreads();
-  const uint32_t tile_base = sb.base;
-  const int n_tile = (int)sb.n;
-  volatile __attribute__((address_space(3))) uint32_t* my_cnt =
-      (volatile __attribute__((address_space(3))) uint32_t*)cnt[wave];
 
-  // stable rank of every record among the records of its wave with the same digit
-  uint64_t rec[kSortItems];
-  uint32_t rank[kSortItems];
+  // stable rank of every record among the records of its wave with the same digit: first among the 64
+  // records of its step (the lanes whose digit differs in no bit) ...
 #pragma unroll
   for (int i = 0; i < kSortItems; ++i) {
     if (i >= items) break;
-    const int q = wave * (items * 64) + i * 64 + lane;
-    const bool valid = q < n_tile;
-    rec[i] = valid ? in[tile_base + q] : ~0ULL;
-    const uint32_t d = sort_digit(rec[i], sb.row_base, shift, mask);
-    uint64_t peers = __ballot(valid);              // lanes of this wave holding the same digit
-    for (int b = 0; b < bits; ++b) {
-      const bool bit = (d >> b) & 1;
-      const uint64_t m = __ballot(bit);
-      peers &= bit ? m : ~m;
+    const uint32_t d = (key[i] >> shift) & mask;
+    const uint64_t valid = __ballot(wave * (items * 64) + i * 64 + lane < n_tile);
+    uint32_t other_lo = ~(uint32_t)valid, other_hi = ~(uint32_t)(valid >> 32);
+#pragma unroll
+    for (int b = 0; b < MaxBits; ++b) {
+      if (b >= bits) break;
+      const uint32_t mine = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);     // all ones where the bit is set
+      const uint64_t m = __ballot(mine != 0);
+      other_lo |= (uint32_t)m ^ mine;
+      other_hi |= (uint32_t)(m >> 32) ^ mine;
     }
-    uint32_t old = 0;
-    int leader = 0;
-    if (valid) {
-      leader = __ffsll((unsigned long long)peers) - 1;
-      if (lane == leader) {
-        old = my_cnt[d];
-        my_cnt[d] = old + (uint32_t)__popcll(peers);
-      }
-    }
-    old = __shfl(old, leader);
-    rank[i] = old + (uint32_t)__popcll(peers & ((1ULL << lane) - 1));
+    const uint32_t below = __builtin_amdgcn_mbcnt_hi(~other_hi, __builtin_amdgcn_mbcnt_lo(~other_lo, 0));
+    rank[i] = below | (uint32_t)(__popc(~other_lo) + __popc(~other_hi)) << 8;
+  }
+  // ... then behind those of the steps before it.  The lanes of a wave read a digit's count before its first
+  // lane raises it (LDS serves a wave in order).
+  volatile __attribute__((address_space(3))) uint32_t* my_cnt =
+      (volatile __attribute__((address_space(3))) uint32_t*)cnt[wave];
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i) {
+    if (i >= items) break;
+    const uint32_t d = (key[i] >> shift) & mask, below = rank[i] & 0xff;
+    const uint32_t old = my_cnt[d];
     __builtin_amdgcn_wave_barrier();
+    if (below == 0 && wave * (items * 64) + i * 64 + lane < n_tile) my_cnt[d] = old + (rank[i] >> 8);
+    __builtin_amdgcn_wave_barrier();
+    rank[i] = old + below;
   }
   __syncthreads();
-  // thread t owns digits t*DPT .. t*DPT+DPT-1: totals over the waves; cnt becomes each
-  // wave's offset inside the digit
+  // thread t owns digits t*DPT .. t*DPT+DPT-1: totals over the waves
   uint32_t tot[DPT];
   uint32_t tsum = 0;
 #pragma unroll
   for (int j = 0; j < DPT; ++j) {
     const int d = tid * DPT + j;
     tot[j] = 0;
-    if (d < radix) {
-      uint32_t run = 0;
-      for (int w = 0; w < kBlock / 64; ++w) {
-        const uint32_t c = cnt[w][d];
-        cnt[w][d] = run;
-        run += c;
-      }
-      tot[j] = run;
-    }
+    if (d < radix)
+      for (int w = 0; w < kBlock / 64; ++w) tot[j] += cnt[w][d];
     tsum += tot[j];
   }
   uint32_t total;
@@ -318,7 +382,7 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
     static_assert(DPT == 4, "a thread reads its digits' counts as one uint4");
     uint4 all = make_uint4(0, 0, 0, 0), before = make_uint4(0, 0, 0, 0);
     if (tid * DPT < radix) {
-      const uint4* __restrict__ h = (const uint4*)(hist + (int64_t)(blockIdx.x - sb.at) * MaxRadix) + tid;
+      const uint4* __restrict__ h = (const uint4*)(hist + (int64_t)(sb.id - sb.at) * MaxRadix) + tid;
       for (uint32_t b = 0; b < sb.nb; b += kScanBatch) {
         uint4 v[kScanBatch];
 #pragma unroll
@@ -343,14 +407,20 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
       at += a[j];
     }
   }
+  // cnt becomes where each wave's first record of the digit lies in the block's sorted tile
   uint32_t ex = dmt::block_exclusive_scan<kBlock / 64>(tsum, sm, total);
 #pragma unroll
   for (int j = 0; j < DPT; ++j) {
     const int d = tid * DPT + j;
     if (d < radix) {
-      tile_start[d] = ex;
       if constexpr (OwnScan) gbase[d] = goes[j] - ex;
-      else gbase[d] = hist[(int64_t)blockIdx.x * MaxRadix + d] - ex;
+      else gbase[d] = hist[(int64_t)sb.id * MaxRadix + d] - ex;
+      uint32_t run = ex;
+      for (int w = 0; w < kBlock / 64; ++w) {
+        const uint32_t c = cnt[w][d];
+        cnt[w][d] = run;
+        run += c;
+      }
     }
     ex += tot[j];
   }
@@ -358,16 +428,27 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
 #pragma unroll
   for (int i = 0; i < kSortItems; ++i) {
     if (i >= items) break;
-    const int q = wave * (items * 64) + i * 64 + lane;
-    if (q < n_tile) {
-      const uint32_t d = sort_digit(rec[i], sb.row_base, shift, mask);
-      buf[tile_start[d] + cnt[wave][d] + rank[i]] = rec[i];
+    if (wave * (items * 64) + i * 64 + lane < n_tile) {
+      const uint32_t at = cnt[wave][(key[i] >> shift) & mask] + rank[i];
+      kbuf[at] = key[i];
+      sbuf[at] = (Sample)smp[i];
     }
   }
   __syncthreads();
-  for (int q = tid; q < n_tile; q += kBlock) {
-    const uint64_t r = buf[q];
-    out[gbase[sort_digit(r, sb.row_base, shift, mask)] + (uint32_t)q] = r;
+  const uint32_t bag0 = sb.f * B;
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i) {
+    const int q = i * kBlock + tid;
+    if (q >= n_tile) break;
+    const uint32_t k = kbuf[q], b = sbuf[q];
+    const uint32_t to = gbase[(k >> shift) & mask] + (uint32_t)q;
+    if constexpr (Last) {
+      const uint32_t gid = (sb.row_base + k) | (k == sb.rows ? kInertBit : 0u);
+      io.pk_out[to] = ((uint64_t)gid << 32) | (bag0 + b);
+    } else {
+      io.key_out[to] = k;
+      io.smp_out[to] = (Sample)b;
+    }
   }
 }
 
@@ -1120,7 +1201,7 @@ __global__ __launch_bounds__(kLeanBlock) void bwd_reduce_update_lean(
     const uint32_t f_l = B == 1 ? bag_l : (__umulhi(bag_l, bag_mul) >> bag_shift);   // bag / B
     const uint32_t f = __builtin_amdgcn_readfirstlane(f_l);
     const int cnt = __popcll(__ballot(lane < nrem && f_l == f));   // records sorted by table: a prefix
-    if (f >= F) {                                  // not a record the key build wrote
+    if (f >= F) {                                  // not a record the sort wrote
       acc = make_float2(0.f, 0.f);
       from_left = 0;
       open_end = false;
@@ -1457,6 +1538,75 @@ void timed_launch(const dmt_plan* plan, dmt_kernel_id id, hipStream_t s, Kernel 
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3((unsigned)threads), 0, s, args...);
 }
 
+// What the sort's launches share.
+struct SortCall {
+  const dmt_plan* plan;
+  const BwdWs* w;
+  const int32_t* indices;
+  const int64_t* offsets;
+  int64_t nnz, B;
+  uint32_t nbags;
+  int log2_bpb;
+  int64_t key_blocks;
+  hipStream_t s;
+};
+
+template <int MaxBits, bool First, bool Last, typename Sample>
+void launch_sort_pass(const SortCall& c, const SortIo<Sample>& io, int shift, int bits) {
+  constexpr bool Wide = MaxBits == kWideRadixBits;
+  const BwdWs& w = *c.w;
+  const dmt_plan* plan = c.plan;
+  const int64_t blocks = w.nblk_sort;
+  timed_launch(plan, DMT_K_BWD_SORT_HIST, c.s, radix_hist<MaxBits, First, Sample>, blocks, kBlock, plan->d_meta, io, shift,
+               bits, w.hist, w.seg_begin, w.seg_blk, w.blk_table, (int)plan->F,
+               plan->row_shards ? nullptr : plan->d_error);
+  if (!Wide)
+    timed_launch(plan, DMT_K_BWD_SORT_SCAN, c.s, radix_scan, plan->F, kScanThreads, w.hist, bits, w.seg_begin, w.seg_blk);
+  timed_launch(plan, DMT_K_BWD_SORT_SCATTER, c.s, radix_scatter<MaxBits, Wide, First, Last, Sample>, blocks, kBlock,
+               plan->d_meta, io, shift, bits, w.hist, w.seg_begin, w.seg_blk, w.blk_table, (int)plan->F, (uint32_t)c.B);
+}
+
+// Stable LSD radix sort inside every table over the bits a row id of the largest table (or its one-past-the-end
+// inert id) can set.  The last pass leaves the records in pk_a; the passes before it take turns in the halves of
+// the record arrays, the one before the last in pk_b, and the samples of the first lie where its output does not.
+template <typename Sample>
+void sort_lookups(const SortCall& c) {
+  const BwdWs& w = *c.w;
+  const dmt_plan* plan = c.plan;
+  int64_t max_rows = 0;
+  for (int32_t f = 0; f < plan->F; ++f) max_rows = std::max<int64_t>(max_rows, plan->meta[f].rows);
+  const int key_bits = ilog2_ceil(max_rows + 1);
+  const int most_bits = w.wide ? kWideRadixBits : kMaxRadixBits;
+  const int passes = (key_bits + most_bits - 1) / most_bits;
+  const int bits_per = (key_bits + passes - 1) / passes;
+  auto region = [&](int pass) { return (passes - pass) & 1 ? w.pk_a : w.pk_b; };   // where a pass writes
+  Sample* const samples = (Sample*)(region(0) == w.pk_a ? w.pk_b : w.pk_a);
+  timed_launch(plan, DMT_K_BWD_KEYS, c.s, bwd_bag_samples<Sample>, c.key_blocks, kBlock, c.offsets, (uint32_t)c.B,
+               c.nbags, c.nnz, (int)plan->F, samples, c.log2_bpb, w.least_items, w.seg_begin, w.seg_blk, w.blk_table,
+               plan->d_error + 1);
+  SortIo<Sample> io{};
+  io.ids = c.indices;
+  io.smp_in = samples;
+  for (int p = 0; p < passes; ++p) {
+    const bool first = p == 0, last = p == passes - 1;
+    const int shift = p * bits_per, bits = std::min(bits_per, key_bits - shift);
+    io.key_out = (uint32_t*)region(p);
+    io.smp_out = (Sample*)(io.key_out + c.nnz);
+    io.pk_out = w.pk_a;
+    auto launch = [&](auto max_bits) {
+      constexpr int M = decltype(max_bits)::value;
+      if (first && last) launch_sort_pass<M, true, true, Sample>(c, io, shift, bits);
+      else if (first) launch_sort_pass<M, true, false, Sample>(c, io, shift, bits);
+      else if (last) launch_sort_pass<M, false, true, Sample>(c, io, shift, bits);
+      else launch_sort_pass<M, false, false, Sample>(c, io, shift, bits);
+    };
+    if (w.wide) launch(std::integral_constant<int, kWideRadixBits>());
+    else launch(std::integral_constant<int, kMaxRadixBits>());
+    io.key_in = io.key_out;
+    io.smp_in = io.smp_out;
+  }
+}
+
 // What the reduce / fix-up launches share.
 struct ReduceCall {
   const dmt_plan* plan;
@@ -1573,10 +1723,10 @@ static dmt_status bwd_update_run(const dmt_plan* plan, const int32_t* indices,
   hipStream_t s = (hipStream_t)stream;
   const uint32_t total_rows = (uint32_t)plan->total_rows;
   const uint32_t nbags = (uint32_t)((int64_t)plan->F * B);
-  const uint64_t* sorted = w.pk_a;
+  const uint64_t* const sorted = w.pk_a;
 
   if (nnz > 0) {
-    // keys; bags per block: about 4096 lookups' worth (a power of two, at most kKeysMaxBags), or
+    // samples; bags per block: about 4096 lookups' worth (a power of two, at most kKeysMaxBags), or
     // what it takes to give every CU four blocks, but at least a lookup per thread (260 K lookups:
     // 51 blocks of 4096 took 25.5 us, 813 of 320 take 5.7)
     const double mean_len = (double)nnz / (double)nbags;
@@ -1585,36 +1735,8 @@ static dmt_status bwd_update_run(const dmt_plan* plan, const int32_t* indices,
     if (plan->sw.keys_lg >= 0) log2_bpb = plan->sw.keys_lg;
     log2_bpb = log2_bpb < 4 ? 4 : (log2_bpb > 10 ? 10 : log2_bpb);
     const int64_t key_blocks = ((int64_t)nbags + (1 << log2_bpb) - 1) >> log2_bpb;
-    timed_launch(plan, DMT_K_BWD_KEYS, s, bwd_build_keys, key_blocks, kBlock, plan->d_meta, indices,
-                 offsets, (uint32_t)B, nbags, nnz, (int)plan->F, w.pk_a, log2_bpb, w.least_items, w.seg_begin,
-                 w.seg_blk, w.blk_table, plan->row_shards ? nullptr : plan->d_error, plan->d_error + 1);
-
-    // stable LSD radix sort inside every table over the bits a row id of the largest table
-    // (or its one-past-the-end inert id) can set
-    int64_t max_rows = 0;
-    for (int32_t f = 0; f < plan->F; ++f) max_rows = std::max<int64_t>(max_rows, plan->meta[f].rows);
-    const int key_bits = ilog2_ceil(max_rows + 1);
-    const int most_bits = w.wide ? kWideRadixBits : kMaxRadixBits;
-    const int passes = (key_bits + most_bits - 1) / most_bits;
-    const int bits_per = (key_bits + passes - 1) / passes;
-    uint64_t* src = w.pk_a;
-    uint64_t* dst = w.pk_b;
-    for (int p = 0; p < passes; ++p) {
-      const int shift = p * bits_per;
-      const int bits = std::min(bits_per, key_bits - shift);
-      timed_launch(plan, DMT_K_BWD_SORT_HIST, s, w.wide ? radix_hist<kWideRadixBits> : radix_hist<kMaxRadixBits>,
-                   w.nblk_sort, kBlock, plan->d_meta, src, shift, bits, w.hist, w.seg_begin, w.seg_blk,
-                   w.blk_table, (int)plan->F);
-      if (!w.wide)
-        timed_launch(plan, DMT_K_BWD_SORT_SCAN, s, radix_scan, plan->F, kScanThreads, w.hist, bits,
-                     w.seg_begin, w.seg_blk);
-      timed_launch(plan, DMT_K_BWD_SORT_SCATTER, s,
-                   w.wide ? radix_scatter<kWideRadixBits, true> : radix_scatter<kMaxRadixBits, false>,
-                   w.nblk_sort, kBlock, plan->d_meta, src, dst, shift, bits, w.hist, w.seg_begin, w.seg_blk,
-                   w.blk_table, (int)plan->F);
-      std::swap(src, dst);
-    }
-    sorted = src;
+    const SortCall sc{plan, &w, indices, offsets, nnz, B, nbags, log2_bpb, key_blocks, s};
+    if (B <= 65536) sort_lookups<uint16_t>(sc); else sort_lookups<uint32_t>(sc);
 
     const ReduceCall call{plan, &w, sorted, nnz, B, nbags, total_rows, grad_pooled, lr, eps, s};
     switch (plan->table_dtype) {

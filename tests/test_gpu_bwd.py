@@ -192,6 +192,31 @@ def test_sort_digit_widths(rows, lens):
     assert np.array_equal(dbg["sorted_bag"].cpu().numpy(), bag[order])
 
 
+@pytest.mark.parametrize("rows", [[200, 1], [1 << 12, 9], [1 << 20, 70000, 3]])      # 1, 2 and 3 passes of narrow digits
+@pytest.mark.parametrize("batch,mean", [(3, 0.0), (700, 0.4), (1025, 900.0), (65536, 5.0), (65537, 5.0)])
+def test_samples_of_the_sorted_lookups(rows, batch, mean):
+    """Samples of 16 bits (up to 65536) and of 32, bags of a table with fewer, as many and more samples than a block of
+    bwd_bag_samples takes, most bags empty or one holding most lookups: order and samples are exact."""
+    F = len(rows)
+    w = wl.dataclasses.replace(
+        wl.scaled(wl.mid(True), max_rows=10, batch=batch, num_tables=F), table_dtype="f32", rows=rows,
+        dims=[4] * F, table_to_tower=[0] * F, tm_out=[32])
+    rng = np.random.default_rng(batch)
+    per_bag = rng.poisson(mean, F * batch).astype(np.int64)
+    if mean < 1:
+        per_bag[[0, F * batch - 1, F * batch // 2]] = [5000, 1, 3]
+    off = np.concatenate([[0], np.cumsum(per_bag)])
+    lens = per_bag.reshape(F, batch).sum(1)
+    idx = np.concatenate([(r * rng.random(n) ** 3).astype(np.int32) for r, n in zip(rows, lens)])
+    dw = DeviceWorkload(w, with_state=True, max_nnz=len(idx))
+    dbg = run_bwd(dw, idx, off, wl.grad_pooled(w), w.lr, w.eps)
+    assert dw.dmt.dmt_last_device_error(dw.plan) == -1
+    key = (np.repeat(np.arange(F, dtype=np.int64), lens) << 32) | idx
+    order = np.argsort(key, kind="stable")
+    assert np.array_equal(dbg["sorted_keys"].cpu().numpy(), key[order])
+    assert np.array_equal(dbg["sorted_bag"].cpu().numpy(), np.repeat(np.arange(F * batch), per_bag)[order])
+
+
 @pytest.mark.parametrize("dims", [[32, 64], [64], [32], [256]])
 def test_narrow_and_wide_rows(dims):
     """Dims up to 128 run the lean walk, 256 the wave-per-tile kernel."""
@@ -264,7 +289,7 @@ def test_out_of_range_ids_are_skipped():
 
 @pytest.mark.parametrize("case", ["first_not_zero", "descending", "last_not_nnz", "beyond_nnz"])
 def test_malformed_offsets_update_nothing_and_are_reported(case):
-    # the host cannot see device offsets; the key build checks them and the update is skipped
+    # the host cannot see device offsets; bwd_bag_samples checks them and the update is skipped
     w = wl.scaled(wl.mid(True), max_rows=100, batch=16, num_tables=8)
     dw = DeviceWorkload(w, with_state=True)
     idx, off = wl.lookup_batch(w)
