@@ -143,8 +143,8 @@ __global__ __launch_bounds__(kBlock) void bwd_bag_samples(
 // 65536 samples), in two arrays: the table is known from the position.  The counting kernels then read 4 bytes
 // a lookup and the scatters move 6 each way, and the first pass reads `indices` as they lie.  Only the last pass
 // writes the 64-bit records the reduce kernels walk.  Records of 8 bytes through all passes, built beforehand
-// / now, us: 64 tables of 164 K lookups, 20 bits of row id: build 41 / samples 18, count 22 / 10-13, scatter 43 / 34-46
-// a pass, the whole sort 253 / 188; 256 of 246 K, 20 bits: 1543 / 908; 128 of 170 K, 23 bits: 563 / 374.  The
+// / now, us: 64 tables of 164 K lookups, 20 bits of row id: build 41 / samples 18, count 22 / 10-13, scatter 43 / 31-33
+// a pass, the whole sort 253 / 165; 256 of 246 K, 20 bits: 1543 / 830; 128 of 170 K, 23 bits: 563 / 328.  The
 // scatters are bound by their instructions (a wave's 64 lanes take four cycles each) as much as by bytes.
 template <typename Sample>
 struct SortIo {
@@ -170,8 +170,12 @@ __device__ __forceinline__ SortBlock sort_block(const DmtTableMeta* __restrict__
                                                 const uint32_t* __restrict__ seg_blk,
                                                 const uint32_t* __restrict__ blk_table, int F) {
   SortBlock sb{};
-  if (blockIdx.x >= seg_blk[F]) return sb;
-  sb.id = blockIdx.x;
+  // Blocks are dealt to the XCDs (block id mod 8) so that neighbours in a table share an L2: a digit's records
+  // come from all of a table's blocks, 16 of a block side by side, and the lines they share are put together
+  // there (first scatter of 64 tables of 164 K lookups 46 -> 33 us, of 128 of 170 K 113 -> 71).
+  const uint32_t nblk = seg_blk[F], per_xcd = (nblk + 7) / 8;
+  sb.id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((blockIdx.x >> 3) >= per_xcd || sb.id >= nblk) return sb;
   const uint32_t packed = blk_table[sb.id], f = packed >> 4;
   sb.items = Wide ? (int)(packed & 15) : kSortItems;
   const uint32_t sort_tile = (uint32_t)(sb.items * kBlock);
@@ -1556,7 +1560,7 @@ void launch_sort_pass(const SortCall& c, const SortIo<Sample>& io, int shift, in
   constexpr bool Wide = MaxBits == kWideRadixBits;
   const BwdWs& w = *c.w;
   const dmt_plan* plan = c.plan;
-  const int64_t blocks = w.nblk_sort;
+  const int64_t blocks = (w.nblk_sort + 7) / 8 * 8;     // as many for every XCD
   timed_launch(plan, DMT_K_BWD_SORT_HIST, c.s, radix_hist<MaxBits, First, Sample>, blocks, kBlock, plan->d_meta, io, shift,
                bits, w.hist, w.seg_begin, w.seg_blk, w.blk_table, (int)plan->F,
                plan->row_shards ? nullptr : plan->d_error);
