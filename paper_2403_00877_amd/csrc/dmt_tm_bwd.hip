@@ -60,6 +60,8 @@ __device__ __forceinline__ void store_f32x8(float* p, int64_t e, const float (&x
   *(float4*)(p + e + 4) = make_float4(x[4], x[5], x[6], x[7]);
 }
 
+__device__ __forceinline__ void pack_dot_weights(const TmbItem& G, int64_t e);
+
 // dz[b][o] = dy[b][o] (zero where ReLU was off: y[b][o] <= 0), rounded to DT, with zero columns
 // O .. Op-1, and the column sums of the rounded values over the rows of each block (the bias
 // gradient's parts): dbp[block][o].  Row b of dy (and y) starts at element b * ldy, or, with
@@ -67,13 +69,18 @@ __device__ __forceinline__ void store_f32x8(float* p, int64_t e, const float (&x
 // side in one row of the output gradient (a per-feature layer).  One pass over dy, bound by its
 // bytes; 2^tc threads take a row's (up to 256) columns, 8 each.
 // a = dy, b = y, o0 = dz, o1 = dbp, n0 = rows, n1 = rows per block, n2 = ldy, i0 = O, i1 = Op,
-// i2 = relu, i3 = rdiv, i4 = ld2, i5 = tc; nbx = blocks along the rows.
+// i2 = relu, i3 = rdiv, i4 = ld2, i5 = tc; nbx = blocks along the rows.  (Items with c set repack a dot tower's
+// weights instead, pack_dot_weights.)
 template <int DT>
 __global__ __launch_bounds__(kBlock) void tmb_prep_dz(const TmbLaunch L) {
   __shared__ float red[kBlock][8];
   const int gi = tmb_find(L);
   const TmbItem& G = L.it[gi];
   const int lb = blockIdx.x - L.block_start[gi];
+  if (G.c) {
+    pack_dot_weights(G, (int64_t)lb * kBlock + threadIdx.x);
+    return;
+  }
   const float* __restrict__ dy = (const float*)G.a;
   const uint16_t* __restrict__ y = (const uint16_t*)G.b;
   uint16_t* __restrict__ dz = (uint16_t*)G.o0;
@@ -169,6 +176,216 @@ __global__ __launch_bounds__(kBlock) void tmb_dot_bwd8(const TmbLaunch L) {
     for (int q = 0; q < 8; ++q) acc[q] += g * xv[q];
   }
   store_f32x8((float*)G.o0, b * wt + r, acc);
+}
+
+// ---- Dot towers of 2 to 8 features of a multiple of 32 columns, 16-bit types: the whole data gradient,
+//   dx[b][i][c] = sum over o of dz[b][o] W[o][np + i n + c] + sum over j != i of dZ[b][p(i,j)] x[b][j][c],
+//   dZ[b][p] = sum over o of dz[b][o] W[o][p],
+// in one kernel.  Bound by the bytes of x and dx: the two contractions and tmb_dot_bwd8 moved the flat part of dZ,
+// as large as dx, through memory and back.  8 towers of 8 features of 128 columns, 256 outputs, batch 8192: 77 + 12 +
+// 148 us, now 116 (0.44 GB at 3.8 TB/s; without the products 105, without the requests of weights and dz 96); 4 of 6 and
+// 7 features, batch 2003: 17 + 16 us, now 18, and the repack of the weights rides with tmb_prep_dz.
+// A wave owns 32 samples and the same 32 columns of EVERY feature, the weights as the first operand, so that a lane
+// holds one sample's values of all features at four consecutive columns and the sum over j needs no other lane's
+// (x comes in the accumulators' layout, 8 bytes a lane).  Four waves share the weights of their columns, which go
+// through LDS in steps of 32 outputs, fragment by fragment as the repacked weights lie; behind them come the dot
+// terms' rows, whose products, a few floats a sample, take the way through LDS to the sample's other lanes.
+constexpr int kDotFeat = 8;                        // features, at most
+constexpr int kDotTerms = kDotFeat * (kDotFeat - 1) / 2, kDotTermTiles = (kDotTerms + 15) / 16;
+constexpr int kDotCols = 32, kDotRows = 128;       // columns of a feature, samples of a block
+constexpr int kDotTiles = kDotFeat * (kDotCols / 16) + kDotTermTiles;
+constexpr int kDotZPitch = kDotTermTiles * 16 + 4; // floats: 16 samples' pieces of 16 bytes on different banks
+// Term of the pair {i, j}, i < j, whatever the number of features.
+__host__ __device__ constexpr int dot_slot(int i, int j) { return i * (2 * kDotFeat - 1 - i) / 2 + j - i - 1; }
+inline bool dot_dgrad_ok(const dmt_plan* p, int nf, int n) { return p->sw.tm_fuse && nf >= 2 && nf <= kDotFeat && n % kDotCols == 0; }
+// Fragments (1 KB) of a tower's repacked weights.
+inline int64_t dot_wt_frags(int nf, int n, int64_t O) {
+  return (int64_t)(n / kDotCols) * ((O + 31) / 32) * (nf * (kDotCols / 16) + kDotTermTiles);
+}
+
+// The weights as tmb_dot_dgrad stages them: [column block][step of 32 outputs][fragment][lane][8], a lane's eight
+// values one column's of outputs 8 (lane / 16) ... of the step; fragments of the features, two each, then of the
+// terms (rows in dot_slot order); zeros past the last output.  One thread per lane's eight values.
+// a = W [O][np + nf n], c = where to, i0 = nf, i1 = n, i2 = O.
+__device__ __forceinline__ void pack_dot_weights(const TmbItem& G, int64_t e) {
+  const int nf = G.i0, n = G.i1, O = G.i2, np = nf * (nf - 1) / 2, ld = np + nf * n;
+  const int tiles = nf * (kDotCols / 16) + kDotTermTiles, steps = (O + 31) / 32;
+  if (e >= (int64_t)(n / kDotCols) * steps * tiles * 64) return;
+  const int lane = (int)(e & 63), m = lane & 15;
+  const int64_t frag = e >> 6;
+  const int tile = (int)(frag % tiles), step = (int)(frag / tiles % steps), cb = (int)(frag / ((int64_t)tiles * steps));
+  int col = -1;
+  if (tile < 2 * nf) {
+    col = np + (tile >> 1) * n + cb * kDotCols + (m >> 2) * 8 + (tile & 1) * 4 + (m & 3);
+  } else {
+    const int slot = (tile - 2 * nf) * 16 + m;
+    for (int i = 0; i + 1 < nf; ++i)
+      if (slot >= dot_slot(i, i + 1) && slot <= dot_slot(i, nf - 1)) col = i * (2 * nf - 1 - i) / 2 + slot - dot_slot(i, i + 1);
+  }
+  const int o0 = step * 32 + (lane >> 4) * 8;
+  const uint16_t* __restrict__ W = (const uint16_t*)G.a;
+  uint32_t v[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) v[q] = col >= 0 && o0 + q < O ? W[(int64_t)(o0 + q) * ld + col] : 0u;
+  ((uint4*)G.c)[e] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+}
+
+// Three stages in LDS, requested two steps ahead (a step is short: 36 instructions of 16 x 16 x 32 a wave); the
+// wave's own dz goes the same way, so that the requests under way can be counted.  The x values are requested
+// ahead of the last step.
+constexpr int kDotStage = kDotTiles * 1024 + kDotRows * 64;      // bytes: weights, then dz (two fragments a wave)
+constexpr int kDotLds = 3 * kDotStage;
+static_assert(kDotLds >= 4 * 32 * kDotZPitch * 4 && 2 * kDotLds <= 160 * 1024, "two blocks per CU");
+
+// a = dz [B][Op], b = repacked weights, c = x, o0 = dx, n0 = B, i0 = nf, i1 = n, i2 = O, i3 = Op.
+template <int DT>
+__global__ __launch_bounds__(kBlock, 2) void tmb_dot_dgrad(const TmbLaunch L) {
+  static_assert(kBlock == 256 && kDotRows == 128, "four waves of 32 samples");
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  // the column blocks of the same samples run side by side on one XCD: they share lines of x and dz
+  const int q8 = gridDim.x >> 3, r8 = gridDim.x & 7, xcd = blockIdx.x & 7;
+  const int id = xcd * q8 + min(xcd, r8) + (blockIdx.x >> 3);
+  int gi = 0;
+  while (gi + 1 < L.n && id >= L.block_start[gi + 1]) ++gi;
+  const TmbItem& G = L.it[gi];
+  const int nf = G.i0, n = G.i1, Op = G.i3, steps = (G.i2 + 31) / 32;
+  const int ncb = n / kDotCols, cb = (id - L.block_start[gi]) % ncb;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), m = lane & 15, h = lane >> 4;
+  const int64_t B = G.n0, s0 = (int64_t)((id - L.block_start[gi]) / ncb) * kDotRows + wave * 32;
+  const int tiles = 2 * nf + kDotTermTiles, per_wave = (tiles + 3) / 4;
+  const int64_t wt = (int64_t)nf * n;
+
+  // a step's requests, 1 KB each: per_wave of the weights (the last waves' past the end are the last fragment again)
+  // and the wave's two of dz
+  const uint32_t panel = (uint32_t)(steps * tiles) * 1024u;
+  const __amdgpu_buffer_rsrc_t wbuf = tm_buffer((const char*)G.b + (int64_t)cb * panel, panel);
+  const int64_t mine = min(max(B - s0, (int64_t)0), (int64_t)32);
+  const __amdgpu_buffer_rsrc_t zbuf = tm_buffer((const uint16_t*)G.a + min(s0, B - 1) * Op, (uint32_t)mine * (uint32_t)Op * 2u);
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint16_t*)lds;
+  auto request = [&](int step) {
+    const uint32_t to = lds0 + (uint32_t)(step % 3) * kDotStage, from = (uint32_t)(step * tiles) * 1024u + lane * 16u;
+    for (int r = 0; r < per_wave; ++r) {
+      const uint32_t t = (uint32_t)min(wave + 4 * r, tiles - 1) * 1024u;
+      tm_request(to + t, wbuf, from + t);
+    }
+    const int k = step * 32 + h * 8;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      tm_request(to + kDotTiles * 1024 + (wave * 2 + s) * 1024, zbuf, k < Op ? (uint32_t)((s * 16 + m) * Op + k) * 2u : kOobOffset);
+  };
+  floatx4 acc[2][kDotFeat][2], accz[2][kDotTermTiles];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+#pragma unroll
+    for (int i = 0; i < kDotFeat; ++i) acc[s][i][0] = acc[s][i][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < kDotTermTiles; ++t) accz[s][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto multiply = [&](int step) {
+    const uint4* w = (const uint4*)(lds + (step % 3) * (kDotStage / 2)) + lane;
+    const uint4 d0 = w[(kDotTiles + wave * 2) * 64], d1 = w[(kDotTiles + wave * 2 + 1) * 64];
+#pragma unroll
+    for (int i = 0; i < kDotFeat; ++i)
+      if (i < nf) {
+        const uint4 w0 = w[(2 * i) * 64], w1 = w[(2 * i + 1) * 64];
+        acc[0][i][0] = mfma16<DT>(w0, d0, acc[0][i][0]);
+        acc[1][i][0] = mfma16<DT>(w0, d1, acc[1][i][0]);
+        acc[1][i][1] = mfma16<DT>(w1, d1, acc[1][i][1]);
+        acc[0][i][1] = mfma16<DT>(w1, d0, acc[0][i][1]);
+      }
+#pragma unroll
+    for (int t = 0; t < kDotTermTiles; ++t) {
+      const uint4 wz = w[(2 * nf + t) * 64];
+      accz[0][t] = mfma16<DT>(wz, d0, accz[0][t]);
+      accz[1][t] = mfma16<DT>(wz, d1, accz[1][t]);
+    }
+  };
+  request(0);
+  if (steps > 1) request(1);
+  for (int step = 0; step + 1 < steps; ++step) {
+    // all of this wave's requests but the next step's have landed; behind the barrier everyone's, and the stage of
+    // the step before is read no more
+    switch (per_wave) {
+      case 2: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+      case 3: asm volatile("s_waitcnt vmcnt(5)" ::: "memory"); break;
+      case 4: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
+      default: asm volatile("s_waitcnt vmcnt(7)" ::: "memory"); break;
+    }
+    __syncthreads();
+    if (step + 2 < steps) request(step + 2);
+    multiply(step);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  uint4 xr[2][kDotFeat];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const uint16_t* x = (const uint16_t*)G.c + min(s0 + s * 16 + m, B - 1) * wt + cb * kDotCols + h * 8;
+#pragma unroll
+    for (int j = 0; j < kDotFeat; ++j) xr[s][j] = *(const uint4*)(x + (j < nf ? j : 0) * n);
+  }
+  multiply(steps - 1);
+  // the samples' dZ to all their lanes, over the stages
+  __syncthreads();
+  float* const z_of = (float*)lds + (wave * 32 + m) * kDotZPitch;
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int t = 0; t < kDotTermTiles; ++t) *(floatx4*)(z_of + s * 16 * kDotZPitch + t * 16 + h * 4) = accz[s][t];
+  // (a wave reads what its own lanes wrote)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    float z[kDotTermTiles * 16];
+#pragma unroll
+    for (int q = 0; q < (kDotTerms + 3) / 4; ++q) {
+      const floatx4 v = *(const floatx4*)(z_of + s * 16 * kDotZPitch + q * 4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z[q * 4 + r] = v[r];
+    }
+    // Two stores of whole lines for the 16 samples of a feature: lane m of the first eight stores its own first four
+    // columns and those of lane m + 8, the others its second four and those of lane m - 8.
+    float* const out = (float*)G.o0 + (s0 + s * 16 + (m & 7)) * wt + cb * kDotCols + h * 8 + (m < 8 ? 0 : 4);
+    const bool on[2] = {s0 + s * 16 + (m & 7) < B, s0 + s * 16 + (m & 7) + 8 < B};
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      float x[kDotFeat][4];
+#pragma unroll
+      for (int j = 0; j < kDotFeat; ++j) {
+        dmt::unpack2<DT>(t == 0 ? xr[s][j].x : xr[s][j].z, x[j][0], x[j][1]);
+        dmt::unpack2<DT>(t == 0 ? xr[s][j].y : xr[s][j].w, x[j][2], x[j][3]);
+      }
+#pragma unroll
+      for (int i = 0; i < kDotFeat; ++i)
+        if (i < nf) {
+#pragma unroll
+          for (int j = 0; j < kDotFeat; ++j)
+            if (j != i && j < nf) {
+              const float g = z[i < j ? dot_slot(i, j) : dot_slot(j, i)];
+#pragma unroll
+              for (int r = 0; r < 4; ++r) acc[s][i][t][r] += g * x[j][r];
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kDotFeat; ++i)
+      if (i < nf) {
+        floatx4 st[2];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          // row_ror:8, written in the last eight lanes of 16 and in the first
+          const int a = __float_as_int(acc[s][i][0][r]), c = __float_as_int(acc[s][i][1][r]);
+          st[0][r] = __int_as_float(__builtin_amdgcn_update_dpp(a, c, 0x128, 0xf, 0xc, false));
+          st[1][r] = __int_as_float(__builtin_amdgcn_update_dpp(c, a, 0x128, 0xf, 0x3, false));
+        }
+        // (nontemporal: dx is read again by the sparse update only, and x, which the weight gradients read next, stays
+        // in the caches: those 51 -> 42 us on 8 towers of 8 features of 128 columns, batch 8192)
+        if (on[0]) __builtin_nontemporal_store(st[0], (floatx4*)(out + i * n));
+        if (on[1]) __builtin_nontemporal_store(st[1], (floatx4*)(out + 8 * wt + i * n));
+      }
+  }
 }
 
 // dw[o][k] = sum over slices s (ascending) of part[s][o][k'], where k' = k for k < np and
@@ -307,6 +524,7 @@ struct TowerBwdWs {
   int64_t Op = 0;
   size_t dz = 0, dbp = 0;      // dy rounded, [B][Op]; parts of its column sums
   size_t p = 0, wp = 0, dZ = 0;                                 // dot towers
+  bool fused = false;          // dot towers: tmb_dot_dgrad, its weights in wp; no dZ
   size_t xl[DMT_MAX_CROSS_LAYERS] = {}, u[DMT_MAX_CROSS_LAYERS] = {};   // cross towers
   size_t dxn = 0, du[2] = {0, 0}, dbc = 0;   // g_l, du of alternating layers, parts of its column sums
   // low-rank cross towers: t_l = V_l x_l per layer; dt (float32 towers), dt rounded
@@ -357,10 +575,15 @@ dmt_status plan_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, in
         if (p->tower_uniform_dim[t] == 0) return DMT_ENOTSUP;
         w.np = nf * (nf - 1) / 2;
         w.np_pad = (w.np + 7) / 8 * 8;
-        w.packed = !dot_weights_as_is(q.w_proj, w.np);
+        w.fused = eb == 2 && dot_dgrad_ok(p, nf, p->tower_uniform_dim[t]);
+        w.packed = !w.fused && !dot_weights_as_is(q.w_proj, w.np);
         w.skip = w.packed ? w.np_pad : w.np;
         w.kin = w.np_pad + (int)wt;
         w.p = take((size_t)B * w.np_pad * eb);
+        if (w.fused) {
+          w.wp = take((size_t)dot_wt_frags(nf, p->tower_uniform_dim[t], q.out_dim) * 1024);
+          break;
+        }
         w.wp = take((size_t)q.out_dim * w.kin * eb);
         w.dZ = take((size_t)B * w.kin * 4);
         break;
@@ -439,7 +662,7 @@ struct TmbBatch {
 
 // False when an item alone exceeds the grid limit (nothing of it is launched).
 template <typename Kernel>
-bool launch_items(const dmt_plan* p, TmbBatch& batch, Kernel kernel, hipStream_t s) {
+bool launch_items(const dmt_plan* p, TmbBatch& batch, Kernel kernel, hipStream_t s, int lds = 0) {
   bool ok = true;
   for (size_t first = 0; first < batch.items.size();) {
     TmbLaunch L;
@@ -456,7 +679,7 @@ bool launch_items(const dmt_plan* p, TmbBatch& batch, Kernel kernel, hipStream_t
     if (L.n == 0) { ok = false; break; }
     L.block_start[L.n] = (int32_t)blocks;
     DmtScope sc_(p, DMT_K_TM_BWD_AUX, s);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kBlock), 0, s, L);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kBlock), lds, s, L);
   }
   batch.items.clear();
   batch.blocks.clear();
@@ -517,7 +740,7 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
     return keptp ? (const void*)(keptp + kept[t].u[l]) : (const void*)(wsp + ws[t].u[l]);
   };
   int max_layers = 0;
-  TmbBatch batch, batch2, batch3, groups_dot;
+  TmbBatch batch, batch2, batch3, groups_dot, dots_fused;
   bool ok = true;
 
   auto z_of = [&](int t) -> const char* {           // dot terms: kept by the forward, or recomputed
@@ -655,7 +878,16 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
     if (w.np > 0) add_wgrad(wgrad2, z_of(t), w.np_pad, w.np_pad, dw);
     if (to_part) add_slices(batch2, wsp + w.part, O, w.np, w.np_pad, wt, w.ksplit, gr[t].dw_proj);
     // data gradient
-    if (dot) {
+    if (dot && w.fused) {
+      const int n = p->tower_uniform_dim[t];
+      TmbItem it{};
+      it.a = q.w_proj; it.c = wsp + w.wp; it.i0 = nf; it.i1 = n; it.i2 = O;
+      batch.add(it, (dot_wt_frags(nf, n, O) * 64 + kBlock - 1) / kBlock);
+      it = TmbItem{};
+      it.a = dz; it.b = wsp + w.wp; it.c = x_of(t); it.o0 = dx_of(t); it.n0 = B;
+      it.i0 = nf; it.i1 = n; it.i2 = O; it.i3 = (int32_t)w.Op;
+      dots_fused.add(it, (B + kDotRows - 1) / kDotRows * (n / kDotCols));
+    } else if (dot) {
       const int64_t ldw = w.skip + wt;
       const char* W = wp_of(t);
       float* dZ = (float*)(wsp + w.dZ);
@@ -711,6 +943,11 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
   join(wgrad, wgrad2);
   launch_groups<DT, OP_ROW, OP_COL>(p, dgrad, s, false, kid);
   launch_groups<DT, OP_ROW, OP_COL>(p, dgrad2, s, false, kid);
+  if (!dots_fused.items.empty()) {
+    static DmtPerDevice configured;
+    dmt_allow_lds(configured, (const void*)tmb_dot_dgrad<DT>, kDotLds);
+    ok &= launch_items(p, dots_fused, tmb_dot_dgrad<DT>, s, kDotLds);
+  }
   launch_groups<DT, OP_COL, OP_COL>(p, wgrad, s, false, kid);
   launch_groups<DT, OP_COL, OP_COL>(p, wgrad2, s, false, kid);
   // ---- weight gradients: add up the slices, strip a dot tower's padding; dot towers: fold

@@ -283,6 +283,22 @@ def test_dlrm_module_odd_widths():
     check_tm_bwd(w)
 
 
+@pytest.mark.parametrize("dt,nfs,dims,outs,batch", [
+    ("bf16", [2, 8], [32, 128], [1, 256], 127), ("f16", [3, 7], [96, 64], [33, 40], 129),
+    ("bf16", [5, 9], [32, 32], [8, 72], 1),          # nine features: the separate kernels, in the same call
+    ("bf16", [8, 6], [128, 96], [250, 300], 300), ("f16", [4, 8], [160, 40], [520, 16], 257),   # 40 columns: likewise
+])
+def test_dot_towers_data_gradient_in_one_kernel(dt, nfs, dims, outs, batch):
+    """2 to 8 features of one to five blocks of 32 columns, one to 17 steps of 32 outputs with and without a remainder,
+    batches around one block of 128 samples."""
+    w = wl.scaled(wl.mid(), max_rows=300, batch=batch, num_tables=sum(nfs))
+    w.table_to_tower = [0] * nfs[0] + [1] * nfs[1]
+    w.dims = [dims[0]] * nfs[0] + [dims[1]] * nfs[1]
+    w.tm_dtype = w.pooled_dtype = dt
+    w.tm_out = outs
+    check_tm_bwd(w, keep=True, guard=True)
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f16"])
 @pytest.mark.parametrize("dim,nf,batch,feat_out,big", [(12, 2, 77, 5, "1"), (12, 4, 301, 24, "2"), (4, 6, 65, 8, "0"),
                                                        (20, 2, 1, 1, "1"), (132, 2, 300, 136, "2")])
