@@ -456,6 +456,148 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
   }
 }
 
+// The whole sort of a call of few lookups in one launch, a block per table: each lookup's sample, the checks of
+// `offsets`, and every pass over digits of up to 10 bits with the records in LDS.  Bound by the chain of its steps; the
+// launches it takes the place of (samples, and two a pass) were bound by that and by their own starts.  A block's time
+// grows with its table's lookups, whoever holds them, and the line (kSmallNnz) lies where one table that holds them all
+// is no slower for it.  Whole update, us, several launches / one: 8 tables of 288 lookups, 1000 rows 23.6 / 16.3; 12 of
+// 590, 20000 rows 33.5 / 20.4; 200 of 35 60.7 / 19.9; 7168 in one table, 1000 rows 29.4 / 27.5, 10^6 rows 34.8 / 31.0;
+// past the line 16384 in one table 29.0 / 42.6 and 38.9 / 56.6, 8 of 2000 26.7 / 20.3.
+constexpr int kSmallBlock = 1024, kSmallItems = (int)(kSmallNnz / kSmallBlock);
+constexpr int kSmallWaves = kSmallBlock / 64, kSmallRadix = 1 << kWideRadixBits;
+static_assert(kSmallRadix == kSmallBlock && kSmallItems * kSmallBlock == kSmallNnz && kSmallNnz < 65536 && kSmallBatch % 8 == 0, "");
+constexpr int kSmallLds = (int)kSmallNnz * 6 + kSmallWaves * kSmallRadix * 2 + ((int)kSmallBatch + 8) * 2;
+__global__ __launch_bounds__(kSmallBlock) void bwd_sort_small(
+    const DmtTableMeta* __restrict__ meta, const int32_t* __restrict__ indices, const int64_t* __restrict__ offsets,
+    uint32_t B, int F, int nnz, uint64_t* __restrict__ pk, unsigned long long* __restrict__ err,
+    unsigned long long* __restrict__ err_offsets) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t kbuf[];          // [kSmallNnz]
+  uint16_t* const sbuf = (uint16_t*)(kbuf + kSmallNnz);                     // [kSmallNnz]
+  uint16_t* const cnt = sbuf + kSmallNnz;                                   // [wave][digit]
+  uint16_t* const offs = cnt + kSmallWaves * kSmallRadix;                   // [B + 1]
+  __shared__ uint32_t sm[kSmallWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, f = blockIdx.x;
+  const uint32_t g0 = (uint32_t)f * B;
+  // (as in bwd_bag_samples)
+  for (uint32_t i = tid; i <= B; i += kSmallBlock) {
+    const int64_t o = offsets[g0 + i];
+    const bool at_end = f == F - 1 && i == B;
+    if (o < 0 || o > nnz || (g0 + i == 0 && o != 0) || (at_end && o != nnz))
+      atomicMin(err_offsets, (unsigned long long)(g0 + i - (at_end ? 1 : 0)));
+    offs[i] = (uint16_t)(o < 0 ? 0 : (o > nnz ? nnz : o));
+  }
+  const DmtTableMeta& m = meta[f];
+  const uint32_t rows = (uint32_t)m.rows, row_base = (uint32_t)m.row_base;
+  const int64_t row_begin = m.row_begin;
+  int bits_all = 1;
+  while ((1ull << bits_all) < (uint64_t)rows + 1) ++bits_all;
+  const int passes = (bits_all + kWideRadixBits - 1) / kWideRadixBits, bits = (bits_all + passes - 1) / passes;
+  __syncthreads();
+  for (uint32_t i = tid; i < B; i += kSmallBlock)
+    if (offs[i] > offs[i + 1]) atomicMin(err_offsets, (unsigned long long)(g0 + i));
+  const int first = offs[0], n = (int)offs[B] - first;
+  if (n <= 0) return;
+  const int items = (n + kSmallBlock - 1) / kSmallBlock, q0 = wave * (items * 64) + lane;      // this lane's first record
+  uint32_t key[kSmallItems], smp[kSmallItems], rank[kSmallItems];
+#pragma unroll
+  for (int i = 0; i < kSmallItems; ++i) {
+    if (i >= items) break;
+    key[i] = (uint32_t)indices[first + min(q0 + i * 64, n - 1)];
+  }
+  // Samples: a bag leaves its number (and one) with its first lookup, a lookup takes the last one left up to it.
+  for (int q = tid; q < n; q += kSmallBlock) sbuf[q] = 0;
+  __syncthreads();
+  for (uint32_t i = tid; i < B; i += kSmallBlock) {
+    const int at = (int)offs[i] - first;
+    if (offs[i] < offs[i + 1] && at >= 0 && at < n) sbuf[at] = (uint16_t)(i + 1);
+  }
+  uint32_t last = 0, past = B;                     // of the wave's first record: offs[last] <= it < offs[past]
+  const int from = first + min(wave * (items * 64), n - 1);
+  while (past - last > 1) {
+    const uint32_t mid = (last + past) >> 1;
+    if (offs[mid] <= from) last = mid; else past = mid;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kSmallItems; ++i) {
+    if (i >= items) break;
+    const int q = q0 + i * 64;
+    const uint32_t left = q < n ? sbuf[q] : 0u;
+    const uint64_t marks = __ballot(left != 0), upto = marks & (~0ull >> (63 - lane));
+    const uint32_t mine = (uint32_t)__shfl((int)left, upto ? 63 - __clzll((long long)upto) : 0);
+    smp[i] = upto ? mine - 1 : last;
+    last = (uint32_t)__shfl((int)smp[i], 63);
+    const int64_t local = (int64_t)(int32_t)key[i] - row_begin;
+    key[i] = (uint64_t)local < (uint64_t)rows ? (uint32_t)local : rows;
+    if (err && q < n && key[i] == rows) atomicMin(err, (unsigned long long)(first + q));
+  }
+  volatile __attribute__((address_space(3))) uint16_t* const my_cnt =
+      (volatile __attribute__((address_space(3))) uint16_t*)(cnt + wave * kSmallRadix);
+  for (int p = 0; p < passes; ++p) {
+    const int shift = p * bits;
+    for (int i = tid; i < kSmallWaves * kSmallRadix / 8; i += kSmallBlock) ((uint4*)cnt)[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    // (ranks as in radix_scatter)
+#pragma unroll
+    for (int i = 0; i < kSmallItems; ++i) {
+      if (i >= items) break;
+      const uint32_t d = key[i] >> shift & ((1u << bits) - 1);
+      const bool valid = q0 + i * 64 < n;
+      const uint64_t v = __ballot(valid);
+      uint32_t other_lo = ~(uint32_t)v, other_hi = ~(uint32_t)(v >> 32);
+#pragma unroll
+      for (int b = 0; b < kWideRadixBits; ++b) {
+        if (b >= bits) break;
+        const uint32_t mine = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);
+        const uint64_t same = __ballot(mine != 0);
+        other_lo |= (uint32_t)same ^ mine;
+        other_hi |= (uint32_t)(same >> 32) ^ mine;
+      }
+      const uint32_t below = __builtin_amdgcn_mbcnt_hi(~other_hi, __builtin_amdgcn_mbcnt_lo(~other_lo, 0));
+      const uint32_t old = my_cnt[d];
+      __builtin_amdgcn_wave_barrier();
+      if (below == 0 && valid) my_cnt[d] = (uint16_t)(old + __popc(~other_lo) + __popc(~other_hi));
+      __builtin_amdgcn_wave_barrier();
+      rank[i] = old + below;
+    }
+    __syncthreads();
+    // a thread owns a digit: each wave's first record of it
+    uint32_t sum = 0, total;
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) sum += cnt[w * kSmallRadix + tid];
+    uint32_t run = dmt::block_exclusive_scan<kSmallWaves>(sum, sm, total);
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+      const uint32_t c = cnt[w * kSmallRadix + tid];
+      cnt[w * kSmallRadix + tid] = (uint16_t)run;
+      run += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSmallItems; ++i) {
+      if (i >= items) break;
+      if (q0 + i * 64 < n) {
+        const uint32_t at = cnt[wave * kSmallRadix + (key[i] >> shift & ((1u << bits) - 1))] + rank[i];
+        kbuf[at] = key[i];
+        sbuf[at] = (uint16_t)smp[i];
+      }
+    }
+    __syncthreads();
+    if (p + 1 == passes) break;
+#pragma unroll
+    for (int i = 0; i < kSmallItems; ++i) {
+      if (i >= items) break;
+      const int q = min(q0 + i * 64, n - 1);
+      key[i] = kbuf[q];
+      smp[i] = sbuf[q];
+    }
+  }
+  for (int q = tid; q < n; q += kSmallBlock) {
+    const uint32_t k = kbuf[q];
+    pk[first + q] = (uint64_t)((row_base + k) | (k == rows ? kInertBit : 0u)) << 32 | (g0 + sbuf[q]);
+  }
+}
+
 // ------------------------------------------------- run heads, segment offsets
 
 // Run-head flags of the 1024 consecutive records a wave owns inside its block's
@@ -1598,6 +1740,15 @@ template <typename Sample>
 void sort_lookups(const SortCall& c) {
   const BwdWs& w = *c.w;
   const dmt_plan* plan = c.plan;
+  if (c.nnz <= kSmallNnz && c.B <= kSmallBatch) {
+    static DmtPerDevice configured;
+    dmt_allow_lds(configured, (const void*)bwd_sort_small, kSmallLds);
+    DmtScope scope(plan, DMT_K_BWD_KEYS, c.s);
+    hipLaunchKernelGGL(bwd_sort_small, dim3((unsigned)plan->F), dim3(kSmallBlock), kSmallLds, c.s, plan->d_meta, c.indices,
+                       c.offsets, (uint32_t)c.B, (int)plan->F, (int)c.nnz, w.pk_a,
+                       plan->row_shards ? nullptr : plan->d_error, plan->d_error + 1);
+    return;
+  }
   int64_t max_rows = 0;
   for (int32_t f = 0; f < plan->F; ++f) max_rows = std::max<int64_t>(max_rows, plan->meta[f].rows);
   const int key_bits = ilog2_ceil(max_rows + 1);

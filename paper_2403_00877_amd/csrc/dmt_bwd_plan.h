@@ -46,6 +46,8 @@ __host__ __device__ inline int table_items(uint32_t len, int least_items) {
   const uint32_t items = (len + kBlock * kTableBlocks - 1) / (kBlock * kTableBlocks);
   return items <= (uint32_t)least_items ? least_items : items < (uint32_t)kSortItems ? (int)items : kSortItems;
 }
+// A call of so few lookups, in tables of so few samples, sorts in one launch (bwd_sort_small).
+constexpr int64_t kSmallNnz = 7168, kSmallBatch = 2048;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kBlock * kScanItems;   // records per head-scan block
 // Sorted records per reduce tile (one wave walks one): 128, or down to 16 where a call is too small

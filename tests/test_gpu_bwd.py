@@ -217,6 +217,39 @@ def test_samples_of_the_sorted_lookups(rows, batch, mean):
     assert np.array_equal(dbg["sorted_bag"].cpu().numpy(), np.repeat(np.arange(F * batch), per_bag)[order])
 
 
+@pytest.mark.parametrize("rows,lens,batch", [
+    ([1000, 7, 1], [1, 0, 64], 3), ([1023, 1024, 40], [1024, 1025, 7168 - 2049], 200), ([1 << 20], [7168], 2048),
+    ([1 << 20], [7168], 2049), ([1 << 20], [7169], 100),     # either line's other side: several launches
+    ([30000] * 70, [13] * 70, 1), ([1 << 21, 3], [63, 65], 2048),
+])
+@pytest.mark.parametrize("bags", ["even", "first", "last", "sparse"])
+def test_sort_of_few_lookups(rows, lens, batch, bags):
+    """One launch sorts them: one to three passes, tables of no, one and many lookups around a wave's and a step's,
+    samples even, all in the first or last bag, or with most bags empty; ids outside their table behind the others."""
+    F = len(rows)
+    w = wl.dataclasses.replace(
+        wl.scaled(wl.mid(True), max_rows=10, batch=batch, num_tables=F), table_dtype="f32", rows=rows,
+        dims=[4] * F, table_to_tower=[0] * F, tm_out=[32])
+    rng = np.random.default_rng(len(rows) + batch)
+    per_bag = np.zeros((F, batch), np.int64)
+    for f, n in enumerate(lens):
+        at = {"even": np.arange(n) % batch, "first": np.zeros(n, int), "last": np.full(n, batch - 1),
+              "sparse": rng.integers(0, max(1, batch // 50), n) * 50 % batch}[bags]
+        np.add.at(per_bag[f], at, 1)
+    per_bag = per_bag.reshape(-1)
+    off = np.concatenate([[0], np.cumsum(per_bag)])
+    idx = np.concatenate([(r * rng.random(n) ** 3).astype(np.int32) for r, n in zip(rows, lens)])
+    outside = rng.random(len(idx)) < 0.01
+    idx[outside] = -5
+    dw = DeviceWorkload(w, with_state=True, max_nnz=len(idx))
+    dbg = run_bwd(dw, idx, off, wl.grad_pooled(w), w.lr, w.eps)
+    assert dw.dmt.dmt_last_device_error(dw.plan) == (np.flatnonzero(outside)[0] if outside.any() else -1)
+    table = np.repeat(np.arange(F, dtype=np.int64), lens)
+    order = np.argsort(table << 32 | np.where(outside, np.array(rows)[table], idx), kind="stable")
+    assert np.array_equal(dbg["sorted_keys"].cpu().numpy(), np.where(outside, -1, table << 32 | idx)[order])
+    assert np.array_equal(dbg["sorted_bag"].cpu().numpy(), np.repeat(np.arange(F * batch), per_bag)[order])
+
+
 @pytest.mark.parametrize("dims", [[32, 64], [64], [32], [256]])
 def test_narrow_and_wide_rows(dims):
     """Dims up to 128 run the lean walk, 256 the wave-per-tile kernel."""
