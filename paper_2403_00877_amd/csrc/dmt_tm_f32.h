@@ -12,7 +12,7 @@
 // staged: a lane may feed the matrix core any k it likes as long as both operands agree, so lane
 // half h takes k + 4 h .. k + 4 h + 3 as one 16-byte load.  One thread per output, the plain
 // kernel before this one, was bound by one dependent load pair per k; 26 features of 64 columns
-// to 64 outputs, batch 2048: 394 -> 21 us forward, 1600 -> 30 us backward (with loads whose
+// to 64 outputs, batch 2048: 394 -> 13 us forward, 1600 -> 26 us backward (with loads whose
 // layout and guards were decided per load instead of per segment, so that each waited for the one
 // before it, and a weight gradient's k left to one wave: 24 and 186 us).
 #pragma once
@@ -55,10 +55,17 @@ enum { F32_ROW = 0, F32_COL = 1, F32_COL2 = 2 };
 
 // Four consecutive k of one operand row (`row` is clamped to a valid one): unguarded, and with
 // zeros from K on.
-template <int LAY>
+template <int LAY, bool ANY>
 __device__ __forceinline__ float4 f32_load4(const float* __restrict__ p, int64_t row, int k, int64_t ld, int div,
                                             int64_t ld2) {
-  if constexpr (LAY == F32_ROW) return *(const float4*)(p + row * ld + k);
+  if constexpr (LAY == F32_ROW) {
+    if constexpr (ANY) {                           // from any 4-byte boundary
+      typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+      const float4u v = *(const float4u*)(p + row * ld + k);
+      return make_float4(v.x, v.y, v.z, v.w);
+    }
+    return *(const float4*)(p + row * ld + k);
+  }
   auto at = [&](int kk) {
     return row + (LAY == F32_COL2 ? (int64_t)(kk / div) * ld + (int64_t)(kk % div) * ld2 : kk * ld);
   };
@@ -87,7 +94,16 @@ struct F32Seg {
 };
 constexpr int kF32Unroll = 4;                      // steps whose operands are requested together
 
+// Whether whole steps of a segment can be read 16 bytes at a time from 16-byte boundaries.
 template <int ALAY, int WLAY, bool MASK>
+__device__ __forceinline__ bool f32_aligned(const F32Seg& g) {
+  return (ALAY != F32_ROW || (((uintptr_t)g.A | (MASK ? (uintptr_t)g.mask : 0)) & 15) + (g.lda & 3) == 0) &&
+         (WLAY != F32_ROW || ((uintptr_t)g.W & 15) + (g.ldw & 3) == 0);
+}
+
+// ANY: rows may start on any 4-byte boundary.  (Otherwise those that are not aligned go step by step, each load behind
+// a guard; one load for both kinds took the aligned ones 13.6 -> 15.1 us.)
+template <int ALAY, int WLAY, bool MASK, bool ANY = false>
 __device__ __forceinline__ void f32_segment(const F32Seg& g, int64_t m, int64_t n, int h4, floatx16& acc, float& db) {
   auto step = [&](float4 a, float4 w, float4 q) __attribute__((always_inline)) {
     if constexpr (MASK) {
@@ -104,9 +120,7 @@ __device__ __forceinline__ void f32_segment(const F32Seg& g, int64_t m, int64_t 
   };
   // whole batches of steps, loads unconditional, a batch ahead of the matrix instructions (the
   // last prefetch reads the last batch once more)
-  const bool vec = (ALAY != F32_ROW || (((uintptr_t)g.A | (MASK ? (uintptr_t)g.mask : 0)) & 15) + (g.lda & 3) == 0) &&
-                   (WLAY != F32_ROW || ((uintptr_t)g.W & 15) + (g.ldw & 3) == 0);
-  const int full = vec ? min(g.hi, g.K / 8) : g.lo;
+  const int full = ANY || f32_aligned<ALAY, WLAY, MASK>(g) ? min(g.hi, g.K / 8) : g.lo;
   const int nb = (full - g.lo) / kF32Unroll;
   int s = g.lo;
   if (nb > 0) {
@@ -115,9 +129,9 @@ __device__ __forceinline__ void f32_segment(const F32Seg& g, int64_t m, int64_t 
 #pragma unroll
       for (int u = 0; u < kF32Unroll; ++u) {
         const int k = (g.lo + b * kF32Unroll + u) * 8 + h4;
-        a[buf][u] = f32_load4<ALAY>(g.A, m, k, g.lda, g.div, g.lda2);
-        w[buf][u] = f32_load4<WLAY>(g.W, n, k, g.ldw, 0, 0);
-        if constexpr (MASK) q[buf][u] = f32_load4<ALAY>(g.mask, m, k, g.lda, g.div, g.lda2);
+        a[buf][u] = f32_load4<ALAY, ANY>(g.A, m, k, g.lda, g.div, g.lda2);
+        w[buf][u] = f32_load4<WLAY, ANY>(g.W, n, k, g.ldw, 0, 0);
+        if constexpr (MASK) q[buf][u] = f32_load4<ALAY, ANY>(g.mask, m, k, g.lda, g.div, g.lda2);
         else q[buf][u] = make_float4(0.f, 0.f, 0.f, 0.f);
       }
     };
@@ -148,6 +162,13 @@ __device__ __forceinline__ void f32_segment(const F32Seg& g, int64_t m, int64_t 
 __host__ __device__ inline int f32_first_step(int steps, int part, int log2_ks) {
   return (int)((int64_t)steps * part >> log2_ks);
 }
+// The same in whole batches of steps, since what is left of a batch goes step by step, each waiting for its loads
+// (26 features of 64 columns to 64 outputs, batch 2048, shares of 6 and 7 steps / 4 and 8: forward 20.9 / 14.1 us, 13.6
+// with the layouts that a forward does not have left out).
+__host__ __device__ inline int f32_share_begin(int steps, int part, int log2_ks) {
+  const int first = f32_first_step((steps + kF32Unroll - 1) / kF32Unroll, part, log2_ks) * kF32Unroll;
+  return first < steps ? first : steps;
+}
 
 template <int TAG = DMT_TM_TAG>
 __global__ __launch_bounds__(kF32Waves * 64) void tm_gemm_f32(const TmF32Launch L) {
@@ -167,19 +188,27 @@ __global__ __launch_bounds__(kF32Waves * 64) void tm_gemm_f32(const TmF32Launch 
   const int m = min(m0 + r, M - 1), n = min(n0 + r, N - 1);   // rows past the edge: the last row, not stored
   // this wave's share of the steps, cut into the two segments
   const int S0 = (G.K0 + 7) / 8, S = S0 + (G.K1 + 7) / 8;
-  const int lo = live ? f32_first_step(S, part, G.log2_ks) : 0, hi = live ? f32_first_step(S, part + 1, G.log2_ks) : 0;
+  const int lo = live ? f32_share_begin(S, part, G.log2_ks) : 0, hi = live ? f32_share_begin(S, part + 1, G.log2_ks) : 0;
   floatx16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
   float db = 0.f;
+  // A dot tower's weights have rows of 78 terms and 208 columns, say, so few of them are aligned (13 features of 16
+  // columns to 64 outputs, batch 107: 16.1 us step by step, 10.6).
+  auto forward = [&](const F32Seg& g) __attribute__((always_inline)) {
+    if (TAG != 0 || f32_aligned<F32_ROW, F32_ROW, false>(g)) f32_segment<F32_ROW, F32_ROW, false>(g, m, n, h4, acc, db);
+    else f32_segment<F32_ROW, F32_ROW, false, true>(g, m, n, h4, acc, db);
+  };
   if (lo < S0) {
     const F32Seg g0{G.A0, G.W0, nullptr, G.lda0, G.ldw0, 0, G.K0, 0, lo, min(hi, S0)};
-    if (G.wcol) f32_segment<F32_ROW, F32_COL, false>(g0, m, n, h4, acc, db);
-    else f32_segment<F32_ROW, F32_ROW, false>(g0, m, n, h4, acc, db);
+    if (TAG != 0 && G.wcol) f32_segment<F32_ROW, F32_COL, false>(g0, m, n, h4, acc, db);
+    else forward(g0);
   }
   if (hi > S0) {
     const F32Seg g1{G.A1, G.W1, G.mask, G.lda1, G.ldw1, G.lda2, G.K1, G.adiv, max(lo, S0) - S0, hi - S0};
-    if (!G.acol) {
+    if (TAG == 0) {                                // (the forward's operands have k contiguous)
+      forward(g1);
+    } else if (!G.acol) {
       if (!G.wcol) f32_segment<F32_ROW, F32_ROW, false>(g1, m, n, h4, acc, db);
       else if (!G.mask) f32_segment<F32_ROW, F32_COL, false>(g1, m, n, h4, acc, db);
       else f32_segment<F32_ROW, F32_COL, true>(g1, m, n, h4, acc, db);
@@ -255,11 +284,16 @@ inline TmF32Group f32_group(const TmGroup& g) {
 inline void launch_f32(const dmt_plan* p, std::vector<TmF32Group>& groups, hipStream_t s, int kid) {
   auto tiles_of = [](const TmF32Group& g) { return (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32); };
   auto steps_of = [](const TmF32Group& g) { return (int64_t)((g.K0 + 7) / 8 + (g.K1 + 7) / 8); };
-  // Waves per tile: doubled while the group has fewer than four waves per SIMD (4096) and a wave
-  // keeps a whole batch of steps.  Groups whose waves work longest go first.
+  // Waves per tile: doubled while groups of about as long a k together have fewer than four waves per SIMD (4096) and
+  // a wave keeps a whole batch of steps.  (Counted group by group, four data gradients of 8 steps took 6656 waves of 4,
+  // which beside the weight gradients' 1664 were just over two rounds of blocks instead of 1.2: 29.6 / 26.3 us.)  Groups
+  // whose waves work longest go first.
   for (TmF32Group& g : groups) {
+    int64_t tiles = 0;
+    for (const TmF32Group& o : groups)
+      if (steps_of(o) <= 2 * steps_of(g) && steps_of(g) <= 2 * steps_of(o)) tiles += tiles_of(o);
     g.log2_ks = 0;
-    while (g.log2_ks < 4 && (tiles_of(g) << (g.log2_ks + 1)) <= 4096 && steps_of(g) >> (g.log2_ks + 1) >= kF32Unroll)
+    while (g.log2_ks < 4 && (tiles << (g.log2_ks + 1)) <= 4096 && steps_of(g) >> (g.log2_ks + 1) >= kF32Unroll)
       ++g.log2_ks;
   }
   std::stable_sort(groups.begin(), groups.end(), [&](const TmF32Group& a, const TmF32Group& b) {
