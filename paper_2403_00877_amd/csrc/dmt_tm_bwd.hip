@@ -184,17 +184,18 @@ __global__ __launch_bounds__(kBlock) void tmb_dot_bwd8(const TmbLaunch L) {
 // in one kernel.  Bound by the bytes of x and dx: the two contractions and tmb_dot_bwd8 moved the flat part of dZ,
 // as large as dx, through memory and back.  8 towers of 8 features of 128 columns, 256 outputs, batch 8192: 77 + 12 +
 // 148 us, now 116 (0.44 GB at 3.8 TB/s; without the products 105, without the requests of weights and dz 96); 4 of 6 and
-// 7 features, batch 2003: 17 + 16 us, now 18, and the repack of the weights rides with tmb_prep_dz.
-// A wave owns 32 samples and the same 32 columns of EVERY feature, the weights as the first operand, so that a lane
+// 7 features, batch 2003: 17 + 16 us, now 15, and the repack of the weights rides with tmb_prep_dz.
+// A wave owns 16 or 32 samples and the same 32 columns of EVERY feature, the weights as the first operand, so that a lane
 // holds one sample's values of all features at four consecutive columns and the sum over j needs no other lane's
 // (x comes in the accumulators' layout, 8 bytes a lane).  Four waves share the weights of their columns, which go
 // through LDS in steps of 32 outputs, fragment by fragment as the repacked weights lie; behind them come the dot
 // terms' rows, whose products, a few floats a sample, take the way through LDS to the sample's other lanes.
 constexpr int kDotFeat = 8;                        // features, at most
 constexpr int kDotTerms = kDotFeat * (kDotFeat - 1) / 2, kDotTermTiles = (kDotTerms + 15) / 16;
-constexpr int kDotCols = 32, kDotRows = 128;       // columns of a feature, samples of a block
+constexpr int kDotCols = 32;                       // columns of a feature that a block takes
 constexpr int kDotTiles = kDotFeat * (kDotCols / 16) + kDotTermTiles;
 constexpr int kDotZPitch = kDotTermTiles * 16 + 4; // floats: 16 samples' pieces of 16 bytes on different banks
+constexpr int64_t kDotFewBlocks = 256;             // of 128 samples: up to here blocks of 64
 // Term of the pair {i, j}, i < j, whatever the number of features.
 __host__ __device__ constexpr int dot_slot(int i, int j) { return i * (2 * kDotFeat - 1 - i) / 2 + j - i - 1; }
 inline bool dot_dgrad_ok(const dmt_plan* p, int nf, int n) { return p->sw.tm_fuse && nf >= 2 && nf <= kDotFeat && n % kDotCols == 0; }
@@ -233,14 +234,18 @@ __device__ __forceinline__ void pack_dot_weights(const TmbItem& G, int64_t e) {
 // Three stages in LDS, requested two steps ahead (a step is short: 36 instructions of 16 x 16 x 32 a wave); the
 // wave's own dz goes the same way, so that the requests under way can be counted.  The x values are requested
 // ahead of the last step.
-constexpr int kDotStage = kDotTiles * 1024 + kDotRows * 64;      // bytes: weights, then dz (two fragments a wave)
-constexpr int kDotLds = 3 * kDotStage;
-static_assert(kDotLds >= 4 * 32 * kDotZPitch * 4 && 2 * kDotLds <= 160 * 1024, "two blocks per CU");
+// S sets of 16 samples a wave: two, or one where that makes more of the blocks that a launch is short of (2 towers of 8
+// features, batch 822: 16.7 -> 11.3 us; 4 of 6 and 7, batch 2003: 18.0 -> 15.1).
+constexpr int dot_rows(int S) { return 4 * 16 * S; }
+constexpr int dot_stage(int S) { return kDotTiles * 1024 + 4 * S * 1024; }      // bytes: weights, then dz (a fragment a set)
+constexpr int dot_lds(int S) { return 3 * dot_stage(S); }
+static_assert(dot_lds(1) >= dot_rows(1) * kDotZPitch * 4 && dot_lds(2) >= dot_rows(2) * kDotZPitch * 4 && 2 * dot_lds(2) <= 160 * 1024,
+              "two blocks per CU");
 
 // a = dz [B][Op], b = repacked weights, c = x, o0 = dx, n0 = B, i0 = nf, i1 = n, i2 = O, i3 = Op.
-template <int DT>
+template <int DT, int S>
 __global__ __launch_bounds__(kBlock, 2) void tmb_dot_dgrad(const TmbLaunch L) {
-  static_assert(kBlock == 256 && kDotRows == 128, "four waves of 32 samples");
+  static_assert(kBlock == 256, "four waves");
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   // the column blocks of the same samples run side by side on one XCD: they share lines of x and dz
   const int q8 = gridDim.x >> 3, r8 = gridDim.x & 7, xcd = blockIdx.x & 7;
@@ -251,7 +256,7 @@ __global__ __launch_bounds__(kBlock, 2) void tmb_dot_dgrad(const TmbLaunch L) {
   const int nf = G.i0, n = G.i1, Op = G.i3, steps = (G.i2 + 31) / 32;
   const int ncb = n / kDotCols, cb = (id - L.block_start[gi]) % ncb;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), m = lane & 15, h = lane >> 4;
-  const int64_t B = G.n0, s0 = (int64_t)((id - L.block_start[gi]) / ncb) * kDotRows + wave * 32;
+  const int64_t B = G.n0, s0 = (int64_t)((id - L.block_start[gi]) / ncb) * dot_rows(S) + wave * (16 * S);
   const int tiles = 2 * nf + kDotTermTiles, per_wave = (tiles + 3) / 4;
   const int64_t wt = (int64_t)nf * n;
 
@@ -259,45 +264,47 @@ __global__ __launch_bounds__(kBlock, 2) void tmb_dot_dgrad(const TmbLaunch L) {
   // and the wave's two of dz
   const uint32_t panel = (uint32_t)(steps * tiles) * 1024u;
   const __amdgpu_buffer_rsrc_t wbuf = tm_buffer((const char*)G.b + (int64_t)cb * panel, panel);
-  const int64_t mine = min(max(B - s0, (int64_t)0), (int64_t)32);
+  const int64_t mine = min(max(B - s0, (int64_t)0), (int64_t)(16 * S));
   const __amdgpu_buffer_rsrc_t zbuf = tm_buffer((const uint16_t*)G.a + min(s0, B - 1) * Op, (uint32_t)mine * (uint32_t)Op * 2u);
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint16_t*)lds;
   auto request = [&](int step) {
-    const uint32_t to = lds0 + (uint32_t)(step % 3) * kDotStage, from = (uint32_t)(step * tiles) * 1024u + lane * 16u;
+    const uint32_t to = lds0 + (uint32_t)(step % 3) * dot_stage(S), from = (uint32_t)(step * tiles) * 1024u + lane * 16u;
     for (int r = 0; r < per_wave; ++r) {
       const uint32_t t = (uint32_t)min(wave + 4 * r, tiles - 1) * 1024u;
       tm_request(to + t, wbuf, from + t);
     }
     const int k = step * 32 + h * 8;
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-      tm_request(to + kDotTiles * 1024 + (wave * 2 + s) * 1024, zbuf, k < Op ? (uint32_t)((s * 16 + m) * Op + k) * 2u : kOobOffset);
+    for (int s = 0; s < S; ++s)
+      tm_request(to + kDotTiles * 1024 + (wave * S + s) * 1024, zbuf, k < Op ? (uint32_t)((s * 16 + m) * Op + k) * 2u : kOobOffset);
   };
-  floatx4 acc[2][kDotFeat][2], accz[2][kDotTermTiles];
+  floatx4 acc[S][kDotFeat][2], accz[S][kDotTermTiles];
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
+  for (int s = 0; s < S; ++s) {
 #pragma unroll
     for (int i = 0; i < kDotFeat; ++i) acc[s][i][0] = acc[s][i][1] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < kDotTermTiles; ++t) accz[s][t] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
   auto multiply = [&](int step) {
-    const uint4* w = (const uint4*)(lds + (step % 3) * (kDotStage / 2)) + lane;
-    const uint4 d0 = w[(kDotTiles + wave * 2) * 64], d1 = w[(kDotTiles + wave * 2 + 1) * 64];
+    const uint4* w = (const uint4*)(lds + (step % 3) * (dot_stage(S) / 2)) + lane;
+    uint4 d[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) d[s] = w[(kDotTiles + wave * S + s) * 64];
 #pragma unroll
     for (int i = 0; i < kDotFeat; ++i)
       if (i < nf) {
         const uint4 w0 = w[(2 * i) * 64], w1 = w[(2 * i + 1) * 64];
-        acc[0][i][0] = mfma16<DT>(w0, d0, acc[0][i][0]);
-        acc[1][i][0] = mfma16<DT>(w0, d1, acc[1][i][0]);
-        acc[1][i][1] = mfma16<DT>(w1, d1, acc[1][i][1]);
-        acc[0][i][1] = mfma16<DT>(w1, d0, acc[0][i][1]);
+#pragma unroll
+        for (int s = 0; s < S; ++s) acc[s][i][0] = mfma16<DT>(w0, d[s], acc[s][i][0]);
+#pragma unroll
+        for (int s = S - 1; s >= 0; --s) acc[s][i][1] = mfma16<DT>(w1, d[s], acc[s][i][1]);
       }
 #pragma unroll
     for (int t = 0; t < kDotTermTiles; ++t) {
       const uint4 wz = w[(2 * nf + t) * 64];
-      accz[0][t] = mfma16<DT>(wz, d0, accz[0][t]);
-      accz[1][t] = mfma16<DT>(wz, d1, accz[1][t]);
+#pragma unroll
+      for (int s = 0; s < S; ++s) accz[s][t] = mfma16<DT>(wz, d[s], accz[s][t]);
     }
   };
   request(0);
@@ -305,10 +312,11 @@ __global__ __launch_bounds__(kBlock, 2) void tmb_dot_dgrad(const TmbLaunch L) {
   for (int step = 0; step + 1 < steps; ++step) {
     // all of this wave's requests but the next step's have landed; behind the barrier everyone's, and the stage of
     // the step before is read no more
-    switch (per_wave) {
-      case 2: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
-      case 3: asm volatile("s_waitcnt vmcnt(5)" ::: "memory"); break;
-      case 4: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
+    switch (per_wave + S) {
+      case 3: asm volatile("s_waitcnt vmcnt(3)" ::: "memory"); break;
+      case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+      case 5: asm volatile("s_waitcnt vmcnt(5)" ::: "memory"); break;
+      case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
       default: asm volatile("s_waitcnt vmcnt(7)" ::: "memory"); break;
     }
     __syncthreads();
@@ -317,9 +325,9 @@ __global__ __launch_bounds__(kBlock, 2) void tmb_dot_dgrad(const TmbLaunch L) {
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  uint4 xr[2][kDotFeat];
+  uint4 xr[S][kDotFeat];
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
+  for (int s = 0; s < S; ++s) {
     const uint16_t* x = (const uint16_t*)G.c + min(s0 + s * 16 + m, B - 1) * wt + cb * kDotCols + h * 8;
 #pragma unroll
     for (int j = 0; j < kDotFeat; ++j) xr[s][j] = *(const uint4*)(x + (j < nf ? j : 0) * n);
@@ -327,9 +335,9 @@ __global__ __launch_bounds__(kBlock, 2) void tmb_dot_dgrad(const TmbLaunch L) {
   multiply(steps - 1);
   // the samples' dZ to all their lanes, over the stages
   __syncthreads();
-  float* const z_of = (float*)lds + (wave * 32 + m) * kDotZPitch;
+  float* const z_of = (float*)lds + (wave * 16 * S + m) * kDotZPitch;
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
+  for (int s = 0; s < S; ++s)
 #pragma unroll
     for (int t = 0; t < kDotTermTiles; ++t) *(floatx4*)(z_of + s * 16 * kDotZPitch + t * 16 + h * 4) = accz[s][t];
   // (a wave reads what its own lanes wrote)
@@ -337,7 +345,7 @@ __global__ __launch_bounds__(kBlock, 2) void tmb_dot_dgrad(const TmbLaunch L) {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
+  for (int s = 0; s < S; ++s) {
     float z[kDotTermTiles * 16];
 #pragma unroll
     for (int q = 0; q < (kDotTerms + 3) / 4; ++q) {
@@ -886,7 +894,7 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
       it = TmbItem{};
       it.a = dz; it.b = wsp + w.wp; it.c = x_of(t); it.o0 = dx_of(t); it.n0 = B;
       it.i0 = nf; it.i1 = n; it.i2 = O; it.i3 = (int32_t)w.Op;
-      dots_fused.add(it, (B + kDotRows - 1) / kDotRows * (n / kDotCols));
+      dots_fused.add(it, (B + dot_rows(2) - 1) / dot_rows(2) * (n / kDotCols));
     } else if (dot) {
       const int64_t ldw = w.skip + wt;
       const char* W = wp_of(t);
@@ -944,9 +952,19 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
   launch_groups<DT, OP_ROW, OP_COL>(p, dgrad, s, false, kid);
   launch_groups<DT, OP_ROW, OP_COL>(p, dgrad2, s, false, kid);
   if (!dots_fused.items.empty()) {
-    static DmtPerDevice configured;
-    dmt_allow_lds(configured, (const void*)tmb_dot_dgrad<DT>, kDotLds);
-    ok &= launch_items(p, dots_fused, tmb_dot_dgrad<DT>, s, kDotLds);
+    int64_t blocks = 0;
+    for (int64_t b : dots_fused.blocks) blocks += b;
+    if (blocks <= kDotFewBlocks) {
+      for (size_t i = 0; i < dots_fused.items.size(); ++i)
+        dots_fused.blocks[i] = (B + dot_rows(1) - 1) / dot_rows(1) * (dots_fused.items[i].i1 / kDotCols);
+      static DmtPerDevice configured;
+      dmt_allow_lds(configured, (const void*)tmb_dot_dgrad<DT, 1>, dot_lds(1));
+      ok &= launch_items(p, dots_fused, tmb_dot_dgrad<DT, 1>, s, dot_lds(1));
+    } else {
+      static DmtPerDevice configured;
+      dmt_allow_lds(configured, (const void*)tmb_dot_dgrad<DT, 2>, dot_lds(2));
+      ok &= launch_items(p, dots_fused, tmb_dot_dgrad<DT, 2>, s, dot_lds(2));
+    }
   }
   launch_groups<DT, OP_COL, OP_COL>(p, wgrad, s, false, kid);
   launch_groups<DT, OP_COL, OP_COL>(p, wgrad2, s, false, kid);

@@ -287,10 +287,12 @@ def test_dlrm_module_odd_widths():
     ("bf16", [2, 8], [32, 128], [1, 256], 127), ("f16", [3, 7], [96, 64], [33, 40], 129),
     ("bf16", [5, 9], [32, 32], [8, 72], 1),          # nine features: the separate kernels, in the same call
     ("bf16", [8, 6], [128, 96], [250, 300], 300), ("f16", [4, 8], [160, 40], [520, 16], 257),   # 40 columns: likewise
+    ("bf16", [8, 4], [128, 128], [64, 32], 4096), ("bf16", [8, 4], [128, 128], [64, 32], 4097),  # blocks of 64 samples, of 128
+    ("f16", [8, 2], [128, 32], [96, 24], 6400),
 ])
 def test_dot_towers_data_gradient_in_one_kernel(dt, nfs, dims, outs, batch):
     """2 to 8 features of one to five blocks of 32 columns, one to 17 steps of 32 outputs with and without a remainder,
-    batches around one block of 128 samples."""
+    batches around one block of 64 and of 128 samples and around the line between the two."""
     w = wl.scaled(wl.mid(), max_rows=300, batch=batch, num_tables=sum(nfs))
     w.table_to_tower = [0] * nfs[0] + [1] * nfs[1]
     w.dims = [dims[0]] * nfs[0] + [dims[1]] * nfs[1]
