@@ -685,7 +685,7 @@ struct TmbBatch {
 
 // False when an item alone exceeds the grid limit (nothing of it is launched).
 template <typename Kernel>
-bool launch_items(const dmt_plan* p, TmbBatch& batch, Kernel kernel, hipStream_t s, int lds = 0) {
+bool launch_items(const dmt_plan* p, TmbBatch& batch, Kernel kernel, hipStream_t s, int lds = 0, int kid = DMT_K_TM_BWD_AUX) {
   bool ok = true;
   for (size_t first = 0; first < batch.items.size();) {
     TmbLaunch L;
@@ -701,7 +701,7 @@ bool launch_items(const dmt_plan* p, TmbBatch& batch, Kernel kernel, hipStream_t
     }
     if (L.n == 0) { ok = false; break; }
     L.block_start[L.n] = (int32_t)blocks;
-    DmtScope sc_(p, DMT_K_TM_BWD_AUX, s);
+    DmtScope sc_(p, kid, s);
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kBlock), lds, s, L);
   }
   batch.items.clear();
@@ -973,11 +973,11 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
         dots_fused.blocks[i] = (B + dot_rows(1) - 1) / dot_rows(1) * (dots_fused.items[i].i1 / kDotCols);
       static DmtPerDevice configured;
       dmt_allow_lds(configured, (const void*)tmb_dot_dgrad<DT, 1>, dot_lds(1));
-      ok &= launch_items(p, dots_fused, tmb_dot_dgrad<DT, 1>, s, dot_lds(1));
+      ok &= launch_items(p, dots_fused, tmb_dot_dgrad<DT, 1>, s, dot_lds(1), kid);
     } else {
       static DmtPerDevice configured;
       dmt_allow_lds(configured, (const void*)tmb_dot_dgrad<DT, 2>, dot_lds(2));
-      ok &= launch_items(p, dots_fused, tmb_dot_dgrad<DT, 2>, s, dot_lds(2));
+      ok &= launch_items(p, dots_fused, tmb_dot_dgrad<DT, 2>, s, dot_lds(2), kid);
     }
   }
   launch_groups<DT, OP_COL, OP_COL>(p, wgrad, s, false, kid);
