@@ -200,7 +200,10 @@ constexpr int kDotZPitch = kDotTermTiles * 16 + 4; // floats: 16 samples' pieces
 constexpr int64_t kDotFewBlocks = 256;             // of 128 samples: up to here blocks of 64
 // Term of the pair {i, j}, i < j, whatever the number of features.
 __host__ __device__ constexpr int dot_slot(int i, int j) { return i * (2 * kDotFeat - 1 - i) / 2 + j - i - 1; }
-inline bool dot_dgrad_ok(const dmt_plan* p, int nf, int n) { return p->sw.tm_fuse && nf >= 2 && nf <= kDotFeat && n % kDotCols == 0; }
+// (32-bit byte offsets into a column block's weights)
+inline bool dot_dgrad_ok(const dmt_plan* p, int nf, int n, int64_t O) {
+  return p->sw.tm_fuse && nf >= 2 && nf <= kDotFeat && n % kDotCols == 0 && (O + 31) / 32 * kDotTiles * 1024 < (1LL << 31);
+}
 // Fragments (1 KB) of a tower's repacked weights.
 inline int64_t dot_wt_frags(int nf, int n, int64_t O) {
   return (int64_t)(n / kDotCols) * ((O + 31) / 32) * (nf * (kDotCols / 16) + kDotTermTiles);
@@ -598,7 +601,7 @@ dmt_status plan_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, in
         if (p->tower_uniform_dim[t] == 0) return DMT_ENOTSUP;
         w.np = nf * (nf - 1) / 2;
         w.np_pad = (w.np + 7) / 8 * 8;
-        w.fused = eb == 2 && dot_dgrad_ok(p, nf, p->tower_uniform_dim[t]);
+        w.fused = eb == 2 && dot_dgrad_ok(p, nf, p->tower_uniform_dim[t], q.out_dim);
         w.packed = !w.fused && !dot_weights_as_is(q.w_proj, w.np);
         w.skip = w.packed ? w.np_pad : w.np;
         w.kin = w.np_pad + (int)wt;

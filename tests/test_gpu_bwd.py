@@ -353,6 +353,14 @@ def test_malformed_offsets_update_nothing_and_are_reported(case):
     assert sum(int((s != 0).sum()) for s in dw.states) > 0
 
 
+@pytest.mark.parametrize("case", ["first_not_zero", "descending", "last_not_nnz", "beyond_nnz"])
+def test_malformed_offsets_of_a_call_that_several_launches_sort(case, monkeypatch):
+    """The same with 19 K lookups: past the line of bwd_sort_small, which makes the checks of the smaller call."""
+    scaled = wl.scaled
+    monkeypatch.setattr(wl, "scaled", lambda w, **sizes: scaled(w, **dict(sizes, batch=120)))
+    test_malformed_offsets_update_nothing_and_are_reported(case)
+
+
 def test_malformed_offsets_of_many_tables_stay_inside_the_workspace():
     """Tables whose first bags start at 0, nnz, 0, nnz ...: added up, the tables' lengths pass 2^32, and blocks that
     start from such a sum would list 16384 sort blocks where the launch has 9216.  Nothing is touched, inside the
