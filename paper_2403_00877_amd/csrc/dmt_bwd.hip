@@ -87,8 +87,12 @@ __global__ __launch_bounds__(kBlock) void bwd_bag_samples(
     uint32_t* __restrict__ seg_blk, uint32_t* __restrict__ blk_table,
     unsigned long long* __restrict__ err_offsets) {
   __shared__ uint32_t offs[kKeysMaxBags + 1];
-  if (blockIdx.x == 0) build_sort_map(offsets, B, F, nnz, least_items, seg_begin, seg_blk, blk_table);
-  const uint32_t g0 = blockIdx.x << log2_bpb;
+  // (a block of its own, the first: with bags beside it, it was the last to end: 26 tables of 10 K lookups 5.6 -> 4.5 us)
+  if (blockIdx.x == 0) {
+    build_sort_map(offsets, B, F, nnz, least_items, seg_begin, seg_blk, blk_table);
+    return;
+  }
+  const uint32_t g0 = (blockIdx.x - 1) << log2_bpb;
   if (g0 >= nbags) return;
   const int nb = (int)min((uint32_t)(1 << log2_bpb), nbags - g0);
   // `offsets` must tile [0, nnz): starts at 0, never descends, ends at nnz.  The first bag
@@ -107,19 +111,20 @@ __global__ __launch_bounds__(kBlock) void bwd_bag_samples(
   for (uint32_t j = (s & ~3u) + threadIdx.x * 4; j < e; j += kBlock * 4) {
     Sample v[4];
     int lo = 0;
+    uint32_t end = 0;                              // of bag lo: offs[lo] <= at < end = offs[lo + 1]
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const uint32_t at = j + u;
-      // offs[lo] <= at < offs[lo + 1]; most lookups lie in the bag of the one before or in the next
-      if (at >= s && at < e && (u == 0 || offs[lo + 1] <= at)) {
-        if (u > 0 && lo + 2 <= nb && offs[lo + 2] > at) {
-          ++lo;
-        } else {
+      // most lookups lie in the bag of the one before or in the next
+      if (at >= s && at < e && at >= end) {
+        if (end != 0) end = offs[++lo + 1];
+        if (at >= end) {
           int hi = nb;
           while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
             if (offs[mid] <= at) lo = mid; else hi = mid;
           }
+          end = offs[lo + 1];
         }
       }
       uint32_t b = b0 + (uint32_t)lo;
@@ -143,7 +148,7 @@ __global__ __launch_bounds__(kBlock) void bwd_bag_samples(
 // 65536 samples), in two arrays: the table is known from the position.  The counting kernels then read 4 bytes
 // a lookup and the scatters move 6 each way, and the first pass reads `indices` as they lie.  Only the last pass
 // writes the 64-bit records the reduce kernels walk.  Records of 8 bytes through all passes, built beforehand
-// / now, us: 64 tables of 164 K lookups, 20 bits of row id: build 41 / samples 18, count 22 / 10-13, scatter 43 / 31-33
+// / now, us: 64 tables of 164 K lookups, 20 bits of row id: build 41 / samples 17, count 22 / 10-13, scatter 43 / 31-33
 // a pass, the whole sort 253 / 165; 256 of 246 K, 20 bits: 1543 / 830; 128 of 170 K, 23 bits: 563 / 328.  The
 // scatters are bound by their instructions (a wave's 64 lanes take four cycles each) as much as by bytes.
 template <typename Sample>
@@ -1757,7 +1762,7 @@ void sort_lookups(const SortCall& c) {
   const int bits_per = (key_bits + passes - 1) / passes;
   auto region = [&](int pass) { return (passes - pass) & 1 ? w.pk_a : w.pk_b; };   // where a pass writes
   Sample* const samples = (Sample*)(region(0) == w.pk_a ? w.pk_b : w.pk_a);
-  timed_launch(plan, DMT_K_BWD_KEYS, c.s, bwd_bag_samples<Sample>, c.key_blocks, kBlock, c.offsets, (uint32_t)c.B,
+  timed_launch(plan, DMT_K_BWD_KEYS, c.s, bwd_bag_samples<Sample>, c.key_blocks + 1, kBlock, c.offsets, (uint32_t)c.B,
                c.nbags, c.nnz, (int)plan->F, samples, c.log2_bpb, w.least_items, w.seg_begin, w.seg_blk, w.blk_table,
                plan->d_error + 1);
   SortIo<Sample> io{};
