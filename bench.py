@@ -106,6 +106,7 @@ def batch_accounting(torch, w, idx, off):
 # kernel (as the profiler names it) -> the family dmt_kernel_name() reports
 FAMILIES = (("lookup_fwd_kernel", "lookup_fwd"), ("bwd_reduce_update", "bwd_reduce_update"),
             ("bwd_fixup_update", "bwd_fixup_update"), ("bwd_bag_samples", "bwd_build_keys"),
+            ("bwd_sort_small", "bwd_build_keys"),
             ("radix_hist", "radix_hist"), ("radix_scan", "radix_scan"), ("radix_scatter", "radix_scatter"),
             ("tm_gemm", "tm_gemm"), ("tm_pack_w", "tm_pack_w"), ("tm_dots", "tm_dots"),
             ("dmt_copy_kernel", "copy"))
