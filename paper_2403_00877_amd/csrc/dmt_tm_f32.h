@@ -162,10 +162,14 @@ __device__ __forceinline__ void f32_segment(const F32Seg& g, int64_t m, int64_t 
 __host__ __device__ inline int f32_first_step(int steps, int part, int log2_ks) {
   return (int)((int64_t)steps * part >> log2_ks);
 }
-// The same in whole batches of steps, since what is left of a batch goes step by step, each waiting for its loads
-// (26 features of 64 columns to 64 outputs, batch 2048, shares of 6 and 7 steps / 4 and 8: forward 20.9 / 14.1 us, 13.6
-// with the layouts that a forward does not have left out).
-__host__ __device__ inline int f32_share_begin(int steps, int part, int log2_ks) {
+// The forward's shares are whole batches of steps, since what is left of a batch goes step by step, each waiting for its
+// loads (26 features of 64 columns to 64 outputs, batch 2048, shares of 6 and 7 steps / 4 and 8: 20.9 / 14.1 us, 13.6
+// with the layouts that a forward does not have left out).  The backward's are single steps: an operand with its row
+// index contiguous takes four loads a step, and a share of two batches loads three (the last prefetch), so it is the
+// longest share that counts (per-feature layers of 6 and 7 features, batch 107, 81 steps to 16 waves, batches / steps:
+// 48.1 / 38.6 us; 14 steps to two 11.8 / 11.4; 26 features of 64 columns, batch 2048, 16 steps a wave, the same).
+__host__ __device__ inline int f32_share_begin(int steps, int part, int log2_ks, bool batches) {
+  if (!batches) return f32_first_step(steps, part, log2_ks);
   const int first = f32_first_step((steps + kF32Unroll - 1) / kF32Unroll, part, log2_ks) * kF32Unroll;
   return first < steps ? first : steps;
 }
@@ -188,7 +192,8 @@ __global__ __launch_bounds__(kF32Waves * 64) void tm_gemm_f32(const TmF32Launch 
   const int m = min(m0 + r, M - 1), n = min(n0 + r, N - 1);   // rows past the edge: the last row, not stored
   // this wave's share of the steps, cut into the two segments
   const int S0 = (G.K0 + 7) / 8, S = S0 + (G.K1 + 7) / 8;
-  const int lo = live ? f32_share_begin(S, part, G.log2_ks) : 0, hi = live ? f32_share_begin(S, part + 1, G.log2_ks) : 0;
+  const int lo = live ? f32_share_begin(S, part, G.log2_ks, TAG == 0) : 0;
+  const int hi = live ? f32_share_begin(S, part + 1, G.log2_ks, TAG == 0) : 0;
   floatx16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;

@@ -24,7 +24,7 @@ def lib(tmp_path_factory):
                 'static DmtPerDevice lds;\n'
                 'extern "C" int allow_lds(int dev, int fail) { g_dev = dev; g_fail = fail; g_sets = 0; dmt_allow_lds(lds, &lds, 1); return g_sets; }\n'
                 'extern "C" int first_step(int steps, int part, int log2_ks) { return f32_first_step(steps, part, log2_ks); }\n'
-                'extern "C" int share_begin(int steps, int part, int log2_ks) { return f32_share_begin(steps, part, log2_ks); }\n'
+                'extern "C" int share_begin(int steps, int part, int log2_ks, int batches) { return f32_share_begin(steps, part, log2_ks, batches); }\n'
                 'extern "C" int slice_end(int K1, int kofs, int klen) { return tm_slice_end(K1, kofs, klen); }\n'
                 '// blocks of a launch of n like groups; *tiles its tiles\n'
                 'extern "C" long blocks_of(int n, int M, int N, int K0, int K1, int reps, long* tiles) {\n'
@@ -57,9 +57,17 @@ def test_waves_share_all_steps_of_a_float32_tile(lib, steps, log2_ks):
 @pytest.mark.parametrize("steps", [0, 1, 3, 4, 5, 48, 63, 2 ** 27 + 3, 2 ** 28 - 15])
 @pytest.mark.parametrize("log2_ks", [0, 2, 4])
 def test_waves_shares_are_whole_batches(lib, steps, log2_ks):
-    begin = [lib.share_begin(steps, q, log2_ks) for q in range((1 << log2_ks) + 1)]
+    begin = [lib.share_begin(steps, q, log2_ks, 1) for q in range((1 << log2_ks) + 1)]
     assert begin[0] == 0 and begin[-1] == steps and begin == sorted(begin)
     assert all(b % 4 == 0 or b == steps for b in begin)
+
+
+@pytest.mark.parametrize("steps", [0, 1, 14, 81, 2 ** 28 - 15])
+@pytest.mark.parametrize("log2_ks", [0, 1, 4])
+def test_waves_shares_of_a_backward_are_as_even_as_steps_allow(lib, steps, log2_ks):
+    begin = [lib.share_begin(steps, q, log2_ks, 0) for q in range((1 << log2_ks) + 1)]
+    shares = [b - a for a, b in zip(begin, begin[1:])]
+    assert begin[0] == 0 and begin[-1] == steps and max(shares) - min(shares) <= 1
 
 
 @pytest.mark.parametrize("K", [1, 64, 1000, 8192, 2 ** 30 + 5, 2 ** 31 - 129, 2 ** 31 - 1])
