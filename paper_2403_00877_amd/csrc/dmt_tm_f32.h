@@ -17,6 +17,7 @@
 // before it, and a weight gradient's k left to one wave: 24 and 186 us).
 #pragma once
 #include <algorithm>
+#include <cstdint>
 #include <vector>
 
 #include "dmt_tm_gemm.h"
@@ -285,25 +286,64 @@ inline TmF32Group f32_group(const TmGroup& g) {
   return f;
 }
 
-// All groups in as few launches as they take (no group of the list may read what another writes).
-inline void launch_f32(const dmt_plan* p, std::vector<TmF32Group>& groups, hipStream_t s, int kid) {
-  auto tiles_of = [](const TmF32Group& g) { return (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32); };
-  auto steps_of = [](const TmF32Group& g) { return (int64_t)((g.K0 + 7) / 8 + (g.K1 + 7) / 8); };
-  // Waves per tile: doubled while groups of about as long a k together have fewer than four waves per SIMD (4096) and
-  // a wave keeps a whole batch of steps.  (Counted group by group, four data gradients of 8 steps took 6656 waves of 4,
-  // which beside the weight gradients' 1664 were just over two rounds of blocks instead of 1.2: 29.6 / 26.3 us.)  Groups
-  // whose waves work longest go first.
-  for (TmF32Group& g : groups) {
-    int64_t tiles = 0;
-    for (const TmF32Group& o : groups)
-      if (steps_of(o) <= 2 * steps_of(g) && steps_of(g) <= 2 * steps_of(o)) tiles += tiles_of(o);
-    g.log2_ks = 0;
-    while (g.log2_ks < 4 && (tiles << (g.log2_ks + 1)) <= 4096 && steps_of(g) >> (g.log2_ks + 1) >= kF32Unroll)
-      ++g.log2_ks;
+inline int64_t f32_tiles(const TmF32Group& g) { return (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32); }
+inline int64_t f32_steps(const TmF32Group& g) { return (int64_t)((g.K0 + 7) / 8 + (g.K1 + 7) / 8); }
+
+// Waves (2^log2_ks) for each of a launch's like tiles of `steps`, `before` waves of longer ones ahead of them; a wave
+// keeps a batch of steps.  4096 waves are resident together, four to a SIMD.
+// Forward: the least of  rounds of 4096 waves x (steps a wave + the start and end of a tile, about four steps, three of
+// a cross layer, whose epilogue the waves share too).  A round and a half is as long as two: us, doubled up to 4096 waves /
+// this: 20 cross towers of 64 columns, batch 6000 (6016 waves of 8 steps / 12032 of 4) 180 / 141; 2 dot towers of 13
+// features of 16 columns (6016 of 4 and 8 / 3008 of 9) 26.8 / 24.8; per-feature layers on 4 towers 67 / 53.
+// Backward: doubled up to 4096 waves, or 8192 while a wave keeps 32 steps: 2560 columns to 512 outputs, batch 512
+// (2560 waves of 64 steps / 5120 of 32) 75 / 72 us; 4 data gradients of 8 steps (3328 tiles) beside weight gradients
+// 26.3 us, as 6656 waves of 4 steps 29.6.
+constexpr int64_t kF32Resident = 4096;
+inline int f32_log2_ks(int64_t steps, int64_t tiles, int64_t before, bool forward, bool cross) {
+  int best = 0;
+  int64_t least = INT64_MAX;
+  for (int l = 0; l <= 4 && (l == 0 || steps >> l >= kF32Unroll); ++l) {
+    const int64_t waves = tiles << l;
+    if (forward) {
+      const int64_t cost = (before + waves + kF32Resident - 1) / kF32Resident * (((steps - 1) >> l) + 1 + (cross ? 3 : 4));
+      if (cost < least) least = cost, best = l;
+    } else if (waves <= kF32Resident || (waves <= 2 * kF32Resident && steps >> l >= 32)) {
+      best = l;
+    }
   }
-  std::stable_sort(groups.begin(), groups.end(), [&](const TmF32Group& a, const TmF32Group& b) {
-    return steps_of(a) >> a.log2_ks > steps_of(b) >> b.log2_ks;
-  });
+  return best;
+}
+
+// The order of the groups, kF32Groups to a launch, and how many waves share a tile's k.  Waves are counted within a launch:
+// counted group by group, the 26.3 us above were 29.6; over all of a stage's groups, 20 towers, which take two
+// launches, got half the waves (192 columns to 64 outputs, batch 2048: 64 us, now 34; per-feature layers of 8 features on
+// 8 towers, backward, 257 / 237).
+inline void f32_arrange(std::vector<TmF32Group>& groups, bool forward) {
+  auto longest_wave_first = [](const TmF32Group& a, const TmF32Group& b) { return f32_steps(a) >> a.log2_ks > f32_steps(b) >> b.log2_ks; };
+  // which groups share a launch: those that would run about as long, each by itself
+  for (TmF32Group& g : groups) g.log2_ks = f32_log2_ks(f32_steps(g), f32_tiles(g), 0, false, false);
+  std::stable_sort(groups.begin(), groups.end(), longest_wave_first);
+  for (size_t first = 0; first < groups.size(); first += kF32Groups) {
+    const auto begin = groups.begin() + first, end = groups.begin() + std::min(groups.size(), first + kF32Groups);
+    std::stable_sort(begin, end, [](const TmF32Group& a, const TmF32Group& b) { return f32_steps(a) > f32_steps(b); });
+    int64_t before = 0;
+    for (auto g = begin; g != end;) {              // groups of about as long a k, down to half of the longest
+      const int64_t steps = f32_steps(*g);
+      int64_t tiles = 0;
+      auto past = g;
+      for (; past != end && 2 * f32_steps(*past) >= steps; ++past) tiles += f32_tiles(*past);
+      const int l = f32_log2_ks(steps, tiles, before, forward, g->epi == EPI_CROSS);
+      for (; g != past; ++g) g->log2_ks = l;
+      before += tiles << l;
+    }
+    std::stable_sort(begin, end, longest_wave_first);
+  }
+}
+
+// All groups in as few launches as they take (no group of the list may read what another writes).  Groups whose waves
+// work longest go first.
+inline void launch_f32(const dmt_plan* p, std::vector<TmF32Group>& groups, hipStream_t s, int kid) {
+  f32_arrange(groups, DMT_TM_TAG == 0);
   for (size_t first = 0; first < groups.size(); first += kF32Groups) {
     TmF32Launch L;
     L.ngroups = (int32_t)std::min<size_t>(kF32Groups, groups.size() - first);
@@ -312,7 +352,7 @@ inline void launch_f32(const dmt_plan* p, std::vector<TmF32Group>& groups, hipSt
       const TmF32Group& g = L.g[i] = groups[first + i];
       L.block_start[i] = blocks;
       const int per_block = kF32Waves >> g.log2_ks;
-      blocks += (int32_t)((tiles_of(g) + per_block - 1) / per_block);
+      blocks += (int32_t)((f32_tiles(g) + per_block - 1) / per_block);
     }
     L.block_start[L.ngroups] = blocks;
     if (blocks == 0) continue;

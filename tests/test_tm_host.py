@@ -25,6 +25,13 @@ def lib(tmp_path_factory):
                 'extern "C" int allow_lds(int dev, int fail) { g_dev = dev; g_fail = fail; g_sets = 0; dmt_allow_lds(lds, &lds, 1); return g_sets; }\n'
                 'extern "C" int first_step(int steps, int part, int log2_ks) { return f32_first_step(steps, part, log2_ks); }\n'
                 'extern "C" int share_begin(int steps, int part, int log2_ks, int batches) { return f32_share_begin(steps, part, log2_ks, batches); }\n'
+                '// n[i] groups of M[i] x N[i], K[i]; each arranged group: which kind it is and the log2 of its waves a tile\n'
+                'extern "C" int arrange(int kinds, const int* n, const int* M, const int* N, const int* K, int epi, int forward, int* kind, int* log2_ks) {\n'
+                '  std::vector<TmF32Group> v;\n'
+                '  for (int i = 0; i < kinds; ++i) for (int j = 0; j < n[i]; ++j) { TmF32Group g{}; g.M = M[i]; g.N = N[i]; g.K1 = K[i]; g.epi = epi; g.lda1 = i; v.push_back(g); }\n'
+                '  f32_arrange(v, forward != 0);\n'
+                '  for (size_t i = 0; i < v.size(); ++i) { kind[i] = v[i].lda1; log2_ks[i] = v[i].log2_ks; }\n'
+                '  return (int)v.size(); }\n'
                 'extern "C" int slice_end(int K1, int kofs, int klen) { return tm_slice_end(K1, kofs, klen); }\n'
                 '// blocks of a launch of n like groups; *tiles its tiles\n'
                 'extern "C" long blocks_of(int n, int M, int N, int K0, int K1, int reps, long* tiles) {\n'
@@ -68,6 +75,44 @@ def test_waves_shares_of_a_backward_are_as_even_as_steps_allow(lib, steps, log2_
     begin = [lib.share_begin(steps, q, log2_ks, 0) for q in range((1 << log2_ks) + 1)]
     shares = [b - a for a, b in zip(begin, begin[1:])]
     assert begin[0] == 0 and begin[-1] == steps and max(shares) - min(shares) <= 1
+
+
+def arrange(lib, kinds, epi=0, forward=True):
+    """kinds: (groups, M, N, K); (kind, log2 of the waves a tile) of every group in order."""
+    cols = [(ctypes.c_int * len(kinds))(*c) for c in zip(*kinds)]
+    total = sum(k[0] for k in kinds)
+    kind, log2_ks = (ctypes.c_int * total)(), (ctypes.c_int * total)()
+    assert lib.arrange(len(kinds), *cols, epi, int(forward), kind, log2_ks) == total
+    return list(zip(kind, log2_ks))
+
+
+@pytest.mark.parametrize("kinds,epi,forward,want", [
+    # the towers beyond a launch of 16 do not take waves from it: 2048 tiles of 24 steps there, 512 in the next
+    ([(20, 2048, 64, 192)], 0, True, [1] * 16 + [2] * 4),
+    ([(26, 2048, 64, 64)], 3, False, [1] * 26),
+    # 16 cross layers of 376 tiles are a round and a half: three rounds of half as long; the other four fit one
+    ([(20, 6000, 64, 64)], 2, True, [1] * 20),
+    # short of a second round that would be half empty
+    ([(2, 6000, 64, 286)], 0, True, [2] * 2),
+    # data gradients of 8 steps beside weight gradients of 256
+    ([(4, 2048, 416, 64), (4, 64, 416, 2048)], 3, False, [4] * 4 + [0] * 4),
+    # a wave may keep 32 steps in a second round
+    ([(1, 512, 2560, 512), (1, 512, 2560, 512)], 3, False, [1] * 2),
+    ([(1, 32, 32, 8), (1, 33, 1, 24)], 0, True, [0, 0]),
+])
+def test_waves_of_float32_tiles_are_counted_by_the_launch(lib, kinds, epi, forward, want):
+    assert [l for _, l in arrange(lib, kinds, epi, forward)] == want
+
+
+@pytest.mark.parametrize("forward", [True, False])
+def test_float32_launches_start_with_the_longest_waves(lib, forward):
+    kinds = [(3, 900, 50, 1391), (14, 107, 64, 96), (9, 640, 32, 107), (4, 32, 64, 40000)]
+    got = arrange(lib, kinds, 3, forward)
+    assert sorted(k for k, _ in got) == sorted(i for i, k in enumerate(kinds) for _ in range(k[0]))
+    for first in range(0, len(got), 16):
+        waves = [(kinds[k][3] + 7) // 8 >> l for k, l in got[first:first + 16]]
+        assert waves == sorted(waves, reverse=True)
+        assert all(l == 0 or (kinds[k][3] + 7) // 8 >> l >= 2 for k, l in got[first:first + 16])
 
 
 @pytest.mark.parametrize("K", [1, 64, 1000, 8192, 2 ** 30 + 5, 2 ** 31 - 129, 2 ** 31 - 1])
