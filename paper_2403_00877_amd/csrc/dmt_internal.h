@@ -90,7 +90,8 @@ struct DmtProfile {
 // both variants of a choice, sweeps need no rebuild); 0 / -1 = the library's own choice.
 struct DmtSwitches {
   int tm_big = 1;        // DMT_TM_BIG=0 / 2 / 3: 128 x 128 / 256 x 256 / (forward) 32 x 32 contraction tiles whatever the size
-  int tm_fuse = 1;       // DMT_TM_FUSE=0: dot terms by their own kernel, not inside the projection
+  int tm_fuse = 1;       // DMT_TM_FUSE=0: dot terms by their own kernel, not inside the projection, and their gradient by
+                         // contractions of its own; 2: the dot towers' data gradient in one kernel whatever the size
   int tmb_ksplit = 0;    // DMT_TMB_KSPLIT=n: slices of every weight gradient
   int bwd_kernel = 0;    // DMT_BWD_KERNEL=1 / 2: the wave-per-tile / lane-group segment reduce
   int keys_lg = -1;      // DMT_KEYS_LG=l: 2^l bags per key-build block

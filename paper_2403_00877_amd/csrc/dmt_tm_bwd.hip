@@ -192,18 +192,12 @@ __global__ __launch_bounds__(kBlock) void tmb_dot_bwd8(const TmbLaunch L) {
 // (x comes in the accumulators' layout, 8 bytes a lane).  Four waves share the weights of their columns, which go
 // through LDS in steps of 32 outputs, fragment by fragment as the repacked weights lie; behind them come the dot
 // terms' rows, whose products, a few floats a sample, take the way through LDS to the sample's other lanes.
-constexpr int kDotFeat = 8;                        // features, at most
-constexpr int kDotTerms = kDotFeat * (kDotFeat - 1) / 2, kDotTermTiles = (kDotTerms + 15) / 16;
-constexpr int kDotCols = 32;                       // columns of a feature that a block takes
-constexpr int kDotTiles = kDotFeat * (kDotCols / 16) + kDotTermTiles;
 constexpr int kDotZPitch = kDotTermTiles * 16 + 4; // floats: 16 samples' pieces of 16 bytes on different banks
-constexpr int64_t kDotFewBlocks = 256;             // of 128 samples: up to here blocks of 64
+// Of 128 samples: up to here blocks of 64 (dot_rows).  8 features of 64 columns to 256 outputs on 4 towers, backward, us, 128
+// / 64: 192 blocks of 128 44.4 / 40.6, 256 46.0 / 42.7, 384 59.1 / 62.4; of 128 columns, 512 blocks 65.0 / 67.7.
+constexpr int64_t kDotFewBlocks = 256;
 // Term of the pair {i, j}, i < j, whatever the number of features.
 __host__ __device__ constexpr int dot_slot(int i, int j) { return i * (2 * kDotFeat - 1 - i) / 2 + j - i - 1; }
-// (32-bit byte offsets into a column block's weights)
-inline bool dot_dgrad_ok(const dmt_plan* p, int nf, int n, int64_t O) {
-  return p->sw.tm_fuse && nf >= 2 && nf <= kDotFeat && n % kDotCols == 0 && (O + 31) / 32 * kDotTiles * 1024 < (1LL << 31);
-}
 // Fragments (1 KB) of a tower's repacked weights.
 inline int64_t dot_wt_frags(int nf, int n, int64_t O) {
   return (int64_t)(n / kDotCols) * ((O + 31) / 32) * (nf * (kDotCols / 16) + kDotTermTiles);
@@ -241,7 +235,6 @@ __device__ __forceinline__ void pack_dot_weights(const TmbItem& G, int64_t e) {
 // ahead of the last step.
 // S sets of 16 samples a wave: two, or one where that makes more of the blocks that a launch is short of (2 towers of 8
 // features, batch 822: 16.7 -> 11.3 us; 4 of 6 and 7, batch 2003: 18.0 -> 15.1).
-constexpr int dot_rows(int S) { return 4 * 16 * S; }
 constexpr int dot_stage(int S) { return kDotTiles * 1024 + 4 * S * 1024; }      // bytes: weights, then dz (a fragment a set)
 constexpr int dot_lds(int S) { return 3 * dot_stage(S); }
 static_assert(dot_lds(1) >= dot_rows(1) * kDotZPitch * 4 && dot_lds(2) >= dot_rows(2) * kDotZPitch * 4 && 2 * dot_lds(2) <= 160 * 1024,
@@ -550,7 +543,7 @@ struct TowerBwdWs {
   int64_t Op = 0;
   size_t dz = 0, dbp = 0;      // dy rounded, [B][Op]; parts of its column sums
   size_t p = 0, wp = 0, dZ = 0;                                 // dot towers
-  bool fused = false;          // dot towers: tmb_dot_dgrad, its weights in wp; no dZ
+  bool fused = false;          // dot towers: tmb_dot_dgrad, its weights in wp; dZ is not used
   size_t xl[DMT_MAX_CROSS_LAYERS] = {}, u[DMT_MAX_CROSS_LAYERS] = {};   // cross towers
   size_t dxn = 0, du[2] = {0, 0}, dbc = 0;   // g_l, du of alternating layers, parts of its column sums
   // low-rank cross towers: t_l = V_l x_l per layer; dt (float32 towers), dt rounded
@@ -581,6 +574,7 @@ dmt_status plan_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, in
     if (q.kind == DMT_TM_CROSS_LOWRANK_LINEAR) tiles_cross.add(wt, q.feat_out);
     if (q.kind == DMT_TM_DLRM) tiles_feat.add(q.feat_out, p->tower_uniform_dim[t]);
   }
+  const DotDgrad dots = dot_dgrad_of(p, tp, B);
   for (int32_t t = 0; t < p->T; ++t) {
     const dmt_tm_params& q = tp[t];
     const int64_t wt = p->tower_width[t];
@@ -601,17 +595,16 @@ dmt_status plan_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, in
         if (p->tower_uniform_dim[t] == 0) return DMT_ENOTSUP;
         w.np = nf * (nf - 1) / 2;
         w.np_pad = (w.np + 7) / 8 * 8;
-        w.fused = eb == 2 && dot_dgrad_ok(p, nf, p->tower_uniform_dim[t], q.out_dim);
+        const bool fusable = eb == 2 && dot_dgrad_ok(p, nf, p->tower_uniform_dim[t], q.out_dim);
+        w.fused = fusable && dot_dgrad_pays(p, nf, q.out_dim, dots);
         w.packed = !w.fused && !dot_weights_as_is(q.w_proj, w.np);
         w.skip = w.packed ? w.np_pad : w.np;
         w.kin = w.np_pad + (int)wt;
         w.p = take((size_t)B * w.np_pad * eb);
-        if (w.fused) {
-          w.wp = take((size_t)dot_wt_frags(nf, p->tower_uniform_dim[t], q.out_dim) * 1024);
-          break;
-        }
-        w.wp = take((size_t)q.out_dim * w.kin * eb);
-        w.dZ = take((size_t)B * w.kin * 4);
+        // (room for either way here and in dZ: a workspace sized for a larger batch serves a smaller one, which may go
+        // the other)
+        w.wp = take(std::max((size_t)q.out_dim * w.kin * eb,
+                             fusable ? (size_t)dot_wt_frags(nf, p->tower_uniform_dim[t], q.out_dim) * 1024 : 0));
         break;
       }
       case DMT_TM_CROSS_LINEAR:
@@ -671,6 +664,10 @@ dmt_status plan_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, in
       part = std::max(part, (size_t)w.ksplit_c * wt * q.feat_out * 4);
     if (part) w.part = take(part);
   }
+  // (behind the rest, since tmb_dot_dgrad does without: between the other pieces it made 6 features of 128 columns, batch
+  // 16384, 163 -> 171 us)
+  for (int32_t t = 0; t < p->T; ++t)
+    if (tp[t].kind == DMT_TM_DOT_LINEAR) (*ws)[t].dZ = take((size_t)B * (*ws)[t].kin * 4);
   *bytes = off;
   return DMT_OK;
 }

@@ -1158,6 +1158,41 @@ __global__ __launch_bounds__(kBlock) void tm_pack_w(const TmAuxLaunch L) {
 // Otherwise (an odd number of dot terms) they are repacked by tm_pack_w first.
 inline bool dot_weights_as_is(const void* w_proj, int np) { return np % 2 == 0 && ((uintptr_t)w_proj & 3) == 0; }
 
+// ---- The dot towers' data gradient in one kernel (tmb_dot_dgrad): its shape, and the towers that take it.
+constexpr int kDotFeat = 8;                        // features, at most
+constexpr int kDotTerms = kDotFeat * (kDotFeat - 1) / 2, kDotTermTiles = (kDotTerms + 15) / 16;
+constexpr int kDotCols = 32;                       // columns of a feature that a block takes
+constexpr int kDotTiles = kDotFeat * (kDotCols / 16) + kDotTermTiles;
+constexpr int dot_rows(int S) { return 4 * 16 * S; }
+// (32-bit byte offsets into a column block's weights)
+inline bool dot_dgrad_ok(const dmt_plan* p, int nf, int n, int64_t O) {
+  return p->sw.tm_fuse && nf >= 2 && nf <= kDotFeat && n % kDotCols == 0 && (O + 31) / 32 * kDotTiles * 1024 < (1LL << 31);
+}
+// The towers that it could serve, and its blocks of 64 samples for all of them.
+struct DotDgrad {
+  int towers = 0;
+  int64_t blocks = 0;
+};
+inline DotDgrad dot_dgrad_of(const dmt_plan* p, const dmt_tm_params* tp, int64_t B) {
+  DotDgrad d;
+  for (int32_t t = 0; t < p->T; ++t)
+    if (tp[t].kind == DMT_TM_DOT_LINEAR && dot_dgrad_ok(p, p->tower_ntab[t], p->tower_uniform_dim[t], tp[t].out_dim)) {
+      ++d.towers;
+      d.blocks += (B + dot_rows(1) - 1) / dot_rows(1) * (p->tower_uniform_dim[t] / kDotCols);
+    }
+  return d;
+}
+// Whether it is the faster one for nf features to O outputs.  A step of 32 outputs takes a lone block longer than the
+// contractions' tiles take, which costs more the longer it goes on and the fewer blocks there are.  Backward, us,
+// separate kernels / this one: 4 towers of 8 features, 32 columns, 16 blocks, 64 outputs 24.0 / 21.8, 256 26.3 / 26.9, 2048
+// 54.4 / 75.6; 64 blocks, 256 33.7 / 32.1, 512 38.4 / 41.4; 128 blocks, 512 45.5 / 43.7, 1024 62.7 / 66.0; 64 columns, 256
+// blocks, 1024 73.9 / 73.0, 2048 107.9 / 118.4; 384 blocks, 2048 167 / 147 (128 columns 129 / 134); one tower, 4 blocks, 5
+// features, 256 22.8 / 21.8, 700 27.9 / 31.3.  More towers than one launch of contractions holds with their dot terms
+// take two: 12 of 2 and 7 features, 24 blocks, 700 50.1 / 41.0 and 59.2 / 54.3.
+inline bool dot_dgrad_pays(const dmt_plan* p, int nf, int64_t O, const DotDgrad& all) {
+  return p->sw.tm_fuse == 2 || 2 * all.towers > kMaxGroups || O <= std::max<int64_t>(6 * all.blocks, 1280 / nf);
+}
+
 // What a training forward keeps for the backward: for every cross layer l of a cross tower
 // (full-rank or low-rank), x_{l+1} and u_l = W_l x_l + b_l, each [B][W_t] in the compute type;
 // for a dot-product tower its dot terms, [B][np_pad] (np_pad = the F (F - 1) / 2 terms rounded

@@ -290,15 +290,31 @@ def test_dlrm_module_odd_widths():
     ("bf16", [8, 4], [128, 128], [64, 32], 4096), ("bf16", [8, 4], [128, 128], [64, 32], 4097),  # blocks of 64 samples, of 128
     ("f16", [8, 2], [128, 32], [96, 24], 6400),
 ])
-def test_dot_towers_data_gradient_in_one_kernel(dt, nfs, dims, outs, batch):
+def test_dot_towers_data_gradient_in_one_kernel(dt, nfs, dims, outs, batch, monkeypatch):
     """2 to 8 features of one to five blocks of 32 columns, one to 17 steps of 32 outputs with and without a remainder,
-    batches around one block of 64 and of 128 samples and around the line between the two."""
+    batches around one block of 64 and of 128 samples and around the line between the two; at any size."""
+    monkeypatch.setenv("DMT_TM_FUSE", "2")
     w = wl.scaled(wl.mid(), max_rows=300, batch=batch, num_tables=sum(nfs))
     w.table_to_tower = [0] * nfs[0] + [1] * nfs[1]
     w.dims = [dims[0]] * nfs[0] + [dims[1]] * nfs[1]
     w.tm_dtype = w.pooled_dtype = dt
     w.tm_out = outs
     check_tm_bwd(w, keep=True, guard=True)
+
+
+@pytest.mark.parametrize("nfs,dim,outs,batch", [
+    ([8, 2], 32, [161, 640], 130),       # 6 blocks of 64 samples: 160 and 640 outputs at most
+    ([5, 3], 64, [256, 427], 640), ([6, 4], 32, [384, 385], 1985),     # 40 and 64 blocks: 256 and 426, 384
+])
+def test_dot_towers_data_gradient_on_either_side_of_its_line(nfs, dim, outs, batch):
+    """Of a tower one output past what one kernel takes in so small a launch, and of one that it takes just so."""
+    w = wl.scaled(wl.mid(), max_rows=300, batch=batch, num_tables=sum(nfs))
+    w.table_to_tower = [0] * nfs[0] + [1] * nfs[1]
+    w.dims = [dim] * sum(nfs)
+    w.tm_dtype = w.pooled_dtype = "bf16"
+    w.tm_out = outs
+    check_tm_bwd(w, keep=True, guard=True)
+    check_tm_bwd(w)
 
 
 @pytest.mark.parametrize("dt", ["bf16", "f16"])

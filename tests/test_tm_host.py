@@ -4,7 +4,9 @@ import os
 import subprocess
 
 import pytest
+import torch
 
+import paper_2403_00877_amd as dmt
 from paper_2403_00877_amd import build as hip_build
 
 
@@ -32,6 +34,12 @@ def lib(tmp_path_factory):
                 '  f32_arrange(v, forward != 0);\n'
                 '  for (size_t i = 0; i < v.size(); ++i) { kind[i] = v[i].lda1; log2_ks[i] = v[i].log2_ks; }\n'
                 '  return (int)v.size(); }\n'
+                '// T like dot towers of nf features of n columns to O outputs\n'
+                'extern "C" int one_kernel(int T, int nf, int n, int O, long B, int fuse) {\n'
+                '  dmt_plan p; p.sw.tm_fuse = fuse; p.T = T; p.tower_ntab.assign(T, nf); p.tower_uniform_dim.assign(T, n);\n'
+                '  dmt_tm_params q{}; q.kind = DMT_TM_DOT_LINEAR; q.out_dim = O;\n'
+                '  std::vector<dmt_tm_params> tp(T, q);\n'
+                '  return dot_dgrad_ok(&p, nf, n, O) && dot_dgrad_pays(&p, nf, O, dot_dgrad_of(&p, tp.data(), B)); }\n'
                 'extern "C" int slice_end(int K1, int kofs, int klen) { return tm_slice_end(K1, kofs, klen); }\n'
                 '// blocks of a launch of n like groups; *tiles its tiles\n'
                 'extern "C" long blocks_of(int n, int M, int N, int K0, int K1, int reps, long* tiles) {\n'
@@ -113,6 +121,39 @@ def test_float32_launches_start_with_the_longest_waves(lib, forward):
         waves = [(kinds[k][3] + 7) // 8 >> l for k, l in got[first:first + 16]]
         assert waves == sorted(waves, reverse=True)
         assert all(l == 0 or (kinds[k][3] + 7) // 8 >> l >= 2 for k, l in got[first:first + 16])
+
+
+@pytest.mark.parametrize("T,nf,n,O,B,want", [
+    (8, 8, 128, 256, 8192, 1), (4, 7, 128, 256, 2003, 1), (4, 4, 64, 256, 200, 1), (1, 8, 32, 128, 1, 1),
+    # few blocks and many outputs: the contractions' more tiles are faster
+    (4, 8, 32, 512, 300, 0), (4, 8, 128, 2048, 300, 0), (4, 6, 32, 2048, 2000, 0), (1, 2, 32, 640, 1, 1), (1, 2, 32, 641, 1, 0),
+    (1, 8, 32, 384, 4096, 1), (1, 8, 32, 385, 4096, 0), (4, 8, 64, 1024, 4096, 1), (8, 8, 128, 2048, 512, 0),
+    (9, 8, 128, 2048, 512, 1),           # beside their dot terms, more than one launch of contractions
+    (4, 9, 32, 64, 4096, 0), (4, 8, 40, 64, 4096, 0), (4, 1, 32, 64, 4096, 0),
+])
+def test_when_a_dot_towers_data_gradient_is_one_kernel(lib, T, nf, n, O, B, want):
+    B = ctypes.c_long(B)
+    assert lib.one_kernel(T, nf, n, O, B, 1) == want
+    assert lib.one_kernel(T, nf, n, O, B, 0) == 0
+    assert lib.one_kernel(T, nf, n, O, B, 2) == (2 <= nf <= 8 and n % 32 == 0)
+
+
+@pytest.mark.parametrize("T,nf,n,O", [(4, 8, 32, 512), (1, 2, 64, 641), (2, 8, 128, 2048), (4, 3, 64, 1000)])
+def test_a_backward_workspace_for_a_larger_batch_serves_a_smaller_one(lib, T, nf, n, O, monkeypatch):
+    """Across the line between the two ways of a dot tower's data gradient, whichever way the smaller batch goes."""
+    batches = [1, 64, 65, 300, 500, 640, 641, 1024, 2000, 2048, 4096, 8192]
+    assert len({lib.one_kernel(T, nf, n, O, ctypes.c_long(B), 1) for B in batches}) == 2
+
+    def sizes(fuse):
+        monkeypatch.setenv("DMT_TM_FUSE", fuse)
+        plan = dmt.dmt_plan_create([10] * (T * nf), [n] * (T * nf), "f32", T, [t for t in range(T) for _ in range(nf)], 8192, 1)
+        w = torch.zeros(4)
+        params = dmt.make_tm_params([dict(kind="dot_linear", out_dim=O, w_proj=w, b_proj=w)] * T)
+        return [dmt.dmt_tm_bwd_workspace_bytes(plan, params, B) for B in batches]
+
+    either = [sizes(fuse) for fuse in "012"]
+    for small in either:
+        assert all(a <= b for a, b in zip(small, sizes("1")[1:])), (small, sizes("1"))
 
 
 @pytest.mark.parametrize("K", [1, 64, 1000, 8192, 2 ** 30 + 5, 2 ** 31 - 129, 2 ** 31 - 1])
