@@ -547,6 +547,7 @@ struct TowerBwdWs {
   size_t dz = 0, dbp = 0;      // dy rounded, [B][Op]; parts of its column sums
   size_t p = 0, wp = 0, dZ = 0;                                 // dot towers
   bool fused = false;          // dot towers: tmb_dot_dgrad, its weights in wp; dZ is not used
+  bool dZ_behind = false;      // dot towers that tmb_dot_dgrad could serve: dZ lies behind all other pieces
   size_t xl[DMT_MAX_CROSS_LAYERS] = {}, u[DMT_MAX_CROSS_LAYERS] = {};   // cross towers
   size_t dxn = 0, du[2] = {0, 0}, dbc = 0;   // g_l, du of alternating layers, parts of its column sums
   // low-rank cross towers: t_l = V_l x_l per layer; dt (float32 towers), dt rounded
@@ -604,10 +605,12 @@ dmt_status plan_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, in
         w.skip = w.packed ? w.np_pad : w.np;
         w.kin = w.np_pad + (int)wt;
         w.p = take((size_t)B * w.np_pad * eb);
-        // (room for either way here and in dZ: a workspace sized for a larger batch serves a smaller one, which may go
+        // (room for either way, here and in dZ: a workspace sized for a larger batch serves a smaller one, which may go
         // the other)
         w.wp = take(std::max((size_t)q.out_dim * w.kin * eb,
                              fusable ? (size_t)dot_wt_frags(nf, p->tower_uniform_dim[t], q.out_dim) * 1024 : 0));
+        if (!fusable) w.dZ = take((size_t)B * w.kin * 4);
+        w.dZ_behind = fusable;
         break;
       }
       case DMT_TM_CROSS_LINEAR:
@@ -667,10 +670,10 @@ dmt_status plan_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, in
       part = std::max(part, (size_t)w.ksplit_c * wt * q.feat_out * 4);
     if (part) w.part = take(part);
   }
-  // (behind the rest, since tmb_dot_dgrad does without: between the other pieces it made 6 features of 128 columns, batch
-  // 16384, 163 -> 171 us)
-  for (int32_t t = 0; t < p->T; ++t)
-    if (tp[t].kind == DMT_TM_DOT_LINEAR) (*ws)[t].dZ = take((size_t)B * (*ws)[t].kin * 4);
+  // (tmb_dot_dgrad does without; between the pieces it uses, that room made 6 features of 128 columns, batch 16384, 163 ->
+  // 171 us)
+  for (TowerBwdWs& w : *ws)
+    if (w.dZ_behind) w.dZ = take((size_t)B * w.kin * 4);
   *bytes = off;
   return DMT_OK;
 }
