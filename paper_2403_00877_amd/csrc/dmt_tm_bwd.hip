@@ -600,7 +600,7 @@ dmt_status plan_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, in
         w.np = nf * (nf - 1) / 2;
         w.np_pad = (w.np + 7) / 8 * 8;
         const bool fusable = eb == 2 && dot_dgrad_ok(p, nf, p->tower_uniform_dim[t], q.out_dim);
-        w.fused = fusable && dot_dgrad_pays(p, nf, q.out_dim, dots);
+        w.fused = fusable && dot_one_kernel(p, t, q.out_dim, dots);
         w.packed = !w.fused && !dot_weights_as_is(q.w_proj, w.np);
         w.skip = w.packed ? w.np_pad : w.np;
         w.kin = w.np_pad + (int)wt;

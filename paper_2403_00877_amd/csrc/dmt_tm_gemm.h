@@ -1168,18 +1168,26 @@ constexpr int dot_rows(int S) { return 4 * 16 * S; }
 inline bool dot_dgrad_ok(const dmt_plan* p, int nf, int n, int64_t O) {
   return p->sw.tm_fuse && nf >= 2 && nf <= kDotFeat && n % kDotCols == 0 && (O + 31) / 32 * kDotTiles * 1024 < (1LL << 31);
 }
-// The towers that it could serve, and its blocks of 64 samples for all of them.
+// The towers that it could serve, its blocks of 64 samples for all of them, their elements, and whether the call has
+// other towers whose data gradients are plain contractions, dot towers among them.
 struct DotDgrad {
   int towers = 0;
-  int64_t blocks = 0;
+  int64_t blocks = 0, elements = 0;
+  bool beside = false, beside_dots = false;
 };
 inline DotDgrad dot_dgrad_of(const dmt_plan* p, const dmt_tm_params* tp, int64_t B) {
   DotDgrad d;
-  for (int32_t t = 0; t < p->T; ++t)
-    if (tp[t].kind == DMT_TM_DOT_LINEAR && dot_dgrad_ok(p, p->tower_ntab[t], p->tower_uniform_dim[t], tp[t].out_dim)) {
+  for (int32_t t = 0; t < p->T; ++t) {
+    const bool dot = tp[t].kind == DMT_TM_DOT_LINEAR;
+    if (dot && dot_dgrad_ok(p, p->tower_ntab[t], p->tower_uniform_dim[t], tp[t].out_dim)) {
       ++d.towers;
       d.blocks += (B + dot_rows(1) - 1) / dot_rows(1) * (p->tower_uniform_dim[t] / kDotCols);
+      d.elements += B * p->tower_ntab[t] * p->tower_uniform_dim[t];
+    } else if (tp[t].kind != DMT_TM_CROSS_LINEAR && tp[t].kind != DMT_TM_CROSS_LOWRANK_LINEAR) {
+      d.beside = true;
+      d.beside_dots = d.beside_dots || dot;
     }
+  }
   return d;
 }
 // Whether it is the faster one for nf features to O outputs.  A step of 32 outputs takes a lone block longer than the
@@ -1189,8 +1197,19 @@ inline DotDgrad dot_dgrad_of(const dmt_plan* p, const dmt_tm_params* tp, int64_t
 // blocks, 1024 73.9 / 73.0, 2048 107.9 / 118.4; 384 blocks, 2048 167 / 147 (128 columns 129 / 134); one tower, 4 blocks, 5
 // features, 256 22.8 / 21.8, 700 27.9 / 31.3.  More towers than one launch of contractions holds with their dot terms
 // take two: 12 of 2 and 7 features, 24 blocks, 700 50.1 / 41.0 and 59.2 / 54.3.
+// Beside towers whose contractions are launched all the same (a cross tower's are a launch of their own) it is one launch
+// more, beside other dot towers, which keep tmb_dot_bwd8, a longer one, and has to save that many bytes: 8 features of 32, 64
+// and 128 columns beside a linear tower, 256 outputs, 2^20 elements 35.8 / 41.1, 37.3 / 41.9 and 37.4 / 43.5, 2^21 47.1 /
+// 46.2, 43.7 / 42.4 and 41.8 / 44.5, 2^22 66.1 / 58.5, 62.7 / 55.0 and 51.9 / 47.2; beside 10 features 2^21 57.9 / 59.7,
+// 53.0 / 57.6 and 48.2 / 55.4, 2^22 85.6 / 84.8, 75.8 / 79.0 and 67.6 / 71.2, 2^23 of 64 and 128 columns 141 / 114 and 119 / 100.
 inline bool dot_dgrad_pays(const dmt_plan* p, int nf, int64_t O, const DotDgrad& all) {
-  return p->sw.tm_fuse == 2 || 2 * all.towers > kMaxGroups || O <= std::max<int64_t>(6 * all.blocks, 1280 / nf);
+  if (p->sw.tm_fuse == 2 || 2 * all.towers > kMaxGroups) return true;
+  if (all.beside && all.elements < (all.beside_dots ? 4000000 : 1 << 21)) return false;
+  return O <= std::max<int64_t>(6 * all.blocks, 1280 / nf);
+}
+// Of a dot tower t in a 16-bit type.
+inline bool dot_one_kernel(const dmt_plan* p, int t, int64_t O, const DotDgrad& all) {
+  return dot_dgrad_ok(p, p->tower_ntab[t], p->tower_uniform_dim[t], O) && dot_dgrad_pays(p, p->tower_ntab[t], O, all);
 }
 
 // What a training forward keeps for the backward: for every cross layer l of a cross tower

@@ -34,12 +34,13 @@ def lib(tmp_path_factory):
                 '  f32_arrange(v, forward != 0);\n'
                 '  for (size_t i = 0; i < v.size(); ++i) { kind[i] = v[i].lda1; log2_ks[i] = v[i].log2_ks; }\n'
                 '  return (int)v.size(); }\n'
-                '// T like dot towers of nf features of n columns to O outputs\n'
-                'extern "C" int one_kernel(int T, int nf, int n, int O, long B, int fuse) {\n'
+                '// T like dot towers of nf features of n columns to O outputs, beside one of a kind and nf2 features (or -1)\n'
+                'extern "C" int one_kernel(int T, int nf, int n, int O, long B, int fuse, int kind, int nf2) {\n'
                 '  dmt_plan p; p.sw.tm_fuse = fuse; p.T = T; p.tower_ntab.assign(T, nf); p.tower_uniform_dim.assign(T, n);\n'
                 '  dmt_tm_params q{}; q.kind = DMT_TM_DOT_LINEAR; q.out_dim = O;\n'
                 '  std::vector<dmt_tm_params> tp(T, q);\n'
-                '  return dot_dgrad_ok(&p, nf, n, O) && dot_dgrad_pays(&p, nf, O, dot_dgrad_of(&p, tp.data(), B)); }\n'
+                '  if (kind >= 0) { q.kind = kind; tp.push_back(q); ++p.T; p.tower_ntab.push_back(nf2); p.tower_uniform_dim.push_back(n); }\n'
+                '  return dot_one_kernel(&p, 0, O, dot_dgrad_of(&p, tp.data(), B)); }\n'
                 'extern "C" int slice_end(int K1, int kofs, int klen) { return tm_slice_end(K1, kofs, klen); }\n'
                 '// blocks of a launch of n like groups; *tiles its tiles\n'
                 'extern "C" long blocks_of(int n, int M, int N, int K0, int K1, int reps, long* tiles) {\n'
@@ -123,6 +124,10 @@ def test_float32_launches_start_with_the_longest_waves(lib, forward):
         assert all(l == 0 or (kinds[k][3] + 7) // 8 >> l >= 2 for k, l in got[first:first + 16])
 
 
+def one_kernel(lib, T, nf, n, O, B, fuse=1, beside=(-1, 0)):
+    return lib.one_kernel(T, nf, n, O, ctypes.c_long(B), fuse, *beside)
+
+
 @pytest.mark.parametrize("T,nf,n,O,B,want", [
     (8, 8, 128, 256, 8192, 1), (4, 7, 128, 256, 2003, 1), (4, 4, 64, 256, 200, 1), (1, 8, 32, 128, 1, 1),
     # few blocks and many outputs: the contractions' more tiles are faster
@@ -132,17 +137,29 @@ def test_float32_launches_start_with_the_longest_waves(lib, forward):
     (4, 9, 32, 64, 4096, 0), (4, 8, 40, 64, 4096, 0), (4, 1, 32, 64, 4096, 0),
 ])
 def test_when_a_dot_towers_data_gradient_is_one_kernel(lib, T, nf, n, O, B, want):
-    B = ctypes.c_long(B)
-    assert lib.one_kernel(T, nf, n, O, B, 1) == want
-    assert lib.one_kernel(T, nf, n, O, B, 0) == 0
-    assert lib.one_kernel(T, nf, n, O, B, 2) == (2 <= nf <= 8 and n % 32 == 0)
+    assert one_kernel(lib, T, nf, n, O, B) == want
+    assert one_kernel(lib, T, nf, n, O, B, fuse=0) == 0
+    assert one_kernel(lib, T, nf, n, O, B, fuse=2) == (2 <= nf <= 8 and n % 32 == 0)
+
+
+@pytest.mark.parametrize("B,linear,dots", [(1000, 0, 0), (2047, 0, 0), (2048, 1, 0), (3906, 1, 0), (3907, 1, 1)])
+def test_a_dot_towers_data_gradient_beside_other_towers(lib, B, linear, dots):
+    """8 features of 128 columns: in a launch of its own where it saves more than that."""
+    assert one_kernel(lib, 1, 8, 128, 256, B) == 1
+    for kind in (dmt.binding.DMT_TM_LINEAR, dmt.binding.DMT_TM_LINEAR_RELU, dmt.binding.DMT_TM_DLRM):
+        assert one_kernel(lib, 1, 8, 128, 256, B, beside=(kind, 8)) == linear
+    assert one_kernel(lib, 1, 8, 128, 256, B, beside=(dmt.binding.DMT_TM_DOT_LINEAR, 9)) == dots
+    assert one_kernel(lib, 1, 8, 128, 256, B, beside=(dmt.binding.DMT_TM_DOT_LINEAR, 2)) == 1
+    assert one_kernel(lib, 1, 8, 128, 256, B, beside=(dmt.binding.DMT_TM_CROSS_LINEAR, 8)) == 1
+    assert one_kernel(lib, 1, 8, 128, 256, B, 2, (dmt.binding.DMT_TM_DOT_LINEAR, 9)) == 1
+    assert one_kernel(lib, 9, 8, 128, 256, B, 1, (dmt.binding.DMT_TM_DOT_LINEAR, 9)) == 1
 
 
 @pytest.mark.parametrize("T,nf,n,O", [(4, 8, 32, 512), (1, 2, 64, 641), (2, 8, 128, 2048), (4, 3, 64, 1000)])
 def test_a_backward_workspace_for_a_larger_batch_serves_a_smaller_one(lib, T, nf, n, O, monkeypatch):
     """Across the line between the two ways of a dot tower's data gradient, whichever way the smaller batch goes."""
     batches = [1, 64, 65, 300, 500, 640, 641, 1024, 2000, 2048, 4096, 8192]
-    assert len({lib.one_kernel(T, nf, n, O, ctypes.c_long(B), 1) for B in batches}) == 2
+    assert len({one_kernel(lib, T, nf, n, O, B) for B in batches}) == 2
 
     def sizes(fuse):
         monkeypatch.setenv("DMT_TM_FUSE", fuse)
