@@ -775,9 +775,8 @@ dmt_status run_tm_bwd(const dmt_plan* p, const dmt_tm_params* tp, const std::vec
     return keptp && kept[t].has_z ? keptp + kept[t].z : (const char*)(wsp + ws[t].p);
   };
   // The projection's weights, repacked where they must be.  The forward has kept a repacked copy if the
-  // terms are odd; otherwise only if ITS weights were not 4-byte aligned, which the weights at hand
-  // do not tell.
-  auto kept_wp = [&](int t) { return keptp && kept[t].has_z && ws[t].np % 2 == 1; };
+  // terms are odd; if they are even, whether ITS weights were 4-byte aligned is more than the weights at hand tell.
+  auto kept_wp = [&](int t) { return keptp && kept[t].has_wp; };
   auto wp_of = [&](int t) -> const char* {
     if (!ws[t].packed) return (const char*)tp[t].w_proj;
     return kept_wp(t) ? keptp + kept[t].wp : (const char*)(wsp + ws[t].wp);

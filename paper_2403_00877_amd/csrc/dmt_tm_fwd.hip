@@ -126,7 +126,7 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
   };
 
   auto wp_of = [&](int t) -> char* {                // ... and its repacked projection weights
-    return keptp && kept[t].has_z ? keptp + kept[t].wp : wsp + ws[t].wp_off;
+    return keptp && kept[t].has_wp ? keptp + kept[t].wp : wsp + ws[t].wp_off;
   };
 
   // A dot-product tower whose shape fits computes its dot terms inside the projection GEMM.
@@ -135,19 +135,23 @@ dmt_status run_tm(const dmt_plan* p, const dmt_tm_params* tp, const std::vector<
     for (int32_t t = 0; t < p->T; ++t)
       fused[t] = tp[t].kind == DMT_TM_DOT_LINEAR && p->tower_ntab[t] >= 2 && p->tower_uniform_dim[t] % 8 == 0 &&
                  ws[t].np_pad <= BK;
-  // ... which, in a small launch, reads its weights at any alignment (a training forward still leaves
-  // the backward its repacked copy)
-  bool dots_any = false;
-  if (!keptp) {
-    std::vector<TmGroup> g;
-    for (int32_t t = 0; t < p->T; ++t)
-      if (fused[t]) {
-        g.push_back(TmGroup{});
-        g.back().M = (int32_t)B;
-        g.back().N = tp[t].out_dim;
-      }
-    dots_any = !g.empty() && take_small(p, g.data(), (int)g.size(), true);
-  }
+  // ... which, in a small launch, reads its weights at any alignment.  A training forward leaves the backward the
+  // repacked copy that it reads, and with more tiles than kSmallTiles repacks for its own sake (4 towers of 6 and 7 features of
+  // 128 columns to 256 outputs, repacked / not, us: 512 tiles 18.6 / 17.8, 1024 30.6 / 34.5; of 7 to 128, 512 19.2 / 18.2, 1008
+  // 30.6 / 33.3).
+  std::vector<TmGroup> fused_groups;
+  bool dots_any = true;
+  int64_t fused_tiles = 0;
+  for (int32_t t = 0; t < p->T; ++t)
+    if (fused[t]) {
+      fused_groups.push_back(TmGroup{});
+      fused_groups.back().M = (int32_t)B;
+      fused_groups.back().N = tp[t].out_dim;
+      fused_tiles += tiles_of(fused_groups.back(), 32);
+      dots_any = dots_any && !(keptp && kept[t].has_wp);
+    }
+  dots_any = dots_any && !fused_groups.empty() && take_small(p, fused_groups.data(), (int)fused_groups.size(), true) &&
+             (!keptp || fused_tiles <= kSmallTiles);
   // (Only the kernel with in-kernel dot terms clears the weights that meet the zeros behind the terms: the
   // pooled values' first ones, where the terms are no multiple of 8.  The others read zeros in the
   // repacked copy.)

@@ -1215,19 +1215,21 @@ inline bool dot_one_kernel(const dmt_plan* p, int t, int64_t O, const DotDgrad& 
 // What a training forward keeps for the backward: for every cross layer l of a cross tower
 // (full-rank or low-rank), x_{l+1} and u_l = W_l x_l + b_l, each [B][W_t] in the compute type;
 // for a dot-product tower its dot terms, [B][np_pad] (np_pad = the F (F - 1) / 2 terms rounded
-// up to 8, zeros behind them), and, where they cannot be read as they are, its projection weights
-// with zero columns inserted to match, [O][np_pad + W_t].  Offsets in bytes from a 256-byte-aligned base; towers of other
-// kinds keep nothing (their backward needs only the pooled values).
+// up to 8, zeros behind them), and, where its backward reads them so whatever their address (an odd number of terms,
+// 16-bit types, not tmb_dot_dgrad), its projection weights with zero columns inserted to match, [O][np_pad + W_t].
+// Offsets in bytes from a 256-byte-aligned base; towers of other kinds keep nothing (their backward needs only the pooled
+// values).
 struct TmKept {
   size_t x[DMT_MAX_CROSS_LAYERS] = {}, u[DMT_MAX_CROSS_LAYERS] = {};
   size_t z = 0, wp = 0;      // dot tower: dot terms, and the projection weights as repacked for them
-  bool has_z = false;
+  bool has_z = false, has_wp = false;
 };
 
 inline size_t plan_tm_kept(const dmt_plan* p, const dmt_tm_params* tp, int64_t B, int eb,
                            std::vector<TmKept>* kept) {
   size_t off = 0;
   kept->assign(p->T, TmKept());
+  const DotDgrad dots = dot_dgrad_of(p, tp, B);
   for (int32_t t = 0; t < p->T; ++t) {
     if (tp[t].kind == DMT_TM_DOT_LINEAR) {
       const int nf = p->tower_ntab[t], np_pad = (nf * (nf - 1) / 2 + 7) / 8 * 8;
@@ -1235,8 +1237,9 @@ inline size_t plan_tm_kept(const dmt_plan* p, const dmt_tm_params* tp, int64_t B
         (*kept)[t].z = off;
         (*kept)[t].has_z = true;
         off += dmt_align_up((size_t)B * np_pad * eb, 256);
+        (*kept)[t].has_wp = eb == 2 && nf * (nf - 1) / 2 % 2 == 1 && !dot_one_kernel(p, t, tp[t].out_dim, dots);
         (*kept)[t].wp = off;
-        off += dmt_align_up((size_t)tp[t].out_dim * (np_pad + p->tower_width[t]) * eb, 256);
+        if ((*kept)[t].has_wp) off += dmt_align_up((size_t)tp[t].out_dim * (np_pad + p->tower_width[t]) * eb, 256);
       }
       continue;
     }
@@ -1306,6 +1309,7 @@ inline bool take_big(const dmt_plan* p, const TmGroup* g, int n) {
 // 768 tiles 10.1 / 10.2; cross layers of 4 towers of 1024 columns, 768 tiles 46.5 / 42.5, 896 tiles 46.4 / 49.3; dots
 // and K = 1052, 1024 tiles 30.2 / 28.6, 1152 tiles 30.1 / 32.9, 4 features of 32, 1024 tiles 14.4 / 11.5, 1152 tiles
 // 14.4 / 14.4.
+constexpr int kSmallTiles = 512;
 inline bool take_small(const dmt_plan* p, const TmGroup* g, int n, bool dots) {
   if (p->sw.tm_big != 1) return p->sw.tm_big == 3;
   int64_t tiles = 0;
@@ -1314,7 +1318,7 @@ inline bool take_small(const dmt_plan* p, const TmGroup* g, int n, bool dots) {
     tiles += tiles_of(g[i], 32);
     cross = cross && g[i].epi == EPI_CROSS;
   }
-  return tiles <= (dots ? 1024 : cross ? 768 : 512);
+  return tiles <= (dots ? 1024 : cross ? 768 : kSmallTiles);
 }
 
 // Cuts a launch's groups into tiles and deals them out; how many blocks it takes.

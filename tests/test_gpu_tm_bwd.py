@@ -225,22 +225,22 @@ def test_kept_dot_terms_on_every_dot_path(dt, fuse, monkeypatch):
     check_tm_bwd(w5, rtol=1e-4 if dt == "f32" else 4e-2, keep=True)
 
 
-@pytest.mark.parametrize("fuse", ["0", "1"])
-@pytest.mark.parametrize("nf,forward_at,backward_at", [(4, 0, 1), (4, 1, 0), (8, 0, 1), (3, 0, 1), (3, 1, 0), (2, 1, 1)])
-def test_kept_activations_serve_weights_at_any_address(nf, forward_at, backward_at, fuse, monkeypatch):
+@pytest.mark.parametrize("fuse,cols", [("0", 24), ("1", 24), ("1", 32)])      # (of 32 columns: tmb_dot_dgrad)
+@pytest.mark.parametrize("nf,forward_at,backward_at", [(4, 0, 1), (4, 1, 0), (8, 0, 1), (3, 0, 1), (3, 1, 0), (2, 1, 1), (2, 0, 0)])
+def test_kept_activations_serve_weights_at_any_address(nf, forward_at, backward_at, fuse, cols, monkeypatch):
     """The same dot-tower weights at an aligned address and 2 bytes behind one (weights there are read
     from a repacked copy; 4 and 8 features: an even number of dot terms, whose aligned weights are read
     as they are), given to the training forward and to the backward in either order."""
     monkeypatch.setenv("DMT_TM_FUSE", fuse)
     w = wl.scaled(wl.mid(), max_rows=100, batch=70, num_tables=nf)
-    w.dims = [24] * nf
+    w.dims = [cols] * nf
     w.table_to_tower = [0] * nf
     w.tm_out = [40]
     w.tm_dtype = w.pooled_dtype = "bf16"
     dw = DeviceWorkload(w)
     tm = TowerModules(dw)
     p = tm.keep[0]
-    x = torch.randn(w.batch * nf * 24, device="cuda").to(torch.bfloat16)
+    x = torch.randn(w.batch * nf * cols, device="cuda").to(torch.bfloat16)
     dy = torch.randn(w.batch * 40, device="cuda")
 
     def weights_at(odd):

@@ -155,6 +155,21 @@ def test_a_dot_towers_data_gradient_beside_other_towers(lib, B, linear, dots):
     assert one_kernel(lib, 9, 8, 128, 256, B, 1, (dmt.binding.DMT_TM_DOT_LINEAR, 9)) == 1
 
 
+@pytest.mark.parametrize("T,nf,n,O,B,copy", [
+    (4, 7, 128, 256, 2003, 0), (4, 8, 128, 2048, 300, 0),      # one kernel, with a layout of its own; an even number of terms
+    (4, 7, 128, 2048, 300, 1), (4, 10, 32, 64, 300, 1), (2, 3, 24, 40, 70, 1),
+])
+def test_a_training_forward_keeps_repacked_weights_for_the_backwards_that_read_them(T, nf, n, O, B, copy):
+    plan = dmt.dmt_plan_create([10] * (T * nf), [n] * (T * nf), "f32", T, [t for t in range(T) for _ in range(nf)], B, 1)
+    w = torch.zeros(4)
+    params = dmt.make_tm_params([dict(kind="dot_linear", out_dim=O, w_proj=w, b_proj=w)] * T)
+    np_pad = -(-(nf * (nf - 1) // 2) // 8) * 8
+    up = lambda b: -(-b // 256) * 256
+    for dtype, eb in ((torch.bfloat16, 2), (torch.float32, 4)):
+        want = T * (up(B * np_pad * eb) + (up(O * (np_pad + nf * n) * eb) if copy and eb == 2 else 0))
+        assert dmt.dmt_tm_kept_bytes(plan, params, B, dtype) == want
+
+
 @pytest.mark.parametrize("T,nf,n,O", [(4, 8, 32, 512), (1, 2, 64, 641), (2, 8, 128, 2048), (4, 3, 64, 1000)])
 def test_a_backward_workspace_for_a_larger_batch_serves_a_smaller_one(lib, T, nf, n, O, monkeypatch):
     """Across the line between the two ways of a dot tower's data gradient, whichever way the smaller batch goes."""
