@@ -164,9 +164,11 @@ def test_rows_of_many_lookups_in_small_calls(dim, counts):
 
 
 @pytest.mark.parametrize("rows,lens", [
-    ([1, 1], [900, 2]),                             # one bit of row id
-    ([1022, 3], [1000, 1]),                         # 10 bits: one pass
-    ([1024, 5, 1023], [2049, 0, 1]),                # 11 bits: two passes; a block of one record
+    ([1, 1], [900, 2]), ([1022, 3], [1000, 1]), ([1024, 5, 1023], [2049, 0, 1]),      # one launch: 1, 10 and 11 bits
+    ([1, 1], [9000, 2]),                            # one bit of row id
+    ([1022, 3], [9000, 1]),                         # 10 bits: one pass
+    ([1024, 5, 1023], [8193, 0, 1]),                # 11 bits: two passes; blocks of one record
+    ([50] * 400, [20] * 400),                       # bags of many tables in one block of bwd_bag_samples; narrow digits
     ([1 << 20, 40], [40000, 3]),                    # 21 bits: three passes; 20 blocks in one table
     ([3000, 70000, 9], [(1 << 18), 1, (1 << 18) - 1]),   # as many lookups as wide digits take
     ([3000, 70000, 9], [(1 << 18), 1, 1 << 18]),    # one more: narrow digits
@@ -193,8 +195,13 @@ def test_sort_digit_widths(rows, lens):
 
 
 @pytest.mark.parametrize("rows", [[200, 1], [1 << 12, 9], [1 << 20, 70000, 3]])      # 1, 2 and 3 passes of narrow digits
-@pytest.mark.parametrize("batch,mean", [(3, 0.0), (700, 0.4), (1025, 900.0), (65536, 5.0), (65537, 5.0)])
-def test_samples_of_the_sorted_lookups(rows, batch, mean):
+@pytest.mark.parametrize("batch,mean,longest", [
+    (3, 0.0, 5000), (700, 0.4, 5000),                # one launch sorts these,
+    (3, 0.0, 9000), (700, 0.4, 9000),                # wide digits these,
+    (3, 0.0, 600_000), (700, 0.4, 600_000),          # and narrow ones these and the others
+    (1025, 900.0, 0), (65536, 5.0, 0), (65537, 5.0, 0),
+])
+def test_samples_of_the_sorted_lookups(rows, batch, mean, longest):
     """Samples of 16 bits (up to 65536) and of 32, bags of a table with fewer, as many and more samples than a block of
     bwd_bag_samples takes, most bags empty or one holding most lookups: order and samples are exact."""
     F = len(rows)
@@ -203,8 +210,8 @@ def test_samples_of_the_sorted_lookups(rows, batch, mean):
         dims=[4] * F, table_to_tower=[0] * F, tm_out=[32])
     rng = np.random.default_rng(batch)
     per_bag = rng.poisson(mean, F * batch).astype(np.int64)
-    if mean < 1:
-        per_bag[[0, F * batch - 1, F * batch // 2]] = [5000, 1, 3]
+    if longest:
+        per_bag[[0, F * batch - 1, F * batch // 2]] = [longest, 1, 3]
     off = np.concatenate([[0], np.cumsum(per_bag)])
     lens = per_bag.reshape(F, batch).sum(1)
     idx = np.concatenate([(r * rng.random(n) ** 3).astype(np.int32) for r, n in zip(rows, lens)])
@@ -215,6 +222,37 @@ def test_samples_of_the_sorted_lookups(rows, batch, mean):
     order = np.argsort(key, kind="stable")
     assert np.array_equal(dbg["sorted_keys"].cpu().numpy(), key[order])
     assert np.array_equal(dbg["sorted_bag"].cpu().numpy(), np.repeat(np.arange(F * batch), per_bag)[order])
+
+
+@pytest.mark.parametrize("rows", [[200, 1], [1 << 12, 9], [1 << 20, 70000, 3]])      # 1, 2 and 3 passes
+@pytest.mark.parametrize("share", [1e-6, 0.3])
+def test_ids_outside_their_table_in_narrow_digits(rows, share):
+    """More than 2^19 lookups: they sort behind the table's rows in the order of the lookups, touch no row, and the first
+    is reported."""
+    F, batch, n = len(rows), 500, 300_000
+    w = wl.dataclasses.replace(
+        wl.scaled(wl.mid(True), max_rows=10, batch=batch, num_tables=F), table_dtype="f32", rows=rows,
+        dims=[4] * F, table_to_tower=[0] * F, tm_out=[32])
+    rng = np.random.default_rng(F)
+    off = np.arange(F * batch + 1, dtype=np.int64) * (n // batch)
+    table = np.repeat(np.arange(F, dtype=np.int64), n)
+    size = np.array(rows)[table]
+    idx = (size * rng.random(F * n) ** 3).astype(np.int32)
+    outside = rng.random(F * n) < share
+    outside[[7, F * n - 1]] = True
+    idx[outside] = np.where(rng.random(outside.sum()) < 0.5, size[outside], -1 - size[outside]).astype(np.int32)
+    dw = DeviceWorkload(w, with_state=True, max_nnz=F * n)
+    before = [t.clone() for t in dw.tables]
+    dbg = run_bwd(dw, idx, off, wl.grad_pooled(w), w.lr, w.eps)
+    assert dw.dmt.dmt_last_device_error(dw.plan) == np.flatnonzero(outside)[0]
+    order = np.argsort(table << 32 | np.where(outside, size, idx), kind="stable")
+    assert np.array_equal(dbg["sorted_keys"].cpu().numpy(), np.where(outside, -1, table << 32 | idx)[order])
+    assert np.array_equal(dbg["sorted_bag"].cpu().numpy(), (np.arange(F * n) // (n // batch))[order])
+    for f in range(F):
+        hit = np.zeros(rows[f], bool)
+        hit[idx[(table == f) & ~outside]] = True
+        same = (dw.tables[f] == before[f]).all(dim=1).cpu().numpy()
+        assert not same[hit].any() and same[~hit].all()
 
 
 @pytest.mark.parametrize("rows,lens,batch", [
