@@ -333,8 +333,9 @@ inline void f32_arrange(std::vector<TmF32Group>& groups, bool forward) {
       auto past = g;
       for (; past != end && 2 * f32_steps(*past) >= steps; ++past) tiles += f32_tiles(*past);
       const int l = f32_log2_ks(steps, tiles, before, forward, g->epi == EPI_CROSS);
-      for (; g != past; ++g) g->log2_ks = l;
       before += tiles << l;
+      for (; g != past; ++g)                       // (every wave keeps a batch: 8 and 4 steps in halves 9.1 us, 8 in halves 6.7)
+        for (g->log2_ks = l; g->log2_ks > 0 && f32_steps(*g) >> g->log2_ks < kF32Unroll;) --g->log2_ks;
     }
     std::stable_sort(begin, end, longest_wave_first);
   }
