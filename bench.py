@@ -103,6 +103,15 @@ def batch_accounting(torch, w, idx, off):
 # L2 <-> fabric bytes per kernel, counted under rocprofv3 in child runs of this same file
 # --------------------------------------------------------------------------------------------
 
+def sort_pass_bytes(w, nnz):
+    """Bytes a lookup that a pass of the sort moves, over all passes: the row inside the table (4 bytes) and the sample (2 up to
+    65536 samples, else 4) read and written; the last pass writes 8."""
+    bits = max(w.rows).bit_length()                     # of a row id or the one past the last row
+    passes = -(-bits // (10 if nnz <= 1 << 19 else 8))
+    record = 4 + (2 if w.batch <= 1 << 16 else 4)
+    return ((2 * passes - 1) * record + 8) / passes
+
+
 # kernel (as the profiler names it) -> the family dmt_kernel_name() reports
 FAMILIES = (("lookup_fwd_kernel", "lookup_fwd"), ("bwd_reduce_update", "bwd_reduce_update"),
             ("bwd_fixup_update", "bwd_fixup_update"), ("bwd_bag_samples", "bwd_build_keys"),
@@ -493,8 +502,7 @@ def run_workload(args, wname, traffic, primary):
         # state read + write; partial sums of rows that span tiles
         "bwd_reduce_update": float((nnz_f * (8 + Df * 4) + U_f * (2 * Df * eb + 8)).sum()
                                    - span * (2 * Dmax * eb + 8) + pslots * Dmax * 4),
-        # one radix pass of three: row and sample read and written, 6 bytes; the last writes 8
-        "radix_scatter": nnz * 38 / 3,
+        "radix_scatter": nnz * sort_pass_bytes(w, nnz),
     }
     compulsory = {
         # each distinct row once; ids, offsets and the pooled store as they are
@@ -502,7 +510,7 @@ def run_workload(args, wname, traffic, primary):
         # each bag's gradient slice once, every sorted record once, each distinct row read and
         # written once with its state
         "bwd_reduce_update": float((B * Df * 4 + nnz_f * 8 + U_f * (2 * Df * eb + 8)).sum()),
-        "radix_scatter": nnz * 38 / 3,
+        "radix_scatter": nnz * sort_pass_bytes(w, nnz),
     }
     kin = w.tm_in_dims()
     tw = w.tower_widths()

@@ -94,7 +94,7 @@ struct DmtSwitches {
                          // contractions of its own; 2: the dot towers' data gradient in one kernel whatever the size
   int tmb_ksplit = 0;    // DMT_TMB_KSPLIT=n: slices of every weight gradient
   int bwd_kernel = 0;    // DMT_BWD_KERNEL=1 / 2: the wave-per-tile / lane-group segment reduce
-  int keys_lg = -1;      // DMT_KEYS_LG=l: 2^l bags per key-build block
+  int keys_lg = -1;      // DMT_KEYS_LG=l: 2^l bags per block of bwd_bag_samples
   int lookup_r = 0;      // DMT_LOOKUP_R=r: row slots per bag
   int lookup_bpg = 0;    // DMT_LOOKUP_BPG=n: bags a lane group pools in turn
   int lookup_long = -1;  // DMT_LOOKUP_LONG=n: bags longer than n ids go to whole waves (0: never)

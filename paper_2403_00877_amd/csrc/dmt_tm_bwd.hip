@@ -185,11 +185,11 @@ __global__ __launch_bounds__(kBlock) void tmb_dot_bwd8(const TmbLaunch L) {
 //   dZ[b][p] = sum over o of dz[b][o] W[o][p],
 // in one kernel.  Bound by the bytes of x and dx: the two contractions and tmb_dot_bwd8 moved the flat part of dZ,
 // as large as dx, through memory and back.  8 towers of 8 features of 128 columns, 256 outputs, batch 8192: 77 + 12 +
-// 148 us, now 116 (0.44 GB at 3.8 TB/s; without the products 105, without the requests of weights and dz 96); 4 of 6 and
-// 7 features, batch 2003: 17 + 16 us, now 15, and the repack of the weights rides with tmb_prep_dz.
+// 148 us, now 116 (0.44 GB at 3.8 TB/s; without the products 105, without the requests of weights and dz 96) and 8 more in
+// tmb_prep_dz, which repacks the weights (22 -> 30); 4 of 6 and 7 features, batch 2003: 17 + 16 us, now 15 + 1.
 // A wave owns 16 or 32 samples and the same 32 columns of EVERY feature, the weights as the first operand, so that a lane
 // holds one sample's values of all features at four consecutive columns and the sum over j needs no other lane's
-// (x comes in the accumulators' layout, 8 bytes a lane).  Four waves share the weights of their columns, which go
+// (x comes in the accumulators' layout, 16 bytes a lane).  Four waves share the weights of their columns, which go
 // through LDS in steps of 32 outputs, fragment by fragment as the repacked weights lie; behind them come the dot
 // terms' rows, whose products, a few floats a sample, take the way through LDS to the sample's other lanes.
 constexpr int kDotZPitch = kDotTermTiles * 16 + 4; // floats: 16 samples' pieces of 16 bytes on different banks
@@ -387,7 +387,9 @@ __global__ __launch_bounds__(kBlock, 2) void tmb_dot_dgrad(const TmbLaunch L) {
           st[1][r] = __int_as_float(__builtin_amdgcn_update_dpp(c, a, 0x128, 0xf, 0x3, false));
         }
         // (nontemporal: dx is read again by the sparse update only, and x, which the weight gradients read next, stays
-        // in the caches: those 51 -> 42 us on 8 towers of 8 features of 128 columns, batch 8192)
+        // in the caches: those 51 -> 42 us on 8 towers of 8 features of 128 columns, batch 8192.  At any size: whole
+        // passes, plain / nontemporal, 27 MB of dx 157.7 / 158.4 us, 160 MB 493 / 487, 218 MB 616 / 610, 25 passes of 7 to
+        // 268 MB 0.2 % shorter together.)
         if (on[0]) __builtin_nontemporal_store(st[0], (floatx4*)(out + i * n));
         if (on[1]) __builtin_nontemporal_store(st[1], (floatx4*)(out + 8 * wt + i * n));
       }

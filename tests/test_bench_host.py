@@ -67,3 +67,15 @@ def test_committed_byte_summaries_parse(name):
         assert per["bwd_reduce_update"]["bytes"] > per["bwd_fixup_update"]["bytes"] > 0
     tj = json.load(open(os.path.join(ROOT, "profiles", "bench_%s_hbm_traffic.json" % name)))
     assert abs(tj["fetch_scale"] - 2.0) < 0.05 and abs(tj["write_scale"] - 1.0) < 0.05
+
+
+@pytest.mark.parametrize("rows,batch,nnz,per_pass", [
+    ([1 << 20, 9], 8192, 10_000_000, 38 / 3), ([1_000_000], 8192, 10_000_000, 38 / 3), ([255], 70_000, 10_000_000, 16.0),
+    ([1 << 20], 8192, 300_000, 38 / 3), ([1_000_000], 8192, 300_000, 13.0),       # digits of 10 bits
+])
+def test_bytes_of_a_sort_pass(rows, batch, nnz, per_pass):
+    class W:
+        pass
+    w = W()
+    w.rows, w.batch = rows, batch
+    assert bench.sort_pass_bytes(w, nnz) == pytest.approx(per_pass)
